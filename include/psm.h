@@ -281,7 +281,9 @@ enum psm_launch_flags {
  * tx in {16,32,64,128,256}) handling tz cells each along z (tz in
  * {1,2,4,8,16,32}), and psm_launch_flags. Rebuilds the tile lists
  * (synchronises); invalidates captured graphs. On failure the previous
- * launch is restored. psm_get_launch: host outputs (flags may be NULL). */
+ * launch is restored. A context starts with 64 x 4 threads and a depth
+ * chosen from its storage form and box sizes (its results are those of depth
+ * 16). psm_get_launch: host outputs (flags may be NULL). */
 int psm_set_launch(psm_ctx* ctx, int tx, int ty, int tz, int flags);
 int psm_get_launch(psm_ctx* ctx, int* tx, int* ty, int* tz, int* flags);
 

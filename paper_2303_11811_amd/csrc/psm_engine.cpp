@@ -64,6 +64,40 @@ static bool shape_allowed(int tx, int ty, int tz) {
 
 static int cdiv(long long a, long long b) { return (int)((a + b - 1) / b); }
 
+// Launch of a context that sets none: tiles of 64 x 4 threads, as many cells
+// deep as the storage form gains from while enough tiles are left to fill 256
+// CUs. us per step at depth 1 / 2 / 4 / 8 / 16 (spheres at 10 %):
+//   FP64  32^3   13.1 / 16.8 / 24.6 / 37.3 / 62.9    256^3  918 / 934 / 979 / 1003 / 1013
+//   FP32  64^3   17.0 / 17.7 / 22.6 / 33.9 / 58.0    256^3  528 / 489 / 506 / 537 / 544
+//   FP16  64^3   14.8 / 15.4 / 20.0 / 30.1 / 53.2    128^3  61.5 / 51.5 / 49.9 / 49.9 / 73.0
+//         96^3   39.5 / 35.1 / 36.2 / 42.1 / 65.1    384^3  1365 / 1058 / 920 / 879 / 888
+// A deeper tile runs its cells one after another in each wave, which is lost
+// time while CUs are idle; the deviation forms, whose spheres cost more beside
+// fewer bytes, gain from staging them once for more cells. The FP32 geometry
+// refers to the centres of blocks 16 planes deep at every depth, so the
+// results do not depend on the depth chosen.
+constexpr int kDefaultRefZ = 16;
+
+static TileShape default_shape(const psm_box_desc* boxes, int nbox, int storage) {
+    struct Depth {
+        int tz;
+        long long tiles;   // fewest tiles it is taken at
+    };
+    static const Depth depths[] = {{8, 8192}, {4, 1800}, {2, 1500}, {1, 0}};
+    const int most = storage == PSM_FP64 ? 1 : (storage == PSM_FP32DEV ? 2 : 8);
+    TileShape ts{64, 4, 1, 0, 0, kDefaultRefZ};
+    for (const Depth& d : depths) {
+        long long T = 0;
+        for (int b = 0; b < nbox; ++b)
+            T += (long long)cdiv(boxes[b].nx, ts.tx) * cdiv(boxes[b].ny, ts.ty) * cdiv(boxes[b].nz, d.tz);
+        if (d.tz <= most && T >= d.tiles) {
+            ts.tz = d.tz;
+            break;
+        }
+    }
+    return ts;
+}
+
 // Largest number of tiles the bounding box [x-(r+1), x+(r+1)] can touch along
 // an axis of L cells cut into tiles of T cells. Its cell range spans at most
 // E = floor(2(r+1)) + 2 cells. On a periodic axis whose last
@@ -211,7 +245,7 @@ struct psm_ctx {
     std::vector<BoxDev> box;     // host copy of the device box table
     std::vector<int> np;         // particles set per box
     int P_total = 0;
-    TileShape ts{64, 4, 16, 0, 0};
+    TileShape ts{64, 4, 16, 0, 0, 16};
     int T_total = 0;
     int grid = 0;
     int parity = 0;
@@ -457,6 +491,7 @@ extern "C" int psm_create(const psm_box_desc* boxes, int nbox, int storage, doub
         c->h_inv = (float)(1.0 / fp16_scale);
     }
     c->P_total = L.P_total;
+    c->ts = default_shape(boxes, nbox, storage);
     c->np.assign(nbox, 0);
     c->box.resize(nbox);
     int pb = 0;
@@ -869,6 +904,7 @@ static int step_params(psm_ctx* c, int parity, StepParams& kp) {
     kp.partial = c->d_partial;
     kp.T_total = c->T_total;
     kp.tx = c->ts.tx; kp.ty = c->ts.ty; kp.tz = c->ts.tz;
+    kp.ref_z = c->ts.ref_z;
     kp.parity = parity;
     kp.h_scale = c->h_scale;
     kp.h_inv = c->h_inv;
@@ -1243,7 +1279,7 @@ extern "C" int psm_set_launch(psm_ctx* c, int tx, int ty, int tz, int flags) {
     if (flags & ~(PSM_LAUNCH_PERSISTENT | PSM_LAUNCH_FILTER)) return fail(PSM_EINVAL, "unknown launch flags %d", flags);
     HIP_TRY(hipStreamSynchronize(c->stream));
     TileShape old = c->ts;
-    c->ts = TileShape{tx, ty, tz, (flags & PSM_LAUNCH_PERSISTENT) ? 1 : 0, (flags & PSM_LAUNCH_FILTER) ? 1 : 0};
+    c->ts = TileShape{tx, ty, tz, (flags & PSM_LAUNCH_PERSISTENT) ? 1 : 0, (flags & PSM_LAUNCH_FILTER) ? 1 : 0, tz};
     assign_tiles(c);
     int rc = upload_box_table(c);
     if (rc == PSM_OK) rc = rebuild_lists(c);
@@ -1481,7 +1517,7 @@ static int autotune_timed(psm_ctx* c, int trial_steps, TileShape& best_out, doub
             // tiles much wider than the widest box only idle lanes
             if (txv > 2 * std::max(maxdim, 16)) continue;
             for (int tzv : kTZ) {
-                TileShape ts{txv, WG / txv, tzv, (fl & PSM_LAUNCH_PERSISTENT) != 0, (fl & PSM_LAUNCH_FILTER) != 0};
+                TileShape ts{txv, WG / txv, tzv, (fl & PSM_LAUNCH_PERSISTENT) != 0, (fl & PSM_LAUNCH_FILTER) != 0, tzv};
                 if (psm_set_launch(c, ts.tx, ts.ty, ts.tz, fl) != PSM_OK) continue;   // not allowed here
                 double per = 0.0;
                 if ((rc = time_current(trial_steps, per))) break;

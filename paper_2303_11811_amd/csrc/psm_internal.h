@@ -97,6 +97,7 @@ struct TileShape {
     int tx, ty, tz;
     int persistent;   // 1: occupancy-sized grid walking the tiles; 0: one workgroup per tile
     int filter;       // 1: per-wave candidate filter before the per-cell mapping
+    int ref_z;        // depth of the z-blocks whose centres the FP32 geometry refers to (a multiple of tz)
 };
 
 // ---------------------------------------------------------------------------
@@ -266,6 +267,7 @@ struct StepParams {
     double* partial;            // [slots][6]
     int T_total;
     int tx, ty, tz;
+    int ref_z;                  // TileShape::ref_z
     int parity;
     float h_scale, h_inv;       // FP16 storage scale and its inverse (1 otherwise)
     int* flags;                 // device error word: |= FLAG_SLOT_OVERFLOW when a cell meets a third sphere

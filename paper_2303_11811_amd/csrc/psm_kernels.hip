@@ -364,7 +364,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(S::DEV ? PSM
 
     __shared__ double s_px[MAXC], s_py[MAXC], s_pz[MAXC], s_pr[MAXC], s_pfr[MAXC];
     __shared__ double s_ux[MAXC], s_uy[MAXC], s_uz[MAXC], s_ox[MAXC], s_oy[MAXC], s_oz[MAXC];
-    // FP32 copies: centre relative to the tile centre (minimum image), the
+    // FP32 copies: centre relative to the tile's reference point (minimum image), the
     // squared reach of the overlap test with a rounding margin, and (for the
     // deviation forms) the velocities
     __shared__ float s_qx[MAXC], s_qy[MAXC], s_qz[MAXC], s_lim2[MAXC], s_rf[MAXC], s_frf[MAXC];
@@ -428,8 +428,10 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(S::DEV ? PSM
         const int nc = tile_off[t + 1] - e0;   // at most MAXC: the scan caps every list
         const double Lx = bx.L[0], Ly = bx.L[1], Lz = bx.L[2];
         const double hLx = bx.halfL[0], hLy = bx.halfL[1], hLz = bx.halfL[2];
-        // tile centre in cell coordinates
-        const double tmx = tcx * TX + 0.5 * TX, tmy = tcy * TY + 0.5 * TY, tmz = tcz * TZ + 0.5 * TZ;
+        // reference point of the FP32 geometry in cell coordinates: the tile's
+        // centre, in z that of the block of ref_z planes the tile lies in
+        const int RZ = kp.ref_z, zb = tcz * TZ / RZ * RZ;
+        const double tmx = tcx * TX + 0.5 * TX, tmy = tcy * TY + 0.5 * TY, tmz = zb + 0.5 * RZ;
 
         if (nc > 0) {
             for (int c = tid; c < nc; c += WG) {
@@ -490,7 +492,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(S::DEV ? PSM
         const R k15 = pick<R>(bx.k15, bx.k15_f);
         const R k45 = pick<R>(bx.k45, bx.k45_f);
         const double cxc = xs + 0.5, cyc = ys + 0.5;
-        // this cell's centre relative to the tile centre (FP32, exact)
+        // this cell's centre relative to the reference point (FP32, exact)
         const float rx = (float)(lx + 0.5 - 0.5 * TX), ry = (float)(ly + 0.5 - 0.5 * TY);
         const float Lxf = (float)Lx, Lyf = (float)Ly, Lzf = (float)Lz;
         const float iLx = 1.0f / Lxf, iLy = 1.0f / Lyf, iLz = 1.0f / Lzf;
@@ -545,7 +547,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(S::DEV ? PSM
             const int z = tcz * TZ + k;
             if (z >= nz) break;
             const double czc = z + 0.5;
-            const float rz = (float)(k + 0.5 - 0.5 * TZ);
+            const float rz = (float)(z - zb + 0.5 - 0.5 * RZ);
             const int zm = z == 0 ? nz - 1 : z - 1, zp = z == nz - 1 ? 0 : z + 1;
             // buffer resources of the source planes z, z-1, z+1 and the
             // destination plane z
