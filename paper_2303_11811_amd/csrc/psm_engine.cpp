@@ -116,12 +116,13 @@ static int max_tiles_axis(double rmax, int T, int L) {
 // Workspace layout
 
 struct Layout {
-    size_t off_boxes, off_tbase, off_partbox, off_pt, off_acc, off_fprev, off_prevok, off_tcnt, off_toff, off_tpid, off_tslot,
-        off_partial, off_misc, off_statpart, off_scan, total;
+    size_t off_boxes, off_tbase, off_partbox, off_pt, off_acc, off_fprev, off_prevok, off_tcnt, off_tent,
+        off_partial, off_misc, off_statpart, total;
     std::vector<size_t> off_grid[2];
     std::vector<int> pblk;
     int T_max;
-    long long cap_max;
+    int list_cap;                // spheres a tile's list holds
+    long long cap_max;           // force-partial slots
     int P_total;
 };
 
@@ -197,6 +198,9 @@ static Layout make_layout(const psm_box_desc* boxes, int nbox, int storage) {
             capmax = std::max(capmax, cap);
         }
     L.T_max = Tmax;
+    int most = 0;
+    for (int b = 0; b < nbox; ++b) most = std::max(most, boxes[b].max_particles);
+    L.list_cap = std::min(MAXC, (most + 7) / 8 * 8);
     L.cap_max = std::max<long long>(capmax, 1);
     size_t o = 0;
     auto take = [&](size_t bytes) {
@@ -208,17 +212,14 @@ static Layout make_layout(const psm_box_desc* boxes, int nbox, int storage) {
     L.off_tbase = take(sizeof(int) * (nbox + 1));
     L.off_partbox = take(sizeof(int) * std::max(P, 1));
     L.off_pt = take(sizeof(double) * 11 * std::max(P, 1));
-    L.off_acc = take(sizeof(double) * 6 * std::max(P, 1) + 64);   // + the device error word
+    L.off_acc = take(sizeof(double) * 6 * std::max(P, 1) + 64);   // + the device error words
     L.off_fprev = take(sizeof(double) * 6 * std::max(P, 1));
     L.off_prevok = take(sizeof(int) * std::max(P, 1));
-    L.off_tcnt = take(sizeof(int) * (size_t)Tmax);
-    L.off_toff = take(sizeof(int) * ((size_t)Tmax + 1));
-    L.off_tpid = take(sizeof(int) * (size_t)L.cap_max);
-    L.off_tslot = take(sizeof(int) * (size_t)L.cap_max);
+    L.off_tcnt = take(sizeof(int) * 2 * (size_t)Tmax);
+    L.off_tent = take(sizeof(int2) * (size_t)Tmax * L.list_cap);
     L.off_partial = take(sizeof(double) * 6 * (size_t)L.cap_max);
     L.off_misc = take(256);
     L.off_statpart = take(sizeof(double) * 4 * (size_t)stats_blocks() + 64);
-    L.off_scan = take(sizeof(int) * 2 * (size_t)scan_chunks(Tmax) + 64);
     for (int p = 0; p < 2; ++p) L.off_grid[p].resize(nbox);
     L.pblk.resize(nbox);
     for (int b = 0; b < nbox; ++b) {
@@ -258,14 +259,17 @@ struct psm_ctx {
     int* d_tbase = nullptr;
     int* d_partbox = nullptr;
     Particles P{};
-    int *d_tcnt = nullptr, *d_toff = nullptr, *d_tpid = nullptr, *d_tslot = nullptr;
+    // tile lists: counts per list parity (each build fills those of the other
+    // parity and zeroes the ones it replaces), entries
+    int* d_tcnt[2] = {nullptr, nullptr};
+    int2* d_tent = nullptr;
+    int list_parity = 0;
     double* d_partial = nullptr;
-    int* d_misc = nullptr;               // [0..1] bin stats, [8..9] dropped (u64),
+    int* d_misc = nullptr;               // [8..9] dropped (u64),
                                          // [32..39] tile counters of the persistent grid
-    int* d_flags = nullptr;              // device error word (FLAG_* bits), right after the force sums
-    int* h_flags = nullptr;              // pinned copy of the device error word
+    int* d_flags = nullptr;              // device error words (FLAG_* bits, list overflows), right after the force sums
+    int* h_flags = nullptr;              // pinned copy of the device error words
     double* d_statpart = nullptr;
-    int* d_scan = nullptr;               // scan scratch (chunk sums and maxima)
     // last uploaded positions and radii per box: unchanged geometry keeps the lists
     std::vector<std::vector<double>> last_xr;
     // pinned host staging: two upload halves (reused once their copy has
@@ -277,19 +281,22 @@ struct psm_ctx {
     // force read-back at the end of psm_step (psm_set_force_readback): the
     // force sums of all boxes and the error word, copied in one piece
     bool rb_on = false, rb_valid = false;
-    double* h_rb = nullptr;          // [6 P_total] sums, then the error word
+    double* h_rb = nullptr;          // [6 P_total] sums, then the error words
     hipEvent_t rb_ev = nullptr;
     hipEvent_t stage_ev[2] = {nullptr, nullptr};
     int stage_next = 0;
     std::vector<std::vector<double>> last_r, last_fr;   // f(r) cache per box
-    // graphs of 10 steps, one per starting parity
+    // graphs of 10 steps, and of 10 (step + sphere update) pairs for the time
+    // step and scheme they were captured with; per starting grid and list
+    // parity (both return to it: the count is even)
     bool use_graph = false;
-    hipGraphExec_t gexec[2] = {nullptr, nullptr};
-    // graphs of 10 (step + sphere update) pairs, per starting parity, for the
-    // time step and scheme they were captured with
-    hipGraphExec_t gexec_dyn[2] = {nullptr, nullptr};
-    double gdyn_dt[2] = {0.0, 0.0};
-    int gdyn_scheme[2] = {-1, -1};
+    struct DynGraph {
+        hipGraphExec_t exec = nullptr;
+        double dt = 0.0;
+        int scheme = -1;
+    };
+    hipGraphExec_t gexec[2][2] = {};
+    DynGraph gdyn[2][2];
     // kernel timing
     bool timing = false;
     std::vector<hipEvent_t> ev;
@@ -301,16 +308,13 @@ struct psm_ctx {
 static const int kGraphSteps = 10;
 
 static void drop_graphs(psm_ctx* c) {
-    for (int p = 0; p < 2; ++p) {
-        if (c->gexec[p]) {
-            (void)hipGraphExecDestroy(c->gexec[p]);
-            c->gexec[p] = nullptr;
+    for (int p = 0; p < 2; ++p)
+        for (int l = 0; l < 2; ++l) {
+            if (c->gexec[p][l]) (void)hipGraphExecDestroy(c->gexec[p][l]);
+            c->gexec[p][l] = nullptr;
+            if (c->gdyn[p][l].exec) (void)hipGraphExecDestroy(c->gdyn[p][l].exec);
+            c->gdyn[p][l].exec = nullptr;
         }
-        if (c->gexec_dyn[p]) {
-            (void)hipGraphExecDestroy(c->gexec_dyn[p]);
-            c->gexec_dyn[p] = nullptr;
-        }
-    }
 }
 
 static int upload_box_table(psm_ctx* c) {
@@ -355,84 +359,81 @@ static void assign_tiles(psm_ctx* c) {
     c->grid = std::max(NXCD, g / NXCD * NXCD);
 }
 
-// Rebuild the per-tile candidate lists of all boxes (synchronises).
+// Parameters of the work per sphere; the lists are those of the other list
+// parity, which become the current ones once list_parity is flipped.
+static SphereParams sphere_params(psm_ctx* c) {
+    SphereParams sp;
+    sp.boxes = c->d_boxes;
+    sp.part_box = c->d_partbox;
+    sp.P = c->P;
+    sp.partial = c->d_partial;
+    sp.P_total = c->P_total;
+    sp.ts = c->ts;
+    sp.dt = 0.0;
+    const int next = c->list_parity ^ 1;
+    sp.cnt = c->d_tcnt[next];
+    sp.cnt_old = c->d_tcnt[c->list_parity];
+    sp.ent = c->d_tent;
+    sp.list_cap = c->L.list_cap;
+    sp.T_total = c->T_total;
+    sp.over = c->d_flags + 1 + next;
+    sp.over_old = c->d_flags + 1 + c->list_parity;
+    return sp;
+}
+
+// Rebuild the lists without waiting for the device: a tile with more spheres
+// than a list holds raises the overflow word of these lists (that of the
+// lists before is cleared); synchronising calls report it. The step kernel
+// stays in bounds on the cut lists.
+static int rebuild_lists_async(psm_ctx* c) {
+    if (c->P_total > 0) {
+        HIP_TRY(launch_spheres(false, SCHEME_NONE, true, sphere_params(c), c->stream));
+        c->list_parity ^= 1;
+    }
+    c->have_particles_lists = true;
+    return PSM_OK;
+}
+
+// Rebuild the per-tile candidate lists of all boxes at a new tile shape
+// (synchronises).
 static int rebuild_lists(psm_ctx* c) {
     // the step kernel must never run on half-built lists
     c->have_particles_lists = false;
-    BinParams bp;
-    bp.boxes = c->d_boxes;
-    bp.part_box = c->d_partbox;
-    bp.P = c->P;
-    bp.tile_cnt = c->d_tcnt;
-    bp.tile_off = c->d_toff;
-    bp.tile_pid = c->d_tpid;
-    bp.tile_slot = c->d_tslot;
-    bp.partial = c->d_partial;
-    bp.P_total = c->P_total;
-    bp.T_total = c->T_total;
-    bp.ts = c->ts;
-    bp.cap = c->L.cap_max;
-    HIP_TRY(launch_bin(bp, c->d_misc, c->d_scan, c->stream));
-    int stats[2] = {0, 0};
-    HIP_TRY(hipMemcpyAsync(stats, c->d_misc, sizeof stats, hipMemcpyDeviceToHost, c->stream));
+    // the tile count may have changed: both sets of counts start from zero
+    for (int l = 0; l < 2; ++l) HIP_TRY(launch_fill_int(c->d_tcnt[l], c->T_total, 0, c->stream));
+    int rc = rebuild_lists_async(c);
+    c->have_particles_lists = false;
+    if (rc) return rc;
+    int over[2] = {0, 0};
+    HIP_TRY(hipMemcpyAsync(over, c->d_flags + 1, sizeof over, hipMemcpyDeviceToHost, c->stream));
     // list flags of earlier builds are void; this build reports its own here
-    HIP_TRY(launch_check_lists(c->d_misc, c->L.cap_max, c->d_flags, 0, c->stream));
+    HIP_TRY(launch_fill_int(c->d_flags + 1, 2, 0, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
-    if (stats[1] > c->L.cap_max)
-        return fail(PSM_ECAPACITY, "tile lists need %d entries, capacity %lld", stats[1], c->L.cap_max);
-    if (stats[0] > MAXC)
-        return fail(PSM_ECAPACITY, "a tile has %d sphere candidates (limit %d): use a smaller tile shape",
-                    stats[0], MAXC);
-    HIP_TRY(launch_bin_fill(bp, c->stream));
+    const int worst = over[c->list_parity];
+    if (worst > MAXC)
+        return fail(PSM_ECAPACITY, "a tile has %d sphere candidates (limit %d): use a smaller tile shape", worst, MAXC);
     c->have_particles_lists = true;
     return PSM_OK;
 }
 
-// Rebuild the lists without waiting for the device: the counts are checked on
-// the device, which replaces the list bits of the error word (the fill and the
-// step kernel stay in bounds on capped lists); synchronising calls report them.
-static int rebuild_lists_async(psm_ctx* c) {
-    BinParams bp;
-    bp.boxes = c->d_boxes;
-    bp.part_box = c->d_partbox;
-    bp.P = c->P;
-    bp.tile_cnt = c->d_tcnt;
-    bp.tile_off = c->d_toff;
-    bp.tile_pid = c->d_tpid;
-    bp.tile_slot = c->d_tslot;
-    bp.partial = c->d_partial;
-    bp.P_total = c->P_total;
-    bp.T_total = c->T_total;
-    bp.ts = c->ts;
-    bp.cap = c->L.cap_max;
-    HIP_TRY(launch_bin(bp, c->d_misc, c->d_scan, c->stream));
-    HIP_TRY(launch_check_lists(c->d_misc, c->L.cap_max, c->d_flags, 1, c->stream));
-    HIP_TRY(launch_bin_fill(bp, c->stream));
-    c->have_particles_lists = true;
-    return PSM_OK;
-}
-
-// Every synchronising call copies the device error word with its read-back
-// (sync_with_flags) and reports it afterwards (take_flags), which clears the
-// word on the device. A list overflow (device-built lists) or, in strict-slot
+// Every synchronising call copies the device error words with its read-back
+// (sync_with_flags) and reports them afterwards (take_flags), which clears the
+// words on the device. A list overflow (device-built lists) or, in strict-slot
 // mode, a third overlap makes the context refuse to step until
 // psm_set_particles; a bad psm_get_pdfs_at index is an argument error.
 static int sync_with_flags(psm_ctx* c) {
-    HIP_TRY(hipMemcpyAsync(c->h_flags, c->d_flags, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(hipMemcpyAsync(c->h_flags, c->d_flags, sizeof(int) * ERR_WORDS, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
     return PSM_OK;
 }
 
 static int take_flags(psm_ctx* c) {
-    const int f = *c->h_flags;
-    if (f == 0) return PSM_OK;
-    *c->h_flags = 0;
-    HIP_TRY(launch_fill_int(c->d_flags, 1, 0, c->stream));
-    if (f & FLAG_LIST_ENTRIES) {
-        c->have_particles_lists = false;
-        return fail(PSM_ECAPACITY, "the spheres need more tile-list entries than the context holds");
-    }
-    if (f & FLAG_LIST_TILE) {
+    const int f = c->h_flags[0];
+    const bool list_tile = c->h_flags[1] != 0 || c->h_flags[2] != 0;   // only the current lists' word is ever set
+    if (f == 0 && !list_tile) return PSM_OK;
+    std::fill(c->h_flags, c->h_flags + ERR_WORDS, 0);
+    HIP_TRY(launch_fill_int(c->d_flags, ERR_WORDS, 0, c->stream));
+    if (list_tile) {
         c->have_particles_lists = false;
         return fail(PSM_ECAPACITY, "the spheres put more than %d candidates into a tile: use a smaller tile shape",
                     MAXC);
@@ -589,15 +590,13 @@ extern "C" int psm_create(const psm_box_desc* boxes, int nbox, int storage, doub
     c->P.acc = (double*)(c->ws + L.off_acc);
     c->P.fprev = (double*)(c->ws + L.off_fprev);
     c->P.prev_ok = (int*)(c->ws + L.off_prevok);
-    c->d_tcnt = (int*)(c->ws + L.off_tcnt);
-    c->d_toff = (int*)(c->ws + L.off_toff);
-    c->d_tpid = (int*)(c->ws + L.off_tpid);
-    c->d_tslot = (int*)(c->ws + L.off_tslot);
+    c->d_tcnt[0] = (int*)(c->ws + L.off_tcnt);
+    c->d_tcnt[1] = c->d_tcnt[0] + L.T_max;
+    c->d_tent = (int2*)(c->ws + L.off_tent);
     c->d_partial = (double*)(c->ws + L.off_partial);
     c->d_misc = (int*)(c->ws + L.off_misc);
     c->d_flags = (int*)(c->P.acc + 6 * P1);
     c->d_statpart = (double*)(c->ws + L.off_statpart);
-    c->d_scan = (int*)(c->ws + L.off_scan);
     c->last_xr.assign(nbox, std::vector<double>());
 
     int err = PSM_OK;
@@ -610,7 +609,7 @@ extern "C" int psm_create(const psm_box_desc* boxes, int nbox, int storage, doub
     if (err) { delete c; return err; }
     c->h_read = c->h_stage + 2 * c->h_half;
     c->h_flags = (int*)(c->h_read + 9 * P1);   // inside the read area's padding
-    *c->h_flags = 0;
+    std::fill(c->h_flags, c->h_flags + ERR_WORDS, 0);
     c->h_rb = c->h_read + 9 * P1 + 64;
     {
         const char* e = std::getenv("PSM_STRICT_SLOTS");
@@ -629,7 +628,7 @@ extern "C" int psm_create(const psm_box_desc* boxes, int nbox, int storage, doub
         for (int p = 0; p < boxes[b].max_particles; ++p) partbox[c->box[b].part_base + p] = b;
     hip_ok(hipMemcpyAsync(c->d_partbox, partbox.data(), sizeof(int) * P1, hipMemcpyHostToDevice, c->stream),
            "upload part_box");
-    hip_ok(hipMemsetAsync(c->P.acc, 0, sizeof(double) * 6 * P1 + 64, c->stream), "clear forces and error word");
+    hip_ok(hipMemsetAsync(c->P.acc, 0, sizeof(double) * 6 * P1 + 64, c->stream), "clear forces and error words");
     hip_ok(hipMemsetAsync(pt, 0, sizeof(double) * 11 * P1, c->stream), "clear particles");
     hip_ok(hipMemsetAsync(c->P.fprev, 0, sizeof(double) * 6 * P1, c->stream), "clear previous forces");
     hip_ok(hipMemsetAsync(c->P.prev_ok, 0, sizeof(int) * P1, c->stream), "clear previous-force flags");
@@ -898,9 +897,9 @@ static int step_params(psm_ctx* c, int parity, StepParams& kp) {
     kp.box_tile_base = c->d_tbase;
     kp.nbox = c->nbox;
     kp.P = c->P;
-    kp.tile_off = c->d_toff;
-    kp.tile_pid = c->d_tpid;
-    kp.tile_slot = c->d_tslot;
+    kp.tile_cnt = c->d_tcnt[c->list_parity];
+    kp.tile_ent = c->d_tent;
+    kp.list_cap = c->L.list_cap;
     kp.partial = c->d_partial;
     kp.T_total = c->T_total;
     kp.tx = c->ts.tx; kp.ty = c->ts.ty; kp.tz = c->ts.tz;
@@ -911,20 +910,6 @@ static int step_params(psm_ctx* c, int parity, StepParams& kp) {
     kp.flags = c->d_flags;
     kp.queue = c->ts.persistent ? c->d_misc + 32 : nullptr;   // ints 32..39 of the counter block
     return PSM_OK;
-}
-
-static ReduceParams reduce_params(psm_ctx* c) {
-    ReduceParams rp;
-    rp.boxes = c->d_boxes;
-    rp.nbox = c->nbox;
-    rp.part_box = c->d_partbox;
-    rp.P = c->P;
-    rp.tile_off = c->d_toff;
-    rp.tile_pid = c->d_tpid;
-    rp.partial = c->d_partial;
-    rp.P_total = c->P_total;
-    rp.ts = c->ts;
-    return rp;
 }
 
 // Kernel timing keeps a fixed pool of events (created when timing is turned
@@ -965,7 +950,9 @@ static hipEvent_t next_event(psm_ctx* c) {
     return c->ev[c->ev_used++];
 }
 
-static int enqueue_step(psm_ctx* c, bool timed) {
+// The step kernel, then per sphere the force reduction; with a scheme, the
+// sphere update and the new lists in the same launch.
+static int enqueue_step(psm_ctx* c, bool timed, int scheme = SCHEME_NONE, double dt = 0.0) {
     StepParams kp;
     step_params(c, c->parity, kp);
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -980,27 +967,34 @@ static int enqueue_step(psm_ctx* c, bool timed) {
     if (kp.queue) HIP_TRY(launch_fill_int(kp.queue, NXCD, 0, c->stream));
     HIP_TRY(launch_step(c->storage, c->map_mode, c->ts.filter != 0, kp, c->grid, c->stream));
     if (timed) HIP_TRY(hipEventRecord(e1, c->stream));
-    HIP_TRY(launch_reduce(reduce_params(c), c->stream));
+    SphereParams sp = sphere_params(c);
+    sp.dt = dt;
+    HIP_TRY(launch_spheres(true, scheme, scheme != SCHEME_NONE, sp, c->stream));
+    if (scheme != SCHEME_NONE && c->P_total > 0) c->list_parity ^= 1;
     c->parity ^= 1;
     c->rb_valid = false;
     return PSM_OK;
 }
 
-static int build_graph(psm_ctx* c, int start_parity) {
+// Capture 10 steps (with a scheme, 10 step + sphere update pairs) from the
+// current parities, which they return to, into *out (replaced).
+static int build_graph(psm_ctx* c, hipGraphExec_t* out, int scheme = SCHEME_NONE, double dt = 0.0) {
     hipGraph_t g = nullptr;
     HIP_TRY(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-    int saved = c->parity;
-    c->parity = start_parity;
+    const int parity = c->parity, list_parity = c->list_parity;
     int rc = PSM_OK;
-    for (int s = 0; s < kGraphSteps && rc == PSM_OK; ++s) rc = enqueue_step(c, false);
-    c->parity = saved;
+    for (int s = 0; s < kGraphSteps && rc == PSM_OK; ++s) rc = enqueue_step(c, false, scheme, dt);
+    c->parity = parity;
+    c->list_parity = list_parity;
     hipError_t e = hipStreamEndCapture(c->stream, &g);
     if (rc != PSM_OK) {
         if (g) (void)hipGraphDestroy(g);
         return rc;
     }
     if (e != hipSuccess) return fail(PSM_EHIP, "hipStreamEndCapture: %s", hipGetErrorString(e));
-    e = hipGraphInstantiate(&c->gexec[start_parity], g, nullptr, nullptr, 0);
+    if (*out) (void)hipGraphExecDestroy(*out);
+    *out = nullptr;
+    e = hipGraphInstantiate(out, g, nullptr, nullptr, 0);
     (void)hipGraphDestroy(g);
     if (e != hipSuccess) return fail(PSM_EHIP, "hipGraphInstantiate: %s", hipGetErrorString(e));
     return PSM_OK;
@@ -1015,12 +1009,12 @@ extern "C" int psm_step(psm_ctx* c, int nsteps) {
     int left = nsteps;
     if (c->use_graph && !c->timing) {
         while (left >= kGraphSteps) {
-            int p = c->parity;
-            if (!c->gexec[p]) {
-                int rc = build_graph(c, p);
+            hipGraphExec_t& g = c->gexec[c->parity][c->list_parity];
+            if (!g) {
+                int rc = build_graph(c, &g);
                 if (rc) return rc;
             }
-            HIP_TRY(hipGraphLaunch(c->gexec[p], c->stream));
+            HIP_TRY(hipGraphLaunch(g, c->stream));
             left -= kGraphSteps;   // an even count: the parity is unchanged
         }
     }
@@ -1029,10 +1023,10 @@ extern "C" int psm_step(psm_ctx* c, int nsteps) {
         if (rc) return rc;
     }
     if (c->rb_on && nsteps > 0) {
-        // the force sums of every box and the error word, one contiguous copy
+        // the force sums of every box and the error words, one contiguous copy
         const size_t P1 = (size_t)std::max(c->P_total, 1);
-        HIP_TRY(hipMemcpyAsync(c->h_rb, c->P.acc, sizeof(double) * 6 * P1 + sizeof(int), hipMemcpyDeviceToHost,
-                               c->stream));
+        HIP_TRY(hipMemcpyAsync(c->h_rb, c->P.acc, sizeof(double) * 6 * P1 + sizeof(int) * ERR_WORDS,
+                               hipMemcpyDeviceToHost, c->stream));
         HIP_TRY(hipEventRecord(c->rb_ev, c->stream));
         c->rb_valid = true;
     }
@@ -1056,10 +1050,11 @@ extern "C" int psm_get_forces(psm_ctx* c, int box, double* F, double* T) {
     if (c->rb_valid) {
         // the copy psm_step made: wait for it, not for work enqueued after it
         HIP_TRY(hipEventSynchronize(c->rb_ev));
-        int f = *(const int*)(c->h_rb + 6 * (size_t)std::max(c->P_total, 1));
+        const int* w = (const int*)(c->h_rb + 6 * (size_t)std::max(c->P_total, 1));
+        int f = w[0];
         if (!c->strict_slots) f &= ~FLAG_SLOT_OVERFLOW;
-        // an error bit: report it the usual way, from the end of the stream
-        if (f && ((rc = sync_with_flags(c)) || (rc = take_flags(c)))) return rc;
+        // an error: report it the usual way, from the end of the stream
+        if ((f || w[1] || w[2]) && ((rc = sync_with_flags(c)) || (rc = take_flags(c)))) return rc;
         st = c->h_rb + 6LL * c->box[box].part_base;
     } else {
         HIP_TRY(hipMemcpyAsync(c->h_read, c->P.acc + 6LL * c->box[box].part_base, sizeof(double) * 6 * n,
@@ -1081,7 +1076,8 @@ extern "C" int psm_get_solid_fraction(psm_ctx* c, int box, double* B, int* pid) 
     if (!B || !pid) return fail(PSM_EINVAL, "B/pid is NULL");
     unsigned long long* dropped = (unsigned long long*)(c->d_misc + 8);
     HIP_TRY(hipMemsetAsync(dropped, 0, sizeof(unsigned long long), c->stream));
-    HIP_TRY(launch_map_dense(c->box[box], c->P, c->d_toff, c->d_tpid, c->ts, B, pid, dropped, c->stream));
+    HIP_TRY(launch_map_dense(c->box[box], c->P, c->d_tcnt[c->list_parity], c->d_tent, c->L.list_cap, c->ts, B, pid,
+                             dropped, c->stream));
     return PSM_OK;
 }
 
@@ -1092,7 +1088,8 @@ extern "C" int psm_get_stats(psm_ctx* c, int box, double* mass, double* momentum
     HIP_TRY(launch_stats(c->storage, c->box[box], c->parity, c->h_inv, c->d_statpart, out, c->stream));
     unsigned long long* dropped = (unsigned long long*)(c->d_misc + 8);
     HIP_TRY(hipMemsetAsync(dropped, 0, sizeof(unsigned long long), c->stream));
-    HIP_TRY(launch_map_dense(c->box[box], c->P, c->d_toff, c->d_tpid, c->ts, nullptr, nullptr, dropped, c->stream));
+    HIP_TRY(launch_map_dense(c->box[box], c->P, c->d_tcnt[c->list_parity], c->d_tent, c->L.list_cap, c->ts, nullptr,
+                             nullptr, dropped, c->stream));
     double* st = c->h_read;
     HIP_TRY(hipMemcpyAsync(st, out, sizeof(double) * 4, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipMemcpyAsync(st + 4, dropped, sizeof(unsigned long long), hipMemcpyDeviceToHost, c->stream));
@@ -1137,13 +1134,13 @@ extern "C" int psm_set_drift_check(psm_ctx* c, int box, double rel_tol) {
 extern "C" int psm_set_strict_slots(psm_ctx* c, int enable) {
     if (!c) return fail(PSM_EINVAL, "ctx is NULL");
     // overlaps seen before the switch do not count
-    HIP_TRY(hipMemcpyAsync(c->h_flags, c->d_flags, sizeof(int), hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
+    int rc = sync_with_flags(c);
+    if (rc) return rc;
     if (*c->h_flags & FLAG_SLOT_OVERFLOW) {
         *c->h_flags &= ~FLAG_SLOT_OVERFLOW;
         HIP_TRY(launch_fill_int(c->d_flags, 1, *c->h_flags, c->stream));
     }
-    *c->h_flags = 0;
+    std::fill(c->h_flags, c->h_flags + ERR_WORDS, 0);
     c->strict_slots = enable != 0;
     return PSM_OK;
 }
@@ -1165,17 +1162,13 @@ extern "C" int psm_set_dynamics(psm_ctx* c, int box, double density_ratio, const
     return upload_box_table(c);
 }
 
-// Sphere update and device-side re-binning (no host state is touched, so
-// that it can be captured).
+// Sphere update and device-side re-binning.
 static int enqueue_integrate(psm_ctx* c, double dt, int scheme) {
-    IntParams ip;
-    ip.boxes = c->d_boxes;
-    ip.part_box = c->d_partbox;
-    ip.P = c->P;
-    ip.P_total = c->P_total;
-    ip.dt = dt;
-    HIP_TRY(launch_integrate(scheme == PSM_EULER ? SCHEME_EULER : SCHEME_VERLET, ip, c->stream));
-    return rebuild_lists_async(c);
+    SphereParams sp = sphere_params(c);
+    sp.dt = dt;
+    HIP_TRY(launch_spheres(false, scheme, true, sp, c->stream));
+    if (c->P_total > 0) c->list_parity ^= 1;
+    return PSM_OK;
 }
 
 static int check_dynamics_args(psm_ctx* c, double dt, int scheme) {
@@ -1189,37 +1182,10 @@ static int check_dynamics_args(psm_ctx* c, double dt, int scheme) {
 extern "C" int psm_integrate(psm_ctx* c, double dt, int scheme) {
     int rc = check_dynamics_args(c, dt, scheme);
     if (rc) return rc;
-    rc = enqueue_integrate(c, dt, scheme);
+    rc = enqueue_integrate(c, dt, scheme == PSM_EULER ? SCHEME_EULER : SCHEME_VERLET);
     // the host copies of positions are stale from here on
     for (auto& v : c->last_xr) v.clear();
     return rc;
-}
-
-static int build_dyn_graph(psm_ctx* c, int start_parity, double dt, int scheme) {
-    hipGraph_t g = nullptr;
-    HIP_TRY(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-    int saved = c->parity;
-    c->parity = start_parity;
-    int rc = PSM_OK;
-    for (int s = 0; s < kGraphSteps && rc == PSM_OK; ++s) {
-        rc = enqueue_step(c, false);
-        if (rc == PSM_OK) rc = enqueue_integrate(c, dt, scheme);
-    }
-    c->parity = saved;
-    hipError_t e = hipStreamEndCapture(c->stream, &g);
-    if (rc != PSM_OK) {
-        if (g) (void)hipGraphDestroy(g);
-        return rc;
-    }
-    if (e != hipSuccess) return fail(PSM_EHIP, "hipStreamEndCapture: %s", hipGetErrorString(e));
-    if (c->gexec_dyn[start_parity]) (void)hipGraphExecDestroy(c->gexec_dyn[start_parity]);
-    c->gexec_dyn[start_parity] = nullptr;
-    e = hipGraphInstantiate(&c->gexec_dyn[start_parity], g, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(g);
-    if (e != hipSuccess) return fail(PSM_EHIP, "hipGraphInstantiate: %s", hipGetErrorString(e));
-    c->gdyn_dt[start_parity] = dt;
-    c->gdyn_scheme[start_parity] = scheme;
-    return PSM_OK;
 }
 
 extern "C" int psm_run(psm_ctx* c, int nsteps, double dt, int scheme) {
@@ -1228,21 +1194,24 @@ extern "C" int psm_run(psm_ctx* c, int nsteps, double dt, int scheme) {
     if (nsteps < 0) return fail(PSM_EINVAL, "nsteps < 0");
     // graph replays enqueue steps without passing through enqueue_step
     if (nsteps > 0) c->rb_valid = false;
+    const int sch = scheme == PSM_EULER ? SCHEME_EULER : SCHEME_VERLET;
     int left = nsteps;
     if (c->use_graph && !c->timing) {
         while (left >= kGraphSteps) {
-            int p = c->parity;
-            if (!c->gexec_dyn[p] || c->gdyn_dt[p] != dt || c->gdyn_scheme[p] != scheme) {
-                rc = build_dyn_graph(c, p, dt, scheme);
+            psm_ctx::DynGraph& g = c->gdyn[c->parity][c->list_parity];
+            if (!g.exec || g.dt != dt || g.scheme != sch) {
+                g.scheme = SCHEME_NONE;   // until the new graph is there
+                rc = build_graph(c, &g.exec, sch, dt);
                 if (rc) return rc;
+                g.dt = dt;
+                g.scheme = sch;
             }
-            HIP_TRY(hipGraphLaunch(c->gexec_dyn[p], c->stream));
+            HIP_TRY(hipGraphLaunch(g.exec, c->stream));
             left -= kGraphSteps;   // an even count: the parity is unchanged
         }
     }
     for (; left > 0; --left) {
-        rc = enqueue_step(c, c->timing);
-        if (rc == PSM_OK) rc = enqueue_integrate(c, dt, scheme);
+        rc = enqueue_step(c, c->timing, sch, dt);
         if (rc) return rc;
     }
     if (nsteps > 0)

@@ -261,9 +261,9 @@ struct StepParams {
     const int* box_tile_base;   // [nbox+1]
     int nbox;
     Particles P;
-    const int* tile_off;        // [T+1]
-    const int* tile_pid;        // [entries] global particle ids
-    const int* tile_slot;       // [entries] force-partial slot of each entry
+    const int* tile_cnt;        // [T] spheres of each tile's list (uncapped)
+    const int2* tile_ent;       // [T][list_cap] global particle id and force-partial slot
+    int list_cap;
     double* partial;            // [slots][6]
     int T_total;
     int tx, ty, tz;
@@ -274,50 +274,30 @@ struct StepParams {
     int* queue;                 // [NXCD] tile counters of the persistent grid (zeroed before the launch), or null
 };
 
-struct ReduceParams {
+// Work per sphere (one wave each): any of the force reduction, the sphere
+// update and the tile lists.
+enum { SCHEME_NONE = -1, SCHEME_EULER = 0, SCHEME_VERLET = 1 };
+struct SphereParams {
     const BoxDev* boxes;
-    int nbox;
     const int* part_box;        // [P] box of each global particle slot
     Particles P;
-    const int* tile_off;
-    const int* tile_pid;
-    const double* partial;
+    double* partial;            // [slots][6] force partials; zeroed for an entry a full list drops
     int P_total;
     TileShape ts;
-};
-
-struct BinParams {
-    const BoxDev* boxes;
-    const int* part_box;
-    Particles P;
-    int* tile_cnt;
-    int* tile_off;
-    int* tile_pid;
-    int* tile_slot;             // [entries] force-partial slot of each entry
-    double* partial;            // [slots][6], zeroed for an entry a full list drops
-    int P_total;
+    double dt;                  // sphere update
+    // tile lists: the counts filled here are zero on entry; those of the
+    // lists they replace are zeroed for the next build
+    int *cnt, *cnt_old;         // [T]
+    int2* ent;                  // [T][list_cap]
+    int list_cap;
     int T_total;
-    TileShape ts;
-    long long cap;              // entries tile_pid holds
-};
-
-// Sphere integration (explicit Euler or velocity Verlet) of every particle.
-enum { SCHEME_EULER = 0, SCHEME_VERLET = 1 };
-struct IntParams {
-    const BoxDev* boxes;
-    const int* part_box;
-    Particles P;
-    int P_total;
-    double dt;
+    int *over, *over_old;       // largest uncapped count where it exceeds MAXC, else 0
 };
 
 hipError_t launch_step(int storage, int map, bool filt, const StepParams& kp, int grid, hipStream_t st);
 hipError_t launch_pattern_copy(int storage, bool shifted, const StepParams& kp, int grid, hipStream_t st);
 int step_blocks_per_cu(int storage, int map, bool filt);
-hipError_t launch_reduce(const ReduceParams& rp, hipStream_t st);
-int scan_chunks(int n);
-hipError_t launch_bin(const BinParams& bp, int* stats, int* scratch, hipStream_t st);
-hipError_t launch_bin_fill(const BinParams& bp, hipStream_t st);
+hipError_t launch_spheres(bool reduce, int scheme, bool bin, const SphereParams& sp, hipStream_t st);
 hipError_t launch_set_pdfs(int storage, const BoxDev& bx, int parity, const double* f, float scale, hipStream_t st);
 hipError_t launch_set_equilibrium(int storage, const BoxDev& bx, int parity, const double* rho, const double* u,
                                   float scale, hipStream_t st);
@@ -326,25 +306,21 @@ hipError_t launch_get_pdfs_at(int storage, const BoxDev& bx, int parity, const i
                               float inv, int* flags, hipStream_t st);
 hipError_t launch_macroscopic(int storage, const BoxDev& bx, int parity, double* rho, double* u, float inv,
                               hipStream_t st);
-hipError_t launch_map_dense(const BoxDev& bx, const Particles& P, const int* tile_off, const int* tile_pid,
-                            TileShape ts, double* B, int* pid, unsigned long long* dropped, hipStream_t st);
+hipError_t launch_map_dense(const BoxDev& bx, const Particles& P, const int* tile_cnt, const int2* tile_ent,
+                            int list_cap, TileShape ts, double* B, int* pid, unsigned long long* dropped, hipStream_t st);
 int stats_blocks();
 hipError_t launch_stats(int storage, const BoxDev& bx, int parity, float inv, double* part, double* out,
                         hipStream_t st);
 hipError_t launch_stream_copy(const void* src, void* dst, size_t bytes, hipStream_t st);
-hipError_t launch_integrate(int scheme, const IntParams& ip, hipStream_t st);
 // Bits of the device error word of a context, set by kernels and read and
 // cleared by the host at its next synchronising call.
 enum {
-    FLAG_LIST_ENTRIES = 1,    // the tile lists need more entries than the context holds
-    FLAG_LIST_TILE = 2,       // a tile lists more than MAXC spheres
     FLAG_SLOT_OVERFLOW = 4,   // a step met a cell overlapped by more than two spheres
     FLAG_BAD_CELL = 8         // psm_get_pdfs_at was given a cell index outside the box
 };
-// Replace the list bits of err: FLAG_LIST_ENTRIES if the lists need more than
-// cap entries, FLAG_LIST_TILE if a tile lists more than MAXC spheres (report =
-// 0: clear the list bits only)
-hipError_t launch_check_lists(const int* stats, long long cap, int* err, int report, hipStream_t st);
+// Two words follow the error word, one per list parity: the largest uncapped
+// count of the lists of that parity where a tile lists more than MAXC spheres.
+constexpr int ERR_WORDS = 3;
 hipError_t launch_fill_int(int* a, long long n, int v, hipStream_t st);
 // FP64 mass and momentum of a canonical field [19][N] into out[4] (device),
 // with the partial sums in the library's static per-GPU array

@@ -16,6 +16,7 @@
 // and sums the per-sphere force/torque of its tile deterministically.
 #include "psm_internal.h"
 
+#include <algorithm>
 #include <mutex>
 
 namespace psm {
@@ -390,7 +391,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(S::DEV ? PSM
     const int t_end = (int)(((long long)kp.T_total * (xcd + 1)) / NXCD);
 
     const PSM_CONST BoxDev* boxes = cptr(kp.boxes);
-    const PSM_CONST int* tile_off = cptr(kp.tile_off);
+    const PSM_CONST int* tile_cnt = cptr(kp.tile_cnt);
 
     // Tile order: with a queue (persistent grid), the workgroups of a die take
     // the next tile of its eighth from that die's counter as they finish one;
@@ -424,8 +425,8 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(S::DEV ? PSM
         const int tcx = lt % ntx;
         const int tcy = (lt / ntx) % nty;
         const int tcz = lt / (ntx * nty);
-        const int e0 = tile_off[t];
-        const int nc = tile_off[t + 1] - e0;   // at most MAXC: the scan caps every list
+        const int nc = tile_cnt[t] < kp.list_cap ? tile_cnt[t] : kp.list_cap;   // at most MAXC
+        const int2* ent = kp.tile_ent + (long long)t * kp.list_cap;
         const double Lx = bx.L[0], Ly = bx.L[1], Lz = bx.L[2];
         const double hLx = bx.halfL[0], hLy = bx.halfL[1], hLz = bx.halfL[2];
         // reference point of the FP32 geometry in cell coordinates: the tile's
@@ -435,9 +436,10 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(S::DEV ? PSM
 
         if (nc > 0) {
             for (int c = tid; c < nc; c += WG) {
-                int p = kp.tile_pid[e0 + c];
+                const int2 e = ent[c];
+                const int p = e.x;
                 s_pid[c] = p;
-                s_slot[c] = kp.tile_slot[e0 + c];
+                s_slot[c] = e.y;
                 const double px = kp.P.x[p], py = kp.P.y[p], pz = kp.P.z[p], pr = kp.P.r[p], pfr = kp.P.fr[p];
                 s_px[c] = px; s_py[c] = py; s_pz[c] = pz;
                 s_pr[c] = pr; s_pfr[c] = pfr;
@@ -878,78 +880,155 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(S::DEV ? PSM
 }
 
 // ---------------------------------------------------------------------------
-// Per-sphere force/torque: sum the tile partials of every tile of the
-// sphere's bounding box, in a fixed tile order (deterministic).
-// One 64-wide wave per sphere: lane l takes the sphere's tiles l, l+64, ...
-// (in the fixed bounding-box order), then a fixed butterfly adds the lanes.
-__global__ __launch_bounds__(256) void k_reduce_forces(ReduceParams rp) {
-    const int lane = threadIdx.x & 63;
-    const int p = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (p >= rp.P_total) return;   // whole wave leaves together
-    const int b = rp.part_box[p];
-    const BoxDev& bx = rp.boxes[b];
-    double acc[6] = {0, 0, 0, 0, 0, 0};
-    if (p - bx.part_base < bx.np) {
-        int lo, hi;
-        aabb_cells(rp.P.x[p], rp.P.r[p], lo, hi);
-        AxisTiles ax = axis_tiles(lo, hi, bx.nx, rp.ts.tx, bx.ntx);
-        aabb_cells(rp.P.y[p], rp.P.r[p], lo, hi);
-        AxisTiles ay = axis_tiles(lo, hi, bx.ny, rp.ts.ty, bx.nty);
-        aabb_cells(rp.P.z[p], rp.P.r[p], lo, hi);
-        AxisTiles az = axis_tiles(lo, hi, bx.nz, rp.ts.tz, bx.ntz);
-        const int ntot = ax.count() * ay.count() * az.count();
-        // the sphere's slots: one per tile of its bounding box, in that order
-        const double* pp = rp.partial + ((long long)bx.pbase + (long long)(p - bx.part_base) * bx.pstride) * 6;
-        for (int k = lane; k < ntot; k += 64) {
-#pragma unroll
-            for (int c = 0; c < 6; ++c) acc[c] += pp[(long long)k * 6 + c];
-        }
-    }
-#pragma unroll
-    for (int c = 0; c < 6; ++c) {
-        double v = wave_sum(acc[c]);
-        if (lane == 0) rp.P.acc[(long long)p * 6 + c] = v;
-    }
+// Work per sphere, one 64-wide wave each:
+//   REDUCE  force and torque: the sum of the tile partials over the tiles of
+//           the sphere's bounding box; lane l takes tiles l, l + 64, ... in
+//           the fixed bounding-box order, then a fixed butterfly adds the
+//           lanes (deterministic).
+//   SCHEME  sphere update (Sec. 2.2.2) for collision-free spheres:
+//           m = rho_p (4/3) pi r^3, I = (2/5) m r^2; the total force is the
+//           hydrodynamic force of the last step plus m times the box's
+//           external acceleration, the torque is the hydrodynamic torque.
+//             Euler:  x += dt U;  U += dt F/m;  Om += dt T/I.
+//             Verlet (eqs. 15-16), once after each fluid step: complete the
+//             velocity with the previous and the new force (skipped until a
+//             previous force exists), then advance the position with the new one.
+//           Positions are wrapped into [0, L) along periodic axes; along an
+//           axis with walls a centre leaving [r + 1, L - r - 1] is mirrored
+//           back and its velocity component reversed (elastic contact keeping
+//           the mapping's one-cell gap). No fused multiply-add, so that the
+//           update is reproducible bit for bit; every lane computes it.
+//   BIN     tile lists (the paper's sub-block particle lists): the lanes walk
+//           the tiles of the (new) bounding box and append the sphere to each.
+// Latency bound: a few dependent loads and an atomic per wave, a few us in
+// all, so what counts is the number of launches. Lists of a fixed capacity
+// are built in one launch (counting, scanning and filling compact lists took
+// seven of 2-5 us each), and psm_run does all three parts in one: 9 launches
+// beside the step kernel became 1.
+__device__ inline void box_tiles(const BoxDev& bx, const TileShape& ts, double x, double y, double z, double r,
+                                 AxisTiles& ax, AxisTiles& ay, AxisTiles& az) {
+    int lo, hi;
+    aabb_cells(x, r, lo, hi);
+    ax = axis_tiles(lo, hi, bx.nx, ts.tx, bx.ntx);
+    aabb_cells(y, r, lo, hi);
+    ay = axis_tiles(lo, hi, bx.ny, ts.ty, bx.nty);
+    aabb_cells(z, r, lo, hi);
+    az = axis_tiles(lo, hi, bx.nz, ts.tz, bx.ntz);
 }
 
-// ---------------------------------------------------------------------------
-// Tile binning (the paper's sub-block particle lists, built on the device):
-// count -> exclusive scan -> fill.
-// One 64-wide wave per sphere; its lanes walk the bounding box's tiles.
-template <bool FILL>
-__global__ __launch_bounds__(256) void k_bin(BinParams bp) {
+template <bool REDUCE, int SCHEME, bool BIN>
+__global__ __launch_bounds__(256) void k_spheres(SphereParams sp) {
+#pragma clang fp contract(off)
+    if (BIN) {
+        // the counts of the lists being replaced, for the build after this one
+        const int i0 = blockIdx.x * 256 + threadIdx.x;
+        for (int i = i0; i < sp.T_total; i += gridDim.x * 256) sp.cnt_old[i] = 0;
+        if (i0 == 0) *sp.over_old = 0;
+    }
     const int lane = threadIdx.x & 63;
     const int p = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (p >= bp.P_total) return;
-    const int b = bp.part_box[p];
-    const BoxDev& bx = bp.boxes[b];
-    if (p - bx.part_base >= bx.np) return;
-    int lo, hi;
-    aabb_cells(bp.P.x[p], bp.P.r[p], lo, hi);
-    AxisTiles ax = axis_tiles(lo, hi, bx.nx, bp.ts.tx, bx.ntx);
-    aabb_cells(bp.P.y[p], bp.P.r[p], lo, hi);
-    AxisTiles ay = axis_tiles(lo, hi, bx.ny, bp.ts.ty, bx.nty);
-    aabb_cells(bp.P.z[p], bp.P.r[p], lo, hi);
-    AxisTiles az = axis_tiles(lo, hi, bx.nz, bp.ts.tz, bx.ntz);
-    const int nxt = ax.count(), nyt = ay.count(), nzt = az.count();
-    const int ntot = nxt * nyt * nzt;
-    for (int k = lane; k < ntot; k += 64) {
-        int kx = k % nxt, ky = (k / nxt) % nyt, kz = k / (nxt * nyt);
-        int t = bx.tile_base + ax.at(kx) + bx.ntx * (ay.at(ky) + bx.nty * az.at(kz));
-        if (!FILL) {
-            atomicAdd(&bp.tile_cnt[t], 1);
-        } else {
-            // a list holds at most MAXC spheres (the scan caps it; the excess
-            // is flagged from the uncapped maximum)
-            int pos = atomicSub(&bp.tile_cnt[t], 1) - 1;
-            long long e = (long long)bp.tile_off[t] + pos;
-            const long long slot = (long long)bx.pbase + (long long)(p - bx.part_base) * bx.pstride + k;
-            if (pos < MAXC && e < bp.cap) {
-                bp.tile_pid[e] = p;
-                bp.tile_slot[e] = (int)slot;
-            } else {
+    if (p >= sp.P_total) return;   // whole wave leaves together
+    const BoxDev& bx = sp.boxes[sp.part_box[p]];
+    const int lp = p - bx.part_base;
+    const bool there = lp < bx.np;
+    const long long slot0 = (long long)bx.pbase + (long long)lp * bx.pstride;
+    double pos[3] = {sp.P.x[p], sp.P.y[p], sp.P.z[p]};
+    const double r = sp.P.r[p];
+    double acc[6];
+    if (REDUCE) {
 #pragma unroll
-                for (int c = 0; c < 6; ++c) bp.partial[slot * 6 + c] = 0.0;
+        for (int c = 0; c < 6; ++c) acc[c] = 0.0;
+        if (there) {
+            AxisTiles ax, ay, az;
+            box_tiles(bx, sp.ts, pos[0], pos[1], pos[2], r, ax, ay, az);
+            const int ntot = ax.count() * ay.count() * az.count();
+            // the sphere's slots: one per tile of its bounding box, in that order
+            const double* pp = sp.partial + slot0 * 6;
+            for (int k = lane; k < ntot; k += 64) {
+#pragma unroll
+                for (int c = 0; c < 6; ++c) acc[c] += pp[(long long)k * 6 + c];
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < 6; ++c) {
+            acc[c] = wave_sum(acc[c]);   // the same bits on every lane
+            if (lane == 0) sp.P.acc[6LL * p + c] = acc[c];
+        }
+    }
+    if (!there) return;
+    if (SCHEME != SCHEME_NONE) {
+        if (!REDUCE) {
+#pragma unroll
+            for (int c = 0; c < 6; ++c) acc[c] = sp.P.acc[6LL * p + c];
+        }
+        const double pi = 3.14159265358979323846;
+        const double dt = sp.dt;
+        const double m = bx.rho_p * (4.0 / 3.0) * pi * r * r * r;
+        const double inertia = 0.4 * m * r * r;
+        double* dpos[3] = {sp.P.x, sp.P.y, sp.P.z};
+        double* dvel[3] = {sp.P.ux, sp.P.uy, sp.P.uz};
+        double* dang[3] = {sp.P.ox, sp.P.oy, sp.P.oz};
+        double* fp = sp.P.fprev + 6LL * p;
+        const bool prev = SCHEME == SCHEME_VERLET && sp.P.prev_ok[p] != 0;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const double F = acc[a] + m * bx.accel[a];
+            const double T = acc[3 + a];
+            double x = pos[a], U = dvel[a][p], W = dang[a][p];
+            if (SCHEME == SCHEME_EULER) {
+                x = x + dt * U;
+                U = U + dt * F / m;
+                W = W + dt * T / inertia;
+            } else {
+                if (prev) {
+                    U = U + dt / (2.0 * m) * (fp[a] + F);
+                    W = W + dt / (2.0 * inertia) * (fp[3 + a] + T);
+                }
+                x = x + (dt * U + dt * dt / (2.0 * m) * F);
+                if (lane == 0) {
+                    fp[a] = F;
+                    fp[3 + a] = T;
+                }
+            }
+            const double L = bx.L[a];
+            const bool walled = a == 2 ? bx.walls != 0 : (bx.walls_xy & (1 << a)) != 0;
+            if (walled) {
+                // elastic contact one cell before the walls: mirror the centre back
+                // into [r + 1, L - r - 1] and reverse the normal velocity
+                const double lo = r + 1.0, hi = L - r - 1.0;
+                if (x < lo) { x = 2.0 * lo - x; U = -U; }
+                else if (x > hi) { x = 2.0 * hi - x; U = -U; }
+            } else {
+                double w = x - L * floor(x / L);
+                if (w >= L) w -= L;
+                if (w < 0.0) w = 0.0;
+                x = w;
+            }
+            pos[a] = x;
+            if (lane == 0) {
+                dpos[a][p] = x;
+                dvel[a][p] = U;
+                dang[a][p] = W;
+            }
+        }
+        if (SCHEME == SCHEME_VERLET && lane == 0) sp.P.prev_ok[p] = 1;
+    }
+    if (BIN) {
+        AxisTiles ax, ay, az;
+        box_tiles(bx, sp.ts, pos[0], pos[1], pos[2], r, ax, ay, az);
+        const int nxt = ax.count(), nyt = ay.count(), nzt = az.count();
+        const int ntot = nxt * nyt * nzt;
+        for (int k = lane; k < ntot; k += 64) {
+            const int kx = k % nxt, ky = (k / nxt) % nyt, kz = k / (nxt * nyt);
+            const int t = bx.tile_base + ax.at(kx) + bx.ntx * (ay.at(ky) + bx.nty * az.at(kz));
+            const int at = atomicAdd(&sp.cnt[t], 1);
+            if (at < sp.list_cap) {
+                sp.ent[(long long)t * sp.list_cap + at] = make_int2(p, (int)(slot0 + k));
+            } else {
+                // a list holds at most MAXC spheres: the excess is dropped and reported
+                atomicMax(sp.over, at + 1);
+#pragma unroll
+                for (int c = 0; c < 6; ++c) sp.partial[(slot0 + k) * 6 + c] = 0.0;
             }
         }
     }
@@ -959,101 +1038,6 @@ __global__ void k_fill_int(int* a, long long n, int v) {
     long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     long long stride = (long long)gridDim.x * blockDim.x;
     for (; i < n; i += stride) a[i] = v;
-}
-
-// Exclusive scan of cnt[0..n) into off[0..n] in three passes over chunks of
-// SCAN_CHUNK counts: chunk sums and maxima, a one-workgroup scan of the chunk
-// sums, then each chunk scanned with its offset. Every list length is capped
-// at MAXC; stats[0] = largest uncapped count, stats[1] = total of the lists.
-constexpr int SCAN_CHUNK = 1024;
-
-__device__ inline int block_incl_scan_256(int v, int* sh) {
-    const int tid = threadIdx.x;
-    sh[tid] = v;
-    __syncthreads();
-    for (int d = 1; d < 256; d <<= 1) {
-        int add = tid >= d ? sh[tid - d] : 0;
-        __syncthreads();
-        sh[tid] += add;
-        __syncthreads();
-    }
-    int r = sh[tid];
-    __syncthreads();
-    return r;
-}
-
-__global__ __launch_bounds__(256) void k_scan_chunks(const int* cnt, int n, int* csum, int* cmax) {
-    __shared__ int s_sum[256], s_max[256];
-    const int tid = threadIdx.x;
-    const int base = blockIdx.x * SCAN_CHUNK;
-    int sum = 0, mx = 0;
-    for (int k = 0; k < SCAN_CHUNK / 256; ++k) {
-        int i = base + k * 256 + tid;
-        int v = i < n ? cnt[i] : 0;
-        sum += v < MAXC ? v : MAXC;   // list lengths are capped at MAXC
-        mx = v > mx ? v : mx;         // the uncapped maximum reports an excess
-    }
-    s_sum[tid] = sum;
-    s_max[tid] = mx;
-    __syncthreads();
-    for (int d = 128; d > 0; d >>= 1) {
-        if (tid < d) {
-            s_sum[tid] += s_sum[tid + d];
-            s_max[tid] = s_max[tid] > s_max[tid + d] ? s_max[tid] : s_max[tid + d];
-        }
-        __syncthreads();
-    }
-    if (tid == 0) {
-        csum[blockIdx.x] = s_sum[0];
-        cmax[blockIdx.x] = s_max[0];
-    }
-}
-
-__global__ __launch_bounds__(256) void k_scan_sums(int* csum, const int* cmax, int nchunk, int* stats) {
-    __shared__ int sh[256];
-    __shared__ int s_carry, s_max;
-    const int tid = threadIdx.x;
-    if (tid == 0) { s_carry = 0; s_max = 0; }
-    __syncthreads();
-    int mymax = 0;
-    for (int base = 0; base < nchunk; base += 256) {
-        int i = base + tid;
-        int v = i < nchunk ? csum[i] : 0;
-        mymax = (i < nchunk && cmax[i] > mymax) ? cmax[i] : mymax;
-        int inc = block_incl_scan_256(v, sh);
-        if (i < nchunk) csum[i] = s_carry + inc - v;   // exclusive offset of chunk i
-        __syncthreads();
-        if (tid == 255) s_carry += inc;
-        __syncthreads();
-    }
-    atomicMax(&s_max, mymax);
-    __syncthreads();
-    if (tid == 0) {
-        stats[0] = s_max;
-        stats[1] = s_carry;
-    }
-}
-
-__global__ __launch_bounds__(256) void k_scan_apply(const int* cnt, int n, const int* coff, int* off,
-                                                    const int* stats) {
-    __shared__ int sh[256];
-    const int tid = threadIdx.x;
-    const int base = blockIdx.x * SCAN_CHUNK;
-    // each thread owns 4 consecutive counts
-    int v[4], loc = 0;
-    for (int k = 0; k < 4; ++k) {
-        int i = base + tid * 4 + k;
-        v[k] = i < n ? (cnt[i] < MAXC ? cnt[i] : MAXC) : 0;
-        loc += v[k];
-    }
-    int inc = block_incl_scan_256(loc, sh);
-    int run = coff[blockIdx.x] + inc - loc;
-    for (int k = 0; k < 4; ++k) {
-        int i = base + tid * 4 + k;
-        if (i < n) off[i] = run;
-        run += v[k];
-    }
-    if (blockIdx.x == gridDim.x - 1 && tid == 0) off[n] = stats[1];
 }
 
 // ---------------------------------------------------------------------------
@@ -1252,18 +1236,18 @@ __global__ void k_macroscopic(BoxDev bx, int parity, double* __restrict__ rho, d
 
 // Dense two-slot solid fractions of one box (readout and overflow count),
 // through the same candidate lists and mapping function as the step kernel.
-__global__ void k_map_dense(BoxDev bx, Particles P, const int* __restrict__ tile_off,
-                            const int* __restrict__ tile_pid, TileShape ts, double* __restrict__ B,
+__global__ void k_map_dense(BoxDev bx, Particles P, const int* __restrict__ tile_cnt,
+                            const int2* __restrict__ tile_ent, int list_cap, TileShape ts, double* __restrict__ B,
                             int* __restrict__ pid, unsigned long long* dropped) {
     long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (n >= bx.N) return;
     int x = n % bx.nx, y = (n / bx.nx) % bx.ny, z = n / ((long long)bx.nx * bx.ny);
     int t = bx.tile_base + x / ts.tx + bx.ntx * (y / ts.ty + bx.nty * (z / ts.tz));
-    int e0 = tile_off[t], e1 = tile_off[t + 1];
+    const int nc = tile_cnt[t] < list_cap ? tile_cnt[t] : list_cap;
     Slots sl;
     slots_init(sl);
-    for (int e = e0; e < e1; ++e) {
-        int p = tile_pid[e];
+    for (int e = 0; e < nc; ++e) {
+        int p = tile_ent[(long long)t * list_cap + e].x;
         double dx = min_image((x + 0.5) - P.x[p], bx.L[0], bx.halfL[0]);
         double dy = min_image((y + 0.5) - P.y[p], bx.L[1], bx.halfL[1]);
         double dz = min_image((z + 0.5) - P.z[p], bx.L[2], bx.halfL[2]);
@@ -1341,85 +1325,6 @@ __global__ __launch_bounds__(256) void k_stream_copy(const double2* __restrict__
                                                      long long n) {
     long long i = (long long)blockIdx.x * 256 + threadIdx.x;
     if (i < n) b[i] = a[i];
-}
-
-// ---------------------------------------------------------------------------
-// Sphere integration (Sec. 2.2.2) for collision-free spheres, one thread per
-// particle slot. m = rho_p (4/3) pi r^3, I = (2/5) m r^2; the total force is
-// the hydrodynamic force of the last step plus m times the box's external
-// acceleration, the torque is the hydrodynamic torque.
-//   Euler:  x += dt U;  U += dt F/m;  Om += dt T/I.
-//   Verlet (eqs. 15-16), once after each fluid step: complete the velocity
-//   with the previous and the new force (skipped until a previous force
-//   exists), then advance the position with the new one.
-// Positions are wrapped into [0, L) along periodic axes; along an axis with
-// walls a centre leaving [r + 1, L - r - 1] is mirrored back and its velocity
-// component reversed (elastic contact keeping the mapping's one-cell gap).
-// No fused multiply-add, so that the update is reproducible bit for bit.
-template <int SCHEME>
-__global__ __launch_bounds__(256) void k_integrate(IntParams ip) {
-#pragma clang fp contract(off)
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= ip.P_total) return;
-    const BoxDev& bx = ip.boxes[ip.part_box[p]];
-    if (p - bx.part_base >= bx.np) return;
-    const double pi = 3.14159265358979323846;
-    const double dt = ip.dt, r = ip.P.r[p];
-    const double m = bx.rho_p * (4.0 / 3.0) * pi * r * r * r;
-    const double inertia = 0.4 * m * r * r;
-    double* pos[3] = {ip.P.x, ip.P.y, ip.P.z};
-    double* vel[3] = {ip.P.ux, ip.P.uy, ip.P.uz};
-    double* ang[3] = {ip.P.ox, ip.P.oy, ip.P.oz};
-    const double* acc = ip.P.acc + 6LL * p;
-    double* fp = ip.P.fprev + 6LL * p;
-    const bool prev = SCHEME == SCHEME_VERLET && ip.P.prev_ok[p] != 0;
-    for (int a = 0; a < 3; ++a) {
-        const double F = acc[a] + m * bx.accel[a];
-        const double T = acc[3 + a];
-        double x = pos[a][p], U = vel[a][p], W = ang[a][p];
-        if (SCHEME == SCHEME_EULER) {
-            x = x + dt * U;
-            U = U + dt * F / m;
-            W = W + dt * T / inertia;
-        } else {
-            if (prev) {
-                U = U + dt / (2.0 * m) * (fp[a] + F);
-                W = W + dt / (2.0 * inertia) * (fp[3 + a] + T);
-            }
-            x = x + (dt * U + dt * dt / (2.0 * m) * F);
-            fp[a] = F;
-            fp[3 + a] = T;
-        }
-        const double L = bx.L[a];
-        const bool walled = a == 2 ? bx.walls != 0 : (bx.walls_xy & (1 << a)) != 0;
-        if (walled) {
-            // elastic contact one cell before the walls: mirror the centre back
-            // into [r + 1, L - r - 1] and reverse the normal velocity
-            const double lo = r + 1.0, hi = L - r - 1.0;
-            if (x < lo) { x = 2.0 * lo - x; U = -U; }
-            else if (x > hi) { x = 2.0 * hi - x; U = -U; }
-        } else {
-            double w = x - L * floor(x / L);
-            if (w >= L) w -= L;
-            if (w < 0.0) w = 0.0;
-            x = w;
-        }
-        pos[a][p] = x;
-        vel[a][p] = U;
-        ang[a][p] = W;
-    }
-    if (SCHEME == SCHEME_VERLET) ip.P.prev_ok[p] = 1;
-}
-
-// Replace the list bits of the error word by those of the lists just built
-// (report = 0: clear them only, for a build whose counts the host checks).
-__global__ void k_check_lists(const int* __restrict__ stats, long long cap, int* __restrict__ err, int report) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        int e = 0;
-        if ((long long)stats[1] > cap) e |= FLAG_LIST_ENTRIES;
-        if (stats[0] > MAXC) e |= FLAG_LIST_TILE;
-        err[0] = (err[0] & ~(FLAG_LIST_ENTRIES | FLAG_LIST_TILE)) | (report ? e : 0);
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1607,34 +1512,30 @@ int step_blocks_per_cu(int storage, int map, bool filt) {
     return nb > 0 ? nb : 1;
 }
 
-hipError_t launch_reduce(const ReduceParams& rp, hipStream_t st) {
-    if (rp.P_total == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_reduce_forces, dim3(blocks_for(rp.P_total, 4)), dim3(256), 0, st, rp);
+// Blocks of 4 spheres, and at least enough to clear the old counts beside them.
+template <bool REDUCE, int SCHEME, bool BIN>
+static hipError_t launch_spheres_of(const SphereParams& sp, hipStream_t st) {
+    unsigned nb = blocks_for(sp.P_total, 4);
+    if (BIN) {
+        const unsigned clear = blocks_for(sp.T_total, 1024);
+        nb = std::max(nb, std::min(clear, 1024u));
+    }
+    hipLaunchKernelGGL((k_spheres<REDUCE, SCHEME, BIN>), dim3(nb), dim3(256), 0, st, sp);
     return hipGetLastError();
 }
 
-int scan_chunks(int n) { return (n + SCAN_CHUNK - 1) / SCAN_CHUNK; }
-
-// scratch: 2 * scan_chunks(T) ints
-hipError_t launch_bin(const BinParams& bp, int* stats, int* scratch, hipStream_t st) {
-    hipLaunchKernelGGL(k_fill_int, dim3(blocks_for(bp.T_total, 256) > 4096 ? 4096 : blocks_for(bp.T_total, 256)),
-                       dim3(256), 0, st, bp.tile_cnt, (long long)bp.T_total, 0);
-    if (bp.P_total > 0)
-        hipLaunchKernelGGL(k_bin<false>, dim3(blocks_for(bp.P_total, 4)), dim3(256), 0, st, bp);
-    int nch = scan_chunks(bp.T_total);
-    int* csum = scratch;
-    int* cmax = scratch + nch;
-    hipLaunchKernelGGL(k_scan_chunks, dim3(nch), dim3(256), 0, st, bp.tile_cnt, bp.T_total, csum, cmax);
-    hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(256), 0, st, csum, cmax, nch, stats);
-    hipLaunchKernelGGL(k_scan_apply, dim3(nch), dim3(256), 0, st, bp.tile_cnt, bp.T_total, csum, bp.tile_off,
-                       stats);
-    return hipGetLastError();
-}
-
-hipError_t launch_bin_fill(const BinParams& bp, hipStream_t st) {
-    if (bp.P_total > 0)
-        hipLaunchKernelGGL(k_bin<true>, dim3(blocks_for(bp.P_total, 4)), dim3(256), 0, st, bp);
-    return hipGetLastError();
+hipError_t launch_spheres(bool reduce, int scheme, bool bin, const SphereParams& sp, hipStream_t st) {
+    if (sp.P_total == 0) return hipSuccess;
+    if (reduce) {
+        if (!bin) return launch_spheres_of<true, SCHEME_NONE, false>(sp, st);
+        return scheme == SCHEME_EULER ? launch_spheres_of<true, SCHEME_EULER, true>(sp, st)
+                                      : launch_spheres_of<true, SCHEME_VERLET, true>(sp, st);
+    }
+    switch (scheme) {
+        case SCHEME_EULER: return launch_spheres_of<false, SCHEME_EULER, true>(sp, st);
+        case SCHEME_VERLET: return launch_spheres_of<false, SCHEME_VERLET, true>(sp, st);
+        default: return launch_spheres_of<false, SCHEME_NONE, true>(sp, st);
+    }
 }
 
 hipError_t launch_set_pdfs(int storage, const BoxDev& bx, int parity, const double* f, float scale,
@@ -1691,10 +1592,10 @@ hipError_t launch_macroscopic(int storage, const BoxDev& bx, int parity, double*
     return hipGetLastError();
 }
 
-hipError_t launch_map_dense(const BoxDev& bx, const Particles& P, const int* tile_off, const int* tile_pid,
-                            TileShape ts, double* B, int* pid, unsigned long long* dropped, hipStream_t st) {
-    hipLaunchKernelGGL(k_map_dense, dim3(blocks_for(bx.N, 256)), dim3(256), 0, st, bx, P, tile_off, tile_pid, ts,
-                       B, pid, dropped);
+hipError_t launch_map_dense(const BoxDev& bx, const Particles& P, const int* tile_cnt, const int2* tile_ent,
+                            int list_cap, TileShape ts, double* B, int* pid, unsigned long long* dropped, hipStream_t st) {
+    hipLaunchKernelGGL(k_map_dense, dim3(blocks_for(bx.N, 256)), dim3(256), 0, st, bx, P, tile_cnt, tile_ent,
+                       list_cap, ts, B, pid, dropped);
     return hipGetLastError();
 }
 
@@ -1709,20 +1610,6 @@ hipError_t launch_stats(int storage, const BoxDev& bx, int parity, float inv, do
         default: hipLaunchKernelGGL(k_stats_partial<St16>, dim3(nb), dim3(256), 0, st, bx, parity, inv, part); break;
     }
     hipLaunchKernelGGL(k_stats_final, dim3(1), dim3(64), 0, st, part, nb, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_integrate(int scheme, const IntParams& ip, hipStream_t st) {
-    if (ip.P_total == 0) return hipSuccess;
-    if (scheme == SCHEME_EULER)
-        hipLaunchKernelGGL(k_integrate<SCHEME_EULER>, dim3(blocks_for(ip.P_total, 256)), dim3(256), 0, st, ip);
-    else
-        hipLaunchKernelGGL(k_integrate<SCHEME_VERLET>, dim3(blocks_for(ip.P_total, 256)), dim3(256), 0, st, ip);
-    return hipGetLastError();
-}
-
-hipError_t launch_check_lists(const int* stats, long long cap, int* err, int report, hipStream_t st) {
-    hipLaunchKernelGGL(k_check_lists, dim3(1), dim3(64), 0, st, stats, cap, err, report);
     return hipGetLastError();
 }
 

@@ -309,3 +309,28 @@ def test_host_coupling_with_split_updates_matches_oracle():
     assert_forces_close(Ts, ref.T, ref.A, lever=spec.r.max() + 1)
     assert np.allclose(xs, dyn.x, rtol=1e-12, atol=1e-12)
     assert np.allclose(Us, dyn.U, rtol=1e-12, atol=1e-15)
+
+
+@pytest.mark.parametrize("nspheres", [1, 7, 9])
+def test_lists_after_launch_changes_between_updates(nspheres):
+    """Launches with few and with many tiles in turn, an odd number of list
+    builds between them: every launch starts from clean counts, so the run is
+    bit for bit the one of a context that keeps the launch (PDFs in FP64 do
+    not depend on the tile shape)."""
+    spec = inputs.random_small((40, 34, 30), nspheres, (2.5, 3.0), seed=37, tau=0.7, vamp=0.08, omamp=0.003)
+    print(f"[case] launch changes n={len(spec.r)}", flush=True)
+    f = []
+    for launches in ([(16, 16, 1, 0)] * 4, [(16, 16, 1, 0), (256, 1, 32, 0), (32, 8, 4, 0), (16, 16, 1, 0)]):
+        eng = make_engine([spec])
+        eng.set_pdfs(0, initial_f(spec))
+        eng.set_particles(0, spec.x, spec.r, spec.U, spec.Om)
+        for launch in launches:
+            eng.set_launch(*launch)
+            eng.step(1)
+            eng.set_particle_positions(0, spec.x + 0.3 * spec.U)
+            eng.set_particle_positions(0, spec.x)
+            eng.set_particles(0, spec.x + 2.0 * spec.U, spec.r, spec.U, spec.Om)
+            eng.step(2)
+        f.append(eng.get_pdfs(0).cpu().numpy())
+        eng.close()
+    assert np.array_equal(f[0], f[1])
