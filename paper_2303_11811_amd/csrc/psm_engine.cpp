@@ -378,6 +378,8 @@ static SphereParams sphere_params(psm_ctx* c) {
     sp.T_total = c->T_total;
     sp.over = c->d_flags + 1 + next;
     sp.over_old = c->d_flags + 1 + c->list_parity;
+    sp.host_acc = nullptr;
+    sp.err = c->d_flags;
     return sp;
 }
 
@@ -416,13 +418,16 @@ static int rebuild_lists(psm_ctx* c) {
     return PSM_OK;
 }
 
-// Every synchronising call copies the device error words with its read-back
-// (sync_with_flags) and reports them afterwards (take_flags), which clears the
+// Every synchronising call brings the device error words to the host with what
+// it reads (fetch_and_sync) and reports them afterwards (take_flags), which clears the
 // words on the device. A list overflow (device-built lists) or, in strict-slot
 // mode, a third overlap makes the context refuse to step until
 // psm_set_particles; a bad psm_get_pdfs_at index is an argument error.
-static int sync_with_flags(psm_ctx* c) {
-    HIP_TRY(hipMemcpyAsync(c->h_flags, c->d_flags, sizeof(int) * ERR_WORDS, hipMemcpyDeviceToHost, c->stream));
+static int fetch_and_sync(psm_ctx* c, DownloadParams dp = DownloadParams{}) {
+    dp.dst = c->h_read;
+    dp.err = c->d_flags;
+    dp.err_dst = c->h_flags;
+    HIP_TRY(launch_download(dp, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
     return PSM_OK;
 }
@@ -729,6 +734,47 @@ static double wrap_coord(double v, double L) {
     return w;
 }
 
+static UploadParams upload_params(psm_ctx* c, int box, const double* staged, int first, int ncols, int n) {
+    UploadParams up;
+    up.src = staged;
+    up.part_base = c->box[box].part_base;
+    up.table = c->P.x + up.part_base;
+    up.pitch = std::max(c->P_total, 1);
+    up.first = first;
+    up.ncols = ncols;
+    up.n = n;
+    up.m = c->desc[box].max_particles;
+    up.prev_ok = nullptr;
+    up.np = nullptr;
+    return up;
+}
+
+// Uploads with new lists of at most this many spheres go in one launch: one
+// position upload after another takes 8.2 / 8.7 / 10.5 / 17.7 us at 8 / 256 /
+// 627 / 2347 spheres against 10.0 / 10.0 / 11.0 / 17.2 in two launches, and
+// with a force read after each 23.5 / 26.5 / 29.3 / 45.4 us against 23.5 /
+// 26.8 / 28.6 / 40.9 (strided copies and the list build: 55 / 57 / 68 / 85).
+constexpr int kFusedUpload = 256;
+
+// Send staged columns (upload half h) to the device and, for new positions,
+// rebuild the lists. The kernels read the pinned staging themselves: a
+// strided copy takes about 10 us of host time and 4 us on the device. Up to
+// kFusedUpload spheres each wave of the list build reads its own sphere's
+// columns (scattered 8-B reads over the host link); more are read by a
+// coalesced kernel of their own first.
+static int send_columns(psm_ctx* c, const UploadParams& up, int h, bool new_lists) {
+    const bool fused = new_lists && up.m > 0 && up.n <= kFusedUpload;
+    if (fused) {
+        HIP_TRY(launch_upload_bin(sphere_params(c), up, c->stream));
+        c->list_parity ^= 1;
+        c->have_particles_lists = true;
+    } else {
+        HIP_TRY(launch_upload(up, c->stream));
+    }
+    HIP_TRY(hipEventRecord(c->stage_ev[h], c->stream));
+    return new_lists && !fused ? rebuild_lists_async(c) : PSM_OK;
+}
+
 extern "C" int psm_set_particles(psm_ctx* c, int box, int n, const double* x, const double* r, const double* U,
                                  const double* omega) {
     int rc = check_box(c, box);
@@ -778,21 +824,7 @@ extern "C" int psm_set_particles(psm_ctx* c, int box, int n, const double* x, co
             st[(8 + a) * m + p] = omega ? omega[3 * p + a] : 0.0;
         }
     }
-    // the 11 device columns are P_total apart: one strided copy moves them all
-    int pb = c->box[box].part_base;
-    size_t P1 = (size_t)std::max(c->P_total, 1);
-    if (n > 0)
-        HIP_TRY(hipMemcpy2DAsync(c->P.x + pb, sizeof(double) * P1, st, sizeof(double) * m, sizeof(double) * n, 11,
-                                 hipMemcpyHostToDevice, c->stream));
-    // new velocities: velocity Verlet starts again from this state
-    HIP_TRY(launch_fill_int(c->P.prev_ok + pb, m, 0, c->stream));
     bool np_changed = c->np[box] != n;
-    if (np_changed) {
-        int* npst = (int*)(st + 11 * (size_t)m);
-        *npst = n;
-        HIP_TRY(hipMemcpyAsync(&c->d_boxes[box].np, npst, sizeof(int), hipMemcpyHostToDevice, c->stream));
-    }
-    HIP_TRY(hipEventRecord(c->stage_ev[h], c->stream));
     // positions (wrapped) and radii decide the tile lists; velocities do not
     bool same_geometry = c->have_particles_lists && !np_changed && (size_t)4 * n == c->last_xr[box].size();
     for (int k = 0; k < 4 && same_geometry; ++k)
@@ -800,24 +832,26 @@ extern "C" int psm_set_particles(psm_ctx* c, int box, int n, const double* x, co
                                     sizeof(double) * n) == 0;
     c->box[box].np = n;
     c->np[box] = n;
-    if (same_geometry) return PSM_OK;
+    // new velocities: velocity Verlet starts again from this state
+    UploadParams up = upload_params(c, box, st, 0, 11, n);
+    up.prev_ok = c->P.prev_ok + c->box[box].part_base;
+    up.np = np_changed ? &c->d_boxes[box].np : nullptr;
     std::vector<double>& xr = c->last_xr[box];
+    if (same_geometry) return send_columns(c, up, h, false);
     xr.resize((size_t)4 * n);
     for (int k = 0; k < 4; ++k) std::memcpy(xr.data() + (size_t)k * n, st + (size_t)k * m, sizeof(double) * n);
-    // lists rebuilt on the device without waiting: an overflow is reported by
-    // the next synchronising call
-    rc = rebuild_lists_async(c);
+    rc = send_columns(c, up, h, true);
     if (rc != PSM_OK) xr.clear();
     return rc;
 }
 
-// Upload some columns of the sphere table of box `box` (n spheres, the
-// current count) through the pinned staging: cols[k] (host, row-major (n,3))
-// goes to the three device columns first_col[k] .. first_col[k] + 2. Checks
-// each value while it stages it (finite; a position column also keeps r + 1
-// from the walls and is wrapped into the box) and enqueues nothing when one
-// fails. Asynchronous.
-static int upload_columns(psm_ctx* c, int box, int n, const double* const* cols, const int* first_col, int ncols) {
+// Stage some columns of the sphere table of box `box` (n spheres, the current
+// count) and send them: cols[k] (host, row-major (n,3)) goes to the three
+// device columns first_col + 3 k .. first_col + 3 k + 2. Checks each value
+// while it stages it (finite; a position column also keeps r + 1 from the
+// walls and is wrapped into the box) and enqueues nothing when one fails.
+// Positions bring new lists. Asynchronous.
+static int upload_columns(psm_ctx* c, int box, int n, const double* const* cols, int first_col, int ncols) {
     const psm_box_desc& d = c->desc[box];
     const int m = d.max_particles;
     const int h = c->stage_next;
@@ -827,13 +861,10 @@ static int upload_columns(psm_ctx* c, int box, int n, const double* const* cols,
     const double L[3] = {(double)d.nx, (double)d.ny, (double)d.nz};
     const int walled[3] = {d.walls_x, d.walls_y, d.walls_z};
     const std::vector<double>& r = c->last_r[box];
-    const int pb = c->box[box].part_base;
-    const size_t P1 = (size_t)std::max(c->P_total, 1);
-    double* dev_cols[11] = {c->P.x, c->P.y, c->P.z, c->P.r, c->P.fr, c->P.ux, c->P.uy, c->P.uz, c->P.ox, c->P.oy, c->P.oz};
     for (int k = 0; k < ncols; ++k) {
         double* sk = st + (size_t)3 * k * m;
         const double* v = cols[k];
-        if (first_col[k] == 0) {
+        if (first_col + 3 * k == 0) {
             for (int p = 0; p < n; ++p)
                 for (int a = 0; a < 3; ++a) {
                     const double xa = v[3 * p + a];
@@ -853,12 +884,10 @@ static int upload_columns(psm_ctx* c, int box, int n, const double* const* cols,
             for (int a = 0; a < 3; ++a) std::fill(sk + (size_t)a * m, sk + (size_t)a * m + n, 0.0);
         }
     }
-    // the three device columns of each are P_total apart: one strided copy
-    for (int k = 0; k < ncols && n > 0; ++k)
-        HIP_TRY(hipMemcpy2DAsync(dev_cols[first_col[k]] + pb, sizeof(double) * P1, st + (size_t)3 * k * m,
-                                 sizeof(double) * m, sizeof(double) * n, 3, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(hipEventRecord(c->stage_ev[h], c->stream));
-    return PSM_OK;
+    UploadParams up = upload_params(c, box, st, first_col, 3 * ncols, n);
+    // new velocities: velocity Verlet starts again from this state
+    if (first_col > 0) up.prev_ok = c->P.prev_ok + c->box[box].part_base;
+    return send_columns(c, up, h, first_col == 0);
 }
 
 static int check_update_args(psm_ctx* c, int box, int n) {
@@ -874,10 +903,9 @@ extern "C" int psm_set_particle_positions(psm_ctx* c, int box, int n, const doub
     if (rc) return rc;
     if (n > 0 && !x) return fail(PSM_EINVAL, "x is NULL");
     const double* cols[1] = {x};
-    const int first[1] = {0};
-    if ((rc = upload_columns(c, box, n, cols, first, 1))) return rc;
+    if ((rc = upload_columns(c, box, n, cols, 0, 1))) return rc;
     c->last_xr[box].clear();   // positions changed outside psm_set_particles
-    return rebuild_lists_async(c);
+    return PSM_OK;
 }
 
 extern "C" int psm_set_particle_velocities(psm_ctx* c, int box, int n, const double* U, const double* omega) {
@@ -885,11 +913,7 @@ extern "C" int psm_set_particle_velocities(psm_ctx* c, int box, int n, const dou
     if (rc) return rc;
     if (n > 0 && !U) return fail(PSM_EINVAL, "U is NULL");
     const double* cols[2] = {U, omega};
-    const int first[2] = {5, 8};
-    if ((rc = upload_columns(c, box, n, cols, first, 2))) return rc;
-    // new velocities: velocity Verlet starts again from this state
-    HIP_TRY(launch_fill_int(c->P.prev_ok + c->box[box].part_base, c->desc[box].max_particles, 0, c->stream));
-    return PSM_OK;
+    return upload_columns(c, box, n, cols, 5, 2);
 }
 
 static int step_params(psm_ctx* c, int parity, StepParams& kp) {
@@ -950,9 +974,10 @@ static hipEvent_t next_event(psm_ctx* c) {
     return c->ev[c->ev_used++];
 }
 
-// The step kernel, then per sphere the force reduction; with a scheme, the
-// sphere update and the new lists in the same launch.
-static int enqueue_step(psm_ctx* c, bool timed, int scheme = SCHEME_NONE, double dt = 0.0) {
+// The step kernel, then per sphere the force reduction (with `readback` also to
+// the host); with a scheme, the sphere update and the new lists in the same
+// launch.
+static int enqueue_step(psm_ctx* c, bool timed, int scheme = SCHEME_NONE, double dt = 0.0, bool readback = false) {
     StepParams kp;
     step_params(c, c->parity, kp);
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -969,6 +994,7 @@ static int enqueue_step(psm_ctx* c, bool timed, int scheme = SCHEME_NONE, double
     if (timed) HIP_TRY(hipEventRecord(e1, c->stream));
     SphereParams sp = sphere_params(c);
     sp.dt = dt;
+    if (readback) sp.host_acc = c->h_rb;
     HIP_TRY(launch_spheres(true, scheme, scheme != SCHEME_NONE, sp, c->stream));
     if (scheme != SCHEME_NONE && c->P_total > 0) c->list_parity ^= 1;
     c->parity ^= 1;
@@ -1018,15 +1044,24 @@ extern "C" int psm_step(psm_ctx* c, int nsteps) {
             left -= kGraphSteps;   // an even count: the parity is unchanged
         }
     }
+    const bool last_eager = left > 0;
     for (; left > 0; --left) {
-        int rc = enqueue_step(c, c->timing);
+        int rc = enqueue_step(c, c->timing, SCHEME_NONE, 0.0, c->rb_on && left == 1);
         if (rc) return rc;
     }
-    if (c->rb_on && nsteps > 0) {
-        // the force sums of every box and the error words, one contiguous copy
-        const size_t P1 = (size_t)std::max(c->P_total, 1);
-        HIP_TRY(hipMemcpyAsync(c->h_rb, c->P.acc, sizeof(double) * 6 * P1 + sizeof(int) * ERR_WORDS,
-                               hipMemcpyDeviceToHost, c->stream));
+    if (c->rb_on && nsteps > 0 && c->P_total > 0) {
+        // the force sums of every box and the error words: the last step's
+        // reduction writes them, after a graph replay a kernel of their own
+        if (!last_eager) {
+            DownloadParams dp{};
+            dp.src[0] = c->P.acc;
+            dp.ncols[0] = 1;
+            dp.n = 6LL * c->P_total;
+            dp.dst = c->h_rb;
+            dp.err = c->d_flags;
+            dp.err_dst = (int*)(c->h_rb + dp.n);
+            HIP_TRY(launch_download(dp, c->stream));
+        }
         HIP_TRY(hipEventRecord(c->rb_ev, c->stream));
         c->rb_valid = true;
     }
@@ -1044,7 +1079,7 @@ extern "C" int psm_get_forces(psm_ctx* c, int box, double* F, double* T) {
     int rc = check_box(c, box);
     if (rc) return rc;
     int n = c->np[box];
-    if (n == 0) return (rc = sync_with_flags(c)) ? rc : take_flags(c);
+    if (n == 0) return (rc = fetch_and_sync(c)) ? rc : take_flags(c);
     if (!F || !T) return fail(PSM_EINVAL, "F/T is NULL");
     const double* st;
     if (c->rb_valid) {
@@ -1054,12 +1089,14 @@ extern "C" int psm_get_forces(psm_ctx* c, int box, double* F, double* T) {
         int f = w[0];
         if (!c->strict_slots) f &= ~FLAG_SLOT_OVERFLOW;
         // an error: report it the usual way, from the end of the stream
-        if ((f || w[1] || w[2]) && ((rc = sync_with_flags(c)) || (rc = take_flags(c)))) return rc;
+        if ((f || w[1] || w[2]) && ((rc = fetch_and_sync(c)) || (rc = take_flags(c)))) return rc;
         st = c->h_rb + 6LL * c->box[box].part_base;
     } else {
-        HIP_TRY(hipMemcpyAsync(c->h_read, c->P.acc + 6LL * c->box[box].part_base, sizeof(double) * 6 * n,
-                               hipMemcpyDeviceToHost, c->stream));
-        if ((rc = sync_with_flags(c)) || (rc = take_flags(c))) return rc;
+        DownloadParams dp{};
+        dp.src[0] = c->P.acc + 6LL * c->box[box].part_base;
+        dp.ncols[0] = 1;
+        dp.n = 6LL * n;
+        if ((rc = fetch_and_sync(c, dp)) || (rc = take_flags(c))) return rc;
         st = c->h_read;
     }
     for (int p = 0; p < n; ++p)
@@ -1093,7 +1130,7 @@ extern "C" int psm_get_stats(psm_ctx* c, int box, double* mass, double* momentum
     double* st = c->h_read;
     HIP_TRY(hipMemcpyAsync(st, out, sizeof(double) * 4, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipMemcpyAsync(st + 4, dropped, sizeof(unsigned long long), hipMemcpyDeviceToHost, c->stream));
-    if ((rc = sync_with_flags(c)) || (rc = take_flags(c))) return rc;
+    if ((rc = fetch_and_sync(c)) || (rc = take_flags(c))) return rc;
     if (mass) *mass = st[0];
     if (momentum)
         for (int a = 0; a < 3; ++a) momentum[a] = st[1 + a];
@@ -1134,7 +1171,7 @@ extern "C" int psm_set_drift_check(psm_ctx* c, int box, double rel_tol) {
 extern "C" int psm_set_strict_slots(psm_ctx* c, int enable) {
     if (!c) return fail(PSM_EINVAL, "ctx is NULL");
     // overlaps seen before the switch do not count
-    int rc = sync_with_flags(c);
+    int rc = fetch_and_sync(c);
     if (rc) return rc;
     if (*c->h_flags & FLAG_SLOT_OVERFLOW) {
         *c->h_flags &= ~FLAG_SLOT_OVERFLOW;
@@ -1223,16 +1260,19 @@ extern "C" int psm_get_particles(psm_ctx* c, int box, double* x, double* U, doub
     int rc = check_box(c, box);
     if (rc) return rc;
     int n = c->np[box];
-    if (n == 0 || (!x && !U && !omega)) return (rc = sync_with_flags(c)) ? rc : take_flags(c);
+    if (n == 0 || (!x && !U && !omega)) return (rc = fetch_and_sync(c)) ? rc : take_flags(c);
     size_t P1 = (size_t)std::max(c->P_total, 1);
     int pb = c->box[box].part_base;
     // columns x y z (0-2), ux uy uz (5-7), ox oy oz (8-10) of the device table
     double* st = c->h_read;
-    HIP_TRY(hipMemcpy2DAsync(st, sizeof(double) * n, c->P.x + pb, sizeof(double) * P1, sizeof(double) * n, 3,
-                             hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipMemcpy2DAsync(st + 3 * (size_t)n, sizeof(double) * n, c->P.ux + pb, sizeof(double) * P1,
-                             sizeof(double) * n, 6, hipMemcpyDeviceToHost, c->stream));
-    if ((rc = sync_with_flags(c)) || (rc = take_flags(c))) return rc;
+    DownloadParams dp{};
+    dp.src[0] = c->P.x + pb;
+    dp.src[1] = c->P.ux + pb;
+    dp.pitch[0] = dp.pitch[1] = (long long)P1;
+    dp.ncols[0] = 3;
+    dp.ncols[1] = 6;
+    dp.n = n;
+    if ((rc = fetch_and_sync(c, dp)) || (rc = take_flags(c))) return rc;
     double* outs[3] = {x, U, omega};
     for (int k = 0; k < 3; ++k) {
         if (!outs[k]) continue;

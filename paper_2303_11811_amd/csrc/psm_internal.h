@@ -292,12 +292,42 @@ struct SphereParams {
     int list_cap;
     int T_total;
     int *over, *over_old;       // largest uncapped count where it exceeds MAXC, else 0
+    // force read-back: pinned host copy of P.acc and the error words behind
+    // it (null: none)
+    double* host_acc;
+    const int* err;
+};
+
+// Sphere-table columns uploaded from pinned host staging: `ncols` columns from
+// column `first` on (x y z r f(r) U Omega), n values each, m apart in the
+// staging and `pitch` apart on the device.
+struct UploadParams {
+    const double* src;
+    double* table;              // column 0 of the box's spheres
+    long long pitch;
+    int first, ncols, n, m;
+    int* prev_ok;               // [m] cleared when velocities are uploaded (null: not)
+    int* np;                    // the box's sphere count, set to n (null: not)
+    int part_base;              // first global sphere slot of the box
+};
+// Sphere data written to pinned host memory, with the error words after it.
+struct DownloadParams {
+    const double* src[2];
+    long long pitch[2];         // doubles between the columns of a range
+    int ncols[2];
+    long long n;                // values per column
+    double* dst;                // the columns one after another
+    const int* err;
+    int* err_dst;
 };
 
 hipError_t launch_step(int storage, int map, bool filt, const StepParams& kp, int grid, hipStream_t st);
 hipError_t launch_pattern_copy(int storage, bool shifted, const StepParams& kp, int grid, hipStream_t st);
 int step_blocks_per_cu(int storage, int map, bool filt);
 hipError_t launch_spheres(bool reduce, int scheme, bool bin, const SphereParams& sp, hipStream_t st);
+hipError_t launch_upload_bin(const SphereParams& sp, const UploadParams& up, hipStream_t st);
+hipError_t launch_upload(const UploadParams& up, hipStream_t st);
+hipError_t launch_download(const DownloadParams& dp, hipStream_t st);
 hipError_t launch_set_pdfs(int storage, const BoxDev& bx, int parity, const double* f, float scale, hipStream_t st);
 hipError_t launch_set_equilibrium(int storage, const BoxDev& bx, int parity, const double* rho, const double* u,
                                   float scale, hipStream_t st);

@@ -916,8 +916,10 @@ __device__ inline void box_tiles(const BoxDev& bx, const TileShape& ts, double x
     az = axis_tiles(lo, hi, bx.nz, ts.tz, bx.ntz);
 }
 
-template <bool REDUCE, int SCHEME, bool BIN>
-__global__ __launch_bounds__(256) void k_spheres(SphereParams sp) {
+//   UPLOAD  the spheres of one box first take new columns from pinned host
+//           staging (lane c reads column c), before their tiles are found.
+template <bool REDUCE, int SCHEME, bool BIN, bool UPLOAD = false>
+__global__ __launch_bounds__(256) void k_spheres(SphereParams sp, UploadParams up = UploadParams{}) {
 #pragma clang fp contract(off)
     if (BIN) {
         // the counts of the lists being replaced, for the build after this one
@@ -927,13 +929,29 @@ __global__ __launch_bounds__(256) void k_spheres(SphereParams sp) {
     }
     const int lane = threadIdx.x & 63;
     const int p = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (REDUCE && sp.host_acc && blockIdx.x == 0 && threadIdx.x < ERR_WORDS)
+        ((int*)(sp.host_acc + 6LL * sp.P_total))[threadIdx.x] = sp.err[threadIdx.x];
     if (p >= sp.P_total) return;   // whole wave leaves together
     const BoxDev& bx = sp.boxes[sp.part_box[p]];
     const int lp = p - bx.part_base;
-    const bool there = lp < bx.np;
+    bool there = lp < bx.np;
     const long long slot0 = (long long)bx.pbase + (long long)lp * bx.pstride;
     double pos[3] = {sp.P.x[p], sp.P.y[p], sp.P.z[p]};
-    const double r = sp.P.r[p];
+    double r = sp.P.r[p];
+    if (UPLOAD && up.part_base == bx.part_base) {
+        there = lp < up.n;
+        double v = 0.0;
+        if (there && lane < up.ncols) {
+            v = up.src[(long long)lane * up.m + lp];
+            up.table[(up.first + lane) * up.pitch + lp] = v;
+        }
+        for (int a = 0; a < 3; ++a) pos[a] = __shfl(v, a, 64);   // an upload with lists starts at x
+        if (up.ncols > 3) r = __shfl(v, 3, 64);
+        if (lane == 0) {
+            if (up.prev_ok) up.prev_ok[lp] = 0;
+            if (up.np && lp == 0) *up.np = up.n;
+        }
+    }
     double acc[6];
     if (REDUCE) {
 #pragma unroll
@@ -953,6 +971,13 @@ __global__ __launch_bounds__(256) void k_spheres(SphereParams sp) {
         for (int c = 0; c < 6; ++c) {
             acc[c] = wave_sum(acc[c]);   // the same bits on every lane
             if (lane == 0) sp.P.acc[6LL * p + c] = acc[c];
+        }
+        if (sp.host_acc) {
+            // lanes 0-5: one 48-B store to the host
+            double v = acc[0];
+#pragma unroll
+            for (int c = 1; c < 6; ++c) v = lane == c ? acc[c] : v;
+            if (lane < 6) sp.host_acc[6LL * p + lane] = v;
         }
     }
     if (!there) return;
@@ -1032,6 +1057,35 @@ __global__ __launch_bounds__(256) void k_spheres(SphereParams sp) {
             }
         }
     }
+}
+
+// Sphere-table columns from pinned host staging, one value per thread
+// (coalesced reads over the host link).
+__global__ __launch_bounds__(256) void k_upload(UploadParams up) {
+    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (i < (long long)up.ncols * up.n) {
+        const int c = (int)(i / up.n), lp = (int)(i - (long long)c * up.n);
+        up.table[(up.first + c) * up.pitch + lp] = up.src[(long long)c * up.m + lp];
+    }
+    if (up.prev_ok && i < up.m) up.prev_ok[i] = 0;
+    if (up.np && i == 0) *up.np = up.n;
+}
+
+// Sphere data and the error words to pinned host memory: one launch where a
+// copy per range and one for the words took 10-20 us.
+__global__ __launch_bounds__(256) void k_download(DownloadParams dp) {
+    const long long stride = (long long)gridDim.x * 256;
+    const long long i0 = (long long)blockIdx.x * 256 + threadIdx.x;
+    double* dst = dp.dst;
+    for (int g = 0; g < 2; ++g) {
+        const long long total = dp.n * dp.ncols[g];
+        for (long long i = i0; i < total; i += stride) {
+            const long long c = i / dp.n;
+            dst[i] = dp.src[g][c * dp.pitch[g] + (i - c * dp.n)];
+        }
+        dst += total;
+    }
+    if (i0 < ERR_WORDS) dp.err_dst[i0] = dp.err[i0];
 }
 
 __global__ void k_fill_int(int* a, long long n, int v) {
@@ -1513,14 +1567,14 @@ int step_blocks_per_cu(int storage, int map, bool filt) {
 }
 
 // Blocks of 4 spheres, and at least enough to clear the old counts beside them.
-template <bool REDUCE, int SCHEME, bool BIN>
-static hipError_t launch_spheres_of(const SphereParams& sp, hipStream_t st) {
+template <bool REDUCE, int SCHEME, bool BIN, bool UPLOAD = false>
+static hipError_t launch_spheres_of(const SphereParams& sp, hipStream_t st, const UploadParams& up = UploadParams{}) {
     unsigned nb = blocks_for(sp.P_total, 4);
     if (BIN) {
         const unsigned clear = blocks_for(sp.T_total, 1024);
         nb = std::max(nb, std::min(clear, 1024u));
     }
-    hipLaunchKernelGGL((k_spheres<REDUCE, SCHEME, BIN>), dim3(nb), dim3(256), 0, st, sp);
+    hipLaunchKernelGGL((k_spheres<REDUCE, SCHEME, BIN, UPLOAD>), dim3(nb), dim3(256), 0, st, sp, up);
     return hipGetLastError();
 }
 
@@ -1536,6 +1590,22 @@ hipError_t launch_spheres(bool reduce, int scheme, bool bin, const SphereParams&
         case SCHEME_VERLET: return launch_spheres_of<false, SCHEME_VERLET, true>(sp, st);
         default: return launch_spheres_of<false, SCHEME_NONE, true>(sp, st);
     }
+}
+
+hipError_t launch_upload_bin(const SphereParams& sp, const UploadParams& up, hipStream_t st) {
+    return launch_spheres_of<false, SCHEME_NONE, true, true>(sp, st, up);
+}
+
+hipError_t launch_upload(const UploadParams& up, hipStream_t st) {
+    const long long n = std::max({(long long)up.ncols * up.n, up.prev_ok ? (long long)up.m : 0LL, 1LL});
+    hipLaunchKernelGGL(k_upload, dim3(blocks_for(n, 256)), dim3(256), 0, st, up);
+    return hipGetLastError();
+}
+
+hipError_t launch_download(const DownloadParams& dp, hipStream_t st) {
+    const long long n = std::max(dp.n * std::max(dp.ncols[0], dp.ncols[1]), 1LL);
+    hipLaunchKernelGGL(k_download, dim3(std::min(blocks_for(n, 256), 4096u)), dim3(256), 0, st, dp);
+    return hipGetLastError();
 }
 
 hipError_t launch_set_pdfs(int storage, const BoxDev& bx, int parity, const double* f, float scale,
