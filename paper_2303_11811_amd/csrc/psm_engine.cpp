@@ -238,6 +238,7 @@ static Layout make_layout(const psm_box_desc* boxes, int nbox, int storage) {
 struct psm_ctx {
     int nbox = 0, storage = 0;
     int map_mode = 0;            // 1 if any box uses sub-division sampling
+    bool walls = false;          // any box has walls or faces
     float h_scale = 1.0f, h_inv = 1.0f;
     hipStream_t stream = nullptr;
     char* ws = nullptr;
@@ -334,6 +335,8 @@ static void assign_tiles(psm_ctx* c) {
         bx.ntx = cdiv(bx.nx, c->ts.tx);
         bx.nty = cdiv(bx.ny, c->ts.ty);
         bx.ntz = cdiv(bx.nz, c->ts.tz);
+        udiv_magic(bx.ntx, bx.div_ntx);
+        udiv_magic(bx.nty, bx.div_nty);
         bx.tile_base = base;
         base += bx.ntx * bx.nty * bx.ntz;
     }
@@ -355,7 +358,7 @@ static void assign_tiles(psm_ctx* c) {
     // one-shot: a workgroup per tile (rounded up to whole XCD rounds);
     // persistent: as many workgroups as fit at once, each walking its tiles
     int full = ((c->T_total + NXCD - 1) / NXCD) * NXCD;
-    int g = c->ts.persistent ? std::min(step_blocks_per_cu(c->storage, c->map_mode, c->ts.filter != 0) * ncu, full) : full;
+    int g = c->ts.persistent ? std::min(step_blocks_per_cu(c->storage, c->map_mode, c->ts.filter != 0, c->walls) * ncu, full) : full;
     c->grid = std::max(NXCD, g / NXCD * NXCD);
 }
 
@@ -490,8 +493,10 @@ extern "C" int psm_create(const psm_box_desc* boxes, int nbox, int storage, doub
     c->ws = (char*)dev_workspace;
     c->L = L;
     c->desc.assign(boxes, boxes + nbox);
-    for (int b = 0; b < nbox; ++b)
+    for (int b = 0; b < nbox; ++b) {
         if (boxes[b].mapping == PSM_MAP_SUBSAMPLE) c->map_mode = 1;
+        if (boxes[b].walls_x || boxes[b].walls_y || boxes[b].walls_z) c->walls = true;
+    }
     if (storage == PSM_FP16DEV) {
         c->h_scale = (float)fp16_scale;
         c->h_inv = (float)(1.0 / fp16_scale);
@@ -990,7 +995,7 @@ static int enqueue_step(psm_ctx* c, bool timed, int scheme = SCHEME_NONE, double
     // the persistent grid's tile counters start at zero (a kernel, not a
     // memset: the step may be captured into a graph)
     if (kp.queue) HIP_TRY(launch_fill_int(kp.queue, NXCD, 0, c->stream));
-    HIP_TRY(launch_step(c->storage, c->map_mode, c->ts.filter != 0, kp, c->grid, c->stream));
+    HIP_TRY(launch_step(c->storage, c->map_mode, c->ts.filter != 0, c->walls, kp, c->grid, c->stream));
     if (timed) HIP_TRY(hipEventRecord(e1, c->stream));
     SphereParams sp = sphere_params(c);
     sp.dt = dt;

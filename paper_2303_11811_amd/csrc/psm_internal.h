@@ -30,6 +30,7 @@ __host__ __device__ constexpr double wq(int q) { return q == 0 ? W0 : (q <= 6 ? 
 struct BoxDev {
     int nx, ny, nz, N;
     int ntx, nty, ntz, tile_base;   // tiles per axis, first global tile
+    unsigned div_ntx[2], div_nty[2];   // udiv_magic of ntx and nty
     int part_base, np, mapping, nsub;
     // force partials of a sphere: slots pbase + (local id) * pstride + k for
     // the k-th tile of its bounding box (pstride bounds the tiles a sphere of
@@ -81,6 +82,17 @@ struct BoxDev {
     double bw[2][NQ];
 };
 enum { FACE_VELOCITY = 0, FACE_PRESSURE = 1 };
+
+// Multiplier and shift of a division by d: with l = ceil(log2 d) and mul =
+// ceil(2^(31+l) / d) < 2^32, n / d = mulhi(mul, n) >> (l - 1) for n < 2^31 (the
+// excess mul n / 2^(31+l) - n / d is below n / 2^(31+l) < 2^-l <= 1 / d).
+// d = 1: mul = 0, which stands for n itself.
+inline void udiv_magic(unsigned d, unsigned out[2]) {
+    unsigned l = 0;
+    while ((1ull << l) < d) ++l;
+    out[0] = l ? (unsigned)(((1ull << (31 + l)) + d - 1) / d) : 0;
+    out[1] = l ? l - 1 : 0;
+}
 
 // Opposite direction: the pairs (1,2), (3,4), ..., (17,18) are opposite.
 __host__ __device__ constexpr int inv_dir(int q) { return q == 0 ? 0 : ((q & 1) ? q + 1 : q - 1); }
@@ -321,9 +333,9 @@ struct DownloadParams {
     int* err_dst;
 };
 
-hipError_t launch_step(int storage, int map, bool filt, const StepParams& kp, int grid, hipStream_t st);
+hipError_t launch_step(int storage, int map, bool filt, bool wall, const StepParams& kp, int grid, hipStream_t st);
 hipError_t launch_pattern_copy(int storage, bool shifted, const StepParams& kp, int grid, hipStream_t st);
-int step_blocks_per_cu(int storage, int map, bool filt);
+int step_blocks_per_cu(int storage, int map, bool filt, bool wall);
 hipError_t launch_spheres(bool reduce, int scheme, bool bin, const SphereParams& sp, hipStream_t st);
 hipError_t launch_upload_bin(const SphereParams& sp, const UploadParams& up, hipStream_t st);
 hipError_t launch_upload(const UploadParams& up, hipStream_t st);

@@ -111,6 +111,12 @@ template <> __device__ __forceinline__ float pick<float>(double, float f) { retu
 __device__ __forceinline__ float fmar(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fmar(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
+// n / d for 0 <= n < 2^31 by the multiplier and shift of udiv_magic: scalar
+// instructions, where a division goes through the vector ALU.
+__device__ __forceinline__ int udiv(int n, unsigned mul, unsigned shift) {
+    return mul ? (int)(__umulhi(mul, (unsigned)n) >> shift) : n;
+}
+
 __device__ inline int find_box(const int* tile_base, int nbox, int t) {
     int lo = 0, hi = nbox - 1;
     while (lo < hi) {
@@ -307,12 +313,19 @@ __device__ __forceinline__ void slot_geometry64(int c, double cxc, double cyc, d
 __device__ __forceinline__ float wrap32(float t, float L, float invL) { return fmar(-L, __builtin_rintf(t * invL), t); }
 
 // Waves per SIMD the register budget of the step kernel is cut for: 3 for
-// FP64 storage (168 VGPRs), 4 for the deviation forms (128 VGPRs).
-#ifndef PSM_WAVES_PER_EU
-#define PSM_WAVES_PER_EU 3
+// FP64 storage (168 VGPRs), 4 for the deviation forms (128 VGPRs), 5 for FP16
+// (96 VGPRs) without sampling and filter, which would spill there: its vector
+// ALU is busy two thirds of the time and hides more with more waves (256^3
+// 284 -> 272 us, 384^3 870 -> 857 us). FP32 spills at 5 waves (512^3 3.67 ->
+// 5.42 ms).
+#ifndef PSM_WAVES_F64
+#define PSM_WAVES_F64 3
 #endif
-#ifndef PSM_WAVES_PER_EU_DEV
-#define PSM_WAVES_PER_EU_DEV 4
+#ifndef PSM_WAVES_DEV
+#define PSM_WAVES_DEV 4
+#endif
+#ifndef PSM_WAVES_F16
+#define PSM_WAVES_F16 5
 #endif
 // Pull order of the step kernel (measured per storage form): the FP32 form
 // pulls the next cell's values while it works on the current one; FP64 issues
@@ -357,8 +370,9 @@ __device__ __forceinline__ float wrap32(float t, float L, float invL) { return f
         F[18] = S::ld(rm, o0p, 18 * QB);     \
     } while (0)
 
-template <class S, int MAP, bool FILT>
-__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(S::DEV ? PSM_WAVES_PER_EU_DEV : PSM_WAVES_PER_EU, 8))) void k_psm_step(
+template <class S, int MAP, bool FILT, bool WALL>
+__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
+    !S::DEV ? PSM_WAVES_F64 : (S::SCALED && MAP == 0 && !FILT ? PSM_WAVES_F16 : PSM_WAVES_DEV), 8))) void k_psm_step(
     StepParams kp) {
     using R = typename S::R;
     using T = typename S::T;
@@ -376,7 +390,6 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(S::DEV ? PSM
 
     const int tid = threadIdx.x;
     const int TX = kp.tx, TY = kp.ty, TZ = kp.tz;
-    const int lx = tid % TX, ly = tid / TX;
     const int wave = tid >> 6, lane = tid & 63;
 
     // XCD-aware persistent schedule: workgroup b runs on die b % 8; each die
@@ -402,7 +415,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(S::DEV ? PSM
     if (queue) {
         if (tid == 0) s_next = t_begin + atomicAdd(queue + xcd, 1);
         __syncthreads();
-        t = s_next;
+        t = __builtin_amdgcn_readfirstlane(s_next);   // uniform: everything of the tile stays scalar
     }
     while (t < t_end) {
         int b = 0;
@@ -422,17 +435,15 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(S::DEV ? PSM
         const bool lin_map = MAP == 0 || bx.mapping == 0;
         const int ntx = bx.ntx, nty = bx.nty;
         const int lt = t - bx.tile_base;
-        const int tcx = lt % ntx;
-        const int tcy = (lt / ntx) % nty;
-        const int tcz = lt / (ntx * nty);
+        const int lr = udiv(lt, bx.div_ntx[0], bx.div_ntx[1]);   // row of tiles
+        const int tcx = lt - lr * ntx;
+        const int tcz = udiv(lr, bx.div_nty[0], bx.div_nty[1]);
+        const int tcy = lr - tcz * nty;
         const int nc = tile_cnt[t] < kp.list_cap ? tile_cnt[t] : kp.list_cap;   // at most MAXC
         const int2* ent = kp.tile_ent + (long long)t * kp.list_cap;
         const double Lx = bx.L[0], Ly = bx.L[1], Lz = bx.L[2];
         const double hLx = bx.halfL[0], hLy = bx.halfL[1], hLz = bx.halfL[2];
-        // reference point of the FP32 geometry in cell coordinates: the tile's
-        // centre, in z that of the block of ref_z planes the tile lies in
-        const int RZ = kp.ref_z, zb = tcz * TZ / RZ * RZ;
-        const double tmx = tcx * TX + 0.5 * TX, tmy = tcy * TY + 0.5 * TY, tmz = zb + 0.5 * RZ;
+        const int RZ = kp.ref_z, zb = tcz * TZ & ~(RZ - 1);
 
         if (nc > 0) {
             for (int c = tid; c < nc; c += WG) {
@@ -443,23 +454,34 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(S::DEV ? PSM
                 const double px = kp.P.x[p], py = kp.P.y[p], pz = kp.P.z[p], pr = kp.P.r[p], pfr = kp.P.fr[p];
                 s_px[c] = px; s_py[c] = py; s_pz[c] = pz;
                 s_pr[c] = pr; s_pfr[c] = pfr;
-                s_qx[c] = (float)min_image(px - tmx, Lx, hLx);
-                s_qy[c] = (float)min_image(py - tmy, Ly, hLy);
-                s_qz[c] = (float)min_image(pz - tmz, Lz, hLz);
-                const double lim = pr + (lin_map ? pfr : bx.reach) + bx.margin32;
-                s_lim2[c] = (float)(lim * lim);
-                s_rf[c] = (float)pr;
-                s_frf[c] = (float)pfr;
                 const double u[6] = {kp.P.ux[p], kp.P.uy[p], kp.P.uz[p], kp.P.ox[p], kp.P.oy[p], kp.P.oz[p]};
-                s_ux[c] = u[0]; s_uy[c] = u[1]; s_uz[c] = u[2];
-                s_ox[c] = u[3]; s_oy[c] = u[4]; s_oz[c] = u[5];
+                if constexpr (S::DEV) {
+                    // reference point of the FP32 geometry in cell coordinates: the
+                    // tile's centre, in z that of the block of ref_z planes it lies in
+                    const double tmx = tcx * TX + 0.5 * TX, tmy = tcy * TY + 0.5 * TY, tmz = zb + 0.5 * RZ;
+                    s_qx[c] = (float)min_image(px - tmx, Lx, hLx);
+                    s_qy[c] = (float)min_image(py - tmy, Ly, hLy);
+                    s_qz[c] = (float)min_image(pz - tmz, Lz, hLz);
+                    const double lim = pr + (lin_map ? pfr : bx.reach) + bx.margin32;
+                    s_lim2[c] = (float)(lim * lim);
+                    s_rf[c] = (float)pr;
+                    s_frf[c] = (float)pfr;
 #pragma unroll
-                for (int k = 0; k < 6; ++k) s_uf[k][c] = (float)u[k];
+                    for (int k = 0; k < 6; ++k) s_uf[k][c] = (float)u[k];
+                } else {
+                    s_ux[c] = u[0]; s_uy[c] = u[1]; s_uz[c] = u[2];
+                    s_ox[c] = u[3]; s_oy[c] = u[4]; s_oz[c] = u[5];
+                }
             }
             for (int i = tid; i < NWAVE * 6 * MAXC; i += WG) (&s_acc[0][0][0])[i] = 0.0;
         }
         __syncthreads();
 
+        // the thread's column in the tile (TX is a power of two), taken from the
+        // thread id again for every tile: held across the staging it is spilled
+        int tl = tid;
+        asm volatile("" : "+v"(tl));
+        const int lx = tl & (TX - 1), ly = tl >> __builtin_ctz(TX);
         const int x = tcx * TX + lx;
         const int y = tcy * TY + ly;
         const bool lane_ok = (x < nx) && (y < ny);
@@ -474,10 +496,10 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(S::DEV ? PSM
             return (unsigned)(((c / BLK) * (NQ * BLK) + (c % BLK)) * (int)sizeof(T));
         };
         // lanes next to a resting side wall (x = 0, nx - 1; y = 0, ny - 1): bits 0-3
-        const int edge = !lane_ok || !bx.walls_xy ? 0
+        const int edge = !WALL || !lane_ok || !bx.walls_xy ? 0
                          : (((bx.walls_xy & 1) && xs == 0) ? 1 : 0) | (((bx.walls_xy & 1) && xs == nx - 1) ? 2 : 0) |
                                (((bx.walls_xy & 2) && ys == 0) ? 4 : 0) | (((bx.walls_xy & 2) && ys == ny - 1) ? 8 : 0);
-        const bool edge_wave = __ballot(edge != 0) != 0ull;
+        const bool edge_wave = WALL && __ballot(edge != 0) != 0ull;
         const unsigned o00 = inplane(xs, ys), om0 = inplane(xm, ys), op0 = inplane(xp, ys);
         const unsigned o0m = inplane(xs, ym), o0p = inplane(xs, yp);
         const unsigned omm = inplane(xm, ym), opp = inplane(xp, yp), omp = inplane(xm, yp), opm = inplane(xp, ym);
@@ -485,14 +507,9 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(S::DEV ? PSM
         const unsigned pb32 = (unsigned)pbytes;
         const char* src = (const char*)bx.grid[kp.parity];
         const char* dst = (const char*)bx.grid[kp.parity ^ 1];
-        const R omega = pick<R>(bx.omega, bx.omega_f);
-        const R om1 = pick<R>(bx.om1, bx.om1_f);
-        const R gx = pick<R>(bx.g[0], bx.g_f[0]), gy = pick<R>(bx.g[1], bx.g_f[1]), gz = pick<R>(bx.g[2], bx.g_f[2]);
         // scaled storage (FP16): the kernel works on s d; the quadratic terms
         // carry 1/s and every particle velocity is multiplied by s
         const R sc = S::SCALED ? (R)kp.h_scale : (R)1;
-        const R k15 = pick<R>(bx.k15, bx.k15_f);
-        const R k45 = pick<R>(bx.k45, bx.k45_f);
         const double cxc = xs + 0.5, cyc = ys + 0.5;
         // this cell's centre relative to the reference point (FP32, exact)
         const float rx = (float)(lx + 0.5 - 0.5 * TX), ry = (float)(ly + 0.5 - 0.5 * TY);
@@ -639,6 +656,13 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(S::DEV ? PSM
             // once per wave; the host reports it in strict-slot mode
             if (psm_wave && __ballot(dropped != 0) != 0ull && lane == 0) atomicOr(kp.flags, FLAG_SLOT_OVERFLOW);
 
+            const R omega = pick<R>(bx.omega, bx.omega_f);
+            const R om1 = pick<R>(bx.om1, bx.om1_f);
+            const R gx = pick<R>(bx.g[0], bx.g_f[0]), gy = pick<R>(bx.g[1], bx.g_f[1]),
+                    gz = pick<R>(bx.g[2], bx.g_f[2]);
+            const R k15 = pick<R>(bx.k15, bx.k15_f);
+            const R k45 = pick<R>(bx.k45, bx.k45_f);
+
             // 2b. boundaries of the pulled values
             R hx = 0, hy = 0, hz = 0;   // 2 j - U, for the force of eq. (21)
             if (lane_ok) {
@@ -646,7 +670,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(S::DEV ? PSM
                 // the population this cell sent against it last step, by the
                 // face rule; computed before the pulls so that its
                 // temporaries are not live beside them (uniform branches)
-                const bool face_plane = bx.walls && (z == 0 || z == nz - 1);
+                const bool face_plane = WALL && bx.walls && (z == 0 || z == nz - 1);
                 R fb[5] = {0, 0, 0, 0, 0};
                 if (face_plane) {
                     const int w = z == 0 ? 0 : 1;
@@ -872,7 +896,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(S::DEV ? PSM
         if (queue) {
             if (tid == 0) s_next = t_begin + atomicAdd(queue + xcd, 1);
             __syncthreads();
-            t = s_next;
+            t = __builtin_amdgcn_readfirstlane(s_next);
         } else {
             t += gx8;
         }
@@ -1460,7 +1484,7 @@ static inline unsigned blocks_for(long long n, int bs) { return (unsigned)((n + 
 
 // The step kernel instance for (storage, map, filt): storage psm_storage;
 // map 0 when every box uses the linear approximation, 1 if any box samples;
-// filt the per-wave candidate filter.
+// filt the per-wave candidate filter; wall if any box has walls or faces.
 // ---------------------------------------------------------------------------
 // Bandwidth reference for the step's access pattern: the tile walk, pulls and
 // stores of k_psm_step with no arithmetic. SHIFT pulls each direction from
@@ -1541,28 +1565,33 @@ hipError_t launch_pattern_copy(int storage, bool shifted, const StepParams& kp, 
     return hipLaunchKernel(k, dim3(grid), dim3(WG), args, 0, st);
 }
 
-template <int MAP, bool FILT>
+template <int MAP, bool FILT, bool WALL>
 static const void* step_kernel_of(int storage) {
     switch (storage) {
-        case 0: return (const void*)k_psm_step<St64, MAP, FILT>;
-        case 1: return (const void*)k_psm_step<St32, MAP, FILT>;
-        default: return (const void*)k_psm_step<St16, MAP, FILT>;
+        case 0: return (const void*)k_psm_step<St64, MAP, FILT, WALL>;
+        case 1: return (const void*)k_psm_step<St32, MAP, FILT, WALL>;
+        default: return (const void*)k_psm_step<St16, MAP, FILT, WALL>;
     }
 }
 
-static const void* step_kernel(int storage, int map, bool filt) {
-    if (map) return filt ? step_kernel_of<1, true>(storage) : step_kernel_of<1, false>(storage);
-    return filt ? step_kernel_of<0, true>(storage) : step_kernel_of<0, false>(storage);
+template <bool WALL>
+static const void* step_kernel_walls(int storage, int map, bool filt) {
+    if (map) return filt ? step_kernel_of<1, true, WALL>(storage) : step_kernel_of<1, false, WALL>(storage);
+    return filt ? step_kernel_of<0, true, WALL>(storage) : step_kernel_of<0, false, WALL>(storage);
 }
 
-hipError_t launch_step(int storage, int map, bool filt, const StepParams& kp, int grid, hipStream_t st) {
+static const void* step_kernel(int storage, int map, bool filt, bool wall) {
+    return wall ? step_kernel_walls<true>(storage, map, filt) : step_kernel_walls<false>(storage, map, filt);
+}
+
+hipError_t launch_step(int storage, int map, bool filt, bool wall, const StepParams& kp, int grid, hipStream_t st) {
     void* args[] = {(void*)&kp};
-    return hipLaunchKernel(step_kernel(storage, map, filt), dim3(grid), dim3(WG), args, 0, st);
+    return hipLaunchKernel(step_kernel(storage, map, filt, wall), dim3(grid), dim3(WG), args, 0, st);
 }
 
-int step_blocks_per_cu(int storage, int map, bool filt) {
+int step_blocks_per_cu(int storage, int map, bool filt, bool wall) {
     int nb = 0;
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, step_kernel(storage, map, filt), WG, 0);
+    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, step_kernel(storage, map, filt, wall), WG, 0);
     return nb > 0 ? nb : 1;
 }
 
