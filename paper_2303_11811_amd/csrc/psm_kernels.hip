@@ -331,7 +331,8 @@ __device__ __forceinline__ float wrap32(float t, float L, float invL) { return f
 // pulls the next cell's values while it works on the current one; FP64 issues
 // each cell's pulls before its mapping (not with the candidate filter, whose
 // registers that would spill); FP16 pulls after the mapping (earlier or ahead
-// was slower there).
+// was slower there). Contexts that sample pull after the mapping: its squares
+// take the registers (FP64 128^3 141 -> 134 us).
 #ifndef PSM_PREFETCH_F32
 #define PSM_PREFETCH_F32 1
 #endif
@@ -549,8 +550,8 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
         // Latency hiding: PREF pulls the next cell's 19 values (one cell up in
         // z) while the current one is mapped and collided; EARLY issues the
         // current cell's pulls before its mapping.
-        constexpr bool PREF = S::DEV && !FILT && (S::SCALED ? PSM_PREFETCH_F16 : PSM_PREFETCH_F32);
-        constexpr bool EARLY = !PREF && !FILT && (S::DEV ? (S::SCALED && PSM_EARLY_PULLS_F16) : PSM_EARLY_PULLS_F64);
+        constexpr bool PREF = S::DEV && !FILT && MAP == 0 && (S::SCALED ? PSM_PREFETCH_F16 : PSM_PREFETCH_F32);
+        constexpr bool EARLY = !PREF && !FILT && MAP == 0 && (S::DEV ? (S::SCALED && PSM_EARLY_PULLS_F16) : PSM_EARLY_PULLS_F64);
         R fn[NQ];
         if constexpr (PREF) {
             const int z0 = tcz * TZ;

@@ -539,3 +539,19 @@ def test_default_depth_keeps_the_results_of_depth_16(storage, dims, depth):
     assert np.array_equal(f, f16)
     scale = 4.0 / 3.0 * np.pi * spec.r[:, None] ** 3 * 0.1   # B |g| over the sphere's cells, |g| below 0.1
     assert np.all(np.abs(F - F16) <= 1e-13 * scale) and np.all(np.abs(T - T16) <= 1e-13 * scale * 5.0)
+
+
+@pytest.mark.parametrize("nsub", [1, 2, 3, 4, 5, 13, 16])
+def test_sampled_fractions_of_every_subdivision(nsub):
+    """Sub-division counts are whole numbers: bit for bit the oracle's for
+    subdivisions below, at, between and at the end of the chunks of four, and
+    the step that uses them agrees."""
+    spec = inputs.random_small((37, 29, 23), 5, (2.0, 4.0), seed=61, tau=0.7, mapping=1)
+    spec.nsub = nsub
+    _print_case("sampling", nsub=nsub)
+    ref = run_oracle(spec, 2)
+    f, F, T, B, pid, eng = run_engine(spec, 2)
+    assert np.array_equal(pid, ref.pid) and np.array_equal(B, ref.B)
+    assert_pdfs_close(f, ref.f, 1e-12)
+    assert_forces_close(F, ref.F, ref.A)
+    eng.close()
