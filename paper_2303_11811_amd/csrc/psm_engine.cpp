@@ -1116,8 +1116,7 @@ extern "C" int psm_get_solid_fraction(psm_ctx* c, int box, double* B, int* pid) 
     int rc = check_box(c, box);
     if (rc) return rc;
     if (!B || !pid) return fail(PSM_EINVAL, "B/pid is NULL");
-    unsigned long long* dropped = (unsigned long long*)(c->d_misc + 8);
-    HIP_TRY(hipMemsetAsync(dropped, 0, sizeof(unsigned long long), c->stream));
+    unsigned long long* dropped = (unsigned long long*)(c->d_misc + 8);   // not read here
     HIP_TRY(launch_map_dense(c->box[box], c->P, c->d_tcnt[c->list_parity], c->d_tent, c->L.list_cap, c->ts, B, pid,
                              dropped, c->stream));
     return PSM_OK;
@@ -1126,16 +1125,20 @@ extern "C" int psm_get_solid_fraction(psm_ctx* c, int box, double* B, int* pid) 
 extern "C" int psm_get_stats(psm_ctx* c, int box, double* mass, double* momentum, long long* slot_overflows) {
     int rc = check_box(c, box);
     if (rc) return rc;
+    // the four totals, then the count of dropped overlaps
     double* out = c->d_statpart + 4 * stats_blocks();
+    unsigned long long* dropped = (unsigned long long*)(out + 4);
     HIP_TRY(launch_stats(c->storage, c->box[box], c->parity, c->h_inv, c->d_statpart, out, c->stream));
-    unsigned long long* dropped = (unsigned long long*)(c->d_misc + 8);
-    HIP_TRY(hipMemsetAsync(dropped, 0, sizeof(unsigned long long), c->stream));
-    HIP_TRY(launch_map_dense(c->box[box], c->P, c->d_tcnt[c->list_parity], c->d_tent, c->L.list_cap, c->ts, nullptr,
-                             nullptr, dropped, c->stream));
+    HIP_TRY(launch_fill_int((int*)dropped, 2, 0, c->stream));
+    if (c->np[box] >= 3)
+        HIP_TRY(launch_map_dense(c->box[box], c->P, c->d_tcnt[c->list_parity], c->d_tent, c->L.list_cap, c->ts, nullptr,
+                                 nullptr, dropped, c->stream));
     double* st = c->h_read;
-    HIP_TRY(hipMemcpyAsync(st, out, sizeof(double) * 4, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipMemcpyAsync(st + 4, dropped, sizeof(unsigned long long), hipMemcpyDeviceToHost, c->stream));
-    if ((rc = fetch_and_sync(c)) || (rc = take_flags(c))) return rc;
+    DownloadParams dp{};
+    dp.src[0] = out;
+    dp.ncols[0] = 1;
+    dp.n = 5;
+    if ((rc = fetch_and_sync(c, dp)) || (rc = take_flags(c))) return rc;
     if (mass) *mass = st[0];
     if (momentum)
         for (int a = 0; a < 3; ++a) momentum[a] = st[1 + a];

@@ -1228,39 +1228,283 @@ __device__ inline void store_cell_slots(const BoxDev& bx, typename S::T* g, int 
     }
 }
 
+// Tiles of the state I/O kernels: 256 cells of one z-plane, rows of 16 to 64,
+// one cell per thread, walked like the step's tiles (each die takes a
+// contiguous eighth, so that the lines two x-neighbouring tiles share in a
+// shifted access meet in one L2). HBM bound. With an index division per cell,
+// 64-bit addresses and boundary rules for every value these kernels moved
+// 1.3-5 TB/s, now 5.2-6.5 like the step's own pattern (us at 256^3):
+//   read-out of rho and u  FP64 904 -> 588, FP32 769 -> 333, FP16 746 -> 209
+//   get_pdfs               FP64 991 -> 942, FP32 784 -> 711, FP16 822 -> 599
+//   set_pdfs               FP64 1210 -> 924, FP32 990 -> 697, FP16 990 -> 593
+// Cells next to a wall or face are left to the general kernels after them.
+struct RowGrid {
+    int shift;            // rows of 1 << shift cells
+    int nbx, nby, T;
+    unsigned div_x[2], div_y[2];
+};
+
+static RowGrid row_grid(const BoxDev& bx) {
+    RowGrid g;
+    g.shift = bx.nx <= 16 ? 4 : (bx.nx <= 32 ? 5 : 6);
+    g.nbx = (bx.nx + (1 << g.shift) - 1) >> g.shift;
+    const int rows = 256 >> g.shift;
+    g.nby = (bx.ny + rows - 1) / rows;
+    g.T = g.nbx * g.nby * bx.nz;
+    udiv_magic(g.nbx, g.div_x);
+    udiv_magic(g.nby, g.div_y);
+    return g;
+}
+
+static unsigned row_blocks(const RowGrid& g) { return (unsigned)(g.T + NXCD - 1) / NXCD * NXCD; }
+
+// The cell of this thread; false past the end of the tiles or of the box.
+__device__ __forceinline__ bool row_cell(const RowGrid& g, const BoxDev& bx, int& x, int& y, int& z) {
+    const int xcd = blockIdx.x % NXCD, m = blockIdx.x / NXCD;
+    const int t = (int)(((long long)g.T * xcd) / NXCD) + m;
+    if (t >= (int)(((long long)g.T * (xcd + 1)) / NXCD)) return false;
+    const int r = udiv(t, g.div_x[0], g.div_x[1]);
+    z = udiv(r, g.div_y[0], g.div_y[1]);
+    const int tid = threadIdx.x;
+    x = ((t - r * g.nbx) << g.shift) + (tid & ((1 << g.shift) - 1));
+    y = (r - z * g.nby) * (256 >> g.shift) + (tid >> g.shift);
+    return x < bx.nx && y < bx.ny;
+}
+
+// True for the cells whose values a wall or face enters.
+__device__ __forceinline__ bool at_wall(const BoxDev& bx, int x, int y, int z) {
+    return (bx.walls && (z == 0 || z == bx.nz - 1)) || ((bx.walls_xy & 1) && (x == 0 || x == bx.nx - 1)) ||
+           ((bx.walls_xy & 2) && (y == 0 || y == bx.ny - 1));
+}
+static bool has_walls(const BoxDev& bx) { return bx.walls || bx.walls_xy; }
+
+// The 19 stored values that stream into cell (x, y, z) of a periodic box (or
+// away from walls), in the units of S::ld.
 template <class S>
-__global__ void k_set_pdfs(BoxDev bx, int parity, const double* __restrict__ f, float scale) {
+__device__ __forceinline__ void pull19(const BoxDev& bx, int parity, int x, int y, int z, typename S::R f[NQ]) {
+    using T = typename S::T;
+    constexpr int QB = BLK * (int)sizeof(T);
+    const int xm = x == 0 ? bx.nx - 1 : x - 1, xp = x == bx.nx - 1 ? 0 : x + 1;
+    const int ym = y == 0 ? bx.ny - 1 : y - 1, yp = y == bx.ny - 1 ? 0 : y + 1;
+    const int zm = z == 0 ? bx.nz - 1 : z - 1, zp = z == bx.nz - 1 ? 0 : z + 1;
+    const int pitch = bx.pitch;
+    auto inplane = [pitch](int xx, int yy) -> unsigned {
+        const int c = xx + pitch * yy;
+        return (unsigned)(((c / BLK) * (NQ * BLK) + (c % BLK)) * (int)sizeof(T));
+    };
+    const unsigned o00 = inplane(x, y), om0 = inplane(xm, y), op0 = inplane(xp, y);
+    const unsigned o0m = inplane(x, ym), o0p = inplane(x, yp);
+    const unsigned omm = inplane(xm, ym), opp = inplane(xp, yp), omp = inplane(xm, yp), opm = inplane(xp, ym);
+    const long long pbytes = bx.plane_elems * (long long)sizeof(T);
+    const char* src = (const char*)bx.grid[parity];
+    const Rsrc rz = plane_rsrc(src + z * pbytes, (unsigned)pbytes);
+    const Rsrc rm = plane_rsrc(src + zm * pbytes, (unsigned)pbytes);
+    const Rsrc rp = plane_rsrc(src + zp * pbytes, (unsigned)pbytes);
+    PSM_LOAD19(f, rz, rm, rp);
+}
+
+// FP32 value of v rounded to odd: rounding it on to FP16 gives the nearest FP16
+// value of v itself (FP32 has more than two bits beyond FP16's). The direct
+// conversion is about 25 instructions.
+__device__ __forceinline__ float to_odd(double v) {
+    const float f = (float)v;
+    const double e = (double)f;
+    unsigned b = __float_as_uint(f);
+    if (e != v) b = (fabs(e) > fabs(v) ? b - 1 : b) | 1u;   // towards zero, last bit set
+    return __uint_as_float(b);
+}
+
+// Store the 19 slots sl (full FP64 values) of cell (x, y, z).
+template <class S>
+__device__ __forceinline__ void store19(const BoxDev& bx, int parity, int x, int y, int z, float scale,
+                                        const double sl[NQ]) {
+    using T = typename S::T;
+    constexpr int QB = BLK * (int)sizeof(T);
+    const int c = x + bx.pitch * y;
+    const unsigned o = (unsigned)(((c / BLK) * (NQ * BLK) + (c % BLK)) * (int)sizeof(T));
+    const long long pbytes = bx.plane_elems * (long long)sizeof(T);
+    const Rsrc d = plane_rsrc((const char*)bx.grid[parity] + z * pbytes, (unsigned)pbytes);
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        double v = sl[q];
+        if constexpr (S::DEV) {
+            // not fused with the product an equilibrium ends in
+#pragma clang fp contract(off)
+            v = v - wq(q);
+        }
+        if constexpr (S::SCALED) S::st(d, o, q * QB, to_odd(v * (double)scale));
+        else S::st(d, o, q * QB, (typename S::R)v);
+    }
+}
+
+// Neighbour x + c_q (periodic): plane and in-plane index of a canonical field.
+struct Around {
+    int z[3];            // z - 1, z, z + 1
+    unsigned xy[3][3];   // [dy + 1][dx + 1]
+    __device__ Around(const BoxDev& bx, int x, int y, int z0) {
+        z[0] = z0 == 0 ? bx.nz - 1 : z0 - 1;
+        z[1] = z0;
+        z[2] = z0 == bx.nz - 1 ? 0 : z0 + 1;
+        const int xs[3] = {x == 0 ? bx.nx - 1 : x - 1, x, x == bx.nx - 1 ? 0 : x + 1};
+        const int ys[3] = {y == 0 ? bx.ny - 1 : y - 1, y, y == bx.ny - 1 ? 0 : y + 1};
+#pragma unroll
+        for (int b = 0; b < 3; ++b)
+#pragma unroll
+            for (int a = 0; a < 3; ++a) xy[b][a] = (unsigned)(xs[a] + bx.nx * ys[b]);
+    }
+};
+
+// E_d(rho, u) of eq. (5)
+__device__ __forceinline__ double equilibrium(int d, double r, double vx, double vy, double vz) {
+    double cv = CX[d] * vx + CY[d] * vy + CZ[d] * vz;
+    double vv = vx * vx + vy * vy + vz * vz;
+    return wq(d) * (r + 3.0 * cv + 4.5 * cv * cv - 1.5 * vv);
+}
+
+template <class S>
+__global__ __launch_bounds__(256) void k_set_pdfs(BoxDev bx, RowGrid rg, int parity, const double* __restrict__ f,
+                                                  float scale) {
+    int x, y, z;
+    if (!row_cell(rg, bx, x, y, z) || at_wall(bx, x, y, z)) return;
+    const Around n(bx, x, y, z);
+    const long long plane = (long long)bx.nx * bx.ny;
+    double sl[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+        sl[q] = (f + (long long)q * bx.N + n.z[CZ[q] + 1] * plane)[n.xy[CY[q] + 1][CX[q] + 1]];
+    store19<S>(bx, parity, x, y, z, scale, sl);
+}
+
+// Slot q of a cell holds the equilibrium of its neighbour x + c_q, so a tile
+// keeps density and velocity of three planes with a rim of one cell in LDS
+// while it marches up z: 6 global loads per cell instead of 76, which left the
+// kernel waiting for them (256^3: FP64 1115 -> 603 us, FP32 874 -> 402, FP16
+// 882 -> 377). LDS reads and FP64 arithmetic bound the FP16 form.
+template <class S, int SHIFT>
+__global__ __launch_bounds__(256) void k_set_equilibrium(BoxDev bx, RowGrid rg, int depth, int parity,
+                                                         const double* __restrict__ rho,
+                                                         const double* __restrict__ u, float scale) {
+    constexpr int W = 1 << SHIFT, H = 256 >> SHIFT, W2 = W + 2, H2 = H + 2, CELLS = W2 * H2;
+    constexpr int PER = (CELLS + 255) / 256;
+    __shared__ double2 s_rx[3][CELLS], s_yz[3][CELLS];   // (rho, u_x), (u_y, u_z)
+    const int tid = threadIdx.x;
+    const int r = udiv(blockIdx.x, rg.div_x[0], rg.div_x[1]);
+    const int tz = udiv(r, rg.div_y[0], rg.div_y[1]);
+    const int x0 = (blockIdx.x - r * rg.nbx) << SHIFT, y0 = (r - tz * rg.nby) * H;
+    const int nx = bx.nx, ny = bx.ny, nz = bx.nz;
+    const int z0 = tz * depth, z1 = min(z0 + depth, nz);
+    const long long plane = (long long)nx * ny, N = bx.N;
+    // the cells of the rimmed tile this thread loads: in-plane index, -1 past the box
+    int at[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int i = tid + 256 * k, cy = i / W2, cx = i - cy * W2;
+        int gx = x0 - 1 + cx, gy = y0 - 1 + cy;
+        const bool in = i < CELLS && gx <= nx && gy <= ny;
+        gx = gx < 0 ? nx - 1 : (gx == nx ? 0 : gx);
+        gy = gy < 0 ? ny - 1 : (gy == ny ? 0 : gy);
+        at[k] = in ? gx + nx * gy : -1;
+    }
+    double2 rx[PER], yz[PER];
+    auto load = [&](int z) {
+        const long long p = (z < 0 ? nz - 1 : (z >= nz ? 0 : z)) * plane;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            if (at[k] < 0) continue;
+            rx[k] = make_double2(rho ? (rho + p)[at[k]] : 1.0, (u + p)[at[k]]);
+            yz[k] = make_double2((u + N + p)[at[k]], (u + 2 * N + p)[at[k]]);
+        }
+    };
+    auto keep = [&](int slot) {
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            if (at[k] < 0) continue;
+            s_rx[slot][tid + 256 * k] = rx[k];
+            s_yz[slot][tid + 256 * k] = yz[k];
+        }
+    };
+    const int lx = tid & (W - 1), ly = tid >> SHIFT;
+    const int x = x0 + lx, y = y0 + ly;
+    const int c0 = (ly + 1) * W2 + lx + 1;
+    int lo = 0, mid = 1, hi = 2;   // LDS planes of z - 1, z, z + 1
+    load(z0 - 1);
+    keep(lo);
+    load(z0);
+    keep(mid);
+    load(z0 + 1);
+    for (int z = z0; z < z1; ++z) {
+        keep(hi);
+        __syncthreads();
+        if (z + 1 < z1) load(z + 2);
+        if (x < nx && y < ny && !at_wall(bx, x, y, z)) {
+            double sl[NQ];
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                const int pl = CZ[q] < 0 ? lo : (CZ[q] > 0 ? hi : mid);
+                const int c = c0 + CX[q] + W2 * CY[q];
+                const double2 a = s_rx[pl][c], b = s_yz[pl][c];
+                sl[q] = equilibrium(q, a.x, a.y, b.x, b.y);
+            }
+            store19<S>(bx, parity, x, y, z, scale, sl);
+        }
+        __syncthreads();
+        const int t = lo;
+        lo = mid; mid = hi; hi = t;
+    }
+}
+
+// The cells at walls and faces (the others return).
+template <class S>
+__global__ void k_set_pdfs_wall(BoxDev bx, int parity, const double* __restrict__ f, float scale) {
     long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (n >= bx.N) return;
     int x = n % bx.nx, y = (n / bx.nx) % bx.ny, z = n / ((long long)bx.nx * bx.ny);
+    if (!at_wall(bx, x, y, z)) return;
     typename S::T* g = (typename S::T*)bx.grid[parity];
     const long long N = bx.N;
     store_cell_slots<S>(bx, g, x, y, z, scale, [&](int d, long long c) { return f[(long long)d * N + c]; });
 }
 
 template <class S>
-__global__ void k_set_equilibrium(BoxDev bx, int parity, const double* __restrict__ rho,
-                                  const double* __restrict__ u, float scale) {
+__global__ void k_set_equilibrium_wall(BoxDev bx, int parity, const double* __restrict__ rho,
+                                       const double* __restrict__ u, float scale) {
     long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (n >= bx.N) return;
     int x = n % bx.nx, y = (n / bx.nx) % bx.ny, z = n / ((long long)bx.nx * bx.ny);
+    if (!at_wall(bx, x, y, z)) return;
     typename S::T* g = (typename S::T*)bx.grid[parity];
     const long long N = bx.N;
-    // E_d(rho, u) of eq. (5) at cell c
     store_cell_slots<S>(bx, g, x, y, z, scale, [&](int d, long long c) {
-        double r = rho ? rho[c] : 1.0;
-        double vx = u[c], vy = u[N + c], vz = u[2 * N + c];
-        double cv = CX[d] * vx + CY[d] * vy + CZ[d] * vz;
-        double vv = vx * vx + vy * vy + vz * vz;
-        return wq(d) * (r + 3.0 * cv + 4.5 * cv * cv - 1.5 * vv);
+        return equilibrium(d, rho ? rho[c] : 1.0, u[c], u[N + c], u[2 * N + c]);
     });
 }
 
+// Canonical value of a pulled one (units of S::ld).
+template <class S> __device__ __forceinline__ double canonical(typename S::R v, int q, float inv) {
+    const double d = S::SCALED ? (double)((float)v * inv) : (double)v;
+    return S::DEV ? d + wq(q) : d;
+}
+
 template <class S>
-__global__ void k_get_pdfs(BoxDev bx, int parity, double* __restrict__ f, float inv) {
+__global__ __launch_bounds__(256) void k_get_pdfs(BoxDev bx, RowGrid rg, int parity, double* __restrict__ f,
+                                                  float inv) {
+    int x, y, z;
+    if (!row_cell(rg, bx, x, y, z) || at_wall(bx, x, y, z)) return;
+    typename S::R v[NQ];
+    pull19<S>(bx, parity, x, y, z, v);
+    const unsigned i = (unsigned)(x + bx.nx * y);
+    const long long p = (long long)z * bx.nx * bx.ny;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+        __builtin_nontemporal_store(canonical<S>(v[q], q, inv), (f + (long long)q * bx.N + p) + i);
+}
+
+template <class S>
+__global__ void k_get_pdfs_wall(BoxDev bx, int parity, double* __restrict__ f, float inv) {
     long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (n >= bx.N) return;
     int x = n % bx.nx, y = (n / bx.nx) % bx.ny, z = n / ((long long)bx.nx * bx.ny);
+    if (!at_wall(bx, x, y, z)) return;
     const typename S::T* g = (const typename S::T*)bx.grid[parity];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
@@ -1292,110 +1536,184 @@ __global__ void k_get_pdfs_at(BoxDev bx, int parity, const int* __restrict__ cel
     }
 }
 
-template <class S>
-__global__ void k_macroscopic(BoxDev bx, int parity, double* __restrict__ rho, double* __restrict__ u,
-                              float inv) {
-    long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= bx.N) return;
-    int x = n % bx.nx, y = (n / bx.nx) % bx.ny, z = n / ((long long)bx.nx * bx.ny);
-    const typename S::T* g = (const typename S::T*)bx.grid[parity];
+// Density and velocity of one cell from its canonical values, in direction order.
+template <class Value>
+__device__ __forceinline__ void write_fields(const BoxDev& bx, long long n, double* __restrict__ rho,
+                                             double* __restrict__ u, Value value) {
     double r = 0, j[3] = {0, 0, 0};
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
-        double v = pull_value<S>(bx, g, q, x, y, z, inv);
-        if (S::DEV) v += wq(q);
+        const double v = value(q);
         r += v;
-        j[0] += v * CX[q]; j[1] += v * CY[q]; j[2] += v * CZ[q];
+        if (CX[q]) j[0] += v * CX[q];
+        if (CY[q]) j[1] += v * CY[q];
+        if (CZ[q]) j[2] += v * CZ[q];
     }
-    rho[n] = r;
-    u[n] = j[0] + 0.5 * bx.g[0];
-    u[bx.N + n] = j[1] + 0.5 * bx.g[1];
-    u[2LL * bx.N + n] = j[2] + 0.5 * bx.g[2];
+    __builtin_nontemporal_store(r, rho + n);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) __builtin_nontemporal_store(j[a] + 0.5 * bx.g[a], u + a * (long long)bx.N + n);
 }
 
-// Dense two-slot solid fractions of one box (readout and overflow count),
-// through the same candidate lists and mapping function as the step kernel.
-__global__ void k_map_dense(BoxDev bx, Particles P, const int* __restrict__ tile_cnt,
-                            const int2* __restrict__ tile_ent, int list_cap, TileShape ts, double* __restrict__ B,
-                            int* __restrict__ pid, unsigned long long* dropped) {
+template <class S>
+__global__ __launch_bounds__(256) void k_macroscopic(BoxDev bx, RowGrid rg, int parity, double* __restrict__ rho,
+                                                     double* __restrict__ u, float inv) {
+    int x, y, z;
+    if (!row_cell(rg, bx, x, y, z) || at_wall(bx, x, y, z)) return;
+    typename S::R f[NQ];
+    pull19<S>(bx, parity, x, y, z, f);
+    write_fields(bx, x + bx.nx * (y + (long long)bx.ny * z), rho, u, [&](int q) { return canonical<S>(f[q], q, inv); });
+}
+
+template <class S>
+__global__ void k_macroscopic_wall(BoxDev bx, int parity, double* __restrict__ rho, double* __restrict__ u,
+                                   float inv) {
     long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (n >= bx.N) return;
     int x = n % bx.nx, y = (n / bx.nx) % bx.ny, z = n / ((long long)bx.nx * bx.ny);
-    int t = bx.tile_base + x / ts.tx + bx.ntx * (y / ts.ty + bx.nty * (z / ts.tz));
+    if (!at_wall(bx, x, y, z)) return;
+    const typename S::T* g = (const typename S::T*)bx.grid[parity];
+    write_fields(bx, n, rho, u, [&](int q) {
+        const double v = pull_value<S>(bx, g, q, x, y, z, inv);
+        return S::DEV ? v + wq(q) : v;
+    });
+}
+
+// Dense two-slot solid fractions of one box (read-out, or with B null the
+// overflow count alone), through the same candidate lists and mapping
+// function as the step kernel: one workgroup per tile of the step, the
+// spheres staged in LDS (256^3: 146 -> 92 us at 24 B per cell). Fewer than
+// three spheres cannot overflow a cell.
+__global__ __launch_bounds__(WG) void k_map_dense(BoxDev bx, Particles P, const int* __restrict__ tile_cnt,
+                                                  const int2* __restrict__ tile_ent, int list_cap, TileShape ts,
+                                                  double* __restrict__ B, int* __restrict__ pid,
+                                                  unsigned long long* dropped) {
+    __shared__ double s_x[MAXC], s_y[MAXC], s_z[MAXC], s_r[MAXC], s_fr[MAXC];
+    __shared__ int s_p[MAXC];
+    const int lt = blockIdx.x, t = bx.tile_base + lt;
     const int nc = tile_cnt[t] < list_cap ? tile_cnt[t] : list_cap;
-    Slots sl;
-    slots_init(sl);
-    for (int e = 0; e < nc; ++e) {
-        int p = tile_ent[(long long)t * list_cap + e].x;
-        double dx = min_image((x + 0.5) - P.x[p], bx.L[0], bx.halfL[0]);
-        double dy = min_image((y + 0.5) - P.y[p], bx.L[1], bx.halfL[1]);
-        double dz = min_image((z + 0.5) - P.z[p], bx.L[2], bx.halfL[2]);
-        double b = bx.mapping == 0 ? overlap_linear(dx, dy, dz, P.r[p], P.fr[p])
-                                   : overlap_subsample(dx, dy, dz, P.r[p], bx.nsub, bx.sub_off, bx.reach);
-        if (b > 0.0) slots_insert(sl, p, p, b);
+    if (!B && nc < 3) return;
+    const int tid = threadIdx.x;
+    if (tid < nc) {
+        const int p = tile_ent[(long long)t * list_cap + tid].x;
+        s_p[tid] = p;
+        s_x[tid] = P.x[p]; s_y[tid] = P.y[p]; s_z[tid] = P.z[p];
+        s_r[tid] = P.r[p]; s_fr[tid] = P.fr[p];
     }
-    slots_finish(sl);
-    if (B) {
-        B[n] = sl.c0 >= 0 ? sl.B0 : 0.0;
-        B[bx.N + n] = sl.c1 >= 0 ? sl.B1 : 0.0;
+    __syncthreads();
+    const int tr = udiv(lt, bx.div_ntx[0], bx.div_ntx[1]);
+    const int tcz = udiv(tr, bx.div_nty[0], bx.div_nty[1]);
+    const int x = (lt - tr * bx.ntx) * ts.tx + (tid & (ts.tx - 1));
+    const int y = (tr - tcz * bx.nty) * ts.ty + (tid >> __builtin_ctz(ts.tx));
+    const int z1 = min((tcz + 1) * ts.tz, bx.nz);
+    int lost = 0;
+    if (x < bx.nx && y < bx.ny) {
+        for (int z = tcz * ts.tz; z < z1; ++z) {
+            Slots sl;
+            slots_init(sl);
+            for (int c = 0; c < nc; ++c) {
+                const double dx = min_image((x + 0.5) - s_x[c], bx.L[0], bx.halfL[0]);
+                const double dy = min_image((y + 0.5) - s_y[c], bx.L[1], bx.halfL[1]);
+                const double dz = min_image((z + 0.5) - s_z[c], bx.L[2], bx.halfL[2]);
+                const double b = bx.mapping == 0
+                                     ? overlap_linear(dx, dy, dz, s_r[c], s_fr[c])
+                                     : overlap_subsample(dx, dy, dz, s_r[c], bx.nsub, bx.sub_off, bx.reach);
+                if (b > 0.0) slots_insert(sl, s_p[c], s_p[c], b);
+            }
+            slots_finish(sl);
+            lost += sl.dropped;
+            const long long n = x + bx.nx * (y + (long long)bx.ny * z);
+            if (B) {
+                __builtin_nontemporal_store(sl.c0 >= 0 ? sl.B0 : 0.0, B + n);
+                __builtin_nontemporal_store(sl.c1 >= 0 ? sl.B1 : 0.0, B + bx.N + n);
+                __builtin_nontemporal_store(sl.c0 >= 0 ? sl.c0 - bx.part_base : -1, pid + n);
+                __builtin_nontemporal_store(sl.c1 >= 0 ? sl.c1 - bx.part_base : -1, pid + bx.N + n);
+            }
+        }
     }
-    if (pid) {
-        pid[n] = sl.c0 >= 0 ? sl.c0 - bx.part_base : -1;
-        pid[bx.N + n] = sl.c1 >= 0 ? sl.c1 - bx.part_base : -1;
+    if (lost) atomicAdd(dropped, (unsigned long long)lost);
+}
+
+// Sum of 4 doubles per thread over the block, in a fixed tree; lane c < 4
+// holds component c.
+__device__ inline double block_sum4(const double v[4], double (*sh)[256]) {
+    const int tid = threadIdx.x;
+    for (int k = 0; k < 4; ++k) sh[k][tid] = v[k];
+    __syncthreads();
+    for (int d = 128; d > 0; d >>= 1) {
+        if (tid < d)
+            for (int k = 0; k < 4; ++k) sh[k][tid] += sh[k][tid + d];
+        __syncthreads();
     }
-    if (sl.dropped) atomicAdd(dropped, (unsigned long long)sl.dropped);
+    return sh[tid & 3][0];
 }
 
 // FP64 mass and momentum of the stored state (each slot is one f_q(x,t)):
-// per-block partial sums, then one block adds them in a fixed order.
-template <class S>
-__global__ __launch_bounds__(256) void k_stats_partial(BoxDev bx, int parity, float inv, double* __restrict__ part) {
-    __shared__ double s[4][256];
-    const typename S::T* g = (const typename S::T*)bx.grid[parity];
+// per-block partial sums, then one block adds them in a fixed order. A wave
+// takes one 64-cell storage block at a time: 19 aligned loads in flight, no
+// index division per cell. A call of psm_get_stats, 256^3: FP64 754 -> 493 us,
+// FP32 963 -> 271, FP16 940 -> 168; 32^3: 150 -> 26 (the final sum over the
+// blocks was serial: 125 us).
+template <class S, bool WALL>
+__global__ __launch_bounds__(256) void k_stats_partial(BoxDev bx, unsigned div0, unsigned div1, unsigned pit0,
+                                                       unsigned pit1, int parity, float inv,
+                                                       double* __restrict__ part) {
+    using T = typename S::T;
+    __shared__ double sh[4][256];
+    const T* g = (const T*)bx.grid[parity];
+    const int lane = threadIdx.x & 63;
     double m = 0, px = 0, py = 0, pz = 0;
-    for (long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x; n < bx.N;
-         n += (long long)gridDim.x * blockDim.x) {
-        int x = n % bx.nx, y = (n / bx.nx) % bx.ny, z = n / ((long long)bx.nx * bx.ny);
-        // each slot is one canonical value: the reader's f_q, or across a face
-        // the cell's own f_opp(q) by the face rule
+    const long long nblk = (long long)bx.pblk * bx.nz;
+    for (long long b = (long long)blockIdx.x * 4 + (threadIdx.x >> 6); b < nblk; b += (long long)gridDim.x * 4) {
+        const int z = udiv((int)b, div0, div1);
+        const int s = ((int)b - z * bx.pblk) * BLK + lane;
+        const int y = udiv(s, pit0, pit1), x = s - y * bx.pitch;
+        if (x >= bx.nx || y >= bx.ny) continue;   // padding is never written
+        const T* c = g + b * (NQ * BLK) + lane;
+        T raw[NQ];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) raw[q] = c[q * BLK];
+        const bool wall = WALL && at_wall(bx, x, y, z);
         double uc[3] = {0.0, 0.0, 0.0};
-        const bool pz_face = bx.walls && ((z == 0 && bx.face_type[0] == FACE_PRESSURE) ||
-                                          (z == bx.nz - 1 && bx.face_type[1] == FACE_PRESSURE));
-        if (pz_face) slot_velocity<S>(bx, g, x, y, z, inv, uc);
+        if (wall) slot_velocity<S>(bx, g, x, y, z, inv, uc);
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
-            double v = S::to_f64(g[pdf_index(bx, q, x, y, z)], inv);
+            double v = S::to_f64(raw[q], inv);
             int d = q;
-            int w = face_of(bx, z + CZ[q]);
-            if (behind_side_wall(bx, x + CX[q], y + CY[q])) {
-                d = inv_dir(q);
-            } else if (w >= 0) {
-                d = inv_dir(q);
-                v = bx.face_type[w] == FACE_PRESSURE
-                        ? abb_value(d, v, S::DEV ? bx.face_rho[w] - 1.0 : bx.face_rho[w], uc)
-                        : v + bx.bw[w][d];
+            if (wall) {
+                // across a wall or face: the cell's own f_opp(q) by its rule
+                const int w = face_of(bx, z + CZ[q]);
+                if (behind_side_wall(bx, x + CX[q], y + CY[q])) {
+                    d = inv_dir(q);
+                } else if (w >= 0) {
+                    d = inv_dir(q);
+                    v = bx.face_type[w] == FACE_PRESSURE
+                            ? abb_value(d, v, S::DEV ? bx.face_rho[w] - 1.0 : bx.face_rho[w], uc)
+                            : v + bx.bw[w][d];
+                }
             }
             if (S::DEV) v += wq(q);
             m += v;
-            px += v * CX[d]; py += v * CY[d]; pz += v * CZ[d];
+            if (WALL) {
+                px += v * CX[d]; py += v * CY[d]; pz += v * CZ[d];
+            } else {
+                if (CX[q]) px += v * CX[q];
+                if (CY[q]) py += v * CY[q];
+                if (CZ[q]) pz += v * CZ[q];
+            }
         }
     }
-    s[0][threadIdx.x] = m; s[1][threadIdx.x] = px; s[2][threadIdx.x] = py; s[3][threadIdx.x] = pz;
-    __syncthreads();
-    for (int d = 128; d > 0; d >>= 1) {
-        if ((int)threadIdx.x < d)
-            for (int k = 0; k < 4; ++k) s[k][threadIdx.x] += s[k][threadIdx.x + d];
-        __syncthreads();
-    }
-    if (threadIdx.x < 4) part[blockIdx.x * 4 + threadIdx.x] = s[threadIdx.x][0];
+    const double v[4] = {m, px, py, pz};
+    const double sum = block_sum4(v, sh);
+    if (threadIdx.x < 4) part[blockIdx.x * 4 + threadIdx.x] = sum;
 }
 
-__global__ void k_stats_final(const double* part, int nblk, double* out) {
-    if (threadIdx.x < 4) {
-        double s = 0;
-        for (int b = 0; b < nblk; ++b) s += part[b * 4 + threadIdx.x];
-        out[threadIdx.x] = s;
-    }
+__global__ __launch_bounds__(256) void k_stats_final(const double* part, int nblk, double* out) {
+    __shared__ double sh[4][256];
+    double v[4] = {0, 0, 0, 0};
+    for (int b = threadIdx.x; b < nblk; b += 256)
+        for (int k = 0; k < 4; ++k) v[k] += part[b * 4 + k];
+    const double sum = block_sum4(v, sh);
+    if (threadIdx.x < 4) out[threadIdx.x] = sum;
 }
 
 // Plain streaming copy (bandwidth reference): one-shot grid, each thread
@@ -1410,38 +1728,38 @@ __global__ __launch_bounds__(256) void k_stream_copy(const double2* __restrict__
 // FP64 totals of a canonical field without a context or a workspace, for
 // callers that cannot allocate device memory. The per-block partial sums go
 // to a library-owned array (one copy per GPU, alive until the process ends):
-// block b sums cells [b * NOALLOC_CELLS_PER_BLOCK, (b + 1) * ...), each
-// thread 64 cells 256 apart in cell order, then a fixed tree in LDS; one
-// more kernel adds the blocks in order. Every partial slot a call reads was
-// written by the same call, so nothing needs clearing; calls that overlap on
-// one GPU (different streams) race on the array.
+// block b sums cells [b * per, (b + 1) * per), each thread every 256th of
+// them in cell order, then a fixed tree in LDS; one more kernel adds the
+// blocks in a fixed order. Every partial slot a call reads was written by the
+// same call, so nothing needs clearing; calls that overlap on one GPU
+// (different streams) race on the array. Cells per block grow only once the
+// array's 4096 blocks are used up (at 64 cells per thread 128^3 cells were 128
+// blocks: 510 -> 68 us; 256^3 776 -> 442).
 constexpr int NOALLOC_BLOCKS = 4096;
-constexpr long long NOALLOC_CELLS_PER_BLOCK = 256LL * 64;
+constexpr long long NOALLOC_CELLS_PER_BLOCK = 256LL * 64;   // the most
 static __device__ __align__(256) double scratch[NOALLOC_BLOCKS * 4];
 
-__global__ __launch_bounds__(256) void k_field_stats_partial(const double* __restrict__ f, long long N,
+__global__ __launch_bounds__(256) void k_field_stats_partial(const double* __restrict__ f, long long N, int per,
                                                              double* __restrict__ part) {
     __shared__ double s[4][256];
     double m = 0.0, px = 0.0, py = 0.0, pz = 0.0;
-    const long long c0 = (long long)blockIdx.x * NOALLOC_CELLS_PER_BLOCK + threadIdx.x;
-    for (int k = 0; k < 64; ++k) {
-        const long long n = c0 + 256LL * k;
-        if (n >= N) break;
+    const long long c0 = (long long)blockIdx.x * per;
+    const long long c1 = c0 + per < N ? c0 + per : N;
+    for (long long n = c0 + threadIdx.x; n < c1; n += 256) {
+        double v[NQ];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) v[q] = f[(long long)q * N + n];
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
-            const double v = f[(long long)q * N + n];
-            m += v;
-            px += v * CX[q]; py += v * CY[q]; pz += v * CZ[q];
+            m += v[q];
+            if (CX[q]) px += v[q] * CX[q];
+            if (CY[q]) py += v[q] * CY[q];
+            if (CZ[q]) pz += v[q] * CZ[q];
         }
     }
-    s[0][threadIdx.x] = m; s[1][threadIdx.x] = px; s[2][threadIdx.x] = py; s[3][threadIdx.x] = pz;
-    __syncthreads();
-    for (int d = 128; d > 0; d >>= 1) {
-        if ((int)threadIdx.x < d)
-            for (int k = 0; k < 4; ++k) s[k][threadIdx.x] += s[k][threadIdx.x + d];
-        __syncthreads();
-    }
-    if (threadIdx.x < 4) part[blockIdx.x * 4 + threadIdx.x] = s[threadIdx.x][0];
+    const double v[4] = {m, px, py, pz};
+    const double sum = block_sum4(v, s);
+    if (threadIdx.x < 4) part[blockIdx.x * 4 + threadIdx.x] = sum;
 }
 
 // Device address of `scratch` on each GPU, looked up once per device with
@@ -1471,10 +1789,11 @@ hipError_t launch_field_stats_noalloc(const double* f, long long N, double* out,
     double* part = nullptr;
     hipError_t e = scratch_of_current_device(&part);
     if (e != hipSuccess) return e;
-    const int nblk = (int)((N + NOALLOC_CELLS_PER_BLOCK - 1) / NOALLOC_CELLS_PER_BLOCK);
-    if (nblk > NOALLOC_BLOCKS) return hipErrorInvalidValue;
-    if (nblk > 0) hipLaunchKernelGGL(k_field_stats_partial, dim3(nblk), dim3(256), 0, st, f, N, part);
-    hipLaunchKernelGGL(k_stats_final, dim3(1), dim3(64), 0, st, part, nblk, out);
+    if (N > noalloc_max_cells()) return hipErrorInvalidValue;
+    const int per = 256 * (int)std::max(1LL, (N + 256LL * NOALLOC_BLOCKS - 1) / (256LL * NOALLOC_BLOCKS));
+    const int nblk = (int)((N + per - 1) / per);
+    if (nblk > 0) hipLaunchKernelGGL(k_field_stats_partial, dim3(nblk), dim3(256), 0, st, f, N, per, part);
+    hipLaunchKernelGGL(k_stats_final, dim3(1), dim3(256), 0, st, part, nblk, out);
     return hipGetLastError();
 }
 
@@ -1638,35 +1957,47 @@ hipError_t launch_download(const DownloadParams& dp, hipStream_t st) {
     return hipGetLastError();
 }
 
+#define PSM_BY_STORAGE(CALL)                \
+    switch (storage) {                      \
+        case 0: { using S = St64; CALL; } break; \
+        case 1: { using S = St32; CALL; } break; \
+        default: { using S = St16; CALL; }       \
+    }
+
 hipError_t launch_set_pdfs(int storage, const BoxDev& bx, int parity, const double* f, float scale,
                            hipStream_t st) {
-    unsigned g = blocks_for(bx.N, 256);
-    switch (storage) {
-        case 0: hipLaunchKernelGGL(k_set_pdfs<St64>, dim3(g), dim3(256), 0, st, bx, parity, f, scale); break;
-        case 1: hipLaunchKernelGGL(k_set_pdfs<St32>, dim3(g), dim3(256), 0, st, bx, parity, f, scale); break;
-        default: hipLaunchKernelGGL(k_set_pdfs<St16>, dim3(g), dim3(256), 0, st, bx, parity, f, scale); break;
-    }
+    const RowGrid rg = row_grid(bx);
+    PSM_BY_STORAGE(hipLaunchKernelGGL(k_set_pdfs<S>, dim3(row_blocks(rg)), dim3(256), 0, st, bx, rg, parity, f, scale));
+    if (has_walls(bx))
+        PSM_BY_STORAGE(hipLaunchKernelGGL(k_set_pdfs_wall<S>, dim3(blocks_for(bx.N, 256)), dim3(256), 0, st, bx, parity,
+                                          f, scale));
     return hipGetLastError();
 }
 
 hipError_t launch_set_equilibrium(int storage, const BoxDev& bx, int parity, const double* rho, const double* u,
                                   float scale, hipStream_t st) {
-    unsigned g = blocks_for(bx.N, 256);
-    switch (storage) {
-        case 0: hipLaunchKernelGGL(k_set_equilibrium<St64>, dim3(g), dim3(256), 0, st, bx, parity, rho, u, scale); break;
-        case 1: hipLaunchKernelGGL(k_set_equilibrium<St32>, dim3(g), dim3(256), 0, st, bx, parity, rho, u, scale); break;
-        default: hipLaunchKernelGGL(k_set_equilibrium<St16>, dim3(g), dim3(256), 0, st, bx, parity, rho, u, scale); break;
+    const RowGrid rg = row_grid(bx);
+    // 16 planes per tile read 18; fewer while that leaves CUs idle
+    int depth = 16;
+    while (depth > 1 && (long long)rg.nbx * rg.nby * ((bx.nz + depth - 1) / depth) < 1024) depth /= 2;
+    const dim3 grid(rg.nbx * rg.nby * ((bx.nz + depth - 1) / depth));
+    switch (rg.shift) {
+        case 4: PSM_BY_STORAGE(hipLaunchKernelGGL((k_set_equilibrium<S, 4>), grid, dim3(256), 0, st, bx, rg, depth, parity, rho, u, scale)); break;
+        case 5: PSM_BY_STORAGE(hipLaunchKernelGGL((k_set_equilibrium<S, 5>), grid, dim3(256), 0, st, bx, rg, depth, parity, rho, u, scale)); break;
+        default: PSM_BY_STORAGE(hipLaunchKernelGGL((k_set_equilibrium<S, 6>), grid, dim3(256), 0, st, bx, rg, depth, parity, rho, u, scale));
     }
+    if (has_walls(bx))
+        PSM_BY_STORAGE(hipLaunchKernelGGL(k_set_equilibrium_wall<S>, dim3(blocks_for(bx.N, 256)), dim3(256), 0, st, bx,
+                                          parity, rho, u, scale));
     return hipGetLastError();
 }
 
 hipError_t launch_get_pdfs(int storage, const BoxDev& bx, int parity, double* f, float inv, hipStream_t st) {
-    unsigned g = blocks_for(bx.N, 256);
-    switch (storage) {
-        case 0: hipLaunchKernelGGL(k_get_pdfs<St64>, dim3(g), dim3(256), 0, st, bx, parity, f, inv); break;
-        case 1: hipLaunchKernelGGL(k_get_pdfs<St32>, dim3(g), dim3(256), 0, st, bx, parity, f, inv); break;
-        default: hipLaunchKernelGGL(k_get_pdfs<St16>, dim3(g), dim3(256), 0, st, bx, parity, f, inv); break;
-    }
+    const RowGrid rg = row_grid(bx);
+    PSM_BY_STORAGE(hipLaunchKernelGGL(k_get_pdfs<S>, dim3(row_blocks(rg)), dim3(256), 0, st, bx, rg, parity, f, inv));
+    if (has_walls(bx))
+        PSM_BY_STORAGE(hipLaunchKernelGGL(k_get_pdfs_wall<S>, dim3(blocks_for(bx.N, 256)), dim3(256), 0, st, bx, parity,
+                                          f, inv));
     return hipGetLastError();
 }
 
@@ -1683,33 +2014,39 @@ hipError_t launch_get_pdfs_at(int storage, const BoxDev& bx, int parity, const i
 
 hipError_t launch_macroscopic(int storage, const BoxDev& bx, int parity, double* rho, double* u, float inv,
                               hipStream_t st) {
-    unsigned g = blocks_for(bx.N, 256);
-    switch (storage) {
-        case 0: hipLaunchKernelGGL(k_macroscopic<St64>, dim3(g), dim3(256), 0, st, bx, parity, rho, u, inv); break;
-        case 1: hipLaunchKernelGGL(k_macroscopic<St32>, dim3(g), dim3(256), 0, st, bx, parity, rho, u, inv); break;
-        default: hipLaunchKernelGGL(k_macroscopic<St16>, dim3(g), dim3(256), 0, st, bx, parity, rho, u, inv); break;
-    }
+    const RowGrid rg = row_grid(bx);
+    PSM_BY_STORAGE(hipLaunchKernelGGL(k_macroscopic<S>, dim3(row_blocks(rg)), dim3(256), 0, st, bx, rg, parity, rho, u,
+                                      inv));
+    if (has_walls(bx))
+        PSM_BY_STORAGE(hipLaunchKernelGGL(k_macroscopic_wall<S>, dim3(blocks_for(bx.N, 256)), dim3(256), 0, st, bx,
+                                          parity, rho, u, inv));
     return hipGetLastError();
 }
 
 hipError_t launch_map_dense(const BoxDev& bx, const Particles& P, const int* tile_cnt, const int2* tile_ent,
                             int list_cap, TileShape ts, double* B, int* pid, unsigned long long* dropped, hipStream_t st) {
-    hipLaunchKernelGGL(k_map_dense, dim3(blocks_for(bx.N, 256)), dim3(256), 0, st, bx, P, tile_cnt, tile_ent,
+    hipLaunchKernelGGL(k_map_dense, dim3(bx.ntx * bx.nty * bx.ntz), dim3(WG), 0, st, bx, P, tile_cnt, tile_ent,
                        list_cap, ts, B, pid, dropped);
     return hipGetLastError();
 }
 
-int stats_blocks() { return 1024; }
+int stats_blocks() { return 2048; }
 
 hipError_t launch_stats(int storage, const BoxDev& bx, int parity, float inv, double* part, double* out,
                         hipStream_t st) {
-    int nb = stats_blocks();
-    switch (storage) {
-        case 0: hipLaunchKernelGGL(k_stats_partial<St64>, dim3(nb), dim3(256), 0, st, bx, parity, inv, part); break;
-        case 1: hipLaunchKernelGGL(k_stats_partial<St32>, dim3(nb), dim3(256), 0, st, bx, parity, inv, part); break;
-        default: hipLaunchKernelGGL(k_stats_partial<St16>, dim3(nb), dim3(256), 0, st, bx, parity, inv, part); break;
-    }
-    hipLaunchKernelGGL(k_stats_final, dim3(1), dim3(64), 0, st, part, nb, out);
+    // a wave per storage block while there are enough blocks of work for all
+    const long long work = ((long long)bx.pblk * bx.nz + 3) / 4;
+    const int nb = (int)std::min<long long>(stats_blocks(), work);
+    unsigned dz[2], dp[2];
+    udiv_magic(bx.pblk, dz);
+    udiv_magic(bx.pitch, dp);
+    if (has_walls(bx))
+        PSM_BY_STORAGE(hipLaunchKernelGGL((k_stats_partial<S, true>), dim3(nb), dim3(256), 0, st, bx, dz[0], dz[1], dp[0],
+                                          dp[1], parity, inv, part))
+    else
+        PSM_BY_STORAGE(hipLaunchKernelGGL((k_stats_partial<S, false>), dim3(nb), dim3(256), 0, st, bx, dz[0], dz[1],
+                                          dp[0], dp[1], parity, inv, part))
+    hipLaunchKernelGGL(k_stats_final, dim3(1), dim3(256), 0, st, part, nb, out);
     return hipGetLastError();
 }
 

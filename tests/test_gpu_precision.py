@@ -28,7 +28,7 @@ import pytest
 import oracle
 import paper_2303_11811_amd as psm
 from paper_2303_11811_amd import inputs
-from psm_cases import initial_f, make_engine, run_oracle
+from psm_cases import CX, CY, CZ, W, initial_f, make_engine, run_oracle
 
 pytestmark = pytest.mark.gpu
 
@@ -194,3 +194,78 @@ def test_fp16_one_step_every_cell_row_layouts(dims):
         ratio = np.max(np.abs(got - ref) / bound)
         print(f"[ratio] max |err|/bound = {ratio:.3g}", flush=True)
         assert np.all(np.abs(got - ref) <= bound), ratio
+
+
+IO_DIMS = [(4, 4, 4), (16, 17, 5), (17, 16, 19), (32, 9, 33), (33, 31, 6), (63, 5, 17), (64, 4, 16), (65, 6, 18),
+           (121, 7, 21), (130, 10, 34)]
+
+
+def _stored(values, storage, scale=1024.0):
+    """Canonical values f [19][N] after one rounding to the storage form."""
+    if storage == psm.PSM_FP64:
+        return values
+    w = W[:, None]
+    if storage == psm.PSM_FP32DEV:
+        return (values - w).astype(np.float32).astype(np.float64) + w
+    return ((values - w) * scale).astype(np.float16).astype(np.float64) / scale + w
+
+
+@pytest.mark.parametrize("storage", [psm.PSM_FP64, psm.PSM_FP32DEV, psm.PSM_FP16DEV])
+@pytest.mark.parametrize("dims", IO_DIMS)
+def test_state_io_rounds_once_and_reads_back(storage, dims):
+    """psm_set_pdfs stores every value of every cell rounded once (to nearest
+    even; for FP16 also where an FP32 value in between would be a tie), in boxes
+    whose rows end anywhere in a tile, and psm_get_pdfs returns the stored
+    values bit for bit; density, velocity and totals follow from them."""
+    import torch
+
+    print(f"[case] state io storage={storage} dims={dims}", flush=True)
+    rng = np.random.default_rng(sum(dims) + storage)
+    N = int(np.prod(dims))
+    f = W[:, None] + (rng.random((19, N)) - 0.5) * 4e-3
+    # an FP16 tie missed by 2^-30 of the scaled value: FP32 cannot hold the difference
+    half = rng.integers(0x3000, 0x4400, (19, N)).astype(np.uint16).view(np.float16).astype(np.float64)
+    step = np.spacing(half.astype(np.float16)).astype(np.float64)
+    tie = (half + 0.5 * step + np.where(rng.random((19, N)) < 0.5, 1, -1) * 2.0 ** -30) / 1024.0
+    f = np.where(rng.random((19, N)) < 0.3, W[:, None] + tie, f)
+    g = (3e-6, -2e-6, 1e-6)
+    eng = psm.Engine([psm.make_desc(*dims, 0.7, fext=g)], storage=storage)
+    eng.set_pdfs(0, f)
+    got = eng.get_pdfs(0).cpu().numpy()
+    rho, u = (a.cpu().numpy() for a in eng.get_macroscopic(0))
+    mass, mom, _ = eng.get_stats(0)
+    totals = torch.empty(4, dtype=torch.float64, device=eng.device)
+    field = torch.as_tensor(got).to(eng.device)
+    torch.cuda.synchronize()
+    psm.psm_field_stats_noalloc(field.data_ptr(), N, totals.data_ptr(), eng.stream.cuda_stream)
+    eng.synchronize()
+    eng.close()
+    assert np.array_equal(got, _stored(f, storage))
+    c = np.stack([CX, CY, CZ])
+    # sums of 19 and of 19 N terms of at most 1/3 and 1/18 each, rounded once per addition
+    assert np.all(np.abs(rho - got.sum(0)) <= 19 * 2.0 ** -52)
+    assert np.all(np.abs(u - (c @ got + 0.5 * np.array(g)[:, None])) <= 19 * 2.0 ** -52)
+    ref = np.array([got.sum(), *(c @ got).sum(1)])
+    bound = 2.0 ** -52 * 19 * N * np.array([1.0, 0.1, 0.1, 0.1])
+    assert np.all(np.abs(np.array([mass, *mom]) - ref) <= bound)
+    assert np.all(np.abs(totals.cpu().numpy() - ref) <= bound)
+
+
+@pytest.mark.parametrize("dims", IO_DIMS)
+def test_equilibrium_start_reaches_every_cell(dims):
+    """psm_set_equilibrium (FP64) gives E_q(rho, u) of eq. (5) in every cell of
+    boxes smaller than, as large as and past its tiles in every axis."""
+    import torch
+
+    print(f"[case] equilibrium dims={dims}", flush=True)
+    rng = np.random.default_rng(sum(dims))
+    N = int(np.prod(dims))
+    rho, u = 1.0 + (rng.random(N) - 0.5) * 1e-2, (rng.random((3, N)) - 0.5) * 0.1
+    for r in (rho, None):
+        eng = psm.Engine([psm.make_desc(*dims, 0.7)])
+        eng.set_equilibrium(0, torch.as_tensor(u), None if r is None else torch.as_tensor(r))
+        got = eng.get_pdfs(0).cpu().numpy()
+        eng.close()
+        cu = np.stack([CX, CY, CZ]).T @ u
+        ref = W[:, None] * ((1.0 if r is None else r) + 3.0 * cu + 4.5 * cu ** 2 - 1.5 * (u ** 2).sum(0))
+        assert np.all(np.abs(got - ref) <= 16 * 2.0 ** -53 * W[:, None])
