@@ -217,7 +217,7 @@ static Layout make_layout(const psm_box_desc* boxes, int nbox, int storage) {
     L.off_prevok = take(sizeof(int) * std::max(P, 1));
     L.off_tcnt = take(sizeof(int) * 2 * (size_t)Tmax);
     L.off_tent = take(sizeof(int2) * (size_t)Tmax * L.list_cap);
-    L.off_partial = take(sizeof(double) * 6 * (size_t)L.cap_max);
+    L.off_partial = take(sizeof(double) * 12 * (size_t)L.cap_max);
     L.off_misc = take(256);
     L.off_statpart = take(sizeof(double) * 4 * (size_t)stats_blocks() + 64);
     for (int p = 0; p < 2; ++p) L.off_grid[p].resize(nbox);
@@ -265,7 +265,7 @@ struct psm_ctx {
     int* d_tcnt[2] = {nullptr, nullptr};
     int2* d_tent = nullptr;
     int list_parity = 0;
-    double* d_partial = nullptr;
+    double* d_partial[2] = {nullptr, nullptr};   // force partials, by the grid parity of the step that writes them
     int* d_misc = nullptr;               // [8..9] dropped (u64),
                                          // [32..39] tile counters of the persistent grid
     int* d_flags = nullptr;              // device error words (FLAG_* bits, list overflows), right after the force sums
@@ -369,7 +369,8 @@ static SphereParams sphere_params(psm_ctx* c) {
     sp.boxes = c->d_boxes;
     sp.part_box = c->d_partbox;
     sp.P = c->P;
-    sp.partial = c->d_partial;
+    sp.partial = c->d_partial[c->parity ^ 1];   // c->parity is the next step's
+    sp.partial_next = c->d_partial[c->parity];
     sp.P_total = c->P_total;
     sp.ts = c->ts;
     sp.dt = 0.0;
@@ -603,7 +604,8 @@ extern "C" int psm_create(const psm_box_desc* boxes, int nbox, int storage, doub
     c->d_tcnt[0] = (int*)(c->ws + L.off_tcnt);
     c->d_tcnt[1] = c->d_tcnt[0] + L.T_max;
     c->d_tent = (int2*)(c->ws + L.off_tent);
-    c->d_partial = (double*)(c->ws + L.off_partial);
+    c->d_partial[0] = (double*)(c->ws + L.off_partial);
+    c->d_partial[1] = c->d_partial[0] + 6 * L.cap_max;
     c->d_misc = (int*)(c->ws + L.off_misc);
     c->d_flags = (int*)(c->P.acc + 6 * P1);
     c->d_statpart = (double*)(c->ws + L.off_statpart);
@@ -929,7 +931,11 @@ static int step_params(psm_ctx* c, int parity, StepParams& kp) {
     kp.tile_cnt = c->d_tcnt[c->list_parity];
     kp.tile_ent = c->d_tent;
     kp.list_cap = c->L.list_cap;
-    kp.partial = c->d_partial;
+    kp.partial = c->d_partial[parity];
+    kp.partial_prev = nullptr;
+    kp.part_box = c->d_partbox;
+    kp.P_total = c->P_total;
+    kp.grid = c->grid;
     kp.T_total = c->T_total;
     kp.tx = c->ts.tx; kp.ty = c->ts.ty; kp.tz = c->ts.tz;
     kp.ref_z = c->ts.ref_z;
@@ -979,12 +985,19 @@ static hipEvent_t next_event(psm_ctx* c) {
     return c->ev[c->ev_used++];
 }
 
-// The step kernel, then per sphere the force reduction (with `readback` also to
-// the host); with a scheme, the sphere update and the new lists in the same
-// launch.
-static int enqueue_step(psm_ctx* c, bool timed, int scheme = SCHEME_NONE, double dt = 0.0, bool readback = false) {
+// What follows or goes along with a step kernel.
+struct AfterStep {
+    bool prev = false;           // reduce the forces of the step before in this launch
+    bool reduce = true;          // reduce this step's forces behind it
+    bool readback = false;       // ... to the host as well
+    int scheme = SCHEME_NONE;    // ... with the sphere update and the new lists
+    double dt = 0.0;
+};
+
+static int enqueue_step(psm_ctx* c, bool timed, const AfterStep& after) {
     StepParams kp;
     step_params(c, c->parity, kp);
+    if (after.prev && c->P_total > 0) kp.partial_prev = c->d_partial[c->parity ^ 1];
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (timed) {
         e0 = next_event(c);
@@ -995,15 +1008,31 @@ static int enqueue_step(psm_ctx* c, bool timed, int scheme = SCHEME_NONE, double
     // the persistent grid's tile counters start at zero (a kernel, not a
     // memset: the step may be captured into a graph)
     if (kp.queue) HIP_TRY(launch_fill_int(kp.queue, NXCD, 0, c->stream));
-    HIP_TRY(launch_step(c->storage, c->map_mode, c->ts.filter != 0, c->walls, kp, c->grid, c->stream));
+    HIP_TRY(launch_step(c->storage, c->map_mode, c->ts.filter != 0, c->walls, kp, c->stream));
     if (timed) HIP_TRY(hipEventRecord(e1, c->stream));
-    SphereParams sp = sphere_params(c);
-    sp.dt = dt;
-    if (readback) sp.host_acc = c->h_rb;
-    HIP_TRY(launch_spheres(true, scheme, scheme != SCHEME_NONE, sp, c->stream));
-    if (scheme != SCHEME_NONE && c->P_total > 0) c->list_parity ^= 1;
     c->parity ^= 1;
     c->rb_valid = false;
+    if (!after.reduce) return PSM_OK;
+    SphereParams sp = sphere_params(c);
+    sp.dt = after.dt;
+    if (after.readback) sp.host_acc = c->h_rb;
+    const bool lists = after.scheme != SCHEME_NONE;
+    HIP_TRY(launch_spheres(true, after.scheme, lists, sp, c->stream));
+    if (lists && c->P_total > 0) c->list_parity ^= 1;
+    return PSM_OK;
+}
+
+// n steps of fixed spheres: the forces of each are reduced in the launch of
+// the next, those of the last in a launch of their own.
+static int enqueue_steps(psm_ctx* c, int n, bool timed, bool readback) {
+    for (int s = 0; s < n; ++s) {
+        AfterStep after;
+        after.prev = s > 0;
+        after.reduce = s == n - 1;
+        after.readback = readback && after.reduce;
+        int rc = enqueue_step(c, timed, after);
+        if (rc) return rc;
+    }
     return PSM_OK;
 }
 
@@ -1014,7 +1043,11 @@ static int build_graph(psm_ctx* c, hipGraphExec_t* out, int scheme = SCHEME_NONE
     HIP_TRY(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
     const int parity = c->parity, list_parity = c->list_parity;
     int rc = PSM_OK;
-    for (int s = 0; s < kGraphSteps && rc == PSM_OK; ++s) rc = enqueue_step(c, false, scheme, dt);
+    if (scheme == SCHEME_NONE) rc = enqueue_steps(c, kGraphSteps, false, false);
+    AfterStep update;
+    update.scheme = scheme;
+    update.dt = dt;
+    for (int s = 0; scheme != SCHEME_NONE && s < kGraphSteps && rc == PSM_OK; ++s) rc = enqueue_step(c, false, update);
     c->parity = parity;
     c->list_parity = list_parity;
     hipError_t e = hipStreamEndCapture(c->stream, &g);
@@ -1050,10 +1083,8 @@ extern "C" int psm_step(psm_ctx* c, int nsteps) {
         }
     }
     const bool last_eager = left > 0;
-    for (; left > 0; --left) {
-        int rc = enqueue_step(c, c->timing, SCHEME_NONE, 0.0, c->rb_on && left == 1);
-        if (rc) return rc;
-    }
+    int rc = enqueue_steps(c, left, c->timing, c->rb_on);
+    if (rc) return rc;
     if (c->rb_on && nsteps > 0 && c->P_total > 0) {
         // the force sums of every box and the error words: the last step's
         // reduction writes them, after a graph replay a kernel of their own
@@ -1255,8 +1286,11 @@ extern "C" int psm_run(psm_ctx* c, int nsteps, double dt, int scheme) {
             left -= kGraphSteps;   // an even count: the parity is unchanged
         }
     }
+    AfterStep update;
+    update.scheme = sch;
+    update.dt = dt;
     for (; left > 0; --left) {
-        rc = enqueue_step(c, c->timing, sch, dt);
+        rc = enqueue_step(c, c->timing, update);
         if (rc) return rc;
     }
     if (nsteps > 0)
@@ -1362,7 +1396,7 @@ extern "C" int psm_pattern_copy(psm_ctx* c, int shifted, int nrep, double* ms) {
     hipError_t err = hipEventCreate(&e[1]);
     if (err == hipSuccess) err = hipEventRecord(e[0], c->stream);
     for (int i = 0; i < nrep && err == hipSuccess; ++i)
-        err = launch_pattern_copy(c->storage, shifted != 0, kp, c->grid, c->stream);
+        err = launch_pattern_copy(c->storage, shifted != 0, kp, c->stream);
     if (err == hipSuccess) err = hipEventRecord(e[1], c->stream);
     if (err == hipSuccess) err = hipEventSynchronize(e[1]);
     float t = 0.0f;

@@ -303,6 +303,12 @@ struct StepParams {
     const int2* tile_ent;       // [T][list_cap] global particle id and force-partial slot
     int list_cap;
     double* partial;            // [slots][6]
+    // force reduction of the step before (its partials; null: none) by the
+    // workgroups from `grid` on, 4 spheres each
+    const double* partial_prev;
+    const int* part_box;        // [P] box of each global particle slot
+    int P_total;
+    int grid;                   // workgroups that walk tiles
     int T_total;
     int tx, ty, tz;
     int ref_z;                  // TileShape::ref_z
@@ -319,7 +325,9 @@ struct SphereParams {
     const BoxDev* boxes;
     const int* part_box;        // [P] box of each global particle slot
     Particles P;
-    double* partial;            // [slots][6] force partials; zeroed for an entry a full list drops
+    // force partials [slots][6] of the last step, and those the next step
+    // writes: both zeroed for an entry a full list drops
+    double *partial, *partial_next;
     int P_total;
     TileShape ts;
     double dt;                  // sphere update
@@ -359,8 +367,8 @@ struct DownloadParams {
     int* err_dst;
 };
 
-hipError_t launch_step(int storage, int map, bool filt, bool wall, const StepParams& kp, int grid, hipStream_t st);
-hipError_t launch_pattern_copy(int storage, bool shifted, const StepParams& kp, int grid, hipStream_t st);
+hipError_t launch_step(int storage, int map, bool filt, bool wall, const StepParams& kp, hipStream_t st);
+hipError_t launch_pattern_copy(int storage, bool shifted, const StepParams& kp, hipStream_t st);
 int step_blocks_per_cu(int storage, int map, bool filt, bool wall);
 hipError_t launch_spheres(bool reduce, int scheme, bool bin, const SphereParams& sp, hipStream_t st);
 hipError_t launch_upload_bin(const SphereParams& sp, const UploadParams& up, hipStream_t st);

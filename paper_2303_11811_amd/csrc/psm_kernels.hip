@@ -371,6 +371,42 @@ __device__ __forceinline__ float wrap32(float t, float L, float invL) { return f
         F[18] = S::ld(rm, o0p, 18 * QB);     \
     } while (0)
 
+__device__ inline void box_tiles(const BoxDev& bx, const TileShape& ts, double x, double y, double z, double r,
+                                 AxisTiles& ax, AxisTiles& ay, AxisTiles& az) {
+    int lo, hi;
+    aabb_cells(x, r, lo, hi);
+    ax = axis_tiles(lo, hi, bx.nx, ts.tx, bx.ntx);
+    aabb_cells(y, r, lo, hi);
+    ay = axis_tiles(lo, hi, bx.ny, ts.ty, bx.nty);
+    aabb_cells(z, r, lo, hi);
+    az = axis_tiles(lo, hi, bx.nz, ts.tz, bx.ntz);
+}
+
+//   UPLOAD  the spheres of one box first take new columns from pinned host
+//           staging (lane c reads column c), before their tiles are found.
+// Force and torque of global sphere p from its tile partials, for the whole
+// wave: lane l takes tiles l, l + 64, ... of the bounding box in a fixed order,
+// then a fixed butterfly adds the lanes (the same bits on every lane).
+__device__ __forceinline__ void reduce_sphere(const BoxDev& bx, const TileShape& ts, const Particles& P,
+                                              const double* partial, int p, int lane, double acc[6]) {
+#pragma unroll
+    for (int c = 0; c < 6; ++c) acc[c] = 0.0;
+    const int lp = p - bx.part_base;
+    if (lp < bx.np) {
+        AxisTiles ax, ay, az;
+        box_tiles(bx, ts, P.x[p], P.y[p], P.z[p], P.r[p], ax, ay, az);
+        const int ntot = ax.count() * ay.count() * az.count();
+        // the sphere's slots: one per tile of its bounding box, in that order
+        const double* pp = partial + ((long long)bx.pbase + (long long)lp * bx.pstride) * 6;
+        for (int k = lane; k < ntot; k += 64) {
+#pragma unroll
+            for (int c = 0; c < 6; ++c) acc[c] += pp[(long long)k * 6 + c];
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < 6; ++c) acc[c] = wave_sum(acc[c]);
+}
+
 template <class S, int MAP, bool FILT, bool WALL>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
     !S::DEV ? PSM_WAVES_F64 : (S::SCALED && MAP == 0 && !FILT ? PSM_WAVES_F16 : PSM_WAVES_DEV), 8))) void k_psm_step(
@@ -393,11 +429,27 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
     const int TX = kp.tx, TY = kp.ty, TZ = kp.tz;
     const int wave = tid >> 6, lane = tid & 63;
 
+    if ((int)blockIdx.x >= kp.grid) {
+        // the force reduction of the step before (k_spheres reduces the last
+        // step of a call): in a launch of its own it takes 4.5 us behind every
+        // step, a third of a 32^3 step
+        const int p = (blockIdx.x - kp.grid) * NWAVE + wave;
+        if (p >= kp.P_total) return;
+        double acc[6];
+        const TileShape ts{kp.tx, kp.ty, kp.tz, 0, 0, 0};
+        reduce_sphere(kp.boxes[kp.part_box[p]], ts, kp.P, kp.partial_prev, p, lane, acc);
+        if (lane == 0) {
+#pragma unroll
+            for (int c = 0; c < 6; ++c) kp.P.acc[6LL * p + c] = acc[c];
+        }
+        return;
+    }
+
     // XCD-aware persistent schedule: workgroup b runs on die b % 8; each die
     // walks one contiguous eighth of the tile list so that x-neighbouring
     // tiles (which share the cache lines of the shifted pulls) meet in the
     // same L2.
-    const int G = gridDim.x;
+    const int G = kp.grid;
     const int xcd = blockIdx.x % NXCD;
     const int gx8 = (G - xcd + NXCD - 1) / NXCD;
     const int m = blockIdx.x / NXCD;
@@ -906,10 +958,8 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
 
 // ---------------------------------------------------------------------------
 // Work per sphere, one 64-wide wave each:
-//   REDUCE  force and torque: the sum of the tile partials over the tiles of
-//           the sphere's bounding box; lane l takes tiles l, l + 64, ... in
-//           the fixed bounding-box order, then a fixed butterfly adds the
-//           lanes (deterministic).
+//   REDUCE  force and torque of the last step (reduce_sphere; earlier steps of
+//           one call are reduced inside the next step's launch).
 //   SCHEME  sphere update (Sec. 2.2.2) for collision-free spheres:
 //           m = rho_p (4/3) pi r^3, I = (2/5) m r^2; the total force is the
 //           hydrodynamic force of the last step plus m times the box's
@@ -930,19 +980,6 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
 // are built in one launch (counting, scanning and filling compact lists took
 // seven of 2-5 us each), and psm_run does all three parts in one: 9 launches
 // beside the step kernel became 1.
-__device__ inline void box_tiles(const BoxDev& bx, const TileShape& ts, double x, double y, double z, double r,
-                                 AxisTiles& ax, AxisTiles& ay, AxisTiles& az) {
-    int lo, hi;
-    aabb_cells(x, r, lo, hi);
-    ax = axis_tiles(lo, hi, bx.nx, ts.tx, bx.ntx);
-    aabb_cells(y, r, lo, hi);
-    ay = axis_tiles(lo, hi, bx.ny, ts.ty, bx.nty);
-    aabb_cells(z, r, lo, hi);
-    az = axis_tiles(lo, hi, bx.nz, ts.tz, bx.ntz);
-}
-
-//   UPLOAD  the spheres of one box first take new columns from pinned host
-//           staging (lane c reads column c), before their tiles are found.
 template <bool REDUCE, int SCHEME, bool BIN, bool UPLOAD = false>
 __global__ __launch_bounds__(256) void k_spheres(SphereParams sp, UploadParams up = UploadParams{}) {
 #pragma clang fp contract(off)
@@ -979,23 +1016,10 @@ __global__ __launch_bounds__(256) void k_spheres(SphereParams sp, UploadParams u
     }
     double acc[6];
     if (REDUCE) {
+        reduce_sphere(bx, sp.ts, sp.P, sp.partial, p, lane, acc);
+        if (lane == 0) {
 #pragma unroll
-        for (int c = 0; c < 6; ++c) acc[c] = 0.0;
-        if (there) {
-            AxisTiles ax, ay, az;
-            box_tiles(bx, sp.ts, pos[0], pos[1], pos[2], r, ax, ay, az);
-            const int ntot = ax.count() * ay.count() * az.count();
-            // the sphere's slots: one per tile of its bounding box, in that order
-            const double* pp = sp.partial + slot0 * 6;
-            for (int k = lane; k < ntot; k += 64) {
-#pragma unroll
-                for (int c = 0; c < 6; ++c) acc[c] += pp[(long long)k * 6 + c];
-            }
-        }
-#pragma unroll
-        for (int c = 0; c < 6; ++c) {
-            acc[c] = wave_sum(acc[c]);   // the same bits on every lane
-            if (lane == 0) sp.P.acc[6LL * p + c] = acc[c];
+            for (int c = 0; c < 6; ++c) sp.P.acc[6LL * p + c] = acc[c];
         }
         if (sp.host_acc) {
             // lanes 0-5: one 48-B store to the host
@@ -1078,7 +1102,10 @@ __global__ __launch_bounds__(256) void k_spheres(SphereParams sp, UploadParams u
                 // a list holds at most MAXC spheres: the excess is dropped and reported
                 atomicMax(sp.over, at + 1);
 #pragma unroll
-                for (int c = 0; c < 6; ++c) sp.partial[(slot0 + k) * 6 + c] = 0.0;
+                for (int c = 0; c < 6; ++c) {
+                    sp.partial[(slot0 + k) * 6 + c] = 0.0;
+                    sp.partial_next[(slot0 + k) * 6 + c] = 0.0;
+                }
             }
         }
     }
@@ -1874,7 +1901,7 @@ __global__ __launch_bounds__(WG) void k_pattern_copy(StepParams kp) {
     }
 }
 
-hipError_t launch_pattern_copy(int storage, bool shifted, const StepParams& kp, int grid, hipStream_t st) {
+hipError_t launch_pattern_copy(int storage, bool shifted, const StepParams& kp, hipStream_t st) {
     const void* k;
     switch (storage) {
         case 0: k = shifted ? (const void*)k_pattern_copy<St64, true> : (const void*)k_pattern_copy<St64, false>; break;
@@ -1882,7 +1909,7 @@ hipError_t launch_pattern_copy(int storage, bool shifted, const StepParams& kp, 
         default: k = shifted ? (const void*)k_pattern_copy<St16, true> : (const void*)k_pattern_copy<St16, false>;
     }
     void* args[] = {(void*)&kp};
-    return hipLaunchKernel(k, dim3(grid), dim3(WG), args, 0, st);
+    return hipLaunchKernel(k, dim3(kp.grid), dim3(WG), args, 0, st);
 }
 
 template <int MAP, bool FILT, bool WALL>
@@ -1904,9 +1931,10 @@ static const void* step_kernel(int storage, int map, bool filt, bool wall) {
     return wall ? step_kernel_walls<true>(storage, map, filt) : step_kernel_walls<false>(storage, map, filt);
 }
 
-hipError_t launch_step(int storage, int map, bool filt, bool wall, const StepParams& kp, int grid, hipStream_t st) {
+hipError_t launch_step(int storage, int map, bool filt, bool wall, const StepParams& kp, hipStream_t st) {
     void* args[] = {(void*)&kp};
-    return hipLaunchKernel(step_kernel(storage, map, filt, wall), dim3(grid), dim3(WG), args, 0, st);
+    const unsigned reduce = kp.partial_prev ? blocks_for(kp.P_total, NWAVE) : 0u;
+    return hipLaunchKernel(step_kernel(storage, map, filt, wall), dim3(kp.grid + reduce), dim3(WG), args, 0, st);
 }
 
 int step_blocks_per_cu(int storage, int map, bool filt, bool wall) {

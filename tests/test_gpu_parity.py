@@ -555,3 +555,33 @@ def test_sampled_fractions_of_every_subdivision(nsub):
     assert_pdfs_close(f, ref.f, 1e-12)
     assert_forces_close(F, ref.F, ref.A)
     eng.close()
+
+
+@pytest.mark.parametrize("storage", [psm.PSM_FP64, psm.PSM_FP16DEV])
+@pytest.mark.parametrize("n", [2, 3, 10, 21])
+def test_steps_in_one_call_equal_single_steps(n, storage):
+    """n steps in one call (their reductions ride on the following launches;
+    with graphs 10 at a time), eager, replayed and on the persistent grid: PDFs,
+    forces and torques of two uneven boxes bit for bit those of n calls, also
+    for a second round of calls."""
+    specs = [inputs.random_small((44, 36, 30), 5, (3.0, 4.5), seed=95, tau=0.62, fext=(1e-5, 0, 0), omamp=0.002),
+             inputs.random_small((21, 50, 17), 3, (2.5, 3.5), seed=96, tau=0.8)]
+    out = []
+    for form, launch in (("single", 0), ("eager", 0), ("graph", 0), ("graph", psm.PSM_LAUNCH_PERSISTENT)):
+        _print_case("steps in one call", n=n, storage=storage, form=form, launch=launch)
+        eng = make_engine(specs, storage=storage)
+        eng.set_launch(32, 8, 2, launch)
+        eng.set_graph(form == "graph")
+        for b, s in enumerate(specs):
+            eng.set_pdfs(b, initial_f(s))
+            eng.set_particles(b, s.x, s.r, s.U, s.Om)
+        got = []
+        for _ in range(2):
+            for _ in range(n if form == "single" else 1):
+                eng.step(1 if form == "single" else n)
+            for b in range(2):
+                got += [*eng.get_forces(b), eng.get_pdfs(b).cpu().numpy()]
+        out.append(got)
+        eng.close()
+    for other in out[1:]:
+        assert all(np.array_equal(a, b) for a, b in zip(out[0], other))
