@@ -114,8 +114,16 @@ def _check(rc):
     return rc
 
 
+_byref, _first_double = ctypes.byref, ctypes.c_double.from_buffer
+
+
 def _dptr(a):
-    return None if a is None else a.ctypes.data_as(_D)
+    if a is None:
+        return None
+    try:
+        return _byref(_first_double(a))   # a quarter of the time of data_as (2 us)
+    except (TypeError, ValueError):       # read-only or empty
+        return a.ctypes.data_as(_D)
 
 
 def make_desc(nx, ny, nz, tau, fext=(0.0, 0.0, 0.0), max_particles=0, max_radius=1.0,
@@ -339,6 +347,7 @@ class Engine:
         # a stream of its own (default priority): graph capture needs a
         # non-legacy stream, and every torch op of this engine runs on it
         self.stream = torch.cuda.Stream(self.device)
+        self._caller_done, self._engine_done = torch.cuda.Event(), torch.cuda.Event()
         nbytes = psm_workspace_size(self.descs, self.storage)
         with torch.cuda.stream(self.stream):
             self.workspace = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
@@ -375,6 +384,21 @@ class Engine:
             t.record_stream(cur)
         return tensors if len(tensors) > 1 else tensors[0]
 
+    def _read_out(self, shapes, launch):
+        """New tensors of the caller's current stream (shapes: (shape, dtype)
+        each), filled by ``launch(pointers...)`` on the engine stream: ordered
+        after what the caller enqueued before and before what comes after, so
+        the tensors belong to the caller's stream alone."""
+        t = self.torch
+        cur = t.cuda.current_stream(self.device)
+        out = [t.empty(shape, dtype=dtype, device=self.device) for shape, dtype in shapes]
+        self._caller_done.record(cur)
+        self.stream.wait_event(self._caller_done)
+        launch(*(o.data_ptr() for o in out))
+        self._engine_done.record(self.stream)
+        cur.wait_event(self._engine_done)
+        return out
+
     def _dev(self, a, dtype=None):
         t = self.torch
         if isinstance(a, t.Tensor):
@@ -395,10 +419,8 @@ class Engine:
             self._keep = (f_d,)
 
     def get_pdfs(self, box=0):
-        with self._enter():
-            f = self.torch.empty((19, self.N(box)), dtype=self.torch.float64, device=self.device)
-            psm_get_pdfs(self.ctx, box, f.data_ptr())
-        return self._hand_back(f)
+        return self._read_out([((19, self.N(box)), self.torch.float64)],
+                              lambda f: psm_get_pdfs(self.ctx, box, f))[0]
 
     def get_pdfs_at(self, box, cells):
         with self._enter():
@@ -411,11 +433,9 @@ class Engine:
         return self._hand_back(out)
 
     def get_macroscopic(self, box=0):
-        with self._enter():
-            rho = self.torch.empty(self.N(box), dtype=self.torch.float64, device=self.device)
-            u = self.torch.empty((3, self.N(box)), dtype=self.torch.float64, device=self.device)
-            psm_get_macroscopic(self.ctx, box, rho.data_ptr(), u.data_ptr())
-        return self._hand_back(rho, u)
+        f64, N = self.torch.float64, self.N(box)
+        return tuple(self._read_out([((N,), f64), ((3, N), f64)],
+                                    lambda rho, u: psm_get_macroscopic(self.ctx, box, rho, u)))
 
     def set_particles(self, box, x, r, U, omega=None):
         psm_set_particles(self.ctx, box, x, r, U, omega)
@@ -446,11 +466,9 @@ class Engine:
         return psm_get_particles(self.ctx, box, self.np[box])
 
     def get_solid_fraction(self, box=0):
-        with self._enter():
-            B = self.torch.empty((2, self.N(box)), dtype=self.torch.float64, device=self.device)
-            pid = self.torch.empty((2, self.N(box)), dtype=self.torch.int32, device=self.device)
-            psm_get_solid_fraction(self.ctx, box, B.data_ptr(), pid.data_ptr())
-        return self._hand_back(B, pid)
+        N = self.N(box)
+        return tuple(self._read_out([((2, N), self.torch.float64), ((2, N), self.torch.int32)],
+                                    lambda B, pid: psm_get_solid_fraction(self.ctx, box, B, pid)))
 
     def get_stats(self, box=0):
         return psm_get_stats(self.ctx, box)

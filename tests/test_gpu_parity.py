@@ -585,3 +585,39 @@ def test_steps_in_one_call_equal_single_steps(n, storage):
         eng.close()
     for other in out[1:]:
         assert all(np.array_equal(a, b) for a, b in zip(out[0], other))
+
+
+@pytest.mark.parametrize("side_stream", [False, True])
+def test_read_outs_follow_the_callers_stream(side_stream):
+    """Fields read from a stream of the caller's own, each dropped at once and
+    its memory overwritten there before the next read: the engine's kernels
+    are ordered after and before that work, so every read has its values."""
+    import contextlib
+
+    import torch
+
+    spec = inputs.random_small((64, 60, 50), 5, (3.0, 4.5), seed=98, tau=0.7)
+    eng = make_engine([spec])
+    eng.set_pdfs(0, initial_f(spec))
+    eng.set_particles(0, spec.x, spec.r, spec.U, spec.Om)
+    eng.step(2)
+    torch.cuda.synchronize()
+    rho0, u0 = (a.clone() for a in eng.get_macroscopic(0))
+    B0, pid0 = (a.clone() for a in eng.get_solid_fraction(0))
+    f0 = eng.get_pdfs(0).clone()
+    torch.cuda.synchronize()
+    _print_case("read-outs", side_stream=side_stream)
+    s = torch.cuda.Stream()
+    same = []
+    with torch.cuda.stream(s) if side_stream else contextlib.nullcontext():
+        for _ in range(20):
+            for read, ref in ((eng.get_macroscopic, (rho0, u0)), (eng.get_solid_fraction, (B0, pid0)),
+                              (lambda b: (eng.get_pdfs(b),), (f0,))):
+                got = read(0)
+                same += [(a == b).all() for a, b in zip(got, ref)]
+                for a in got:
+                    a.fill_(7)
+                del got
+    torch.cuda.synchronize()
+    assert all(bool(v) for v in same)
+    eng.close()
