@@ -67,35 +67,47 @@ static int cdiv(long long a, long long b) { return (int)((a + b - 1) / b); }
 // Launch of a context that sets none: tiles of 64 x 4 threads, as many cells
 // deep as the storage form gains from while enough tiles are left to fill 256
 // CUs. us per step at depth 1 / 2 / 4 / 8 / 16 (spheres at 10 %):
-//   FP64  32^3   13.1 / 16.8 / 24.6 / 37.3 / 62.9    256^3  918 / 934 / 979 / 1003 / 1013
-//   FP32  64^3   17.0 / 17.7 / 22.6 / 33.9 / 58.0    256^3  528 / 489 / 506 / 537 / 544
-//   FP16  64^3   14.8 / 15.4 / 20.0 / 30.1 / 53.2    128^3  61.5 / 51.5 / 49.9 / 49.9 / 73.0
-//         96^3   39.5 / 35.1 / 36.2 / 42.1 / 65.1    384^3  1365 / 1058 / 920 / 879 / 888
+//   FP64  32^3   8.5 / 16.8 / 24.6 / 37.3 / 62.9      256^3  918 / 934 / 979 / 1003 / 1013
+//   FP32  88^3  34.8 / 35.3 / 38.9 / 40.3 / 58.8      96^3  38.9 / 37.6 / 41.6 / 47.0 / 64.2
+//         256^3  506 / 474 / 498 / 529 / 533
+//   FP16  64^3   9.6 / 10.6 / 15.3 / 24.2 / 46.2      72^3  16.5 / 15.6 / 17.4 / 27.8 / 45.8
+//         144^3 84.2 / 73.0 / 75.8 / 84.8 / 89.7      160^3  102 / 83.2 / 80.7 / 87.3 / 94.5
+//         384^3  848 at depth 4, 857 at 8
 // A deeper tile runs its cells one after another in each wave, which is lost
 // time while CUs are idle; the deviation forms, whose spheres cost more beside
 // fewer bytes, gain from staging them once for more cells. The FP32 geometry
-// refers to the centres of blocks 16 planes deep at every depth, so the
-// results do not depend on the depth chosen.
+// refers to the centres of blocks 64 x 4 cells wide and 16 planes deep at every
+// depth, so the results do not depend on the depth chosen. FP64, which has no
+// such reference, takes 32 x 8 threads where the narrowest box fills at most 3/4
+// of its 64-wide tiles (us at 64 x 4 / 32 x 8: 68^3 31.4 / 28.8, 80^3 39.9 /
+// 34.2, 96^3 58.9 / 54.4; 132^3, where it would save a sixth, 163 / 183).
 constexpr int kDefaultRefZ = 16;
 
 static TileShape default_shape(const psm_box_desc* boxes, int nbox, int storage) {
     struct Depth {
         int tz;
-        long long tiles;   // fewest tiles it is taken at
+        long long tiles;   // fewest tiles FP32 and FP16 take it at
     };
-    static const Depth depths[] = {{8, 8192}, {4, 1800}, {2, 1500}, {1, 0}};
-    const int most = storage == PSM_FP64 ? 1 : (storage == PSM_FP32DEV ? 2 : 8);
+    static const Depth f32[] = {{2, 2000}, {1, 0}}, f16[] = {{4, 4500}, {2, 1300}, {1, 0}};
     TileShape ts{64, 4, 1, 0, 0, kDefaultRefZ};
-    for (const Depth& d : depths) {
+    if (storage == PSM_FP64) {
+        bool narrow = true;
+        for (int b = 0; b < nbox; ++b) narrow = narrow && 4 * cdiv(boxes[b].nx, 32) <= 6 * cdiv(boxes[b].nx, 64);
+        if (narrow) {
+            ts.tx = 32;
+            ts.ty = 8;
+        }
+        return ts;
+    }
+    for (const Depth* d = storage == PSM_FP32DEV ? f32 : f16;; ++d) {
         long long T = 0;
         for (int b = 0; b < nbox; ++b)
-            T += (long long)cdiv(boxes[b].nx, ts.tx) * cdiv(boxes[b].ny, ts.ty) * cdiv(boxes[b].nz, d.tz);
-        if (d.tz <= most && T >= d.tiles) {
-            ts.tz = d.tz;
-            break;
+            T += (long long)cdiv(boxes[b].nx, ts.tx) * cdiv(boxes[b].ny, ts.ty) * cdiv(boxes[b].nz, d->tz);
+        if (T >= d->tiles) {
+            ts.tz = d->tz;
+            return ts;
         }
     }
-    return ts;
 }
 
 // Largest number of tiles the bounding box [x-(r+1), x+(r+1)] can touch along

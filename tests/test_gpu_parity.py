@@ -511,25 +511,25 @@ def test_state_and_argument_errors_on_a_live_context():
     eng.close()
 
 
-@pytest.mark.parametrize("storage,dims,depth", [
-    (psm.PSM_FP64, (70, 21, 18), 1), (psm.PSM_FP32DEV, (33, 40, 27), 1), (psm.PSM_FP32DEV, (130, 98, 81), 2),
-    (psm.PSM_FP16DEV, (45, 38, 31), 1), (psm.PSM_FP16DEV, (130, 98, 81), 2), (psm.PSM_FP16DEV, (140, 130, 101), 4),
-    (psm.PSM_FP16DEV, (256, 256, 249), 8)])
-def test_default_depth_keeps_the_results_of_depth_16(storage, dims, depth):
-    """The launch a context starts with (64 x 4 threads, a depth chosen from
-    storage and size) gives bit for bit the PDFs of 64 x 4 x 16; the force
+@pytest.mark.parametrize("storage,dims,launch", [
+    (psm.PSM_FP64, (30, 21, 18), (32, 8, 1, 0)), (psm.PSM_FP64, (70, 21, 18), (32, 8, 1, 0)),
+    (psm.PSM_FP64, (97, 21, 18), (64, 4, 1, 0)), (psm.PSM_FP32DEV, (33, 40, 27), (64, 4, 1, 0)),
+    (psm.PSM_FP32DEV, (130, 98, 81), (64, 4, 2, 0)), (psm.PSM_FP16DEV, (45, 38, 31), (64, 4, 1, 0)),
+    (psm.PSM_FP16DEV, (130, 98, 81), (64, 4, 2, 0)), (psm.PSM_FP16DEV, (190, 160, 152), (64, 4, 4, 0))])
+def test_default_depth_keeps_the_results_of_depth_16(storage, dims, launch):
+    """The launch a context starts with (chosen from storage and size) gives bit for bit the PDFs of 64 x 4 x 16; the force
     sums add the same FP64 wave sums in another order (below 1e-13 of the
     magnitude of their terms, a few thousand of them)."""
     n = 6 if dims[0] < 100 else 40
     spec = inputs.random_small(dims, n, (2.5, 4.0), seed=17, tau=0.63, fext=(1e-5, 0.0, -4e-6), omamp=0.003)
     out = []
-    for launch in (None, (64, 4, 16, 0)):
-        _print_case("default depth", storage=storage, dims=dims, launch=launch)
+    for default in (True, False):
+        _print_case("default depth", storage=storage, dims=dims, default=default)
         eng = make_engine([spec], storage=storage)
-        if launch is None:
-            assert eng.get_launch() == (64, 4, depth, 0)
+        if default:
+            assert eng.get_launch() == launch
         else:
-            eng.set_launch(*launch)
+            eng.set_launch(64, 4, 16, 0)
         eng.set_equilibrium(0, spec.u0, spec.rho0)
         eng.set_particles(0, spec.x, spec.r, spec.U, spec.Om)
         eng.step(3)
