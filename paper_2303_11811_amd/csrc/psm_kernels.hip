@@ -407,12 +407,34 @@ __device__ __forceinline__ void reduce_sphere(const BoxDev& bx, const TileShape&
     for (int c = 0; c < 6; ++c) acc[c] = wave_sum(acc[c]);
 }
 
+// Byte offset of a cell inside a z-plane (direction 0): its block of 64 cells
+// is NQ runs long. In-plane cells are below 2^24 (a plane holds fewer than
+// 2^31 bytes in FP64), so the products are 24-bit ones.
+template <class T> __device__ __forceinline__ unsigned cell_offset(int x, int y, int pitch) {
+    const unsigned c = (unsigned)x + __umul24((unsigned)pitch, (unsigned)y);
+    return __umul24(c & ~(unsigned)(BLK - 1), (NQ - 1) * (unsigned)sizeof(T)) + c * (unsigned)sizeof(T);
+}
+
+// The step kernel's arguments, read anew at each use of this function: held in
+// scalar registers from the start of the kernel they are spilled lane by
+// lane to vector registers and back (130 vector instructions per wave).
+__device__ __forceinline__ const PSM_CONST StepParams* step_args() {
+    const PSM_CONST StepParams* p = (const PSM_CONST StepParams*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+}
+__device__ __forceinline__ Particles particles(const PSM_CONST StepParams* a) {
+    return Particles{a->P.x, a->P.y, a->P.z, a->P.r, a->P.fr, a->P.ux, a->P.uy, a->P.uz,
+                     a->P.ox, a->P.oy, a->P.oz, a->P.acc, a->P.fprev, a->P.prev_ok};
+}
+
 template <class S, int MAP, bool FILT, bool WALL>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
     !S::DEV ? PSM_WAVES_F64 : (S::SCALED && MAP == 0 && !FILT ? PSM_WAVES_F16 : PSM_WAVES_DEV), 8))) void k_psm_step(
-    StepParams kp) {
+    StepParams) {
     using R = typename S::R;
     using T = typename S::T;
+    const PSM_CONST StepParams* ka = step_args();
 
     __shared__ double s_px[MAXC], s_py[MAXC], s_pz[MAXC], s_pr[MAXC], s_pfr[MAXC];
     __shared__ double s_ux[MAXC], s_uy[MAXC], s_uz[MAXC], s_ox[MAXC], s_oy[MAXC], s_oz[MAXC];
@@ -426,21 +448,22 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
     __shared__ unsigned long long s_cmask[NWAVE][TZ_MAX];
 
     const int tid = threadIdx.x;
-    const int TX = kp.tx, TY = kp.ty, TZ = kp.tz;
+    const int TX = ka->tx, TY = ka->ty, TZ = ka->tz;
     const int wave = tid >> 6, lane = tid & 63;
 
-    if ((int)blockIdx.x >= kp.grid) {
+    if ((int)blockIdx.x >= ka->grid) {
         // the force reduction of the step before (k_spheres reduces the last
         // step of a call): in a launch of its own it takes 4.5 us behind every
         // step, a third of a 32^3 step
-        const int p = (blockIdx.x - kp.grid) * NWAVE + wave;
-        if (p >= kp.P_total) return;
+        const int p = (blockIdx.x - ka->grid) * NWAVE + wave;
+        if (p >= ka->P_total) return;
         double acc[6];
-        const TileShape ts{kp.tx, kp.ty, kp.tz, 0, 0, 0};
-        reduce_sphere(kp.boxes[kp.part_box[p]], ts, kp.P, kp.partial_prev, p, lane, acc);
+        const TileShape ts{TX, TY, TZ, 0, 0, 0};
+        const Particles P = particles(ka);
+        reduce_sphere(ka->boxes[ka->part_box[p]], ts, P, ka->partial_prev, p, lane, acc);
         if (lane == 0) {
 #pragma unroll
-            for (int c = 0; c < 6; ++c) kp.P.acc[6LL * p + c] = acc[c];
+            for (int c = 0; c < 6; ++c) P.acc[6LL * p + c] = acc[c];
         }
         return;
     }
@@ -449,21 +472,19 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
     // walks one contiguous eighth of the tile list so that x-neighbouring
     // tiles (which share the cache lines of the shifted pulls) meet in the
     // same L2.
-    const int G = kp.grid;
+    const int G = ka->grid;
     const int xcd = blockIdx.x % NXCD;
     const int gx8 = (G - xcd + NXCD - 1) / NXCD;
     const int m = blockIdx.x / NXCD;
-    const int t_begin = (int)(((long long)kp.T_total * xcd) / NXCD);
-    const int t_end = (int)(((long long)kp.T_total * (xcd + 1)) / NXCD);
+    const int t_begin = (int)(((long long)ka->T_total * xcd) / NXCD);
+    const int t_end = (int)(((long long)ka->T_total * (xcd + 1)) / NXCD);
 
-    const PSM_CONST BoxDev* boxes = cptr(kp.boxes);
-    const PSM_CONST int* tile_cnt = cptr(kp.tile_cnt);
 
     // Tile order: with a queue (persistent grid), the workgroups of a die take
     // the next tile of its eighth from that die's counter as they finish one;
     // otherwise workgroup m of a die takes tiles m, m + gx8, ...
     __shared__ int s_next;
-    int* const queue = kp.queue;
+    int* const queue = ka->queue;
     int t = t_begin + m;
     if (queue) {
         if (tid == 0) s_next = t_begin + atomicAdd(queue + xcd, 1);
@@ -471,17 +492,18 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
         t = __builtin_amdgcn_readfirstlane(s_next);   // uniform: everything of the tile stays scalar
     }
     while (t < t_end) {
+        ka = step_args();
         int b = 0;
-        if (kp.nbox > 1) {
-            const PSM_CONST int* tb = cptr(kp.box_tile_base);
-            int lo = 0, hi = kp.nbox - 1;
+        if (ka->nbox > 1) {
+            const PSM_CONST int* tb = cptr(ka->box_tile_base);
+            int lo = 0, hi = ka->nbox - 1;
             while (lo < hi) {
                 int mid = (lo + hi + 1) >> 1;
                 if (tb[mid] <= t) lo = mid; else hi = mid - 1;
             }
             b = lo;
         }
-        const PSM_CONST BoxDev& bx = boxes[b];
+        const PSM_CONST BoxDev& bx = cptr(ka->boxes)[b];
         const int nx = bx.nx, ny = bx.ny, nz = bx.nz;
         // MAP = 1 instantiates the sampling path for contexts in which any box
         // samples; each box still uses its own mapping
@@ -492,11 +514,12 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
         const int tcx = lt - lr * ntx;
         const int tcz = udiv(lr, bx.div_nty[0], bx.div_nty[1]);
         const int tcy = lr - tcz * nty;
-        const int nc = tile_cnt[t] < kp.list_cap ? tile_cnt[t] : kp.list_cap;   // at most MAXC
-        const int2* ent = kp.tile_ent + (long long)t * kp.list_cap;
+        const int listed = cptr(ka->tile_cnt)[t], cap = ka->list_cap;
+        const int nc = listed < cap ? listed : cap;   // at most MAXC
+        const int2* ent = ka->tile_ent + (long long)t * cap;
         const double Lx = bx.L[0], Ly = bx.L[1], Lz = bx.L[2];
         const double hLx = bx.halfL[0], hLy = bx.halfL[1], hLz = bx.halfL[2];
-        const int RZ = kp.ref_z, zb = tcz * TZ & ~(RZ - 1);
+        const int RZ = ka->ref_z, zb = tcz * TZ & ~(RZ - 1);
 
         if (nc > 0) {
             for (int c = tid; c < nc; c += WG) {
@@ -504,10 +527,10 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
                 const int p = e.x;
                 s_pid[c] = p;
                 s_slot[c] = e.y;
-                const double px = kp.P.x[p], py = kp.P.y[p], pz = kp.P.z[p], pr = kp.P.r[p], pfr = kp.P.fr[p];
+                const double px = ka->P.x[p], py = ka->P.y[p], pz = ka->P.z[p], pr = ka->P.r[p], pfr = ka->P.fr[p];
                 s_px[c] = px; s_py[c] = py; s_pz[c] = pz;
                 s_pr[c] = pr; s_pfr[c] = pfr;
-                const double u[6] = {kp.P.ux[p], kp.P.uy[p], kp.P.uz[p], kp.P.ox[p], kp.P.oy[p], kp.P.oz[p]};
+                const double u[6] = {ka->P.ux[p], ka->P.uy[p], ka->P.uz[p], ka->P.ox[p], ka->P.oy[p], ka->P.oz[p]};
                 if constexpr (S::DEV) {
                     // reference point of the FP32 geometry in cell coordinates: the
                     // tile's centre, in z that of the block of ref_z planes it lies in
@@ -530,6 +553,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
         }
         __syncthreads();
 
+        ka = step_args();
         // the thread's column in the tile (TX is a power of two), taken from the
         // thread id again for every tile: held across the staging it is spilled
         int tl = tid;
@@ -544,10 +568,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
         // byte offsets inside a z-plane of the nine (x, y) source columns;
         // they do not depend on z (a plane holds fewer than 2^31 bytes)
         const int pitch = bx.pitch;
-        auto inplane = [pitch](int xx, int yy) -> unsigned {
-            int c = xx + pitch * yy;
-            return (unsigned)(((c / BLK) * (NQ * BLK) + (c % BLK)) * (int)sizeof(T));
-        };
+        auto inplane = [pitch](int xx, int yy) -> unsigned { return cell_offset<T>(xx, yy, pitch); };
         // lanes next to a resting side wall (x = 0, nx - 1; y = 0, ny - 1): bits 0-3
         const int edge = !WALL || !lane_ok || !bx.walls_xy ? 0
                          : (((bx.walls_xy & 1) && xs == 0) ? 1 : 0) | (((bx.walls_xy & 1) && xs == nx - 1) ? 2 : 0) |
@@ -558,11 +579,11 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
         const unsigned omm = inplane(xm, ym), opp = inplane(xp, yp), omp = inplane(xm, yp), opm = inplane(xp, ym);
         const long long pbytes = bx.plane_elems * (long long)sizeof(T);
         const unsigned pb32 = (unsigned)pbytes;
-        const char* src = (const char*)bx.grid[kp.parity];
-        const char* dst = (const char*)bx.grid[kp.parity ^ 1];
+        const char* src = (const char*)bx.grid[ka->parity];
+        const char* dst = (const char*)bx.grid[ka->parity ^ 1];
         // scaled storage (FP16): the kernel works on s d; the quadratic terms
         // carry 1/s and every particle velocity is multiplied by s
-        const R sc = S::SCALED ? (R)kp.h_scale : (R)1;
+        const R sc = S::SCALED ? (R)ka->h_scale : (R)1;
         const double cxc = xs + 0.5, cyc = ys + 0.5;
         // this cell's centre relative to the reference point (FP32, exact)
         const float rx = (float)(lx + 0.5 - 0.5 * TX), ry = (float)(ly + 0.5 - 0.5 * TY);
@@ -707,7 +728,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
             const bool psm_wave = __ballot(c0 >= 0) != 0ull;
             // a third overlap is dropped (the two strongest slots stay) and flagged
             // once per wave; the host reports it in strict-slot mode
-            if (psm_wave && __ballot(dropped != 0) != 0ull && lane == 0) atomicOr(kp.flags, FLAG_SLOT_OVERFLOW);
+            if (psm_wave && __ballot(dropped != 0) != 0ull && lane == 0) atomicOr(step_args()->flags, FLAG_SLOT_OVERFLOW);
 
             const R omega = pick<R>(bx.omega, bx.omega_f);
             const R om1 = pick<R>(bx.om1, bx.om1_f);
@@ -919,7 +940,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
                             slot_geometry64(c, cxc, cyc, czc, Lx, hLx, Ly, hLy, Lz, hLz, s_px, s_py, s_pz, s_ux,
                                             s_uy, s_uz, s_ox, s_oy, s_oz, dx, dy, dz, Vx, Vy, Vz);
                         }
-                        const R Bh = (R)(S::SCALED ? Bs * (double)kp.h_inv : Bs);
+                        const R Bh = (R)(S::SCALED ? Bs * (double)step_args()->h_inv : Bs);
                         const R fx = Bh * (hx - Vx), fy = Bh * (hy - Vy), fz = Bh * (hz - Vz);
                         v[0] = fx;
                         v[1] = fy;
@@ -936,12 +957,13 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
 
         __syncthreads();
         if (nc > 0) {
+            double* const partial = step_args()->partial;
             for (int i = tid; i < nc * 6; i += WG) {
                 int c = i / 6, k6 = i - 6 * c;
                 double s = 0.0;
 #pragma unroll
                 for (int w = 0; w < NWAVE; ++w) s += s_acc[w][k6][c];
-                kp.partial[(long long)s_slot[c] * 6 + k6] = s;
+                partial[(long long)s_slot[c] * 6 + k6] = s;
             }
         }
         __syncthreads();
@@ -1315,10 +1337,7 @@ __device__ __forceinline__ void pull19(const BoxDev& bx, int parity, int x, int 
     const int ym = y == 0 ? bx.ny - 1 : y - 1, yp = y == bx.ny - 1 ? 0 : y + 1;
     const int zm = z == 0 ? bx.nz - 1 : z - 1, zp = z == bx.nz - 1 ? 0 : z + 1;
     const int pitch = bx.pitch;
-    auto inplane = [pitch](int xx, int yy) -> unsigned {
-        const int c = xx + pitch * yy;
-        return (unsigned)(((c / BLK) * (NQ * BLK) + (c % BLK)) * (int)sizeof(T));
-    };
+    auto inplane = [pitch](int xx, int yy) -> unsigned { return cell_offset<T>(xx, yy, pitch); };
     const unsigned o00 = inplane(x, y), om0 = inplane(xm, y), op0 = inplane(xp, y);
     const unsigned o0m = inplane(x, ym), o0p = inplane(x, yp);
     const unsigned omm = inplane(xm, ym), opp = inplane(xp, yp), omp = inplane(xm, yp), opm = inplane(xp, ym);
@@ -1347,8 +1366,7 @@ __device__ __forceinline__ void store19(const BoxDev& bx, int parity, int x, int
                                         const double sl[NQ]) {
     using T = typename S::T;
     constexpr int QB = BLK * (int)sizeof(T);
-    const int c = x + bx.pitch * y;
-    const unsigned o = (unsigned)(((c / BLK) * (NQ * BLK) + (c % BLK)) * (int)sizeof(T));
+    const unsigned o = cell_offset<T>(x, y, bx.pitch);
     const long long pbytes = bx.plane_elems * (long long)sizeof(T);
     const Rsrc d = plane_rsrc((const char*)bx.grid[parity] + z * pbytes, (unsigned)pbytes);
 #pragma unroll
