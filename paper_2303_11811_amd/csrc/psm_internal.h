@@ -367,9 +367,16 @@ struct DownloadParams {
     int* err_dst;
 };
 
-hipError_t launch_step(int storage, int map, bool filt, bool wall, const StepParams& kp, hipStream_t st);
+// Instance of the step kernel.
+struct StepForm {
+    bool map;       // a box samples its fractions
+    bool filter;    // per-wave candidate filter
+    bool walls;     // a box has walls or faces
+    bool cached;    // stores that stay in the caches (not with the filter)
+};
+hipError_t launch_step(int storage, const StepForm& form, const StepParams& kp, hipStream_t st);
 hipError_t launch_pattern_copy(int storage, bool shifted, const StepParams& kp, hipStream_t st);
-int step_blocks_per_cu(int storage, int map, bool filt, bool wall);
+int step_blocks_per_cu(int storage, const StepForm& form);
 hipError_t launch_spheres(bool reduce, int scheme, bool bin, const SphereParams& sp, hipStream_t st);
 hipError_t launch_upload_bin(const SphereParams& sp, const UploadParams& up, hipStream_t st);
 hipError_t launch_upload(const UploadParams& up, hipStream_t st);

@@ -32,7 +32,8 @@ typedef unsigned int u32x2 __attribute__((__vector_size__(8)));
 constexpr int RSRC_WORD3 = 0x00020000;   // raw 32-bit data format, no swizzle
 
 // Cache policy of the PDF streams (compile-time switches, measured by the
-// tuning sweeps): nontemporal stores / loads bypass cache retention.
+// tuning sweeps): nontemporal stores / loads bypass cache retention. The step
+// kernel's CACHED instances store without it (grids that fit the caches).
 #ifndef PSM_NT_STORE
 #define PSM_NT_STORE 1
 #endif
@@ -50,7 +51,7 @@ __device__ __forceinline__ Rsrc plane_rsrc(const void* base, unsigned bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, RSRC_WORD3);
 }
 #define PSM_LD(B, T, r, vo, so) __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_##B(r, vo, so, LD_AUX))
-#define PSM_ST(B, U, v, r, vo, so) __builtin_amdgcn_raw_buffer_store_##B(__builtin_bit_cast(U, v), r, vo, so, ST_AUX)
+#define PSM_ST(B, U, v, r, vo, so, aux) __builtin_amdgcn_raw_buffer_store_##B(__builtin_bit_cast(U, v), r, vo, so, aux)
 #else
 // plain global accesses from the plane's base address (compile-time alternative)
 typedef const char* RsrcPtr;
@@ -58,7 +59,7 @@ typedef const char* RsrcPtr;
 __device__ __forceinline__ Rsrc plane_rsrc(const void* base, unsigned) { return (const char*)base; }
 #define GLB __attribute__((address_space(1)))
 #define PSM_LD(B, T, r, vo, so) (*(const GLB T*)((r) + (so) + (vo)))
-#define PSM_ST(B, U, v, r, vo, so) __builtin_nontemporal_store(v, (GLB decltype(v)*)((r) + (so) + (vo)))
+#define PSM_ST(B, U, v, r, vo, so, aux) __builtin_nontemporal_store(v, (GLB decltype(v)*)((r) + (so) + (vo)))
 #endif
 
 // ---------------------------------------------------------------------------
@@ -70,7 +71,9 @@ struct St64 {
     static constexpr bool DEV = false;
     static constexpr bool SCALED = false;
     __device__ static R ld(Rsrc r, unsigned vo, int so) { return PSM_LD(b64, double, r, vo, so); }
-    __device__ static void st(Rsrc r, unsigned vo, int so, R v) { PSM_ST(b64, u32x2, v, r, vo, so); }
+    template <int AUX = ST_AUX> __device__ static void st(Rsrc r, unsigned vo, int so, R v) {
+        PSM_ST(b64, u32x2, v, r, vo, so, AUX);
+    }
     __device__ static double to_f64(T v, float) { return v; }
     __device__ static T from_f64(double v, float) { return v; }
 };
@@ -80,7 +83,9 @@ struct St32 {
     static constexpr bool DEV = true;
     static constexpr bool SCALED = false;
     __device__ static R ld(Rsrc r, unsigned vo, int so) { return PSM_LD(b32, float, r, vo, so); }
-    __device__ static void st(Rsrc r, unsigned vo, int so, R v) { PSM_ST(b32, unsigned int, v, r, vo, so); }
+    template <int AUX = ST_AUX> __device__ static void st(Rsrc r, unsigned vo, int so, R v) {
+        PSM_ST(b32, unsigned int, v, r, vo, so, AUX);
+    }
     __device__ static double to_f64(T v, float) { return (double)v; }
     __device__ static T from_f64(double v, float) { return (float)v; }
 };
@@ -93,9 +98,9 @@ struct St16 {
     // stores are bare conversions. State I/O converts with the scale.
     static constexpr bool SCALED = true;
     __device__ static R ld(Rsrc r, unsigned vo, int so) { return (float)PSM_LD(b16, _Float16, r, vo, so); }
-    __device__ static void st(Rsrc r, unsigned vo, int so, R v) {
+    template <int AUX = ST_AUX> __device__ static void st(Rsrc r, unsigned vo, int so, R v) {
         const _Float16 h = (_Float16)v;
-        PSM_ST(b16, unsigned short, h, r, vo, so);
+        PSM_ST(b16, unsigned short, h, r, vo, so, AUX);
     }
     // scale is a power of two: multiplication by it and by 1/scale is exact
     __device__ static double to_f64(T v, float inv) { return (double)((float)v * inv); }
@@ -428,7 +433,7 @@ __device__ __forceinline__ Particles particles(const PSM_CONST StepParams* a) {
                      a->P.ox, a->P.oy, a->P.oz, a->P.acc, a->P.fprev, a->P.prev_ok};
 }
 
-template <class S, int MAP, bool FILT, bool WALL>
+template <class S, int MAP, bool FILT, bool WALL, bool CACHED>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
     !S::DEV ? PSM_WAVES_F64 : (S::SCALED && MAP == 0 && !FILT ? PSM_WAVES_F16 : PSM_WAVES_DEV), 8))) void k_psm_step(
     StepParams) {
@@ -832,7 +837,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
                 }
 #define PSM_FA(Q) pick<R>(S::SCALED ? bx.fa_scaled[Q / 2] : bx.fa[Q / 2], S::SCALED ? bx.fa_scaled_f[Q / 2] : bx.fa_f[Q / 2])
 #define PSM_FS(Q) pick<R>(bx.fs[Q / 2], bx.fs_f[Q / 2])
-#define PSM_STORE(Q) S::st(dz_, o00, (Q) * QB, f[Q])
+#define PSM_STORE(Q) S::template st<CACHED ? 0 : ST_AUX>(dz_, o00, (Q) * QB, f[Q])
 
                 // 4. collision; each pair is stored as soon as it is final
                 if (!psm_wave) {
@@ -1849,7 +1854,8 @@ static inline unsigned blocks_for(long long n, int bs) { return (unsigned)((n + 
 
 // The step kernel instance for (storage, map, filt): storage psm_storage;
 // map 0 when every box uses the linear approximation, 1 if any box samples;
-// filt the per-wave candidate filter; wall if any box has walls or faces.
+// filt the per-wave candidate filter; wall if any box has walls or faces;
+// cached for grids that fit the last-level cache.
 // ---------------------------------------------------------------------------
 // Bandwidth reference for the step's access pattern: the tile walk, pulls and
 // stores of k_psm_step with no arithmetic. SHIFT pulls each direction from
@@ -1930,34 +1936,35 @@ hipError_t launch_pattern_copy(int storage, bool shifted, const StepParams& kp, 
     return hipLaunchKernel(k, dim3(kp.grid), dim3(WG), args, 0, st);
 }
 
-template <int MAP, bool FILT, bool WALL>
+template <int MAP, bool FILT, bool WALL, bool CACHED>
 static const void* step_kernel_of(int storage) {
     switch (storage) {
-        case 0: return (const void*)k_psm_step<St64, MAP, FILT, WALL>;
-        case 1: return (const void*)k_psm_step<St32, MAP, FILT, WALL>;
-        default: return (const void*)k_psm_step<St16, MAP, FILT, WALL>;
+        case 0: return (const void*)k_psm_step<St64, MAP, FILT, WALL, CACHED>;
+        case 1: return (const void*)k_psm_step<St32, MAP, FILT, WALL, CACHED>;
+        default: return (const void*)k_psm_step<St16, MAP, FILT, WALL, CACHED>;
     }
 }
 
 template <bool WALL>
-static const void* step_kernel_walls(int storage, int map, bool filt) {
-    if (map) return filt ? step_kernel_of<1, true, WALL>(storage) : step_kernel_of<1, false, WALL>(storage);
-    return filt ? step_kernel_of<0, true, WALL>(storage) : step_kernel_of<0, false, WALL>(storage);
+static const void* step_kernel_walls(int storage, const StepForm& f) {
+    if (f.filter) return f.map ? step_kernel_of<1, true, WALL, false>(storage) : step_kernel_of<0, true, WALL, false>(storage);
+    if (f.cached) return f.map ? step_kernel_of<1, false, WALL, true>(storage) : step_kernel_of<0, false, WALL, true>(storage);
+    return f.map ? step_kernel_of<1, false, WALL, false>(storage) : step_kernel_of<0, false, WALL, false>(storage);
 }
 
-static const void* step_kernel(int storage, int map, bool filt, bool wall) {
-    return wall ? step_kernel_walls<true>(storage, map, filt) : step_kernel_walls<false>(storage, map, filt);
+static const void* step_kernel(int storage, const StepForm& f) {
+    return f.walls ? step_kernel_walls<true>(storage, f) : step_kernel_walls<false>(storage, f);
 }
 
-hipError_t launch_step(int storage, int map, bool filt, bool wall, const StepParams& kp, hipStream_t st) {
+hipError_t launch_step(int storage, const StepForm& form, const StepParams& kp, hipStream_t st) {
     void* args[] = {(void*)&kp};
     const unsigned reduce = kp.partial_prev ? blocks_for(kp.P_total, NWAVE) : 0u;
-    return hipLaunchKernel(step_kernel(storage, map, filt, wall), dim3(kp.grid + reduce), dim3(WG), args, 0, st);
+    return hipLaunchKernel(step_kernel(storage, form), dim3(kp.grid + reduce), dim3(WG), args, 0, st);
 }
 
-int step_blocks_per_cu(int storage, int map, bool filt, bool wall) {
+int step_blocks_per_cu(int storage, const StepForm& form) {
     int nb = 0;
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, step_kernel(storage, map, filt, wall), WG, 0);
+    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, step_kernel(storage, form), WG, 0);
     return nb > 0 ? nb : 1;
 }
 
