@@ -166,7 +166,8 @@ int psm_set_particle_velocities(psm_ctx* ctx, int box, int n, const double* U, c
 
 /* Advance every box by nsteps time steps: per step, fused mapping +
  * stream-collide + force/torque partial sums (one launch over the tiles of all
- * boxes) and the per-particle reduction. With graphs enabled, runs of 10 steps
+ * boxes) and the per-particle reduction (of all but the call's last step in
+ * the launch of the step after it). With graphs enabled, runs of 10 steps
  * replay a captured HIP graph. Asynchronous. */
 int psm_step(psm_ctx* ctx, int nsteps);
 
@@ -271,15 +272,18 @@ enum psm_launch_flags {
     PSM_LAUNCH_PERSISTENT = 1,  /* grid sized to the workgroups that fit on the chip at once; the
                                    workgroups on each of the 8 dies take the next tile of that die's
                                    eighth of the tile list from a counter the library zeroes before
-                                   every step (else one workgroup per tile); same results bit for bit */
+                                   every step (else one workgroup per tile, or per part of a tile that
+                                   several share along z); same results bit for bit */
     PSM_LAUNCH_FILTER = 2       /* per wave and z, test each staged sphere against the rectangle of
                                    the wave's cells first; the per-cell mapping of Sec. 2.3.2 then
                                    visits only spheres that can reach them (same results) */
 };
 
-/* Launch shape of the step kernel: a tile of tx*ty threads (tx*ty == 256,
- * tx in {16,32,64,128,256}) handling tz cells each along z (tz in
- * {1,2,4,8,16,32}), and psm_launch_flags. Rebuilds the tile lists
+/* Launch shape of the step kernel: tiles of tx*ty threads (tx*ty == 256,
+ * tx in {16,32,64,128,256}) and tz cells each along z (tz in
+ * {1,2,4,8,16,32}), and psm_launch_flags. A tile has one candidate list; up
+ * to 8 workgroups share its cells along z where that keeps more of the chip
+ * busy. Rebuilds the tile lists
  * (synchronises); invalidates captured graphs. On failure the previous
  * launch is restored. A context starts with 64 x 4 threads and a depth
  * chosen from its storage form and box sizes (its results are those of depth

@@ -64,50 +64,80 @@ static bool shape_allowed(int tx, int ty, int tz) {
 
 static int cdiv(long long a, long long b) { return (int)((a + b - 1) / b); }
 
-// Launch of a context that sets none: tiles of 64 x 4 threads, as many cells
-// deep as the storage form gains from while enough tiles are left to fill 256
-// CUs. us per step at depth 1 / 2 / 4 / 8 / 16 (spheres at 10 %):
+// Cells per thread along z: as many as the storage form gains from while
+// enough workgroups are left to fill 256 CUs. us per step at depth 1 / 2 / 4 / 8 /
+// 16 (64 x 4 threads, spheres at 10 %):
 //   FP64  32^3   8.5 / 16.8 / 24.6 / 37.3 / 62.9      256^3  918 / 934 / 979 / 1003 / 1013
 //   FP32  88^3  34.8 / 35.3 / 38.9 / 40.3 / 58.8      96^3  38.9 / 37.6 / 41.6 / 47.0 / 64.2
 //         256^3  506 / 474 / 498 / 529 / 533
 //   FP16  64^3   9.6 / 10.6 / 15.3 / 24.2 / 46.2      72^3  16.5 / 15.6 / 17.4 / 27.8 / 45.8
 //         144^3 84.2 / 73.0 / 75.8 / 84.8 / 89.7      160^3  102 / 83.2 / 80.7 / 87.3 / 94.5
 //         384^3  848 at depth 4, 857 at 8
-// A deeper tile runs its cells one after another in each wave, which is lost
-// time while CUs are idle; the deviation forms, whose spheres cost more beside
-// fewer bytes, gain from staging them once for more cells. The FP32 geometry
-// refers to the centres of blocks 64 x 4 cells wide and 16 planes deep at every
-// depth, so the results do not depend on the depth chosen. FP64, which has no
-// such reference, takes 32 x 8 threads where the narrowest box fills at most 3/4
-// of its 64-wide tiles (us at 64 x 4 / 32 x 8: 68^3 31.4 / 28.8, 80^3 39.9 /
-// 34.2, 96^3 58.9 / 54.4; 132^3, where it would save a sixth, 163 / 183).
+// More cells run one after another in each wave, which is lost time while CUs
+// are idle, and spread what the chip works on at one time over more planes
+// (a copy of the access pattern alone slows by 13 % from depth 1 to 8); the
+// deviation forms, whose spheres cost more beside fewer bytes, gain from
+// staging them once for more cells.
+static int best_depth(const psm_box_desc* boxes, int nbox, int storage, int tx, int ty) {
+    struct Depth {
+        int tz;
+        long long parts;   // fewest workgroups it is taken at
+    };
+    static const Depth f64[] = {{1, 0}}, f32[] = {{2, 2000}, {1, 0}}, f16[] = {{4, 4500}, {2, 1300}, {1, 0}};
+    for (const Depth* d = storage == PSM_FP64 ? f64 : (storage == PSM_FP32DEV ? f32 : f16);; ++d) {
+        long long T = 0;
+        for (int b = 0; b < nbox; ++b)
+            T += (long long)cdiv(boxes[b].nx, tx) * cdiv(boxes[b].ny, ty) * cdiv(boxes[b].nz, d->tz);
+        if (T >= d->parts) return d->tz;
+    }
+}
+
+// A tile deeper than that keeps its one list, and up to 8 workgroups share its
+// cells along z, each with its own force partials (one workgroup / shared, us:
+// 32^3 FP16 at 64 x 4 x 8 20.2 / 6.5, 128^3 FP64 at 128 x 2 x 8 129 / 118, 256^3
+// FP32 at 30 % solid and 64 x 4 x 8 555 / 504, the 500 x 200 x 800 bed in FP64 at
+// 128 x 2 x 8 4834 / 4414). Where half the waves of the tiles lie past the box,
+// more parts only stage more spheres for idle waves once the chip holds no more
+// at a time (3, 4 and 5 workgroups on each of 256 CUs): FP32 at 128 x 2 x 2, 32^3,
+// 576 parts after it, 8.6 / 7.0, but 64^3, 2048, 13.7 / 15.2; FP16 at 256 x 1 x 4,
+// 128^3, 8192, 49.7 / 52.4. Parts of tiles and their partial slots are counted in int.
+static int z_shift(const psm_box_desc* boxes, int nbox, int storage, int tx, int ty, int tz, long long slots) {
+    const int wx = std::min(tx, 64), wy = 64 / wx;
+    long long T = 0, waves = 0;
+    for (int b = 0; b < nbox; ++b) {
+        const long long nz = cdiv(boxes[b].nz, tz);
+        T += nz * cdiv(boxes[b].nx, tx) * cdiv(boxes[b].ny, ty);
+        waves += nz * cdiv(boxes[b].nx, wx) * cdiv(boxes[b].ny, wy);
+    }
+    const bool idle = 2 * waves <= T * (WG / 64);
+    const long long resident = 256 * (storage == PSM_FP64 ? 3 : (storage == PSM_FP32DEV ? 4 : 5));
+    const int depth = std::max(best_depth(boxes, nbox, storage, tx, ty), tz / 8);
+    int shift = 0;
+    while (tz >> (shift + 1) >= depth && std::max(T, slots) << (shift + 1) < (1LL << 30) &&
+           (!idle || T << (shift + 1) <= resident))
+        ++shift;
+    return shift;
+}
+
+// Launch of a context that sets none: tiles of 64 x 4 threads of that depth.
+// The FP32 geometry refers to the centres of blocks 64 x 4 cells wide and 16
+// planes deep at every depth, so the results do not depend on the depth
+// chosen. FP64, which has no such reference, takes 32 x 8 threads where the
+// widest box fills at most 3/4 of its 64-wide tiles (us at 64 x 4 / 32 x 8: 68^3
+// 31.4 / 28.8, 80^3 39.9 / 34.2, 96^3 58.9 / 54.4; 132^3, where it would save a
+// sixth, 163 / 183).
 constexpr int kDefaultRefZ = 16;
 
 static TileShape default_shape(const psm_box_desc* boxes, int nbox, int storage) {
-    struct Depth {
-        int tz;
-        long long tiles;   // fewest tiles FP32 and FP16 take it at
-    };
-    static const Depth f32[] = {{2, 2000}, {1, 0}}, f16[] = {{4, 4500}, {2, 1300}, {1, 0}};
-    TileShape ts{64, 4, 1, 0, 0, kDefaultRefZ};
-    if (storage == PSM_FP64) {
-        bool narrow = true;
-        for (int b = 0; b < nbox; ++b) narrow = narrow && 4 * cdiv(boxes[b].nx, 32) <= 6 * cdiv(boxes[b].nx, 64);
-        if (narrow) {
-            ts.tx = 32;
-            ts.ty = 8;
-        }
-        return ts;
+    TileShape ts{64, 4, 1, 0, 0, kDefaultRefZ, 0};
+    bool narrow = storage == PSM_FP64;
+    for (int b = 0; b < nbox; ++b) narrow = narrow && 4 * cdiv(boxes[b].nx, 32) <= 6 * cdiv(boxes[b].nx, 64);
+    if (narrow) {
+        ts.tx = 32;
+        ts.ty = 8;
     }
-    for (const Depth* d = storage == PSM_FP32DEV ? f32 : f16;; ++d) {
-        long long T = 0;
-        for (int b = 0; b < nbox; ++b)
-            T += (long long)cdiv(boxes[b].nx, ts.tx) * cdiv(boxes[b].ny, ts.ty) * cdiv(boxes[b].nz, d->tz);
-        if (T >= d->tiles) {
-            ts.tz = d->tz;
-            return ts;
-        }
-    }
+    ts.tz = best_depth(boxes, nbox, storage, ts.tx, ts.ty);
+    return ts;
 }
 
 // Largest number of tiles the bounding box [x-(r+1), x+(r+1)] can touch along
@@ -207,7 +237,7 @@ static Layout make_layout(const psm_box_desc* boxes, int nbox, int storage) {
                            max_tiles_axis(d.max_radius, ty, d.ny) * max_tiles_axis(d.max_radius, tz, d.nz);
             }
             Tmax = (int)std::max<long long>(Tmax, T);
-            capmax = std::max(capmax, cap);
+            capmax = std::max(capmax, cap << z_shift(boxes, nbox, storage, tx, ty, tz, cap));
         }
     L.T_max = Tmax;
     int most = 0;
@@ -260,7 +290,7 @@ struct psm_ctx {
     std::vector<BoxDev> box;     // host copy of the device box table
     std::vector<int> np;         // particles set per box
     int P_total = 0;
-    TileShape ts{64, 4, 16, 0, 0, 16};
+    TileShape ts{64, 4, 16, 0, 0, 16, 0};
     int T_total = 0;
     int grid = 0;
     int parity = 0;
@@ -385,12 +415,13 @@ static void assign_tiles(psm_ctx* c) {
         bx.pbase = (int)pbase;
         pbase += (long long)d.max_particles * bx.pstride;
     }
+    c->ts.zshift = z_shift(c->desc.data(), c->nbox, c->storage, c->ts.tx, c->ts.ty, c->ts.tz, pbase);
     int dev = 0, ncu = 256;
     (void)hipGetDevice(&dev);
     (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
     // one-shot: a workgroup per tile (rounded up to whole XCD rounds);
     // persistent: as many workgroups as fit at once, each walking its tiles
-    int full = ((c->T_total + NXCD - 1) / NXCD) * NXCD;
+    int full = (((c->T_total << c->ts.zshift) + NXCD - 1) / NXCD) * NXCD;
     int g = c->ts.persistent ? std::min(step_blocks_per_cu(c->storage, step_form(c)) * ncu, full) : full;
     c->grid = std::max(NXCD, g / NXCD * NXCD);
 }
@@ -972,8 +1003,10 @@ static int step_params(psm_ctx* c, int parity, StepParams& kp) {
     kp.part_box = c->d_partbox;
     kp.P_total = c->P_total;
     kp.grid = c->grid;
-    kp.T_total = c->T_total;
+    kp.T_total = c->T_total << c->ts.zshift;
     kp.tx = c->ts.tx; kp.ty = c->ts.ty; kp.tz = c->ts.tz;
+    kp.depth = c->ts.tz >> c->ts.zshift;
+    kp.zshift = c->ts.zshift;
     kp.ref_z = c->ts.ref_z;
     kp.parity = parity;
     kp.h_scale = c->h_scale;
@@ -1366,7 +1399,7 @@ extern "C" int psm_set_launch(psm_ctx* c, int tx, int ty, int tz, int flags) {
     if (flags & ~(PSM_LAUNCH_PERSISTENT | PSM_LAUNCH_FILTER)) return fail(PSM_EINVAL, "unknown launch flags %d", flags);
     HIP_TRY(hipStreamSynchronize(c->stream));
     TileShape old = c->ts;
-    c->ts = TileShape{tx, ty, tz, (flags & PSM_LAUNCH_PERSISTENT) ? 1 : 0, (flags & PSM_LAUNCH_FILTER) ? 1 : 0, tz};
+    c->ts = TileShape{tx, ty, tz, (flags & PSM_LAUNCH_PERSISTENT) ? 1 : 0, (flags & PSM_LAUNCH_FILTER) ? 1 : 0, tz, 0};
     assign_tiles(c);
     int rc = upload_box_table(c);
     if (rc == PSM_OK) rc = rebuild_lists(c);
@@ -1604,7 +1637,7 @@ static int autotune_timed(psm_ctx* c, int trial_steps, TileShape& best_out, doub
             // tiles much wider than the widest box only idle lanes
             if (txv > 2 * std::max(maxdim, 16)) continue;
             for (int tzv : kTZ) {
-                TileShape ts{txv, WG / txv, tzv, (fl & PSM_LAUNCH_PERSISTENT) != 0, (fl & PSM_LAUNCH_FILTER) != 0, tzv};
+                TileShape ts{txv, WG / txv, tzv, (fl & PSM_LAUNCH_PERSISTENT) != 0, (fl & PSM_LAUNCH_FILTER) != 0, tzv, 0};
                 if (psm_set_launch(c, ts.tx, ts.ty, ts.tz, fl) != PSM_OK) continue;   // not allowed here
                 double per = 0.0;
                 if ((rc = time_current(trial_steps, per))) break;

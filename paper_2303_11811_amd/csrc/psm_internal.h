@@ -34,7 +34,8 @@ struct BoxDev {
     int part_base, np, mapping, nsub;
     // force partials of a sphere: slots pbase + (local id) * pstride + k for
     // the k-th tile of its bounding box (pstride bounds the tiles a sphere of
-    // this box can touch at the current tile shape)
+    // this box can touch at the current tile shape), each one partial per
+    // workgroup that shares the tile
     int pstride, pbase;
     // PDF storage: each z-plane holds pblk blocks of 64 cells (pitch*ny
     // rounded up); a block stores its 19 directions one after another, 64
@@ -110,6 +111,7 @@ struct TileShape {
     int persistent;   // 1: occupancy-sized grid walking the tiles; 0: one workgroup per tile
     int filter;       // 1: per-wave candidate filter before the per-cell mapping
     int ref_z;        // depth of the z-blocks whose centres the FP32 geometry refers to (a multiple of tz)
+    int zshift;       // 1 << zshift workgroups share a tile's cells along z
 };
 
 // ---------------------------------------------------------------------------
@@ -302,15 +304,16 @@ struct StepParams {
     const int* tile_cnt;        // [T] spheres of each tile's list (uncapped)
     const int2* tile_ent;       // [T][list_cap] global particle id and force-partial slot
     int list_cap;
-    double* partial;            // [slots][6]
+    double* partial;            // [slots << zshift][6]
     // force reduction of the step before (its partials; null: none) by the
     // workgroups from `grid` on, 4 spheres each
     const double* partial_prev;
     const int* part_box;        // [P] box of each global particle slot
     int P_total;
     int grid;                   // workgroups that walk tiles
-    int T_total;
+    int T_total;                // parts of tiles: tiles << zshift
     int tx, ty, tz;
+    int depth, zshift;          // cells per thread: tz >> zshift, TileShape::zshift
     int ref_z;                  // TileShape::ref_z
     int parity;
     float h_scale, h_inv;       // FP16 storage scale and its inverse (1 otherwise)
@@ -325,7 +328,7 @@ struct SphereParams {
     const BoxDev* boxes;
     const int* part_box;        // [P] box of each global particle slot
     Particles P;
-    // force partials [slots][6] of the last step, and those the next step
+    // force partials [slots << zshift][6] of the last step, and those the next step
     // writes: both zeroed for an entry a full list drops
     double *partial, *partial_next;
     int P_total;

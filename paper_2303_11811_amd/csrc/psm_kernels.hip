@@ -401,9 +401,9 @@ __device__ __forceinline__ void reduce_sphere(const BoxDev& bx, const TileShape&
         AxisTiles ax, ay, az;
         box_tiles(bx, ts, P.x[p], P.y[p], P.z[p], P.r[p], ax, ay, az);
         const int ntot = ax.count() * ay.count() * az.count();
-        // the sphere's slots: one per tile of its bounding box, in that order
-        const double* pp = partial + ((long long)bx.pbase + (long long)lp * bx.pstride) * 6;
-        for (int k = lane; k < ntot; k += 64) {
+        // the sphere's slots: one run per tile of its bounding box, in that order
+        const double* pp = partial + (((long long)bx.pbase + (long long)lp * bx.pstride) << ts.zshift) * 6;
+        for (int k = lane; k < ntot << ts.zshift; k += 64) {
 #pragma unroll
             for (int c = 0; c < 6; ++c) acc[c] += pp[(long long)k * 6 + c];
         }
@@ -453,7 +453,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
     __shared__ unsigned long long s_cmask[NWAVE][TZ_MAX];
 
     const int tid = threadIdx.x;
-    const int TX = ka->tx, TY = ka->ty, TZ = ka->tz;
+    const int TX = ka->tx, TY = ka->ty, TZ = ka->depth;
     const int wave = tid >> 6, lane = tid & 63;
 
     if ((int)blockIdx.x >= ka->grid) {
@@ -463,7 +463,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
         const int p = (blockIdx.x - ka->grid) * NWAVE + wave;
         if (p >= ka->P_total) return;
         double acc[6];
-        const TileShape ts{TX, TY, TZ, 0, 0, 0};
+        const TileShape ts{TX, TY, ka->tz, 0, 0, 0, ka->zshift};
         const Particles P = particles(ka);
         reduce_sphere(ka->boxes[ka->part_box[p]], ts, P, ka->partial_prev, p, lane, acc);
         if (lane == 0) {
@@ -498,13 +498,16 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
     }
     while (t < t_end) {
         ka = step_args();
+        // part t of the tiles: 1 << zs of them along z share a tile and its list,
+        // in the order that tiles of their own depth would have
+        const int zs = ka->zshift;
         int b = 0;
         if (ka->nbox > 1) {
             const PSM_CONST int* tb = cptr(ka->box_tile_base);
             int lo = 0, hi = ka->nbox - 1;
             while (lo < hi) {
                 int mid = (lo + hi + 1) >> 1;
-                if (tb[mid] <= t) lo = mid; else hi = mid - 1;
+                if (tb[mid] << zs <= t) lo = mid; else hi = mid - 1;
             }
             b = lo;
         }
@@ -514,14 +517,15 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
         // samples; each box still uses its own mapping
         const bool lin_map = MAP == 0 || bx.mapping == 0;
         const int ntx = bx.ntx, nty = bx.nty;
-        const int lt = t - bx.tile_base;
+        const int lt = t - (bx.tile_base << zs);
         const int lr = udiv(lt, bx.div_ntx[0], bx.div_ntx[1]);   // row of tiles
         const int tcx = lt - lr * ntx;
         const int tcz = udiv(lr, bx.div_nty[0], bx.div_nty[1]);
         const int tcy = lr - tcz * nty;
-        const int listed = cptr(ka->tile_cnt)[t], cap = ka->list_cap;
+        const int tile = bx.tile_base + tcx + ntx * (tcy + nty * (tcz >> zs));
+        const int listed = cptr(ka->tile_cnt)[tile], cap = ka->list_cap;
         const int nc = listed < cap ? listed : cap;   // at most MAXC
-        const int2* ent = ka->tile_ent + (long long)t * cap;
+        const int2* ent = ka->tile_ent + (long long)tile * cap;
         const double Lx = bx.L[0], Ly = bx.L[1], Lz = bx.L[2];
         const double hLx = bx.halfL[0], hLy = bx.halfL[1], hLz = bx.halfL[2];
         const int RZ = ka->ref_z, zb = tcz * TZ & ~(RZ - 1);
@@ -531,7 +535,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
                 const int2 e = ent[c];
                 const int p = e.x;
                 s_pid[c] = p;
-                s_slot[c] = e.y;
+                s_slot[c] = (e.y << zs) + (tcz & ((1 << zs) - 1));
                 const double px = ka->P.x[p], py = ka->P.y[p], pz = ka->P.z[p], pr = ka->P.r[p], pfr = ka->P.fr[p];
                 s_px[c] = px; s_py[c] = py; s_pz[c] = pz;
                 s_pr[c] = pr; s_pfr[c] = pfr;
@@ -1128,10 +1132,9 @@ __global__ __launch_bounds__(256) void k_spheres(SphereParams sp, UploadParams u
             } else {
                 // a list holds at most MAXC spheres: the excess is dropped and reported
                 atomicMax(sp.over, at + 1);
-#pragma unroll
-                for (int c = 0; c < 6; ++c) {
-                    sp.partial[(slot0 + k) * 6 + c] = 0.0;
-                    sp.partial_next[(slot0 + k) * 6 + c] = 0.0;
+                for (int c = 0; c < 6 << sp.ts.zshift; ++c) {
+                    sp.partial[((slot0 + k) << sp.ts.zshift) * 6 + c] = 0.0;
+                    sp.partial_next[((slot0 + k) << sp.ts.zshift) * 6 + c] = 0.0;
                 }
             }
         }
@@ -1867,7 +1870,7 @@ __global__ __launch_bounds__(WG) void k_pattern_copy(StepParams kp) {
     using R = typename S::R;
     using T = typename S::T;
     const int tid = threadIdx.x;
-    const int TX = kp.tx, TY = kp.ty, TZ = kp.tz;
+    const int TX = kp.tx, TY = kp.ty, TZ = kp.depth, zs = kp.zshift;
     const int lx = tid % TX, ly = tid / TX;
     const int G = gridDim.x;
     const int xcd = blockIdx.x % NXCD;
@@ -1882,13 +1885,13 @@ __global__ __launch_bounds__(WG) void k_pattern_copy(StepParams kp) {
             int lo = 0, hi = kp.nbox - 1;
             while (lo < hi) {
                 int mid = (lo + hi + 1) >> 1;
-                if (tb[mid] <= t) lo = mid; else hi = mid - 1;
+                if (tb[mid] << zs <= t) lo = mid; else hi = mid - 1;
             }
             b = lo;
         }
         const PSM_CONST BoxDev& bx = boxes[b];
         const int nx = bx.nx, ny = bx.ny, nz = bx.nz;
-        const int lt = t - bx.tile_base;
+        const int lt = t - (bx.tile_base << zs);
         const int tcx = lt % bx.ntx, tcy = (lt / bx.ntx) % bx.nty, tcz = lt / (bx.ntx * bx.nty);
         const int x = tcx * TX + lx, y = tcy * TY + ly;
         if (x >= nx || y >= ny) continue;

@@ -621,3 +621,35 @@ def test_read_outs_follow_the_callers_stream(side_stream):
     torch.cuda.synchronize()
     assert all(bool(v) for v in same)
     eng.close()
+
+
+@pytest.mark.parametrize("flags", [0, psm.PSM_LAUNCH_PERSISTENT, psm.PSM_LAUNCH_FILTER])
+@pytest.mark.parametrize("launch", [(16, 16, 32), (32, 8, 16), (64, 4, 8), (128, 2, 2), (256, 1, 4)])
+def test_tiles_shared_by_workgroups_keep_the_results(launch, flags):
+    """Deep tiles, whose cells several workgroups share, in boxes that end
+    inside a tile or a part of one: FP64 PDFs bit for bit those of tiles one
+    cell deep, before and after the spheres moved; the force sums add the same
+    FP64 terms in another order (below 1e-13 of the magnitude of their
+    terms, a few thousand of them)."""
+    specs = [inputs.random_small((70, 37, 21), 7, (2.5, 4.5), seed=71, tau=0.66, fext=(1e-5, 0, 0), omamp=0.003),
+             inputs.random_small((19, 33, 11), 2, (2.0, 3.0), seed=72, tau=0.8, omamp=0.003)]
+    out = []
+    for shape in ((64, 4, 1), launch):
+        _print_case("shared tiles", shape=shape, flags=flags)
+        eng = make_engine(specs)
+        eng.set_launch(*shape, flags)
+        got = []
+        for b, s in enumerate(specs):
+            eng.set_pdfs(b, initial_f(s))
+        for shift in (0.0, 1.7):
+            for b, s in enumerate(specs):
+                eng.set_particles(b, (s.x + shift) % np.array(s.dims), s.r, s.U, s.Om)
+            eng.step(3)
+            for b in range(2):
+                got.append((eng.get_pdfs(b).cpu().numpy(), *eng.get_forces(b)))
+        out.append(got)
+        eng.close()
+    for (f, F, T), (f1, F1, T1), s in zip(out[1], out[0], specs * 2):
+        assert np.array_equal(f, f1)
+        scale = 4.0 / 3.0 * np.pi * s.r[:, None] ** 3 * 0.1   # B |g| over the sphere's cells, |g| below 0.1
+        assert np.all(np.abs(F - F1) <= 1e-13 * scale) and np.all(np.abs(T - T1) <= 1e-13 * scale * 5.0)
