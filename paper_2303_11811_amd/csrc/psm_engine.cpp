@@ -237,7 +237,9 @@ static Layout make_layout(const psm_box_desc* boxes, int nbox, int storage) {
                            max_tiles_axis(d.max_radius, ty, d.ny) * max_tiles_axis(d.max_radius, tz, d.nz);
             }
             Tmax = (int)std::max<long long>(Tmax, T);
-            capmax = std::max(capmax, cap << z_shift(boxes, nbox, storage, tx, ty, tz, cap));
+            // the same slots whatever the storage form
+            for (int st : {PSM_FP64, PSM_FP32DEV, PSM_FP16DEV})
+                capmax = std::max(capmax, cap << z_shift(boxes, nbox, st, tx, ty, tz, cap));
         }
     L.T_max = Tmax;
     int most = 0;
