@@ -157,20 +157,61 @@ static int max_tiles_axis(double rmax, int T, int L) {
 // ---------------------------------------------------------------------------
 // Workspace layout
 
+// A step's stores bypass cache retention (nontemporal: 512^3 runs 3 % faster)
+// unless the next step can read them from the 256 MB last-level cache, which
+// keeps no nontemporal line. us per step, nontemporal / cached, by the MiB of
+// both grids:
+//   FP64  48^3 (32) 11.6 / 11.6   64^3 (76) 21.1 / 17.2   84^3 (172) 45.9 / 31.6   96^3 (256) 55.0 / 49.8
+//         104^3 (326) 71.8 / 78.7
+//   FP32  64^3 (38) 12.7 / 11.7   80^3 (74) 27.7 / 22.0   108^3 (183) 57.9 / 38.9  136^3 (365) 90.5 / 96.9
+//   FP16  64^3 (19) 9.0 / 9.3     96^3 (64) 26.5 / 23.2   128^3 (152) 40.2 / 34.6  152^3 (255) 91.2 / 67.8
+//         160^3 (297) 80.8 / 85.4
+constexpr long long kCachedMin = 24LL << 20, kCachedMax = 256LL << 20;
+
 struct Layout {
     size_t off_boxes, off_tbase, off_partbox, off_pt, off_acc, off_fprev, off_prevok, off_tcnt, off_tent,
         off_partial, off_misc, off_statpart, total;
     std::vector<size_t> off_grid[2];
-    std::vector<int> pblk;
+    std::vector<int> pitch, pblk;   // per box: row pitch in cells, 64-cell blocks per z-plane
     int T_max;
     int list_cap;                // spheres a tile's list holds
     long long cap_max;           // force-partial slots
     int P_total;
 };
 
-static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
-
 static size_t storage_bytes(int storage) { return storage == PSM_FP64 ? 8 : (storage == PSM_FP32DEV ? 4 : 2); }
+
+// Row pitches: row_pitch() where both grids fit the last-level cache, which the
+// packed rows fill best. Larger grids that it leaves packed start every row at a
+// 128-byte line: the waves of two tiles otherwise write parts of one line, which
+// nontemporal stores take to memory one by one. us per step, packed rows with
+// nontemporal / ordinary stores / rows from a line:
+//   FP64  150^3 241 / 216 / 207   220^3 685 / 659 / 618   200^3 474 / 499 / 465
+//   FP32  150^3 154 / 132 / 115   220^3 509 / 417 / 337   200^3 343 / 304 / 269
+//   FP16  170^3 137 / 112 /  91   220^3 365 / 251 / 199   200^3 266 / 194 / 165
+// (in the cache, FP16 150^3: 63 packed, 73 from a line). Grids beyond 64 GiB
+// keep the packed rows: they may fill the memory.
+constexpr long long kLineMax = 64LL << 30;
+
+static std::vector<int> row_pitches(const psm_box_desc* boxes, int nbox, int storage) {
+    const int line = 128 / (int)storage_bytes(storage);
+    std::vector<int> packed(nbox), lined(nbox);
+    long long bytes[2] = {0, 0};
+    bool fits = true;
+    for (int b = 0; b < nbox; ++b) {
+        const psm_box_desc& d = boxes[b];
+        packed[b] = row_pitch(d.nx);
+        lined[b] = cdiv(packed[b], line) * line;
+        for (int k = 0; k < 2; ++k)
+            bytes[k] += 2LL * d.nz * cdiv((long long)(k ? lined[b] : packed[b]) * d.ny, BLK) * NQ * BLK *
+                        (long long)storage_bytes(storage);
+        // byte offsets inside a z-plane: the bound of the descriptor checks
+        fits = fits && ((long long)lined[b] * d.ny + BLK) * NQ * 8 < (1LL << 31);
+    }
+    return fits && bytes[0] > kCachedMax && bytes[1] <= kLineMax ? lined : packed;
+}
+
+static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 static int validate(const psm_box_desc* boxes, int nbox, int storage) {
     if (!boxes || nbox <= 0) return fail(PSM_EINVAL, "need at least one box descriptor");
@@ -265,9 +306,10 @@ static Layout make_layout(const psm_box_desc* boxes, int nbox, int storage) {
     L.off_misc = take(256);
     L.off_statpart = take(sizeof(double) * 4 * (size_t)stats_blocks() + 64);
     for (int p = 0; p < 2; ++p) L.off_grid[p].resize(nbox);
+    L.pitch = row_pitches(boxes, nbox, storage);
     L.pblk.resize(nbox);
     for (int b = 0; b < nbox; ++b) {
-        int pb = cdiv((long long)row_pitch(boxes[b].nx) * boxes[b].ny, BLK);   // 64-cell blocks per z-plane
+        int pb = cdiv((long long)L.pitch[b] * boxes[b].ny, BLK);
         L.pblk[b] = pb;
         size_t elems = (size_t)boxes[b].nz * pb * NQ * BLK;
         for (int p = 0; p < 2; ++p) L.off_grid[p][b] = take(s * elems);
@@ -372,17 +414,6 @@ static int upload_box_table(psm_ctx* c) {
     HIP_TRY(hipStreamSynchronize(c->stream));   // the host vectors are pageable temporaries
     return PSM_OK;
 }
-
-// A step's stores bypass cache retention (nontemporal: 512^3 runs 3 % faster)
-// unless the next step can read them from the 256 MB last-level cache, which
-// keeps no nontemporal line. us per step, nontemporal / cached, by the MiB of
-// both grids:
-//   FP64  48^3 (32) 11.6 / 11.6   64^3 (76) 21.1 / 17.2   84^3 (172) 45.9 / 31.6   96^3 (256) 55.0 / 49.8
-//         104^3 (326) 71.8 / 78.7
-//   FP32  64^3 (38) 12.7 / 11.7   80^3 (74) 27.7 / 22.0   108^3 (183) 57.9 / 38.9  136^3 (365) 90.5 / 96.9
-//   FP16  64^3 (19) 9.0 / 9.3     96^3 (64) 26.5 / 23.2   128^3 (152) 40.2 / 34.6  152^3 (255) 91.2 / 67.8
-//         160^3 (297) 80.8 / 85.4
-constexpr long long kCachedMin = 24LL << 20, kCachedMax = 256LL << 20;
 
 static StepForm step_form(const psm_ctx* c) {
     StepForm f;
@@ -584,7 +615,7 @@ extern "C" int psm_create(const psm_box_desc* boxes, int nbox, int storage, doub
         bx.np = 0;
         bx.mapping = d.mapping;
         bx.nsub = d.mapping == PSM_MAP_SUBSAMPLE ? d.subsample_n : 1;
-        bx.pitch = row_pitch(d.nx);
+        bx.pitch = L.pitch[b];
         bx.pblk = L.pblk[b];
         bx.plane_elems = (long long)L.pblk[b] * NQ * BLK;
         bx.grid[0] = c->ws + L.off_grid[0][b];

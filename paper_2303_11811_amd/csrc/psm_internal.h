@@ -40,7 +40,7 @@ struct BoxDev {
     // PDF storage: each z-plane holds pblk blocks of 64 cells (pitch*ny
     // rounded up); a block stores its 19 directions one after another, 64
     // values each. Cell (x, y) of a plane is in-plane cell x + pitch*y.
-    int pitch;                      // row pitch in cells, see row_pitch()
+    int pitch;                      // row pitch in cells, see row_pitch() and row_pitches()
     int pblk;                       // blocks per z-plane
     long long plane_elems;          // values per z-plane, pblk * 19 * 64
     void* grid[2];                  // ping-pong PDF grids, nz * plane_elems values
@@ -157,7 +157,8 @@ __host__ __device__ inline void aabb_cells(double x, double r, int& lo, int& hi)
 // blocks is padded to the next block boundary when that costs at most 1/8 of
 // the row, so that every row of a tile starts on a block and a wave's loads
 // and stores of one direction stay in one block (or two, for a shift in x).
-// Narrower rows are packed back to back.
+// Narrower rows are packed back to back, unless the host's choice for large
+// grids lets each start at a line.
 __host__ __device__ inline int row_pitch(int nx) {
     int up = (nx + BLK - 1) / BLK * BLK;
     return 8LL * up <= 9LL * nx ? up : nx;

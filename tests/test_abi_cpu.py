@@ -189,3 +189,25 @@ def test_plane_size_limit():
     with pytest.raises(psm.PsmError) as e:
         psm.psm_workspace_size([psm.make_desc(4096, 3450, 4, 0.6)], psm.PSM_FP16DEV)
     assert e.value.code == psm.PSM_EINVAL and "2^31" in str(e.value)
+
+
+@pytest.mark.parametrize("storage,line", [(0, 16), (1, 32), (2, 64)])
+def test_rows_of_large_grids_start_at_a_line(storage, line):
+    """Grids beyond the last-level cache (256 MiB, both grids) whose rows are
+    not padded to whole blocks start each at 128 bytes; smaller ones, and those
+    beyond 64 GiB, are packed."""
+    size = 8 >> storage
+
+    def ws(nx, ny, nz):
+        return psm.psm_workspace_size([psm.make_desc(nx, ny, nz, 0.6)], storage)
+
+    def grids(pitch, ny, nz):
+        return 2 * nz * -(-(pitch * ny) // 64) * 19 * 64 * size
+
+    for nx, ny, nz in ((70, 64, 16), (70, 512, 128 << storage), (70, 4096, 2048 << (storage > 0))):
+        packed, lined = grids(nx, ny, nz), grids(-(-nx // line) * line, ny, nz)
+        extra = ws(nx, ny, nz) - ws(64, ny, nz) - (packed - grids(64, ny, nz))
+        large = packed > 256 << 20 and lined <= 64 << 30
+        tables = ws(64, ny, nz) - grids(64, ny, nz)   # nx 70 has up to twice the tiles of nx 64
+        pad = lined - packed if large else 0
+        assert pad <= extra <= pad + tables, (nx, ny, nz, large)

@@ -653,3 +653,37 @@ def test_tiles_shared_by_workgroups_keep_the_results(launch, flags):
         assert np.array_equal(f, f1)
         scale = 4.0 / 3.0 * np.pi * s.r[:, None] ** 3 * 0.1   # B |g| over the sphere's cells, |g| below 0.1
         assert np.all(np.abs(F - F1) <= 1e-13 * scale) and np.all(np.abs(T - T1) <= 1e-13 * scale * 5.0)
+
+
+@pytest.mark.parametrize("storage,line", [(psm.PSM_FP64, 16), (psm.PSM_FP32DEV, 32), (psm.PSM_FP16DEV, 64)])
+@pytest.mark.parametrize("nx", [6, 33, 49, 72, 131])
+def test_rows_from_a_line_keep_the_results(nx, storage, line):
+    """A narrow box beside one large enough that every row starts at a
+    128-byte line (the workspace has the padded rows) gives bit for bit what it
+    gives alone with packed rows: state in and out, steps, totals, fields and
+    forces, periodic and between walls."""
+    from dataclasses import replace
+
+    spec = inputs.random_small((nx, 22, 21), 0 if nx < 10 else 5, (2.0, 3.5), seed=nx, tau=0.66, fext=(1e-5, 0, 0),
+                               omamp=0.003)
+    wide = inputs.BoxSpec(dims=(192, 192, 128), tau=0.8)
+    for s in (spec, replace(spec, x=spec.x[:0], r=spec.r[:0], U=spec.U[:0], Om=spec.Om[:0], walls_z=True)):
+        out = []
+        for boxes in ([s], [s, wide]):
+            _print_case("rows", nx=nx, storage=storage, walls=s.walls_z, boxes=len(boxes))
+            eng = make_engine(boxes, storage=storage)
+            eng.set_launch(64, 4, 1, 0)
+            for b, box in enumerate(boxes):
+                eng.set_equilibrium(b, np.random.default_rng(nx).random((3, int(np.prod(box.dims)))) * 0.01)
+            got = [eng.get_pdfs(0).cpu().numpy()]
+            eng.set_pdfs(0, initial_f(s))
+            eng.set_particles(0, s.x, s.r, s.U, s.Om)
+            eng.step(3)
+            mass, mom, _ = eng.get_stats(0)
+            got += [eng.get_pdfs(0).cpu().numpy(), *(a.cpu().numpy() for a in eng.get_macroscopic(0)),
+                    *(a.cpu().numpy() for a in eng.get_solid_fraction(0)), *eng.get_forces(0)]
+            eng.close()
+            out.append((got, np.array([mass, *mom])))
+        assert all(np.array_equal(a, b) for a, b in zip(out[0][0], out[1][0]))
+        # totals: 19 N terms of at most 1/3, summed in another order
+        assert np.all(np.abs(out[0][1] - out[1][1]) <= 2.0 ** -52 * 19 * s.N)
