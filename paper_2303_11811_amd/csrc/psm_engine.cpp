@@ -166,7 +166,20 @@ static int max_tiles_axis(double rmax, int T, int L) {
 //   FP32  64^3 (38) 12.7 / 11.7   80^3 (74) 27.7 / 22.0   108^3 (183) 57.9 / 38.9  136^3 (365) 90.5 / 96.9
 //   FP16  64^3 (19) 9.0 / 9.3     96^3 (64) 26.5 / 23.2   128^3 (152) 40.2 / 34.6  152^3 (255) 91.2 / 67.8
 //         160^3 (297) 80.8 / 85.4
-constexpr long long kCachedMin = 24LL << 20, kCachedMax = 256LL << 20;
+// Well beyond it, the loads of the nine directions without an x component are
+// nontemporal too; the lines of the others are read by two waves, and by the
+// second from the caches (all 19 nontemporal: 2 to 10 % slower at 512^3). us per
+// step, ordinary / nontemporal loads, by the MiB of both grids:
+//   FP64  100^3 (325) 65.5 / 66.5  128^3 (608) 118.1 / 116.2  192^3 (2052) 382.6 / 377.3  512^3 (38912) 7075 / 7031
+//   FP32  130^3 (393) 80.5 / 81.8  150^3 (521) 114.3 / 111.9  192^3 (1026) 197.6 / 196.0  280^3 (3637) 677.5 / 682.0
+//   FP16  170^3 (402) 90.7 / 95.3  200^3 (742) 165.4 / 159.0  240^3 (1069) 259.2 / 254.0  300^3 (2088) 471.9 / 475.6
+constexpr long long kCachedMin = 24LL << 20, kCachedMax = 256LL << 20, kStreamMin = 448LL << 20,
+                    kStreamMaxDev = 1280LL << 20;
+
+static int cache_form(long long grid_bytes, int storage) {
+    if (grid_bytes >= kCachedMin && grid_bytes <= kCachedMax) return KEEP;
+    return grid_bytes >= kStreamMin && (storage == PSM_FP64 || grid_bytes <= kStreamMaxDev) ? STREAM : MIXED;
+}
 
 struct Layout {
     size_t off_boxes, off_tbase, off_partbox, off_pt, off_acc, off_fprev, off_prevok, off_tcnt, off_tent,
@@ -325,7 +338,7 @@ struct psm_ctx {
     int nbox = 0, storage = 0;
     int map_mode = 0;            // 1 if any box uses sub-division sampling
     bool walls = false;          // any box has walls or faces
-    bool cached = false;         // both grids fit the last-level cache
+    int cache = MIXED;           // by the bytes of both grids
     float h_scale = 1.0f, h_inv = 1.0f;
     hipStream_t stream = nullptr;
     char* ws = nullptr;
@@ -420,7 +433,7 @@ static StepForm step_form(const psm_ctx* c) {
     f.map = c->map_mode != 0;
     f.filter = c->ts.filter != 0;
     f.walls = c->walls;
-    f.cached = c->cached;
+    f.cache = c->cache;
     return f;
 }
 
@@ -689,7 +702,7 @@ extern "C" int psm_create(const psm_box_desc* boxes, int nbox, int storage, doub
         bx.margin32 = 1e-3 + 16.0 * std::ldexp(256.0 + (d.max_particles > 0 ? d.max_radius : 1.0) + 2.0, -24);
         pb += d.max_particles;
     }
-    c->cached = grid_bytes >= kCachedMin && grid_bytes <= kCachedMax;
+    c->cache = cache_form(grid_bytes, storage);
     c->d_boxes = (BoxDev*)(c->ws + L.off_boxes);
     c->d_tbase = (int*)(c->ws + L.off_tbase);
     c->d_partbox = (int*)(c->ws + L.off_partbox);

@@ -372,11 +372,16 @@ struct DownloadParams {
 };
 
 // Instance of the step kernel.
+enum CacheForm {
+    MIXED,     // nontemporal stores
+    KEEP,      // ordinary loads and stores
+    STREAM,    // nontemporal stores, and loads of the lines that one wave alone reads
+};
 struct StepForm {
     bool map;       // a box samples its fractions
     bool filter;    // per-wave candidate filter
     bool walls;     // a box has walls or faces
-    bool cached;    // stores that stay in the caches (not with the filter)
+    int cache;      // CacheForm (MIXED with the filter)
 };
 hipError_t launch_step(int storage, const StepForm& form, const StepParams& kp, hipStream_t st);
 hipError_t launch_pattern_copy(int storage, bool shifted, const StepParams& kp, hipStream_t st);

@@ -33,7 +33,8 @@ constexpr int RSRC_WORD3 = 0x00020000;   // raw 32-bit data format, no swizzle
 
 // Cache policy of the PDF streams (compile-time switches, measured by the
 // tuning sweeps): nontemporal stores / loads bypass cache retention. The step
-// kernel's CACHED instances store without it (grids that fit the caches).
+// kernel's KEEP instances store without it (grids that fit the caches), its
+// STREAM instances also load so what no other wave reads.
 #ifndef PSM_NT_STORE
 #define PSM_NT_STORE 1
 #endif
@@ -50,7 +51,7 @@ constexpr int ST_AUX = PSM_NT_STORE ? 2 : 0;
 __device__ __forceinline__ Rsrc plane_rsrc(const void* base, unsigned bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, RSRC_WORD3);
 }
-#define PSM_LD(B, T, r, vo, so) __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_##B(r, vo, so, LD_AUX))
+#define PSM_LD(B, T, r, vo, so, aux) __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_##B(r, vo, so, aux))
 #define PSM_ST(B, U, v, r, vo, so, aux) __builtin_amdgcn_raw_buffer_store_##B(__builtin_bit_cast(U, v), r, vo, so, aux)
 #else
 // plain global accesses from the plane's base address (compile-time alternative)
@@ -58,7 +59,7 @@ typedef const char* RsrcPtr;
 #define Rsrc RsrcPtr
 __device__ __forceinline__ Rsrc plane_rsrc(const void* base, unsigned) { return (const char*)base; }
 #define GLB __attribute__((address_space(1)))
-#define PSM_LD(B, T, r, vo, so) (*(const GLB T*)((r) + (so) + (vo)))
+#define PSM_LD(B, T, r, vo, so, aux) (*(const GLB T*)((r) + (so) + (vo)))
 #define PSM_ST(B, U, v, r, vo, so, aux) __builtin_nontemporal_store(v, (GLB decltype(v)*)((r) + (so) + (vo)))
 #endif
 
@@ -70,7 +71,7 @@ struct St64 {
     using R = double;
     static constexpr bool DEV = false;
     static constexpr bool SCALED = false;
-    __device__ static R ld(Rsrc r, unsigned vo, int so) { return PSM_LD(b64, double, r, vo, so); }
+    template <int AUX = LD_AUX> __device__ static R ld(Rsrc r, unsigned vo, int so) { return PSM_LD(b64, double, r, vo, so, AUX); }
     template <int AUX = ST_AUX> __device__ static void st(Rsrc r, unsigned vo, int so, R v) {
         PSM_ST(b64, u32x2, v, r, vo, so, AUX);
     }
@@ -82,7 +83,7 @@ struct St32 {
     using R = float;
     static constexpr bool DEV = true;
     static constexpr bool SCALED = false;
-    __device__ static R ld(Rsrc r, unsigned vo, int so) { return PSM_LD(b32, float, r, vo, so); }
+    template <int AUX = LD_AUX> __device__ static R ld(Rsrc r, unsigned vo, int so) { return PSM_LD(b32, float, r, vo, so, AUX); }
     template <int AUX = ST_AUX> __device__ static void st(Rsrc r, unsigned vo, int so, R v) {
         PSM_ST(b32, unsigned int, v, r, vo, so, AUX);
     }
@@ -97,7 +98,7 @@ struct St16 {
     // scale s is folded into the collision constants), so its loads and
     // stores are bare conversions. State I/O converts with the scale.
     static constexpr bool SCALED = true;
-    __device__ static R ld(Rsrc r, unsigned vo, int so) { return (float)PSM_LD(b16, _Float16, r, vo, so); }
+    template <int AUX = LD_AUX> __device__ static R ld(Rsrc r, unsigned vo, int so) { return (float)PSM_LD(b16, _Float16, r, vo, so, AUX); }
     template <int AUX = ST_AUX> __device__ static void st(Rsrc r, unsigned vo, int so, R v) {
         const _Float16 h = (_Float16)v;
         PSM_ST(b16, unsigned short, h, r, vo, so, AUX);
@@ -352,28 +353,30 @@ __device__ __forceinline__ float wrap32(float t, float L, float invL) { return f
 #endif
 
 // pull of the 19 values of one cell from the source planes z (rz), z-1 (rm)
-// and z+1 (rp); direction q lies q * QB bytes into a block
-#define PSM_LOAD19(F, rz, rm, rp)            \
-    do {                                     \
-        F[0] = S::ld(rz, o00, 0 * QB);       \
-        F[1] = S::ld(rz, om0, 1 * QB);       \
-        F[2] = S::ld(rz, op0, 2 * QB);       \
-        F[3] = S::ld(rz, o0m, 3 * QB);       \
-        F[4] = S::ld(rz, o0p, 4 * QB);       \
-        F[5] = S::ld(rm, o00, 5 * QB);       \
-        F[6] = S::ld(rp, o00, 6 * QB);       \
-        F[7] = S::ld(rz, omm, 7 * QB);       \
-        F[8] = S::ld(rz, opp, 8 * QB);       \
-        F[9] = S::ld(rz, omp, 9 * QB);       \
-        F[10] = S::ld(rz, opm, 10 * QB);     \
-        F[11] = S::ld(rm, om0, 11 * QB);     \
-        F[12] = S::ld(rp, op0, 12 * QB);     \
-        F[13] = S::ld(rp, om0, 13 * QB);     \
-        F[14] = S::ld(rm, op0, 14 * QB);     \
-        F[15] = S::ld(rm, o0m, 15 * QB);     \
-        F[16] = S::ld(rp, o0p, 16 * QB);     \
-        F[17] = S::ld(rp, o0m, 17 * QB);     \
-        F[18] = S::ld(rm, o0p, 18 * QB);     \
+// and z+1 (rp); direction q lies q * QB bytes into a block. The nine directions
+// without an x component, whose lines no other wave reads, are loaded with
+// cache policy AUX0.
+#define PSM_LOAD19(F, rz, rm, rp, AUX0)                         \
+    do {                                                        \
+        F[0] = S::template ld<AUX0>(rz, o00, 0 * QB);           \
+        F[1] = S::ld(rz, om0, 1 * QB);                          \
+        F[2] = S::ld(rz, op0, 2 * QB);                          \
+        F[3] = S::template ld<AUX0>(rz, o0m, 3 * QB);           \
+        F[4] = S::template ld<AUX0>(rz, o0p, 4 * QB);           \
+        F[5] = S::template ld<AUX0>(rm, o00, 5 * QB);           \
+        F[6] = S::template ld<AUX0>(rp, o00, 6 * QB);           \
+        F[7] = S::ld(rz, omm, 7 * QB);                          \
+        F[8] = S::ld(rz, opp, 8 * QB);                          \
+        F[9] = S::ld(rz, omp, 9 * QB);                          \
+        F[10] = S::ld(rz, opm, 10 * QB);                        \
+        F[11] = S::ld(rm, om0, 11 * QB);                        \
+        F[12] = S::ld(rp, op0, 12 * QB);                        \
+        F[13] = S::ld(rp, om0, 13 * QB);                        \
+        F[14] = S::ld(rm, op0, 14 * QB);                        \
+        F[15] = S::template ld<AUX0>(rm, o0m, 15 * QB);         \
+        F[16] = S::template ld<AUX0>(rp, o0p, 16 * QB);         \
+        F[17] = S::template ld<AUX0>(rp, o0m, 17 * QB);         \
+        F[18] = S::template ld<AUX0>(rm, o0p, 18 * QB);         \
     } while (0)
 
 __device__ inline void box_tiles(const BoxDev& bx, const TileShape& ts, double x, double y, double z, double r,
@@ -433,7 +436,7 @@ __device__ __forceinline__ Particles particles(const PSM_CONST StepParams* a) {
                      a->P.ox, a->P.oy, a->P.oz, a->P.acc, a->P.fprev, a->P.prev_ok};
 }
 
-template <class S, int MAP, bool FILT, bool WALL, bool CACHED>
+template <class S, int MAP, bool FILT, bool WALL, int CACHE>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
     !S::DEV ? PSM_WAVES_F64 : (S::SCALED && MAP == 0 && !FILT ? PSM_WAVES_F16 : PSM_WAVES_DEV), 8))) void k_psm_step(
     StepParams) {
@@ -634,6 +637,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
         // current cell's pulls before its mapping.
         constexpr bool PREF = S::DEV && !FILT && MAP == 0 && (S::SCALED ? PSM_PREFETCH_F16 : PSM_PREFETCH_F32);
         constexpr bool EARLY = !PREF && !FILT && MAP == 0 && (S::DEV ? (S::SCALED && PSM_EARLY_PULLS_F16) : PSM_EARLY_PULLS_F64);
+        constexpr int LINE_AUX = CACHE == STREAM ? 2 : LD_AUX;
         R fn[NQ];
         if constexpr (PREF) {
             const int z0 = tcz * TZ;
@@ -641,7 +645,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
                 const int zm0 = z0 == 0 ? nz - 1 : z0 - 1, zp0 = z0 == nz - 1 ? 0 : z0 + 1;
                 const Rsrc a = plane_rsrc(src + z0 * pbytes, pb32), am = plane_rsrc(src + zm0 * pbytes, pb32),
                            ap = plane_rsrc(src + zp0 * pbytes, pb32);
-                PSM_LOAD19(fn, a, am, ap);
+                PSM_LOAD19(fn, a, am, ap, LINE_AUX);
             }
         }
 
@@ -667,10 +671,10 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
                 if (lane_ok && k + 1 < TZ && z1 < nz) {
                     // planes z + 1 (own), z (below) and z + 2 (above, periodic)
                     const Rsrc a2 = plane_rsrc(src + (z1 == nz - 1 ? 0 : z1 + 1) * pbytes, pb32);
-                    PSM_LOAD19(fn, sp, sz, a2);
+                    PSM_LOAD19(fn, sp, sz, a2, LINE_AUX);
                 }
             } else if constexpr (EARLY) {
-                if (lane_ok) PSM_LOAD19(f, sz, sm, sp);
+                if (lane_ok) PSM_LOAD19(f, sz, sm, sp, LINE_AUX);
             }
 
             // 1. solid fractions of this cell from the staged candidates (Sec. 2.3.2);
@@ -785,7 +789,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
                         }
                     }
                 }
-                if constexpr (!PREF && !EARLY) PSM_LOAD19(f, sz, sm, sp);
+                if constexpr (!PREF && !EARLY) PSM_LOAD19(f, sz, sm, sp, LINE_AUX);
                 if (face_plane) {
                     if (z == 0) {
                         f[5] = fb[0]; f[11] = fb[1]; f[14] = fb[2]; f[15] = fb[3]; f[18] = fb[4];
@@ -841,7 +845,7 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
                 }
 #define PSM_FA(Q) pick<R>(S::SCALED ? bx.fa_scaled[Q / 2] : bx.fa[Q / 2], S::SCALED ? bx.fa_scaled_f[Q / 2] : bx.fa_f[Q / 2])
 #define PSM_FS(Q) pick<R>(bx.fs[Q / 2], bx.fs_f[Q / 2])
-#define PSM_STORE(Q) S::template st<CACHED ? 0 : ST_AUX>(dz_, o00, (Q) * QB, f[Q])
+#define PSM_STORE(Q) S::template st<CACHE == KEEP ? 0 : ST_AUX>(dz_, o00, (Q) * QB, f[Q])
 
                 // 4. collision; each pair is stored as soon as it is final
                 if (!psm_wave) {
@@ -1354,7 +1358,7 @@ __device__ __forceinline__ void pull19(const BoxDev& bx, int parity, int x, int 
     const Rsrc rz = plane_rsrc(src + z * pbytes, (unsigned)pbytes);
     const Rsrc rm = plane_rsrc(src + zm * pbytes, (unsigned)pbytes);
     const Rsrc rp = plane_rsrc(src + zp * pbytes, (unsigned)pbytes);
-    PSM_LOAD19(f, rz, rm, rp);
+    PSM_LOAD19(f, rz, rm, rp, LD_AUX);
 }
 
 // FP32 value of v rounded to odd: rounding it on to FP16 gives the nearest FP16
@@ -1921,7 +1925,7 @@ __global__ __launch_bounds__(WG) void k_pattern_copy(StepParams kp) {
             const Rsrc sp = SHIFT ? plane_rsrc(src + zp * pbytes, pb32) : sz;
             const Rsrc dz_ = plane_rsrc(dst + z * pbytes, pb32);
             R f[NQ];
-            PSM_LOAD19(f, sz, sm, sp);
+            PSM_LOAD19(f, sz, sm, sp, LD_AUX);
 #pragma unroll
             for (int q = 0; q < NQ; ++q) S::st(dz_, o00, q * QB, f[q]);
         }
@@ -1939,20 +1943,21 @@ hipError_t launch_pattern_copy(int storage, bool shifted, const StepParams& kp, 
     return hipLaunchKernel(k, dim3(kp.grid), dim3(WG), args, 0, st);
 }
 
-template <int MAP, bool FILT, bool WALL, bool CACHED>
+template <int MAP, bool FILT, bool WALL, int CACHE>
 static const void* step_kernel_of(int storage) {
     switch (storage) {
-        case 0: return (const void*)k_psm_step<St64, MAP, FILT, WALL, CACHED>;
-        case 1: return (const void*)k_psm_step<St32, MAP, FILT, WALL, CACHED>;
-        default: return (const void*)k_psm_step<St16, MAP, FILT, WALL, CACHED>;
+        case 0: return (const void*)k_psm_step<St64, MAP, FILT, WALL, CACHE>;
+        case 1: return (const void*)k_psm_step<St32, MAP, FILT, WALL, CACHE>;
+        default: return (const void*)k_psm_step<St16, MAP, FILT, WALL, CACHE>;
     }
 }
 
 template <bool WALL>
 static const void* step_kernel_walls(int storage, const StepForm& f) {
-    if (f.filter) return f.map ? step_kernel_of<1, true, WALL, false>(storage) : step_kernel_of<0, true, WALL, false>(storage);
-    if (f.cached) return f.map ? step_kernel_of<1, false, WALL, true>(storage) : step_kernel_of<0, false, WALL, true>(storage);
-    return f.map ? step_kernel_of<1, false, WALL, false>(storage) : step_kernel_of<0, false, WALL, false>(storage);
+    if (f.filter) return f.map ? step_kernel_of<1, true, WALL, MIXED>(storage) : step_kernel_of<0, true, WALL, MIXED>(storage);
+    if (f.cache == KEEP) return f.map ? step_kernel_of<1, false, WALL, KEEP>(storage) : step_kernel_of<0, false, WALL, KEEP>(storage);
+    if (f.cache == STREAM) return f.map ? step_kernel_of<1, false, WALL, STREAM>(storage) : step_kernel_of<0, false, WALL, STREAM>(storage);
+    return f.map ? step_kernel_of<1, false, WALL, MIXED>(storage) : step_kernel_of<0, false, WALL, MIXED>(storage);
 }
 
 static const void* step_kernel(int storage, const StepForm& f) {

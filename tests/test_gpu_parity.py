@@ -687,3 +687,31 @@ def test_rows_from_a_line_keep_the_results(nx, storage, line):
         assert all(np.array_equal(a, b) for a, b in zip(out[0][0], out[1][0]))
         # totals: 19 N terms of at most 1/3, summed in another order
         assert np.all(np.abs(out[0][1] - out[1][1]) <= 2.0 ** -52 * 19 * s.N)
+
+
+@pytest.mark.parametrize("storage", [psm.PSM_FP64, psm.PSM_FP32DEV, psm.PSM_FP16DEV])
+@pytest.mark.parametrize("mapping,walls", [(0, False), (1, False), (0, True)])
+def test_streamed_loads_keep_the_results(mapping, walls, storage):
+    """A box beside one large enough that the step loads past the caches
+    (448 MiB of grids) gives bit for bit what it gives alone."""
+    from dataclasses import replace
+
+    spec = inputs.random_small((65, 30, 24), 5, (2.0, 3.5), seed=83, tau=0.66, fext=(1e-5, 0, 0), omamp=0.003,
+                               mapping=mapping)
+    spec = replace(spec, nsub=3, walls_z=walls)
+    if walls:
+        spec.x[:, 2] = np.clip(spec.x[:, 2], spec.r + 1.0, 24 - spec.r - 1.0)
+    wide = inputs.BoxSpec(dims=(256, 192, 128), tau=0.8)
+    out = []
+    for boxes in ([spec], [spec, wide]):
+        _print_case("streamed", storage=storage, mapping=mapping, walls=walls, boxes=len(boxes))
+        eng = make_engine(boxes, storage=storage)
+        eng.set_launch(64, 4, 1, 0)
+        if len(boxes) == 2:
+            eng.set_equilibrium(1, np.zeros((3, 256 * 192 * 128)))
+        eng.set_pdfs(0, initial_f(spec))
+        eng.set_particles(0, spec.x, spec.r, spec.U, spec.Om)
+        eng.step(3)
+        out.append([eng.get_pdfs(0).cpu().numpy(), *eng.get_forces(0)])
+        eng.close()
+    assert all(np.array_equal(a, b) for a, b in zip(*out))
