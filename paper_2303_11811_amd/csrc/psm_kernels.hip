@@ -1339,6 +1339,48 @@ __device__ __forceinline__ bool at_wall(const BoxDev& bx, int x, int y, int z) {
 }
 static bool has_walls(const BoxDev& bx) { return bx.walls || bx.walls_xy; }
 
+// Number of those cells, and cell i of them: the two z planes, then of the
+// planes between the two rows at y, then of the rows between the two ends. The
+// kernels over them launch one thread for each (500 x 200 x 800 with walls on
+// all sides, fields of its 1.3 M such cells: a thread per cell of the box 1113
+// us, these about 200; psm_get_macroscopic 3861 / 2947).
+__host__ __device__ inline long long wall_cells(const BoxDev& bx) {
+    const long long nzi = bx.nz - (bx.walls ? 2 : 0), nyi = bx.ny - ((bx.walls_xy & 2) ? 2 : 0);
+    return (bx.walls ? 2LL * bx.nx * bx.ny : 0) + ((bx.walls_xy & 2) ? 2 * nzi * bx.nx : 0) +
+           ((bx.walls_xy & 1) ? 2 * nzi * nyi : 0);
+}
+__device__ __forceinline__ bool wall_cell(const BoxDev& bx, long long i, int& x, int& y, int& z) {
+    if (i >= wall_cells(bx)) return false;
+    unsigned k = (unsigned)i;   // cells of a box are counted in int
+    const unsigned nx = bx.nx, plane = nx * bx.ny;
+    if (bx.walls) {
+        if (k < 2 * plane) {
+            z = k < plane ? 0 : bx.nz - 1;
+            k -= k < plane ? 0 : plane;
+            y = k / nx;
+            x = k - y * nx;
+            return true;
+        }
+        k -= 2 * plane;
+    }
+    const int z0 = bx.walls ? 1 : 0, nzi = bx.nz - 2 * z0, y0 = (bx.walls_xy & 2) ? 1 : 0;
+    if (y0) {
+        if (k < 2 * nx * nzi) {
+            const unsigned row = k / nx;
+            x = k - row * nx;
+            z = z0 + (row >> 1);
+            y = row & 1 ? bx.ny - 1 : 0;
+            return true;
+        }
+        k -= 2 * nx * nzi;
+    }
+    const unsigned nyi = bx.ny - 2 * y0, row = k >> 1;
+    x = k & 1 ? bx.nx - 1 : 0;
+    z = z0 + row / nyi;
+    y = y0 + row % nyi;
+    return true;
+}
+
 // The 19 stored values that stream into cell (x, y, z) of a periodic box (or
 // away from walls), in the units of S::ld.
 template <class S>
@@ -1510,13 +1552,11 @@ __global__ __launch_bounds__(256) void k_set_equilibrium(BoxDev bx, RowGrid rg, 
     }
 }
 
-// The cells at walls and faces (the others return).
+// The cells at walls and faces.
 template <class S>
 __global__ void k_set_pdfs_wall(BoxDev bx, int parity, const double* __restrict__ f, float scale) {
-    long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= bx.N) return;
-    int x = n % bx.nx, y = (n / bx.nx) % bx.ny, z = n / ((long long)bx.nx * bx.ny);
-    if (!at_wall(bx, x, y, z)) return;
+    int x, y, z;
+    if (!wall_cell(bx, (long long)blockIdx.x * blockDim.x + threadIdx.x, x, y, z)) return;
     typename S::T* g = (typename S::T*)bx.grid[parity];
     const long long N = bx.N;
     store_cell_slots<S>(bx, g, x, y, z, scale, [&](int d, long long c) { return f[(long long)d * N + c]; });
@@ -1525,10 +1565,8 @@ __global__ void k_set_pdfs_wall(BoxDev bx, int parity, const double* __restrict_
 template <class S>
 __global__ void k_set_equilibrium_wall(BoxDev bx, int parity, const double* __restrict__ rho,
                                        const double* __restrict__ u, float scale) {
-    long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= bx.N) return;
-    int x = n % bx.nx, y = (n / bx.nx) % bx.ny, z = n / ((long long)bx.nx * bx.ny);
-    if (!at_wall(bx, x, y, z)) return;
+    int x, y, z;
+    if (!wall_cell(bx, (long long)blockIdx.x * blockDim.x + threadIdx.x, x, y, z)) return;
     typename S::T* g = (typename S::T*)bx.grid[parity];
     const long long N = bx.N;
     store_cell_slots<S>(bx, g, x, y, z, scale, [&](int d, long long c) {
@@ -1558,10 +1596,9 @@ __global__ __launch_bounds__(256) void k_get_pdfs(BoxDev bx, RowGrid rg, int par
 
 template <class S>
 __global__ void k_get_pdfs_wall(BoxDev bx, int parity, double* __restrict__ f, float inv) {
-    long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= bx.N) return;
-    int x = n % bx.nx, y = (n / bx.nx) % bx.ny, z = n / ((long long)bx.nx * bx.ny);
-    if (!at_wall(bx, x, y, z)) return;
+    int x, y, z;
+    if (!wall_cell(bx, (long long)blockIdx.x * blockDim.x + threadIdx.x, x, y, z)) return;
+    const long long n = (long long)z * bx.nx * bx.ny + bx.nx * y + x;
     const typename S::T* g = (const typename S::T*)bx.grid[parity];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
@@ -1624,10 +1661,9 @@ __global__ __launch_bounds__(256) void k_macroscopic(BoxDev bx, RowGrid rg, int 
 template <class S>
 __global__ void k_macroscopic_wall(BoxDev bx, int parity, double* __restrict__ rho, double* __restrict__ u,
                                    float inv) {
-    long long n = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= bx.N) return;
-    int x = n % bx.nx, y = (n / bx.nx) % bx.ny, z = n / ((long long)bx.nx * bx.ny);
-    if (!at_wall(bx, x, y, z)) return;
+    int x, y, z;
+    if (!wall_cell(bx, (long long)blockIdx.x * blockDim.x + threadIdx.x, x, y, z)) return;
+    const long long n = (long long)z * bx.nx * bx.ny + bx.nx * y + x;
     const typename S::T* g = (const typename S::T*)bx.grid[parity];
     write_fields(bx, n, rho, u, [&](int q) {
         const double v = pull_value<S>(bx, g, q, x, y, z, inv);
@@ -2030,7 +2066,7 @@ hipError_t launch_set_pdfs(int storage, const BoxDev& bx, int parity, const doub
     const RowGrid rg = row_grid(bx);
     PSM_BY_STORAGE(hipLaunchKernelGGL(k_set_pdfs<S>, dim3(row_blocks(rg)), dim3(256), 0, st, bx, rg, parity, f, scale));
     if (has_walls(bx))
-        PSM_BY_STORAGE(hipLaunchKernelGGL(k_set_pdfs_wall<S>, dim3(blocks_for(bx.N, 256)), dim3(256), 0, st, bx, parity,
+        PSM_BY_STORAGE(hipLaunchKernelGGL(k_set_pdfs_wall<S>, dim3(blocks_for(wall_cells(bx), 256)), dim3(256), 0, st, bx, parity,
                                           f, scale));
     return hipGetLastError();
 }
@@ -2048,7 +2084,7 @@ hipError_t launch_set_equilibrium(int storage, const BoxDev& bx, int parity, con
         default: PSM_BY_STORAGE(hipLaunchKernelGGL((k_set_equilibrium<S, 6>), grid, dim3(256), 0, st, bx, rg, depth, parity, rho, u, scale));
     }
     if (has_walls(bx))
-        PSM_BY_STORAGE(hipLaunchKernelGGL(k_set_equilibrium_wall<S>, dim3(blocks_for(bx.N, 256)), dim3(256), 0, st, bx,
+        PSM_BY_STORAGE(hipLaunchKernelGGL(k_set_equilibrium_wall<S>, dim3(blocks_for(wall_cells(bx), 256)), dim3(256), 0, st, bx,
                                           parity, rho, u, scale));
     return hipGetLastError();
 }
@@ -2057,7 +2093,7 @@ hipError_t launch_get_pdfs(int storage, const BoxDev& bx, int parity, double* f,
     const RowGrid rg = row_grid(bx);
     PSM_BY_STORAGE(hipLaunchKernelGGL(k_get_pdfs<S>, dim3(row_blocks(rg)), dim3(256), 0, st, bx, rg, parity, f, inv));
     if (has_walls(bx))
-        PSM_BY_STORAGE(hipLaunchKernelGGL(k_get_pdfs_wall<S>, dim3(blocks_for(bx.N, 256)), dim3(256), 0, st, bx, parity,
+        PSM_BY_STORAGE(hipLaunchKernelGGL(k_get_pdfs_wall<S>, dim3(blocks_for(wall_cells(bx), 256)), dim3(256), 0, st, bx, parity,
                                           f, inv));
     return hipGetLastError();
 }
@@ -2079,7 +2115,7 @@ hipError_t launch_macroscopic(int storage, const BoxDev& bx, int parity, double*
     PSM_BY_STORAGE(hipLaunchKernelGGL(k_macroscopic<S>, dim3(row_blocks(rg)), dim3(256), 0, st, bx, rg, parity, rho, u,
                                       inv));
     if (has_walls(bx))
-        PSM_BY_STORAGE(hipLaunchKernelGGL(k_macroscopic_wall<S>, dim3(blocks_for(bx.N, 256)), dim3(256), 0, st, bx,
+        PSM_BY_STORAGE(hipLaunchKernelGGL(k_macroscopic_wall<S>, dim3(blocks_for(wall_cells(bx), 256)), dim3(256), 0, st, bx,
                                           parity, rho, u, inv));
     return hipGetLastError();
 }

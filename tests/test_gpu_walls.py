@@ -395,3 +395,29 @@ def test_deviation_forms_one_step_every_value_with_boundaries(storage, case):
         ratio = float(np.max(np.abs(got - ref) / bound))
         print(f"[ratio] max |err|/bound = {ratio:.3g}", flush=True)
         assert ratio <= 1.0
+
+
+@pytest.mark.parametrize("walls", ["x", "y", "z", "xy", "xz", "yz", "xyz"])
+@pytest.mark.parametrize("dims", [(4, 4, 4), (5, 7, 4), (66, 9, 6)])
+def test_every_wall_cell_is_set_and_read_once(dims, walls):
+    """Set and read back a random state of boxes with resting walls on any
+    sides: canonical PDFs (each a stored value, or one bounced back, with at
+    most one rounding), density and velocity of every cell."""
+    print(f"[case] wall cells {dims} {walls}", flush=True)
+    spec = inputs.BoxSpec(dims=dims, tau=0.7, walls_x="x" in walls, walls_y="y" in walls, walls_z="z" in walls)
+    N = int(np.prod(dims))
+    rng = np.random.default_rng(N + len(walls))
+    w = np.array([1 / 3] + [1 / 18] * 6 + [1 / 36] * 12)
+    c = np.array([(0, 0, 0), (1, 0, 0), (-1, 0, 0), (0, 1, 0), (0, -1, 0), (0, 0, 1), (0, 0, -1), (1, 1, 0),
+                  (-1, -1, 0), (1, -1, 0), (-1, 1, 0), (1, 0, 1), (-1, 0, -1), (1, 0, -1), (-1, 0, 1), (0, 1, 1),
+                  (0, -1, -1), (0, 1, -1), (0, -1, 1)])
+    f = w[:, None] * (1.0 + 0.02 * (rng.random((19, N)) - 0.5))
+    eng = make_engine([spec])
+    eng.set_pdfs(0, f)
+    got = eng.get_pdfs(0).cpu().numpy()
+    rho, u = (a.cpu().numpy() for a in eng.get_macroscopic(0))
+    eng.close()
+    assert np.all(np.abs(got - f) <= 2.0 ** -53)
+    # sums of 19 terms of at most 1/3 and 1/18, one rounding per addition
+    assert np.all(np.abs(rho - got.sum(0)) <= 19 * 2.0 ** -52)
+    assert np.all(np.abs(u - c.T @ got) <= 19 * 2.0 ** -52)
