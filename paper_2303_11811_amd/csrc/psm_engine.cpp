@@ -5,7 +5,8 @@
 // per-tile candidate lists, the per-(tile, sphere) force partials and a few
 // scratch words. Particle uploads go through pinned staging. The time step
 // of Sec. 3.1 of the paper (mapping -> PSM kernel -> force reduction) is one
-// fused launch over the tiles of all boxes plus one small reduction launch;
+// fused launch over the tiles of all boxes, which also reduces the forces of
+// the step before it (the last step of a call: one small launch behind it);
 // 10-step runs can be replayed from captured HIP graphs. The sphere update of
 // Sec. 2.2.2 and the re-binning it needs run on the device as well.
 #include <hip/hip_runtime.h>
@@ -465,7 +466,7 @@ static void assign_tiles(psm_ctx* c) {
     int dev = 0, ncu = 256;
     (void)hipGetDevice(&dev);
     (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-    // one-shot: a workgroup per tile (rounded up to whole XCD rounds);
+    // one-shot: a workgroup per part of a tile (rounded up to whole XCD rounds);
     // persistent: as many workgroups as fit at once, each walking its tiles
     int full = (((c->T_total << c->ts.zshift) + NXCD - 1) / NXCD) * NXCD;
     int g = c->ts.persistent ? std::min(step_blocks_per_cu(c->storage, step_form(c)) * ncu, full) : full;

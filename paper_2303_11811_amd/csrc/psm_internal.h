@@ -108,7 +108,7 @@ struct Particles {
 
 struct TileShape {
     int tx, ty, tz;
-    int persistent;   // 1: occupancy-sized grid walking the tiles; 0: one workgroup per tile
+    int persistent;   // 1: occupancy-sized grid walking the tiles; 0: a workgroup per part of a tile
     int filter;       // 1: per-wave candidate filter before the per-cell mapping
     int ref_z;        // depth of the z-blocks whose centres the FP32 geometry refers to (a multiple of tz)
     int zshift;       // 1 << zshift workgroups share a tile's cells along z

@@ -13,7 +13,8 @@
 // The paper's separate mapping / setU / redF kernels are fused into the
 // stream-collide launch: each workgroup stages its tile's sphere candidates in
 // LDS, maps solid fractions in registers, evaluates U_p(x) (eq. 20) on the fly
-// and sums the per-sphere force/torque of its tile deterministically.
+// and sums the per-sphere force/torque of its tile deterministically; the
+// launch of the next step adds them per sphere.
 #include "psm_internal.h"
 
 #include <algorithm>
@@ -323,7 +324,10 @@ __device__ __forceinline__ float wrap32(float t, float L, float invL) { return f
 // (96 VGPRs) without sampling and filter, which would spill there: its vector
 // ALU is busy two thirds of the time and hides more with more waves (256^3
 // 284 -> 272 us, 384^3 870 -> 857 us). FP32 spills at 5 waves (512^3 3.67 ->
-// 5.42 ms).
+// 5.42 ms). Sampling keeps 16 squares beside the rest: at 4 waves 16 to 33
+// registers of the deviation forms went to scratch memory, so it takes 3 (4^3
+// points, FP32 256^3 896 -> 552 us, 128^3 119 -> 79, 32^3 11.2 -> 9.8; FP16 256^3
+// 475 -> 459, 32^3 11.0 -> 9.9, 128^3 70.8 -> 71.0).
 #ifndef PSM_WAVES_F64
 #define PSM_WAVES_F64 3
 #endif
@@ -332,6 +336,9 @@ __device__ __forceinline__ float wrap32(float t, float L, float invL) { return f
 #endif
 #ifndef PSM_WAVES_F16
 #define PSM_WAVES_F16 5
+#endif
+#ifndef PSM_WAVES_MAP
+#define PSM_WAVES_MAP 3
 #endif
 // Pull order of the step kernel (measured per storage form): the FP32 form
 // pulls the next cell's values while it works on the current one; FP64 issues
@@ -436,9 +443,16 @@ __device__ __forceinline__ Particles particles(const PSM_CONST StepParams* a) {
                      a->P.ox, a->P.oy, a->P.oz, a->P.acc, a->P.fprev, a->P.prev_ok};
 }
 
+// Bound by memory where the grids exceed the last-level cache: a copy with the
+// same tiles, pulls and stores takes as long (512^3 FP64 7.05 ms a step, copy
+// 7.05, at 5.8 of the 6.25 TB/s of a plain copy; FP32 3.66, FP16 2.00 against
+// 1.92, its vector ALU busy two thirds of the time). In the cache by the latency
+// of staging, pulls and mapping in sequence (FP64 64^3 18 us, copy 13), and below
+// by that of one cell (32^3 7.7 us). Two or three workgroups per CU instead of
+// three to five leave FP64 and FP32 unchanged there, FP16 slows by 4 and 20 %.
 template <class S, int MAP, bool FILT, bool WALL, int CACHE>
 __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
-    !S::DEV ? PSM_WAVES_F64 : (S::SCALED && MAP == 0 && !FILT ? PSM_WAVES_F16 : PSM_WAVES_DEV), 8))) void k_psm_step(
+    !S::DEV ? PSM_WAVES_F64 : (MAP != 0 ? PSM_WAVES_MAP : (S::SCALED && !FILT ? PSM_WAVES_F16 : PSM_WAVES_DEV)), 8))) void k_psm_step(
     StepParams) {
     using R = typename S::R;
     using T = typename S::T;
@@ -486,7 +500,6 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
     const int m = blockIdx.x / NXCD;
     const int t_begin = (int)(((long long)ka->T_total * xcd) / NXCD);
     const int t_end = (int)(((long long)ka->T_total * (xcd + 1)) / NXCD);
-
 
     // Tile order: with a queue (persistent grid), the workgroups of a die take
     // the next tile of its eighth from that die's counter as they finish one;
