@@ -285,8 +285,9 @@ enum psm_launch_flags {
  * to 8 workgroups share its cells along z where that keeps more of the chip
  * busy. Rebuilds the tile lists
  * (synchronises); invalidates captured graphs. On failure the previous
- * launch is restored. A context starts with 64 x 4 threads and a depth
- * chosen from its storage form and box sizes (its results are those of depth
+ * launch is restored. A context starts with 64 x 4 threads (FP64 boxes that
+ * would leave many of them idle, with room for at most 64 spheres each: 32 x 8)
+ * and a depth chosen from its storage form and box sizes (its results are those of depth
  * 16). psm_get_launch: host outputs (flags may be NULL). */
 int psm_set_launch(psm_ctx* ctx, int tx, int ty, int tz, int flags);
 int psm_get_launch(psm_ctx* ctx, int* tx, int* ty, int* tz, int* flags);

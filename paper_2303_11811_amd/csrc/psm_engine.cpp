@@ -126,13 +126,16 @@ static int z_shift(const psm_box_desc* boxes, int nbox, int storage, int tx, int
 // chosen. FP64, which has no such reference, takes 32 x 8 threads where the
 // widest box fills at most 3/4 of its 64-wide tiles (us at 64 x 4 / 32 x 8: 68^3
 // 31.4 / 28.8, 80^3 39.9 / 34.2, 96^3 58.9 / 54.4; 132^3, where it would save a
-// sixth, 163 / 183).
+// sixth, 163 / 183) and a list can hold every sphere: such a tile meets spheres
+// over 8 rows, so its list could overflow with spheres that the lists of 64 x 4
+// tiles hold.
 constexpr int kDefaultRefZ = 16;
 
 static TileShape default_shape(const psm_box_desc* boxes, int nbox, int storage) {
     TileShape ts{64, 4, 1, 0, 0, kDefaultRefZ, 0};
     bool narrow = storage == PSM_FP64;
-    for (int b = 0; b < nbox; ++b) narrow = narrow && 4 * cdiv(boxes[b].nx, 32) <= 6 * cdiv(boxes[b].nx, 64);
+    for (int b = 0; b < nbox; ++b)
+        narrow = narrow && 4 * cdiv(boxes[b].nx, 32) <= 6 * cdiv(boxes[b].nx, 64) && boxes[b].max_particles <= MAXC;
     if (narrow) {
         ts.tx = 32;
         ts.ty = 8;

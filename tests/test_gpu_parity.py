@@ -715,3 +715,20 @@ def test_streamed_loads_keep_the_results(mapping, walls, storage):
         out.append([eng.get_pdfs(0).cpu().numpy(), *eng.get_forces(0)])
         eng.close()
     assert all(np.array_equal(a, b) for a, b in zip(*out))
+
+
+def test_default_launch_lists_a_thin_sheet_of_spheres():
+    """70 spheres in one sheet that meet 8 rows of a narrow FP64 box, at most 56
+    of them any 4: the launch a context starts with lists them all (run_engine
+    reads the forces, which reports a list cut short)."""
+    x, y = np.meshgrid(1.0 + 2.2 * np.arange(14), 7.0 + 2.2 * np.arange(5), indexing="ij")
+    pos = np.stack([x.ravel(), y.ravel(), np.full(x.size, 12.0)], axis=1)
+    spec = inputs.BoxSpec(dims=(32, 32, 24), tau=0.8, x=pos, r=np.ones(70), U=np.zeros((70, 3)), Om=np.zeros((70, 3)),
+                          fext=(1e-5, 0.0, 0.0))
+    _print_case("sheet")
+    ref = run_oracle(spec, 2)
+    f, F, T, B, pid, eng = run_engine(spec, 2)
+    assert eng.get_launch() == (64, 4, 1, 0)
+    assert np.array_equal(pid, ref.pid)
+    assert_pdfs_close(f, ref.f, 1e-12)
+    eng.close()
