@@ -1643,7 +1643,9 @@ __global__ void k_get_pdfs_at(BoxDev bx, int parity, const int* __restrict__ cel
     }
 }
 
-// Density and velocity of one cell from its canonical values, in direction order.
+// Density and velocity of one cell from its canonical values, in direction
+// order. The terms of zero velocity components are added too: they carry a
+// NaN or infinity of any population into every component.
 template <class Value>
 __device__ __forceinline__ void write_fields(const BoxDev& bx, long long n, double* __restrict__ rho,
                                              double* __restrict__ u, Value value) {
@@ -1652,9 +1654,7 @@ __device__ __forceinline__ void write_fields(const BoxDev& bx, long long n, doub
     for (int q = 0; q < NQ; ++q) {
         const double v = value(q);
         r += v;
-        if (CX[q]) j[0] += v * CX[q];
-        if (CY[q]) j[1] += v * CY[q];
-        if (CZ[q]) j[2] += v * CZ[q];
+        j[0] += v * CX[q]; j[1] += v * CY[q]; j[2] += v * CZ[q];
     }
     __builtin_nontemporal_store(r, rho + n);
 #pragma unroll
@@ -1799,13 +1799,7 @@ __global__ __launch_bounds__(256) void k_stats_partial(BoxDev bx, unsigned div0,
             }
             if (S::DEV) v += wq(q);
             m += v;
-            if (WALL) {
-                px += v * CX[d]; py += v * CY[d]; pz += v * CZ[d];
-            } else {
-                if (CX[q]) px += v * CX[q];
-                if (CY[q]) py += v * CY[q];
-                if (CZ[q]) pz += v * CZ[q];
-            }
+            px += v * CX[d]; py += v * CY[d]; pz += v * CZ[d];
         }
     }
     const double v[4] = {m, px, py, pz};
@@ -1858,9 +1852,7 @@ __global__ __launch_bounds__(256) void k_field_stats_partial(const double* __res
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
             m += v[q];
-            if (CX[q]) px += v[q] * CX[q];
-            if (CY[q]) py += v[q] * CY[q];
-            if (CZ[q]) pz += v[q] * CZ[q];
+            px += v[q] * CX[q]; py += v[q] * CY[q]; pz += v[q] * CZ[q];
         }
     }
     const double v[4] = {m, px, py, pz};

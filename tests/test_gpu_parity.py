@@ -10,7 +10,7 @@ import pytest
 import oracle
 import paper_2303_11811_amd as psm
 from paper_2303_11811_amd import inputs
-from psm_cases import (assert_forces_close, assert_pdfs_close, initial_f, make_engine, run_engine,
+from psm_cases import (CX, CY, CZ, assert_forces_close, assert_pdfs_close, initial_f, make_engine, run_engine,
                        run_oracle)
 
 pytestmark = pytest.mark.gpu
@@ -387,6 +387,46 @@ def test_nonfinite_state_is_reported():
     with pytest.raises(psm.PsmError) as e:
         eng.get_stats(0)
     assert e.value.code == psm.PSM_ENONFINITE
+
+
+@pytest.mark.parametrize("storage", [psm.PSM_FP64, psm.PSM_FP32DEV, psm.PSM_FP16DEV])
+@pytest.mark.parametrize("walls", [False, True])
+@pytest.mark.parametrize("q,value", [(0, np.nan), (1, np.inf), (4, np.nan), (6, -np.inf), (12, np.inf)])
+def test_nonfinite_population_reaches_every_component(q, value, walls, storage):
+    """Velocity and momentum are sums over all 19 populations, zero velocity
+    components included: one that is not finite shows in all three, as 0 times
+    it does (NaN), in the fields of its cell, the totals of the context and
+    those of a canonical field."""
+    import ctypes
+
+    import torch
+
+    _print_case("nonfinite", q=q, value=value, walls=walls, storage=storage)
+    spec = inputs.BoxSpec(dims=(21, 9, 6), tau=0.7, fext=(1e-5, 2e-5, -1e-5), walls_z=walls)
+    f = initial_f(spec).copy()
+    cells = [0, 21 * 9 * 3 + 21 * 4 + 20, spec.N - 1]   # in an edge of the box, at its side, in a corner
+    f[q, cells] = value
+    eng = make_engine([spec], storage=storage)
+    eng.set_pdfs(0, f)
+    rho, u = (a.cpu().numpy() for a in eng.get_macroscopic(0))
+    mass, mom = ctypes.c_double(0.0), np.zeros(3)
+    rc = psm.lib().psm_get_stats(eng.ctx, 0, ctypes.byref(mass), psm._dptr(mom), None)
+    totals = torch.empty(4, dtype=torch.float64, device=eng.device)
+    field = torch.as_tensor(f).to(eng.device)
+    torch.cuda.synchronize()
+    psm.psm_field_stats_noalloc(field.data_ptr(), spec.N, totals.data_ptr(), eng.stream.cuda_stream)
+    eng.synchronize()
+    eng.close()
+    with np.errstate(invalid="ignore"):
+        expect = np.array([0.0 * value if a == 0 else a * value for a in (CX[q], CY[q], CZ[q])])
+    bad = np.zeros(spec.N, bool)
+    bad[cells] = True
+    assert np.array_equal(rho[bad], np.full(3, value), equal_nan=True) and np.isfinite(rho[~bad]).all()
+    assert np.array_equal(u[:, bad], np.repeat(expect[:, None], 3, axis=1), equal_nan=True)
+    assert np.isfinite(u[:, ~bad]).all()
+    assert rc == psm.PSM_ENONFINITE
+    assert np.array_equal([mass.value, *mom], [value, *expect], equal_nan=True)
+    assert np.array_equal(totals.cpu().numpy(), [value, *expect], equal_nan=True)
 
 
 @pytest.mark.parametrize("storage", [psm.PSM_FP64, psm.PSM_FP32DEV, psm.PSM_FP16DEV])
