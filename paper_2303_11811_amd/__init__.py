@@ -388,15 +388,17 @@ class Engine:
         """New tensors of the caller's current stream (shapes: (shape, dtype)
         each), filled by ``launch(pointers...)`` on the engine stream: ordered
         after what the caller enqueued before and before what comes after, so
-        the tensors belong to the caller's stream alone."""
+        the tensors belong to the caller's stream alone. The launch runs with
+        the engine's device current."""
         t = self.torch
-        cur = t.cuda.current_stream(self.device)
-        out = [t.empty(shape, dtype=dtype, device=self.device) for shape, dtype in shapes]
-        self._caller_done.record(cur)
-        self.stream.wait_event(self._caller_done)
-        launch(*(o.data_ptr() for o in out))
-        self._engine_done.record(self.stream)
-        cur.wait_event(self._engine_done)
+        with t.cuda.device(self.stream.device):
+            cur = t.cuda.current_stream(self.device)
+            out = [t.empty(shape, dtype=dtype, device=self.device) for shape, dtype in shapes]
+            self._caller_done.record(cur)
+            self.stream.wait_event(self._caller_done)
+            launch(*(o.data_ptr() for o in out))
+            self._engine_done.record(self.stream)
+            cur.wait_event(self._engine_done)
         return out
 
     def _dev(self, a, dtype=None):

@@ -4,6 +4,8 @@ PSM_EINVAL before anything is enqueued."""
 import ctypes
 import os
 import re
+import threading
+import types
 
 import pytest
 
@@ -211,3 +213,59 @@ def test_rows_of_large_grids_start_at_a_line(storage, line):
         tables = ws(64, ny, nz) - grids(64, ny, nz)   # nx 70 has up to twice the tiles of nx 64
         pad = lined - packed if large else 0
         assert pad <= extra <= pad + tables, (nx, ny, nz, large)
+
+
+class _FakeTorch:
+    """Streams, events and the current device of torch, as a log of what each
+    thread did; the caller's stream of a thread is its name."""
+    float64 = "float64"
+
+    def __init__(self):
+        fake = self
+        self.now, self.log = threading.local(), []
+
+        class Event:
+            def record(self, stream):
+                fake.log.append((threading.current_thread().name, "record", stream))
+
+        class device:
+            def __init__(self, index):
+                self.index = index
+
+            def __enter__(self):
+                self.before, fake.now.device = getattr(fake.now, "device", 0), self.index
+
+            def __exit__(self, *exc):
+                fake.now.device = self.before
+
+        class cuda:
+            pass
+        cuda.Event, cuda.device = Event, device
+        cuda.current_stream = staticmethod(lambda dev: fake.Stream(threading.current_thread().name))
+        self.cuda = cuda
+
+    def Stream(self, name, device=0):
+        stream = types.SimpleNamespace(name=name, device=device)
+        stream.wait_event = lambda ev: self.log.append((threading.current_thread().name, "wait", name))
+        return stream
+
+    def empty(self, shape, dtype, device):
+        return types.SimpleNamespace(data_ptr=lambda: 0)
+
+
+def _fake_engine():
+    eng = psm.Engine.__new__(psm.Engine)
+    eng.torch = _FakeTorch()
+    eng.ctx, eng.device, eng.stream = None, "cuda:1", eng.torch.Stream("engine", device=1)
+    eng._caller_done, eng._engine_done = eng.torch.cuda.Event(), eng.torch.cuda.Event()
+    return eng
+
+
+def test_read_outs_launch_with_the_engines_device_current():
+    """An engine on GPU 1 called while GPU 0 is current: the library launches
+    with GPU 1 current, and GPU 0 is current again afterwards."""
+    eng = _fake_engine()
+    eng.torch.now.device = 0
+    seen = []
+    eng._read_out([((4,), "float64")], lambda p: seen.append(eng.torch.now.device))
+    assert seen == [1] and eng.torch.now.device == 0
