@@ -12,6 +12,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import threading
 
 import numpy as np
 
@@ -348,6 +349,7 @@ class Engine:
         # non-legacy stream, and every torch op of this engine runs on it
         self.stream = torch.cuda.Stream(self.device)
         self._caller_done, self._engine_done = torch.cuda.Event(), torch.cuda.Event()
+        self._events = threading.Lock()   # held from a record of the two to its wait
         nbytes = psm_workspace_size(self.descs, self.storage)
         with torch.cuda.stream(self.stream):
             self.workspace = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
@@ -394,11 +396,12 @@ class Engine:
         with t.cuda.device(self.stream.device):
             cur = t.cuda.current_stream(self.device)
             out = [t.empty(shape, dtype=dtype, device=self.device) for shape, dtype in shapes]
-            self._caller_done.record(cur)
-            self.stream.wait_event(self._caller_done)
-            launch(*(o.data_ptr() for o in out))
-            self._engine_done.record(self.stream)
-            cur.wait_event(self._engine_done)
+            with self._events:
+                self._caller_done.record(cur)
+                self.stream.wait_event(self._caller_done)
+                launch(*(o.data_ptr() for o in out))
+                self._engine_done.record(self.stream)
+                cur.wait_event(self._engine_done)
         return out
 
     def _dev(self, a, dtype=None):

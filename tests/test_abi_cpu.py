@@ -258,6 +258,7 @@ def _fake_engine():
     eng.torch = _FakeTorch()
     eng.ctx, eng.device, eng.stream = None, "cuda:1", eng.torch.Stream("engine", device=1)
     eng._caller_done, eng._engine_done = eng.torch.cuda.Event(), eng.torch.cuda.Event()
+    eng._events = threading.Lock()
     return eng
 
 
@@ -269,3 +270,28 @@ def test_read_outs_launch_with_the_engines_device_current():
     seen = []
     eng._read_out([((4,), "float64")], lambda p: seen.append(eng.torch.now.device))
     assert seen == [1] and eng.torch.now.device == 0
+
+
+def test_read_outs_of_two_threads_do_not_mix_their_events():
+    """A second thread's read-out does not record the engine's events between a
+    first one's record and wait (its own thread-local stream would be waited
+    for in place of the first's)."""
+    eng = _fake_engine()
+    inside, second = threading.Event(), threading.Event()
+
+    def first_launch(p):
+        inside.set()
+        second.wait(0.5)   # time for the second thread to get in, if it can
+
+    def other():
+        inside.wait()
+        eng._read_out([((4,), "float64")], lambda p: None)
+        second.set()
+
+    a = threading.Thread(target=lambda: eng._read_out([((4,), "float64")], first_launch), name="a")
+    b = threading.Thread(target=other, name="b")
+    for t in (a, b):
+        t.start()
+    for t in (a, b):
+        t.join()
+    assert [who for who, _, _ in eng.torch.log] == ["a"] * 4 + ["b"] * 4
