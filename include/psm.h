@@ -98,6 +98,9 @@ typedef struct psm_box_desc {
 typedef struct psm_ctx psm_ctx;
 
 /* Bytes of device workspace a context over these boxes needs (host-only call).
+ * Grids beyond 256 MiB (both together) start the rows of boxes wider than 64
+ * cells at 128 bytes, which adds at most 8 GiB and nothing to grids that
+ * exceed 64 GiB with it.
  * boxes: host array of nbox descriptors. bytes: host output. */
 int psm_workspace_size(const psm_box_desc* boxes, int nbox, int storage, size_t* bytes);
 

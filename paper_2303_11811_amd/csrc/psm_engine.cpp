@@ -199,16 +199,23 @@ struct Layout {
 static size_t storage_bytes(int storage) { return storage == PSM_FP64 ? 8 : (storage == PSM_FP32DEV ? 4 : 2); }
 
 // Row pitches: row_pitch() where both grids fit the last-level cache, which the
-// packed rows fill best. Larger grids that it leaves packed start every row at a
-// 128-byte line: the waves of two tiles otherwise write parts of one line, which
-// nontemporal stores take to memory one by one. us per step, packed rows with
-// nontemporal / ordinary stores / rows from a line:
-//   FP64  150^3 241 / 216 / 207   220^3 685 / 659 / 618   200^3 474 / 499 / 465
-//   FP32  150^3 154 / 132 / 115   220^3 509 / 417 / 337   200^3 343 / 304 / 269
-//   FP16  170^3 137 / 112 /  91   220^3 365 / 251 / 199   200^3 266 / 194 / 165
-// (in the cache, FP16 150^3: 63 packed, 73 from a line). Grids beyond 64 GiB
-// keep the packed rows: they may fill the memory.
-constexpr long long kLineMax = 64LL << 30;
+// packed rows fill best. In larger grids the rows of boxes wider than a tile
+// that it leaves packed start at a 128-byte line: the waves of two tiles
+// otherwise write parts of one line, which nontemporal stores take to memory one
+// by one. us per step, packed / from a line, 1 GiB of packed grids, no spheres
+// (packed with ordinary stores, FP16 220^3: 251 beside 365 / 199):
+//   FP64  nx 65 336 / 247   70 308 / 228    90 276 / 229   130 250 / 218   200 206 / 199
+//   FP32  nx 65 411 / 313   70 377 / 288    90 367 / 256   130 341 / 248   200 295 / 224
+//   FP16  nx 65 653 / 455   70 637 / 407    90 586 / 328   130 502 / 311   200 475 / 273
+// One tile covers a narrower row, and its lines are shared by waves that run
+// side by side; padding only adds bytes:
+//   FP64  nx 9 333 / 591   20 198 / 357   33 242 / 302   53 231 / 246
+//   FP32  nx 9 578 / 832   20 309 / 528   33 312 / 432   53 298 / 326
+//   FP16  nx 9 1149 / 1897 20 591 / 840   33 447 / 668   48 338 / 442   53 430 / 389
+// (in the cache, FP16 150^3: 63 packed, 73 from a line). The padding (at most
+// 1.97 times the packed row, nx 65 in FP16) may not fill the memory: it takes 8
+// GiB of a context at most, and none of one whose grids exceed 64 GiB with it.
+constexpr long long kLineMax = 64LL << 30, kLineExtra = 8LL << 30;
 
 static std::vector<int> row_pitches(const psm_box_desc* boxes, int nbox, int storage) {
     const int line = 128 / (int)storage_bytes(storage);
@@ -218,14 +225,15 @@ static std::vector<int> row_pitches(const psm_box_desc* boxes, int nbox, int sto
     for (int b = 0; b < nbox; ++b) {
         const psm_box_desc& d = boxes[b];
         packed[b] = row_pitch(d.nx);
-        lined[b] = cdiv(packed[b], line) * line;
+        lined[b] = d.nx > 64 ? cdiv(packed[b], line) * line : packed[b];
         for (int k = 0; k < 2; ++k)
             bytes[k] += 2LL * d.nz * cdiv((long long)(k ? lined[b] : packed[b]) * d.ny, BLK) * NQ * BLK *
                         (long long)storage_bytes(storage);
         // byte offsets inside a z-plane: the bound of the descriptor checks
         fits = fits && ((long long)lined[b] * d.ny + BLK) * NQ * 8 < (1LL << 31);
     }
-    return fits && bytes[0] > kCachedMax && bytes[1] <= kLineMax ? lined : packed;
+    const bool pays = bytes[0] > kCachedMax && bytes[1] <= kLineMax && bytes[1] - bytes[0] <= kLineExtra;
+    return fits && pays ? lined : packed;
 }
 
 static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }

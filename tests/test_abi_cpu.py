@@ -215,6 +215,30 @@ def test_rows_of_large_grids_start_at_a_line(storage, line):
         assert pad <= extra <= pad + tables, (nx, ny, nz, large)
 
 
+@pytest.mark.parametrize("storage", [0, 1, 2])
+def test_row_padding_of_large_grids_is_bounded(storage):
+    """Rows of one tile or less stay packed, however large the grids and
+    whatever box is beside them, and the padding of a context's rows never
+    takes more than 8 GiB."""
+    size = 8 >> storage
+
+    def ws(*dims):
+        return psm.psm_workspace_size([psm.make_desc(*d, 0.6) for d in dims], storage)
+
+    def grids(pitch, ny, nz):
+        return 2 * nz * -(-(pitch * ny) // 64) * 19 * 64 * size
+
+    for nx in (4, 9, 24, 33, 48, 56, 64):
+        nz = (512 << 20) // (304 >> storage) // (nx * 512) + 1
+        pitch = 64 if nx > 56 else nx
+        tables = 8 * 512 * nz + (1 << 20)   # beside the grids: two counts per tile, one tile per row at most
+        assert ws((nx, 512, nz)) - grids(pitch, 512, nz) <= tables, nx
+        both = ws((nx, 512, nz), (192, 192, 128)) - grids(192, 192, 128)
+        assert both - grids(pitch, 512, nz) <= tables + 8 * 192 * 128 * 12, nx
+    for nx, ny, nz in ((65, 1024, 4096), (65, 2048, 4096), (65, 1024, 1024), (130, 1024, 1024)):
+        assert ws((nx, ny, nz)) - grids(nx, ny, nz) <= (8 << 30) + (1 << 30), (nx, ny, nz)
+
+
 class _FakeTorch:
     """Streams, events and the current device of torch, as a log of what each
     thread did; the caller's stream of a thread is its name."""
