@@ -100,7 +100,10 @@ typedef struct psm_ctx psm_ctx;
 /* Bytes of device workspace a context over these boxes needs (host-only call).
  * Grids beyond 256 MiB (both together) start the rows of boxes wider than 64
  * cells at 128 bytes, which adds at most 8 GiB and nothing to grids that
- * exceed 64 GiB with it.
+ * exceed 64 GiB with it. Beside the grids, each sphere needs 56 bytes per tile
+ * it can touch at the tile shape where these are most, each tile 8; faster
+ * forms of the tile lists and force partials take up to a quarter of that sum
+ * (at least 64 MiB) as long as the whole stays below 64 GiB.
  * boxes: host array of nbox descriptors. bytes: host output. */
 int psm_workspace_size(const psm_box_desc* boxes, int nbox, int storage, size_t* bytes);
 

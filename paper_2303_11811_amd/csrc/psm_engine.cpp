@@ -186,13 +186,13 @@ static int cache_form(long long grid_bytes, int storage) {
 }
 
 struct Layout {
-    size_t off_boxes, off_tbase, off_partbox, off_pt, off_acc, off_fprev, off_prevok, off_tcnt, off_tent,
-        off_partial, off_misc, off_statpart, total;
+    size_t off_boxes, off_tbase, off_partbox, off_pt, off_acc, off_fprev, off_prevok, off_pool, off_misc, off_statpart,
+        total;
     std::vector<size_t> off_grid[2];
     std::vector<int> pitch, pblk;   // per box: row pitch in cells, 64-cell blocks per z-plane
-    int T_max;
+    size_t pool;                 // bytes of the tile lists and force partials, see pool_plan()
     int list_cap;                // spheres a tile's list holds
-    long long cap_max;           // force-partial slots
+    long long cap_max;           // most force-partial slots of a tile shape, one per tile a sphere can touch
     int P_total;
 };
 
@@ -283,14 +283,54 @@ static int validate(const psm_box_desc* boxes, int nbox, int storage) {
     return PSM_OK;
 }
 
+// How the pool holds the lists and partials of a tile shape with T tiles and cap
+// slots (a sphere's slots: one per tile it can touch).
+struct PoolPlan {
+    bool compact;   // lists back to back behind an offset per tile, else list_cap entries per tile
+    int sets;       // 2: a step's partials stay while the next step writes its own
+    int zshift;     // workgroups that share a tile, see z_shift()
+    size_t off_ent, off_part, bytes;
+};
+
+static PoolPlan pool_layout(long long T, long long cap, int list_cap, bool compact, int sets, int zshift) {
+    PoolPlan p{compact, sets, zshift, 0, 0, 0};
+    // counts of both list parities; or counts, offsets and the entries given out
+    p.off_ent = align256(sizeof(int) * (2 * (size_t)T + (compact ? 1 : 0)));
+    p.off_part = p.off_ent + align256(sizeof(int2) * (size_t)(compact ? cap : T * list_cap));
+    p.bytes = p.off_part + sets * align256(48 * ((size_t)cap << zshift));
+    return p;
+}
+
+// The best plan that fits so many bytes. Given up first is the second set (it
+// saves a launch of 4.5 us per step), then the fixed capacity of the lists (three
+// launches per rebuild), last the shared tiles (up to a tenth of a step at sizes
+// where this matters).
+static PoolPlan pool_plan(size_t pool, long long T, long long cap, int list_cap, int zshift) {
+    for (int z = zshift; z >= 0; --z)
+        for (int form = 0; form < 3; ++form) {
+            const PoolPlan p = pool_layout(T, cap, list_cap, form == 2, form == 0 ? 2 : 1, z);
+            if (p.bytes <= pool) return p;
+        }
+    return pool_layout(T, cap, list_cap, true, 1, 0);   // not reached: make_layout reserves this for every shape
+}
+
+// Beyond what every tile shape needs at least (compact lists, one set of
+// partials, unshared tiles), the pool takes the room of the best plan of every
+// shape as long as the whole workspace grows by at most a quarter (or 64 MiB) and
+// not beyond 64 GiB: contexts that fill the memory keep it for their grids.
+constexpr size_t kPoolSlack = (size_t)64 << 20, kPoolMax = (size_t)64 << 30;
+
 static Layout make_layout(const psm_box_desc* boxes, int nbox, int storage) {
     Layout L{};
     size_t s = storage_bytes(storage);
-    int P = 0;
-    for (int b = 0; b < nbox; ++b) P += boxes[b].max_particles;
+    int P = 0, most = 0;
+    for (int b = 0; b < nbox; ++b) {
+        P += boxes[b].max_particles;
+        most = std::max(most, boxes[b].max_particles);
+    }
     L.P_total = P;
-    int Tmax = 0;
-    long long capmax = 0;
+    L.list_cap = std::min(MAXC, (most + 7) / 8 * 8);
+    size_t least = 0, best = 0;
     for (int tx : kTX)
         for (int tz : kTZ) {
             int ty = WG / tx;
@@ -302,16 +342,13 @@ static Layout make_layout(const psm_box_desc* boxes, int nbox, int storage) {
                     cap += (long long)d.max_particles * max_tiles_axis(d.max_radius, tx, d.nx) *
                            max_tiles_axis(d.max_radius, ty, d.ny) * max_tiles_axis(d.max_radius, tz, d.nz);
             }
-            Tmax = (int)std::max<long long>(Tmax, T);
-            // the same slots whatever the storage form
+            L.cap_max = std::max({L.cap_max, cap, 1LL});
+            least = std::max(least, pool_layout(T, cap, L.list_cap, true, 1, 0).bytes);
+            // the same room whatever the storage form
             for (int st : {PSM_FP64, PSM_FP32DEV, PSM_FP16DEV})
-                capmax = std::max(capmax, cap << z_shift(boxes, nbox, st, tx, ty, tz, cap));
+                best = std::max(best, pool_layout(T, cap, L.list_cap, false, 2,
+                                                  z_shift(boxes, nbox, st, tx, ty, tz, cap)).bytes);
         }
-    L.T_max = Tmax;
-    int most = 0;
-    for (int b = 0; b < nbox; ++b) most = std::max(most, boxes[b].max_particles);
-    L.list_cap = std::min(MAXC, (most + 7) / 8 * 8);
-    L.cap_max = std::max<long long>(capmax, 1);
     size_t o = 0;
     auto take = [&](size_t bytes) {
         size_t at = o;
@@ -325,9 +362,6 @@ static Layout make_layout(const psm_box_desc* boxes, int nbox, int storage) {
     L.off_acc = take(sizeof(double) * 6 * std::max(P, 1) + 64);   // + the device error words
     L.off_fprev = take(sizeof(double) * 6 * std::max(P, 1));
     L.off_prevok = take(sizeof(int) * std::max(P, 1));
-    L.off_tcnt = take(sizeof(int) * 2 * (size_t)Tmax);
-    L.off_tent = take(sizeof(int2) * (size_t)Tmax * L.list_cap);
-    L.off_partial = take(sizeof(double) * 12 * (size_t)L.cap_max);
     L.off_misc = take(256);
     L.off_statpart = take(sizeof(double) * 4 * (size_t)stats_blocks() + 64);
     for (int p = 0; p < 2; ++p) L.off_grid[p].resize(nbox);
@@ -339,6 +373,10 @@ static Layout make_layout(const psm_box_desc* boxes, int nbox, int storage) {
         size_t elems = (size_t)boxes[b].nz * pb * NQ * BLK;
         for (int p = 0; p < 2; ++p) L.off_grid[p][b] = take(s * elems);
     }
+    const size_t plain = o + least;
+    const size_t room = std::max(plain, std::min(std::max(plain + plain / 4, plain + kPoolSlack), kPoolMax)) - o;
+    L.pool = std::max(least, std::min(best, room));
+    L.off_pool = take(L.pool);
     L.total = o;
     return L;
 }
@@ -372,12 +410,16 @@ struct psm_ctx {
     int* d_tbase = nullptr;
     int* d_partbox = nullptr;
     Particles P{};
-    // tile lists: counts per list parity (each build fills those of the other
-    // parity and zeroes the ones it replaces), entries
+    // tile lists, placed in the pool for the tile shape: counts per list parity
+    // (each build fills those of the other parity and zeroes the ones it
+    // replaces; compact lists have one array of them), offsets of compact lists
+    // (else null), entries
     int* d_tcnt[2] = {nullptr, nullptr};
+    int* d_toff = nullptr;
     int2* d_tent = nullptr;
     int list_parity = 0;
-    double* d_partial[2] = {nullptr, nullptr};   // force partials, by the grid parity of the step that writes them
+    double* d_partial[2] = {nullptr, nullptr};   // force partials, by the grid parity of the step that writes
+                                                 // them (one set: the same)
     int* d_misc = nullptr;               // [8..9] dropped (u64),
                                          // [32..39] tile counters of the persistent grid
     int* d_flags = nullptr;              // device error words (FLAG_* bits, list overflows), right after the force sums
@@ -463,7 +505,7 @@ static void assign_tiles(psm_ctx* c) {
     }
     c->T_total = base;
     // force-partial slots: per sphere, one per tile its bounding box can
-    // touch at this tile shape (at most the capacity the layout reserves)
+    // touch at this tile shape
     long long pbase = 0;
     for (int b = 0; b < c->nbox; ++b) {
         const psm_box_desc& d = c->desc[b];
@@ -473,7 +515,16 @@ static void assign_tiles(psm_ctx* c) {
         bx.pbase = (int)pbase;
         pbase += (long long)d.max_particles * bx.pstride;
     }
-    c->ts.zshift = z_shift(c->desc.data(), c->nbox, c->storage, c->ts.tx, c->ts.ty, c->ts.tz, pbase);
+    const PoolPlan plan = pool_plan(c->L.pool, base, pbase, c->L.list_cap,
+                                    z_shift(c->desc.data(), c->nbox, c->storage, c->ts.tx, c->ts.ty, c->ts.tz, pbase));
+    c->ts.zshift = plan.zshift;
+    char* pool = c->ws + c->L.off_pool;
+    c->d_tcnt[0] = (int*)pool;
+    c->d_tcnt[1] = plan.compact ? c->d_tcnt[0] : c->d_tcnt[0] + base;
+    c->d_toff = plan.compact ? c->d_tcnt[0] + base : nullptr;
+    c->d_tent = (int2*)(pool + plan.off_ent);
+    c->d_partial[0] = (double*)(pool + plan.off_part);
+    c->d_partial[1] = (double*)(pool + plan.off_part + (plan.sets - 1) * align256(48 * ((size_t)pbase << plan.zshift)));
     int dev = 0, ncu = 256;
     (void)hipGetDevice(&dev);
     (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
@@ -499,9 +550,11 @@ static SphereParams sphere_params(psm_ctx* c) {
     const int next = c->list_parity ^ 1;
     sp.cnt = c->d_tcnt[next];
     sp.cnt_old = c->d_tcnt[c->list_parity];
+    sp.off = c->d_toff;
+    sp.count_only = 0;
     sp.ent = c->d_tent;
     sp.list_cap = c->L.list_cap;
-    sp.T_total = c->T_total;
+    sp.T_total = c->d_toff ? 0 : c->T_total;
     sp.over = c->d_flags + 1 + next;
     sp.over_old = c->d_flags + 1 + c->list_parity;
     sp.host_acc = nullptr;
@@ -509,17 +562,33 @@ static SphereParams sphere_params(psm_ctx* c) {
     return sp;
 }
 
+// New lists of the spheres (launch_spheres with lists, or an upload with them),
+// which become the current ones. Compact lists take three launches more: the
+// counts are cleared, taken, turned into offsets, and the entries filled in.
+static int enqueue_lists(psm_ctx* c, bool reduce, int scheme, SphereParams sp, const UploadParams* up = nullptr) {
+    if (c->P_total == 0) return PSM_OK;
+    if (c->d_toff) {
+        HIP_TRY(launch_fill_int(c->d_tcnt[0], 2LL * c->T_total + 1, 0, c->stream));
+        sp.count_only = 1;
+    }
+    HIP_TRY(up ? launch_upload_bin(sp, *up, c->stream) : launch_spheres(reduce, scheme, true, sp, c->stream));
+    if (c->d_toff) {
+        HIP_TRY(launch_list_offsets(c->d_tcnt[0], c->d_toff, c->T_total, c->L.list_cap, c->stream));
+        sp.count_only = 0;
+        HIP_TRY(launch_spheres(false, SCHEME_NONE, true, sp, c->stream));
+    }
+    c->list_parity ^= 1;
+    return PSM_OK;
+}
+
 // Rebuild the lists without waiting for the device: a tile with more spheres
 // than a list holds raises the overflow word of these lists (that of the
 // lists before is cleared); synchronising calls report it. The step kernel
 // stays in bounds on the cut lists.
 static int rebuild_lists_async(psm_ctx* c) {
-    if (c->P_total > 0) {
-        HIP_TRY(launch_spheres(false, SCHEME_NONE, true, sphere_params(c), c->stream));
-        c->list_parity ^= 1;
-    }
-    c->have_particles_lists = true;
-    return PSM_OK;
+    int rc = enqueue_lists(c, false, SCHEME_NONE, sphere_params(c));
+    if (rc == PSM_OK) c->have_particles_lists = true;
+    return rc;
 }
 
 // Rebuild the per-tile candidate lists of all boxes at a new tile shape
@@ -527,8 +596,9 @@ static int rebuild_lists_async(psm_ctx* c) {
 static int rebuild_lists(psm_ctx* c) {
     // the step kernel must never run on half-built lists
     c->have_particles_lists = false;
-    // the tile count may have changed: both sets of counts start from zero
-    for (int l = 0; l < 2; ++l) HIP_TRY(launch_fill_int(c->d_tcnt[l], c->T_total, 0, c->stream));
+    // the tile count may have changed: both sets of counts start from zero (or
+    // the counts and offsets of compact lists, with the entries given out)
+    HIP_TRY(launch_fill_int(c->d_tcnt[0], 2LL * c->T_total + (c->d_toff ? 1 : 0), 0, c->stream));
     int rc = rebuild_lists_async(c);
     c->have_particles_lists = false;
     if (rc) return rc;
@@ -726,11 +796,6 @@ extern "C" int psm_create(const psm_box_desc* boxes, int nbox, int storage, doub
     c->P.acc = (double*)(c->ws + L.off_acc);
     c->P.fprev = (double*)(c->ws + L.off_fprev);
     c->P.prev_ok = (int*)(c->ws + L.off_prevok);
-    c->d_tcnt[0] = (int*)(c->ws + L.off_tcnt);
-    c->d_tcnt[1] = c->d_tcnt[0] + L.T_max;
-    c->d_tent = (int2*)(c->ws + L.off_tent);
-    c->d_partial[0] = (double*)(c->ws + L.off_partial);
-    c->d_partial[1] = c->d_partial[0] + 6 * L.cap_max;
     c->d_misc = (int*)(c->ws + L.off_misc);
     c->d_flags = (int*)(c->P.acc + 6 * P1);
     c->d_statpart = (double*)(c->ws + L.off_statpart);
@@ -897,8 +962,8 @@ constexpr int kFusedUpload = 256;
 static int send_columns(psm_ctx* c, const UploadParams& up, int h, bool new_lists) {
     const bool fused = new_lists && up.m > 0 && up.n <= kFusedUpload;
     if (fused) {
-        HIP_TRY(launch_upload_bin(sphere_params(c), up, c->stream));
-        c->list_parity ^= 1;
+        int rc = enqueue_lists(c, false, SCHEME_NONE, sphere_params(c), &up);
+        if (rc) return rc;
         c->have_particles_lists = true;
     } else {
         HIP_TRY(launch_upload(up, c->stream));
@@ -1055,7 +1120,7 @@ static int step_params(psm_ctx* c, int parity, StepParams& kp) {
     kp.P = c->P;
     kp.tile_cnt = c->d_tcnt[c->list_parity];
     kp.tile_ent = c->d_tent;
-    kp.list_cap = c->L.list_cap;
+    kp.list_cap = c->d_toff ? -c->L.list_cap : c->L.list_cap;
     kp.partial = c->d_partial[parity];
     kp.partial_prev = nullptr;
     kp.part_box = c->d_partbox;
@@ -1143,20 +1208,21 @@ static int enqueue_step(psm_ctx* c, bool timed, const AfterStep& after) {
     SphereParams sp = sphere_params(c);
     sp.dt = after.dt;
     if (after.readback) sp.host_acc = c->h_rb;
-    const bool lists = after.scheme != SCHEME_NONE;
-    HIP_TRY(launch_spheres(true, after.scheme, lists, sp, c->stream));
-    if (lists && c->P_total > 0) c->list_parity ^= 1;
+    if (after.scheme != SCHEME_NONE) return enqueue_lists(c, true, after.scheme, sp);
+    HIP_TRY(launch_spheres(true, SCHEME_NONE, false, sp, c->stream));
     return PSM_OK;
 }
 
 // n steps of fixed spheres: the forces of each are reduced in the launch of
-// the next, those of the last in a launch of their own.
+// the next where its partials stay until then, those of the last in a launch of
+// their own.
 static int enqueue_steps(psm_ctx* c, int n, bool timed, bool readback) {
+    const bool ride = c->d_partial[0] != c->d_partial[1];
     for (int s = 0; s < n; ++s) {
         AfterStep after;
-        after.prev = s > 0;
-        after.reduce = s == n - 1;
-        after.readback = readback && after.reduce;
+        after.prev = ride && s > 0;
+        after.reduce = !ride || s == n - 1;
+        after.readback = readback && s == n - 1;
         int rc = enqueue_step(c, timed, after);
         if (rc) return rc;
     }
@@ -1275,8 +1341,8 @@ extern "C" int psm_get_solid_fraction(psm_ctx* c, int box, double* B, int* pid) 
     if (rc) return rc;
     if (!B || !pid) return fail(PSM_EINVAL, "B/pid is NULL");
     unsigned long long* dropped = (unsigned long long*)(c->d_misc + 8);   // not read here
-    HIP_TRY(launch_map_dense(c->box[box], c->P, c->d_tcnt[c->list_parity], c->d_tent, c->L.list_cap, c->ts, B, pid,
-                             dropped, c->stream));
+    HIP_TRY(launch_map_dense(c->box[box], c->P, c->d_tcnt[c->list_parity], c->d_toff, c->d_tent, c->L.list_cap, c->ts, B,
+                             pid, dropped, c->stream));
     return PSM_OK;
 }
 
@@ -1289,8 +1355,8 @@ extern "C" int psm_get_stats(psm_ctx* c, int box, double* mass, double* momentum
     HIP_TRY(launch_stats(c->storage, c->box[box], c->parity, c->h_inv, c->d_statpart, out, c->stream));
     HIP_TRY(launch_fill_int((int*)dropped, 2, 0, c->stream));
     if (c->np[box] >= 3)
-        HIP_TRY(launch_map_dense(c->box[box], c->P, c->d_tcnt[c->list_parity], c->d_tent, c->L.list_cap, c->ts, nullptr,
-                                 nullptr, dropped, c->stream));
+        HIP_TRY(launch_map_dense(c->box[box], c->P, c->d_tcnt[c->list_parity], c->d_toff, c->d_tent, c->L.list_cap, c->ts,
+                                 nullptr, nullptr, dropped, c->stream));
     double* st = c->h_read;
     DownloadParams dp{};
     dp.src[0] = out;
@@ -1369,9 +1435,7 @@ extern "C" int psm_set_dynamics(psm_ctx* c, int box, double density_ratio, const
 static int enqueue_integrate(psm_ctx* c, double dt, int scheme) {
     SphereParams sp = sphere_params(c);
     sp.dt = dt;
-    HIP_TRY(launch_spheres(false, scheme, true, sp, c->stream));
-    if (c->P_total > 0) c->list_parity ^= 1;
-    return PSM_OK;
+    return enqueue_lists(c, false, scheme, sp);
 }
 
 static int check_dynamics_args(psm_ctx* c, double dt, int scheme) {

@@ -302,9 +302,9 @@ struct StepParams {
     const int* box_tile_base;   // [nbox+1]
     int nbox;
     Particles P;
-    const int* tile_cnt;        // [T] spheres of each tile's list (uncapped)
-    const int2* tile_ent;       // [T][list_cap] global particle id and force-partial slot
-    int list_cap;
+    const int* tile_cnt;        // [T] spheres of each tile's list (uncapped); compact lists: then [T] their first entries
+    const int2* tile_ent;       // global particle id and force-partial slot
+    int list_cap;               // entries per list; compact lists: minus the most that one holds
     double* partial;            // [slots << zshift][6]
     // force reduction of the step before (its partials; null: none) by the
     // workgroups from `grid` on, 4 spheres each
@@ -338,9 +338,11 @@ struct SphereParams {
     // tile lists: the counts filled here are zero on entry; those of the
     // lists they replace are zeroed for the next build
     int *cnt, *cnt_old;         // [T]
-    int2* ent;                  // [T][list_cap]
+    const int* off;             // [T] first entry of each list (compact lists; null: list_cap entries each)
+    int count_only;             // count the lists' spheres only (compact lists, before their offsets)
+    int2* ent;
     int list_cap;
-    int T_total;
+    int T_total;                // counts to zero (compact lists: none)
     int *over, *over_old;       // largest uncapped count where it exceeds MAXC, else 0
     // force read-back: pinned host copy of P.acc and the error words behind
     // it (null: none)
@@ -387,6 +389,7 @@ hipError_t launch_step(int storage, const StepForm& form, const StepParams& kp, 
 hipError_t launch_pattern_copy(int storage, bool shifted, const StepParams& kp, hipStream_t st);
 int step_blocks_per_cu(int storage, const StepForm& form);
 hipError_t launch_spheres(bool reduce, int scheme, bool bin, const SphereParams& sp, hipStream_t st);
+hipError_t launch_list_offsets(int* cnt, int* off, int T, int list_cap, hipStream_t st);
 hipError_t launch_upload_bin(const SphereParams& sp, const UploadParams& up, hipStream_t st);
 hipError_t launch_upload(const UploadParams& up, hipStream_t st);
 hipError_t launch_download(const DownloadParams& dp, hipStream_t st);
@@ -398,8 +401,9 @@ hipError_t launch_get_pdfs_at(int storage, const BoxDev& bx, int parity, const i
                               float inv, int* flags, hipStream_t st);
 hipError_t launch_macroscopic(int storage, const BoxDev& bx, int parity, double* rho, double* u, float inv,
                               hipStream_t st);
-hipError_t launch_map_dense(const BoxDev& bx, const Particles& P, const int* tile_cnt, const int2* tile_ent,
-                            int list_cap, TileShape ts, double* B, int* pid, unsigned long long* dropped, hipStream_t st);
+hipError_t launch_map_dense(const BoxDev& bx, const Particles& P, const int* tile_cnt, const int* tile_off,
+                            const int2* tile_ent, int list_cap, TileShape ts, double* B, int* pid,
+                            unsigned long long* dropped, hipStream_t st);
 int stats_blocks();
 hipError_t launch_stats(int storage, const BoxDev& bx, int parity, float inv, double* part, double* out,
                         hipStream_t st);

@@ -539,9 +539,10 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
         const int tcz = udiv(lr, bx.div_nty[0], bx.div_nty[1]);
         const int tcy = lr - tcz * nty;
         const int tile = bx.tile_base + tcx + ntx * (tcy + nty * (tcz >> zs));
-        const int listed = cptr(ka->tile_cnt)[tile], cap = ka->list_cap;
+        const int listed = cptr(ka->tile_cnt)[tile], lcap = ka->list_cap, cap = lcap < 0 ? -lcap : lcap;
         const int nc = listed < cap ? listed : cap;   // at most MAXC
-        const int2* ent = ka->tile_ent + (long long)tile * cap;
+        const int2* ent = ka->tile_ent + (lcap < 0 ? (long long)cptr(ka->tile_cnt)[(ka->T_total >> zs) + tile]
+                                                   : (long long)tile * cap);
         const double Lx = bx.L[0], Ly = bx.L[1], Lz = bx.L[2];
         const double hLx = bx.halfL[0], hLy = bx.halfL[1], hLz = bx.halfL[2];
         const int RZ = ka->ref_z, zb = tcz * TZ & ~(RZ - 1);
@@ -1144,8 +1145,9 @@ __global__ __launch_bounds__(256) void k_spheres(SphereParams sp, UploadParams u
             const int kx = k % nxt, ky = (k / nxt) % nyt, kz = k / (nxt * nyt);
             const int t = bx.tile_base + ax.at(kx) + bx.ntx * (ay.at(ky) + bx.nty * az.at(kz));
             const int at = atomicAdd(&sp.cnt[t], 1);
+            if (sp.count_only) continue;
             if (at < sp.list_cap) {
-                sp.ent[(long long)t * sp.list_cap + at] = make_int2(p, (int)(slot0 + k));
+                sp.ent[(sp.off ? (long long)sp.off[t] : (long long)t * sp.list_cap) + at] = make_int2(p, (int)(slot0 + k));
             } else {
                 // a list holds at most MAXC spheres: the excess is dropped and reported
                 atomicMax(sp.over, at + 1);
@@ -1155,6 +1157,26 @@ __global__ __launch_bounds__(256) void k_spheres(SphereParams sp, UploadParams u
                 }
             }
         }
+    }
+}
+
+// Compact lists: the first entry of each tile's list from the counts, which
+// start again from zero for the fill; off[T], zero on entry, counts the entries
+// given out. Which run of entries a tile gets does not matter.
+__global__ __launch_bounds__(256) void k_list_offsets(int* cnt, int* off, int T, int list_cap) {
+    const int t = blockIdx.x * 256 + threadIdx.x, lane = threadIdx.x & 63;
+    const int n = t < T ? min(cnt[t], list_cap) : 0;
+    int sum = n;   // of the lanes up to this one
+    for (int d = 1; d < 64; d <<= 1) {
+        const int below = __shfl_up(sum, d, 64);
+        sum += lane >= d ? below : 0;
+    }
+    int base = 0;
+    if (lane == 63 && sum > 0) base = atomicAdd(off + T, sum);
+    base = __shfl(base, 63, 64);
+    if (t < T) {
+        off[t] = base + sum - n;
+        cnt[t] = 0;
     }
 }
 
@@ -1690,6 +1712,7 @@ __global__ void k_macroscopic_wall(BoxDev bx, int parity, double* __restrict__ r
 // spheres staged in LDS (256^3: 146 -> 92 us at 24 B per cell). Fewer than
 // three spheres cannot overflow a cell.
 __global__ __launch_bounds__(WG) void k_map_dense(BoxDev bx, Particles P, const int* __restrict__ tile_cnt,
+                                                  const int* __restrict__ tile_off,
                                                   const int2* __restrict__ tile_ent, int list_cap, TileShape ts,
                                                   double* __restrict__ B, int* __restrict__ pid,
                                                   unsigned long long* dropped) {
@@ -1700,7 +1723,7 @@ __global__ __launch_bounds__(WG) void k_map_dense(BoxDev bx, Particles P, const 
     if (!B && nc < 3) return;
     const int tid = threadIdx.x;
     if (tid < nc) {
-        const int p = tile_ent[(long long)t * list_cap + tid].x;
+        const int p = tile_ent[(tile_off ? (long long)tile_off[t] : (long long)t * list_cap) + tid].x;
         s_p[tid] = p;
         s_x[tid] = P.x[p]; s_y[tid] = P.y[p]; s_z[tid] = P.z[p];
         s_r[tid] = P.r[p]; s_fr[tid] = P.fr[p];
@@ -2043,6 +2066,11 @@ hipError_t launch_spheres(bool reduce, int scheme, bool bin, const SphereParams&
     }
 }
 
+hipError_t launch_list_offsets(int* cnt, int* off, int T, int list_cap, hipStream_t st) {
+    hipLaunchKernelGGL(k_list_offsets, dim3(blocks_for(T, 256)), dim3(256), 0, st, cnt, off, T, list_cap);
+    return hipGetLastError();
+}
+
 hipError_t launch_upload_bin(const SphereParams& sp, const UploadParams& up, hipStream_t st) {
     return launch_spheres_of<false, SCHEME_NONE, true, true>(sp, st, up);
 }
@@ -2125,10 +2153,11 @@ hipError_t launch_macroscopic(int storage, const BoxDev& bx, int parity, double*
     return hipGetLastError();
 }
 
-hipError_t launch_map_dense(const BoxDev& bx, const Particles& P, const int* tile_cnt, const int2* tile_ent,
-                            int list_cap, TileShape ts, double* B, int* pid, unsigned long long* dropped, hipStream_t st) {
-    hipLaunchKernelGGL(k_map_dense, dim3(bx.ntx * bx.nty * bx.ntz), dim3(WG), 0, st, bx, P, tile_cnt, tile_ent,
-                       list_cap, ts, B, pid, dropped);
+hipError_t launch_map_dense(const BoxDev& bx, const Particles& P, const int* tile_cnt, const int* tile_off,
+                            const int2* tile_ent, int list_cap, TileShape ts, double* B, int* pid,
+                            unsigned long long* dropped, hipStream_t st) {
+    hipLaunchKernelGGL(k_map_dense, dim3(bx.ntx * bx.nty * bx.ntz), dim3(WG), 0, st, bx, P, tile_cnt, tile_off,
+                       tile_ent, list_cap, ts, B, pid, dropped);
     return hipGetLastError();
 }
 

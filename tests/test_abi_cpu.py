@@ -239,6 +239,35 @@ def test_row_padding_of_large_grids_is_bounded(storage):
         assert ws((nx, ny, nz)) - grids(nx, ny, nz) <= (8 << 30) + (1 << 30), (nx, ny, nz)
 
 
+def _plain_workspace(nx, ny, nz, n, rmax, size):
+    """Bytes of the packed grids and of what every tile shape needs at least: 8
+    per tile, and per slot (a tile a sphere can touch) a list entry and six
+    sums; with 256 per sphere for the tables and 1 MiB for the rest."""
+    tiles = slots = 0
+    for tx in (16, 32, 64, 128, 256):
+        for tz in (1, 2, 4, 8, 16, 32):
+            T, reach = 1, n
+            for L, t in ((nx, tx), (ny, 256 // tx), (nz, tz)):
+                nt = -(-L // t)
+                T *= nt
+                reach *= min(nt, 2 + -(-max(int(2 * (rmax + 1)) + 2 - (L - (nt - 1) * t), 0) // t))
+            tiles, slots = max(tiles, T), max(slots, reach)
+    return 2 * nz * -(-(nx * ny) // 64) * 19 * 64 * size + 8 * tiles + 56 * slots + 256 * n + (1 << 20)
+
+
+@pytest.mark.parametrize("storage,dims,n,rmax", [
+    (0, (960, 960, 960), 885000, 4.0), (0, (960, 960, 960), 100, 4.0), (2, (1024, 1000, 1000), 1000000, 4.0),
+    (2, (1024, 1024, 900), 40, 4.0), (2, (256, 256, 256), 1000000, 1.0), (1, (512, 512, 512), 2347, 10.0),
+    (0, (64, 64, 64), 200000, 1.0), (1, (32, 32, 32), 8, 4.0), (2, (64, 64, 64), 0, 1.0)])
+def test_lists_and_partials_leave_the_memory_to_the_grids(storage, dims, n, rmax):
+    """Room for lists of a fixed capacity, a second set of force partials and
+    shared tiles is at most a quarter of the plain workspace or 64 MiB, and
+    nothing beyond 64 GiB (boxes of whole 64-cell blocks, so rows are packed)."""
+    plain = _plain_workspace(*dims, n, rmax, 8 >> storage)
+    got = psm.psm_workspace_size([psm.make_desc(*dims, 0.6, max_particles=n, max_radius=rmax)], storage)
+    assert got <= max(plain, min(max(plain + plain // 4, plain + (64 << 20)), 64 << 30))
+
+
 class _FakeTorch:
     """Streams, events and the current device of torch, as a log of what each
     thread did; the caller's stream of a thread is its name."""

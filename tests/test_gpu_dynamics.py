@@ -334,3 +334,84 @@ def test_lists_after_launch_changes_between_updates(nspheres):
         f.append(eng.get_pdfs(0).cpu().numpy())
         eng.close()
     assert np.array_equal(f[0], f[1])
+
+
+def _motions(eng, x, r, U, cells, rng):
+    """Steps, uploads and device updates of spheres far from the edges of the
+    box: everything the force reduction and the tile lists give."""
+    out = []
+    eng.set_particles(0, x, r, U, np.zeros_like(U))
+    eng.step(3)
+    out += [*eng.get_forces(0), eng.get_pdfs_at(0, cells).cpu().numpy()]
+    eng.set_particle_positions(0, x + rng.uniform(-1.0, 1.0, x.shape))
+    eng.set_force_readback(True)
+    eng.step(2)
+    out += [*eng.get_forces(0)]
+    eng.set_force_readback(False)
+    eng.set_graph(True)
+    eng.run(10, 1.0, psm.PSM_VERLET)
+    eng.set_graph(False)
+    eng.run(1, 1.0, psm.PSM_EULER)
+    eng.integrate(1.0, psm.PSM_EULER)
+    eng.step(1)
+    return out + [*eng.get_forces(0), *eng.get_particles(0), eng.get_pdfs_at(0, cells).cpu().numpy(),
+                  np.array(eng.get_stats(0)[2])]
+
+
+def _cloud(n, lo, hi, r, seed):
+    rng = np.random.default_rng(seed)
+    x = rng.uniform(lo, hi, (n, 3))
+    return x, np.full(n, r), inputs.uniform_velocities(rng, n, 0.01)
+
+
+@pytest.mark.parametrize("storage", [psm.PSM_FP64, psm.PSM_FP16DEV])
+@pytest.mark.parametrize("launch", [(64, 4, 8, 0), (256, 1, 1, 0), (16, 16, 16, psm.PSM_LAUNCH_PERSISTENT)])
+def test_one_set_of_partials_keeps_the_results(launch, storage):
+    """A context with room for so many spheres that its partials have one set
+    (its workspace is too small for two) gives bit for bit what one with room
+    for the spheres gives."""
+    print(f"[case] one set of partials {launch} storage={storage}", flush=True)
+    x, r, U = _cloud(40, 20.0, 44.0, 1.5, 5)
+    cells = np.random.default_rng(6).integers(0, 64 ** 3, 500)
+    got = []
+    for room in (40, 200000):
+        eng = psm.Engine([psm.make_desc(64, 64, 64, 0.7, max_particles=room, max_radius=1.5)], storage=storage)
+        eng.set_launch(*launch)
+        eng.set_equilibrium(0, np.zeros((3, 64 ** 3)))
+        got.append(_motions(eng, x, r, U, cells, np.random.default_rng(7)))
+        eng.close()
+    assert all(np.array_equal(a, b) for a, b in zip(*got))
+
+
+@pytest.mark.parametrize("n", [40, 300])
+def test_compact_lists_of_a_huge_context_keep_the_results(n):
+    """A context beyond 64 GiB lists its spheres back to back (its workspace
+    has no room for lists of a fixed capacity): forces, motion, PDFs and the
+    count of dropped overlaps are bit for bit those of a 96^3 box, whose edges
+    the motion does not reach, and a crowded tile is reported."""
+    print(f"[case] compact lists n={n}", flush=True)
+    import torch
+
+    x, r, U = _cloud(n, 32.0, 64.0, 1.0, 8)
+    at = np.random.default_rng(9).integers(0, 96, (500, 3))
+    got = []
+    for d in ((96, 96, 96), (1024, 1024, 900)):
+        N = int(np.prod(d))
+        desc = psm.make_desc(*d, 0.7, max_particles=n, max_radius=1.0)
+        if N > 96 ** 3:
+            fixed = 76 * N + 8 * (N // 256) * min(64, n)
+            assert psm.psm_workspace_size([desc], psm.PSM_FP16DEV) < fixed
+        eng = psm.Engine([desc], storage=psm.PSM_FP16DEV)
+        eng.set_launch(64, 4, 1, 0)
+        u = torch.zeros((3, N), dtype=torch.float64, device=eng.device)
+        eng.set_equilibrium(0, u)
+        del u
+        got.append(_motions(eng, x, r, U, at @ [1, d[0], d[0] * d[1]], np.random.default_rng(10)))
+        if n > 64:
+            eng.set_particles(0, x * 0.0 + 40.0, r, U)
+            with pytest.raises(psm.PsmError) as e:
+                eng.get_forces(0)
+            assert e.value.code == psm.PSM_ECAPACITY
+        eng.close()
+    torch.cuda.empty_cache()
+    assert all(np.array_equal(a, b) for a, b in zip(*got))
