@@ -150,7 +150,8 @@ int psm_get_macroscopic(psm_ctx* ctx, int box, double* rho, double* u);
  * per-tile candidate lists on the device. Nothing waits for the device: if
  * a tile would list more candidates than the kernel stages, its list is cut
  * (the steps stay in bounds, their results are not valid) and the next
- * synchronising call returns PSM_ECAPACITY, after which the context refuses
+ * synchronising call returns PSM_ECAPACITY (also if later positions have
+ * replaced lists that a step has run on), after which the context refuses
  * to step until a valid set is given. PSM_ECAPACITY at once if
  * n > max_particles. */
 int psm_set_particles(psm_ctx* ctx, int box, int n, const double* x, const double* r,

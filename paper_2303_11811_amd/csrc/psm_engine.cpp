@@ -616,7 +616,8 @@ static int rebuild_lists(psm_ctx* c) {
 
 // Every synchronising call brings the device error words to the host with what
 // it reads (fetch_and_sync) and reports them afterwards (take_flags), which clears the
-// words on the device. A list overflow (device-built lists) or, in strict-slot
+// words on the device. A list overflow (of the current lists or of any that a
+// step has run on since the last such call) or, in strict-slot
 // mode, a third overlap makes the context refuse to step until
 // psm_set_particles; a bad psm_get_pdfs_at index is an argument error.
 static int fetch_and_sync(psm_ctx* c, DownloadParams dp = DownloadParams{}) {
@@ -630,7 +631,8 @@ static int fetch_and_sync(psm_ctx* c, DownloadParams dp = DownloadParams{}) {
 
 static int take_flags(psm_ctx* c) {
     const int f = c->h_flags[0];
-    const bool list_tile = c->h_flags[1] != 0 || c->h_flags[2] != 0;   // only the current lists' word is ever set
+    // lists a step has used, or the current ones (only their word is ever set)
+    const bool list_tile = (f & FLAG_LIST_CUT) || c->h_flags[1] != 0 || c->h_flags[2] != 0;
     if (f == 0 && !list_tile) return PSM_OK;
     std::fill(c->h_flags, c->h_flags + ERR_WORDS, 0);
     HIP_TRY(launch_fill_int(c->d_flags, ERR_WORDS, 0, c->stream));

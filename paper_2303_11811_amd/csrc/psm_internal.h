@@ -318,7 +318,8 @@ struct StepParams {
     int ref_z;                  // TileShape::ref_z
     int parity;
     float h_scale, h_inv;       // FP16 storage scale and its inverse (1 otherwise)
-    int* flags;                 // device error word: |= FLAG_SLOT_OVERFLOW when a cell meets a third sphere
+    int* flags;                 // device error word: |= FLAG_SLOT_OVERFLOW when a cell meets a third sphere,
+                                // FLAG_LIST_CUT when a tile's list was cut
     int* queue;                 // [NXCD] tile counters of the persistent grid (zeroed before the launch), or null
 };
 
@@ -411,11 +412,13 @@ hipError_t launch_stream_copy(const void* src, void* dst, size_t bytes, hipStrea
 // Bits of the device error word of a context, set by kernels and read and
 // cleared by the host at its next synchronising call.
 enum {
+    FLAG_LIST_CUT = 2,        // a step ran on a tile list that holds fewer spheres than reach the tile
     FLAG_SLOT_OVERFLOW = 4,   // a step met a cell overlapped by more than two spheres
     FLAG_BAD_CELL = 8         // psm_get_pdfs_at was given a cell index outside the box
 };
 // Two words follow the error word, one per list parity: the largest uncapped
-// count of the lists of that parity where a tile lists more than MAXC spheres.
+// count of the lists of that parity where a tile lists more than MAXC spheres
+// (lists that no step has used may still be replaced without harm).
 constexpr int ERR_WORDS = 3;
 hipError_t launch_fill_int(int* a, long long n, int v, hipStream_t st);
 // FP64 mass and momentum of a canonical field [19][N] into out[4] (device),

@@ -576,6 +576,9 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
                 }
             }
             for (int i = tid; i < NWAVE * 6 * MAXC; i += WG) (&s_acc[0][0][0])[i] = 0.0;
+            // a list cut short: the results are not valid from here on, whatever
+            // the lists of later steps hold
+            if (listed > cap && tid == 0) atomicOr(step_args()->flags, FLAG_LIST_CUT);
         }
         __syncthreads();
 

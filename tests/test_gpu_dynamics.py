@@ -135,6 +135,53 @@ def test_force_readback_follows_graph_replays():
     assert not np.array_equal(out[1][0][0], out[1][1][0])
 
 
+@pytest.mark.parametrize("how", ["run", "graph", "upload", "readback", "unused"])
+def test_tile_overflow_that_passes_is_reported(how):
+    """Seventy unit spheres that meet at one point for one step and part again
+    before the host looks: the step ran on a cut list, so the next synchronising
+    call reports PSM_ECAPACITY although the lists hold every sphere by then.
+    Lists that were replaced before any step ran on them are not reported."""
+    print(f"[case] passing overflow {how}", flush=True)
+    n = 48
+    g = np.array([(i, j, k) for i in range(5) for j in range(5) for k in range(3)], dtype=float)[:70]
+    x0 = 4.0 + g * np.array([9.0, 9.0, 14.0])
+    r = np.full(70, 1.0)
+    centre = np.array([24.3, 24.7, 24.1])
+    dt = 1000.0
+    U = (centre - x0) / dt               # one Euler update to the centre, the next away from it
+    eng = psm.Engine([psm.make_desc(n, n, n, 0.7, max_particles=70, max_radius=1.0)])
+    eng.set_launch(32, 8, 4, 0)
+    eng.set_dynamics(0, 1e12)            # the fluid does not turn the spheres
+    eng.set_equilibrium(0, np.zeros((3, n ** 3)))
+    eng.set_particles(0, x0, r, U)
+    if how in ("run", "graph"):
+        eng.set_graph(how == "graph")
+        eng.run(2 if how == "run" else 10, dt, psm.PSM_EULER)
+    else:
+        eng.set_force_readback(how == "readback")
+        eng.step(1)
+        eng.set_particle_positions(0, np.tile(centre, (70, 1)))
+        if how != "unused":
+            eng.step(1)
+        eng.set_particle_positions(0, x0)
+        eng.step(1)
+    if how == "unused":
+        F, _ = eng.get_forces(0)
+        assert np.all(np.isfinite(F))
+    else:
+        with pytest.raises(psm.PsmError) as ei:
+            eng.get_forces(0)
+        assert ei.value.code == psm.PSM_ECAPACITY
+        with pytest.raises(psm.PsmError) as ei:
+            eng.step(1)
+        assert ei.value.code == psm.PSM_ESTATE
+        eng.set_particles(0, x0, r, U)
+        eng.set_equilibrium(0, np.zeros((3, n ** 3)))
+        eng.step(1)
+        assert np.all(np.isfinite(eng.get_forces(0)[0]))
+    eng.close()
+
+
 @pytest.mark.parametrize("readback", [False, True])
 def test_tile_overflow_after_host_upload_is_reported(readback):
     """The same gathering uploaded by the host right after a step: without the
