@@ -177,12 +177,25 @@ static int max_tiles_axis(double rmax, int T, int L) {
 //   FP64  100^3 (325) 65.5 / 66.5  128^3 (608) 118.1 / 116.2  192^3 (2052) 382.6 / 377.3  512^3 (38912) 7075 / 7031
 //   FP32  130^3 (393) 80.5 / 81.8  150^3 (521) 114.3 / 111.9  192^3 (1026) 197.6 / 196.0  280^3 (3637) 677.5 / 682.0
 //   FP16  170^3 (402) 90.7 / 95.3  200^3 (742) 165.4 / 159.0  240^3 (1069) 259.2 / 254.0  300^3 (2088) 471.9 / 475.6
+// The deviation forms stop at 1280 MiB, where what the cache keeps of a plane is
+// a small part either way: without spheres, FP16 272^3 to 512^3 and FP32 224^3 to
+// 384^3, the two differ by -1.1 to +1.3 %, slower where the last tile of a row is
+// mostly idle (FP16 300^3 453 / 459, FP32 280^3 668 / 673), faster at whole tiles
+// (FP16 384^3 799 / 790, FP32 384^3 1537 / 1528).
 constexpr long long kCachedMin = 24LL << 20, kCachedMax = 256LL << 20, kStreamMin = 448LL << 20,
                     kStreamMaxDev = 1280LL << 20;
 
-static int cache_form(long long grid_bytes, int storage) {
+// That one wave alone reads a line of those directions holds for tiles whose rows
+// are whole lines: at least 128 bytes wide, and starting at one where a box is
+// wider than a tile. Else the workgroups that share a line fetch it once each
+// (ordinary / nontemporal, us: FP16 256^3 at 16 x 16 threads 691 / 828, at 32 x 8
+// 299 / 306; FP32 192^3 at 16 x 16 243 / 275; FP64 24 x 300^2 at 16 x 16, packed
+// rows, 141 / 150; FP32 33 x 300 x 400 at 32 x 8 202 / 212, at 64 x 4, one tile,
+// 145 / 142).
+static int cache_form(long long grid_bytes, int storage, bool whole_lines) {
     if (grid_bytes >= kCachedMin && grid_bytes <= kCachedMax) return KEEP;
-    return grid_bytes >= kStreamMin && (storage == PSM_FP64 || grid_bytes <= kStreamMaxDev) ? STREAM : MIXED;
+    return whole_lines && grid_bytes >= kStreamMin && (storage == PSM_FP64 || grid_bytes <= kStreamMaxDev) ? STREAM
+                                                                                                            : MIXED;
 }
 
 struct Layout {
@@ -388,7 +401,8 @@ struct psm_ctx {
     int nbox = 0, storage = 0;
     int map_mode = 0;            // 1 if any box uses sub-division sampling
     bool walls = false;          // any box has walls or faces
-    int cache = MIXED;           // by the bytes of both grids
+    long long grid_bytes = 0;    // of both grids of every box
+    int cache = MIXED;           // cache_form() of the tile shape
     float h_scale = 1.0f, h_inv = 1.0f;
     hipStream_t stream = nullptr;
     char* ws = nullptr;
@@ -504,6 +518,10 @@ static void assign_tiles(psm_ctx* c) {
         base += bx.ntx * bx.nty * bx.ntz;
     }
     c->T_total = base;
+    const int size = (int)storage_bytes(c->storage);
+    bool whole_lines = c->ts.tx * size >= 128;
+    for (const BoxDev& bx : c->box) whole_lines = whole_lines && (bx.nx <= c->ts.tx || bx.pitch * size % 128 == 0);
+    c->cache = cache_form(c->grid_bytes, c->storage, whole_lines);
     // force-partial slots: per sphere, one per tile its bounding box can
     // touch at this tile shape
     long long pbase = 0;
@@ -701,7 +719,6 @@ extern "C" int psm_create(const psm_box_desc* boxes, int nbox, int storage, doub
     c->np.assign(nbox, 0);
     c->box.resize(nbox);
     int pb = 0;
-    long long grid_bytes = 0;
     for (int b = 0; b < nbox; ++b) {
         const psm_box_desc& d = boxes[b];
         BoxDev& bx = c->box[b];
@@ -717,7 +734,7 @@ extern "C" int psm_create(const psm_box_desc* boxes, int nbox, int storage, doub
         bx.plane_elems = (long long)L.pblk[b] * NQ * BLK;
         bx.grid[0] = c->ws + L.off_grid[0][b];
         bx.grid[1] = c->ws + L.off_grid[1][b];
-        grid_bytes += 2 * bx.plane_elems * d.nz * (long long)storage_bytes(storage);
+        c->grid_bytes += 2 * bx.plane_elems * d.nz * (long long)storage_bytes(storage);
         bx.omega = 1.0 / d.tau;
         bx.pref = 1.0 - 1.0 / (2.0 * d.tau);
         for (int a = 0; a < 3; ++a) bx.g[a] = d.fext[a];
@@ -786,7 +803,6 @@ extern "C" int psm_create(const psm_box_desc* boxes, int nbox, int storage, doub
         bx.margin32 = 1e-3 + 16.0 * std::ldexp(256.0 + (d.max_particles > 0 ? d.max_radius : 1.0) + 2.0, -24);
         pb += d.max_particles;
     }
-    c->cache = cache_form(grid_bytes, storage);
     c->d_boxes = (BoxDev*)(c->ws + L.off_boxes);
     c->d_tbase = (int*)(c->ws + L.off_tbase);
     c->d_partbox = (int*)(c->ws + L.off_partbox);

@@ -757,6 +757,28 @@ def test_streamed_loads_keep_the_results(mapping, walls, storage):
     assert all(np.array_equal(a, b) for a, b in zip(*out))
 
 
+@pytest.mark.parametrize("storage", [psm.PSM_FP64, psm.PSM_FP32DEV, psm.PSM_FP16DEV])
+@pytest.mark.parametrize("launch", [(16, 16, 2, 0), (32, 8, 1, 0), (32, 8, 4, psm.PSM_LAUNCH_PERSISTENT), (128, 2, 2, 0)])
+def test_tile_widths_in_large_contexts_keep_the_results(launch, storage):
+    """Tiles of less and of more than a 128-byte line, beside a box so large
+    that the step's loads may bypass the caches: bit for bit the results of the
+    box alone."""
+    spec = inputs.random_small((72, 26, 24), 5, (2.0, 3.5), seed=89, tau=0.66, fext=(1e-5, 0, 0), omamp=0.003)
+    out = []
+    for boxes in ([spec], [spec, inputs.BoxSpec(dims=(256, 192, 128), tau=0.8)]):
+        _print_case("tile widths", storage=storage, launch=launch, boxes=len(boxes))
+        eng = make_engine(boxes, storage=storage)
+        eng.set_launch(*launch)
+        if len(boxes) == 2:
+            eng.set_equilibrium(1, np.zeros((3, 256 * 192 * 128)))
+        eng.set_pdfs(0, initial_f(spec))
+        eng.set_particles(0, spec.x, spec.r, spec.U, spec.Om)
+        eng.step(3)
+        out.append(eng.get_pdfs(0).cpu().numpy())
+        eng.close()
+    assert np.array_equal(*out)
+
+
 def test_default_launch_lists_a_thin_sheet_of_spheres():
     """70 spheres in one sheet that meet 8 rows of a narrow FP64 box, at most 56
     of them any 4: the launch a context starts with lists them all (run_engine
