@@ -106,7 +106,8 @@ struct St16 {
     }
     // scale is a power of two: multiplication by it and by 1/scale is exact
     __device__ static double to_f64(T v, float inv) { return (double)((float)v * inv); }
-    __device__ static T from_f64(double v, float scale) { return (_Float16)(float)(v * (double)scale); }
+    // (rounded once: not by way of FP32)
+    __device__ static T from_f64(double v, float scale) { return (_Float16)(v * (double)scale); }
 };
 
 // The box constant of the collision's precision R: the FP64 value or its

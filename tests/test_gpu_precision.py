@@ -269,3 +269,25 @@ def test_equilibrium_start_reaches_every_cell(dims):
         cu = np.stack([CX, CY, CZ]).T @ u
         ref = W[:, None] * ((1.0 if r is None else r) + 3.0 * cu + 4.5 * cu ** 2 - 1.5 * (u ** 2).sum(0))
         assert np.all(np.abs(got - ref) <= 16 * 2.0 ** -53 * W[:, None])
+
+
+@pytest.mark.parametrize("storage", [psm.PSM_FP64, psm.PSM_FP32DEV, psm.PSM_FP16DEV])
+@pytest.mark.parametrize("walls", ["x", "yz", "xyz"])
+@pytest.mark.parametrize("dims", [(4, 4, 4), (66, 9, 6)])
+def test_state_io_rounds_once_at_walls(dims, walls, storage):
+    """Every value of every cell between resting walls is stored rounded once
+    and read back bit for bit, with values near FP16 ties as in periodic boxes
+    (those cells are set by kernels of their own)."""
+    print(f"[case] state io at walls storage={storage} dims={dims} walls={walls}", flush=True)
+    rng = np.random.default_rng(sum(dims) + storage)
+    N = int(np.prod(dims))
+    half = rng.integers(0x3000, 0x4400, (19, N)).astype(np.uint16).view(np.float16).astype(np.float64)
+    step = np.spacing(half.astype(np.float16)).astype(np.float64)
+    tie = (half + 0.5 * step + np.where(rng.random((19, N)) < 0.5, 1, -1) * 2.0 ** -30) / 1024.0
+    f = W[:, None] + np.where(rng.random((19, N)) < 0.5, tie, (rng.random((19, N)) - 0.5) * 4e-3)
+    eng = psm.Engine([psm.make_desc(*dims, 0.7, walls_x="x" in walls, walls_y="y" in walls, walls_z="z" in walls)],
+                     storage=storage)
+    eng.set_pdfs(0, f)
+    got = eng.get_pdfs(0).cpu().numpy()
+    eng.close()
+    assert np.array_equal(got, _stored(f, storage))
