@@ -307,7 +307,7 @@ int psm_get_launch(psm_ctx* ctx, int* tx, int* ty, int* tz, int* flags);
  * state after tuning. Synchronises. best_ms: ms per step of the chosen launch
  * in the second round.
  * The pick is cached for the process, keyed by the GPU architecture, the
- * storage form, the mapping and, per box, its dimensions, walls and sphere
+ * library's sources (another version tunes anew), the storage form, the mapping and, per box, its dimensions, walls and sphere
  * volume fraction (a power-of-two class); a context of a cached class gets
  * the cached launch and time without any trial (its state is then not
  * advanced). If the environment variable PSM_TUNE_CACHE names a file, its

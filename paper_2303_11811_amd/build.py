@@ -5,6 +5,7 @@ Packed-FP32 instruction selection is disabled for all device code.
 """
 from __future__ import annotations
 
+import hashlib
 import os
 import subprocess
 import sys
@@ -24,13 +25,23 @@ HIPCC_FLAGS = [
 ]
 
 
+def source_hash() -> str:
+    """Of the sources that decide how fast a launch is: the autotuner keeps its
+    picks apart by it."""
+    h = hashlib.sha256()
+    for f in SOURCES + ["psm_internal.h"]:
+        with open(os.path.join(CSRC, f), "rb") as fh:
+            h.update(fh.read())
+    return h.hexdigest()[:12]
+
+
 def build(verbose: bool = False, extra_flags=None) -> str:
     """Compile every source and link libpsm.so (always rebuilds)."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     objs = []
     for src in SOURCES:
         obj = os.path.join(CSRC, src + ".o")
-        cmd = [hipcc, *HIPCC_FLAGS, *(extra_flags or []), "-c", os.path.join(CSRC, src), "-o", obj]
+        cmd = [hipcc, *HIPCC_FLAGS, f'-DPSM_SOURCE_HASH="{source_hash()}"', *(extra_flags or []), "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         subprocess.check_call(cmd)

@@ -1639,16 +1639,22 @@ static std::mutex g_tune_mu;
 static std::map<std::string, TuneEntry> g_tune;
 static bool g_tune_loaded = false;
 
-// The class of a context: GPU architecture, storage form, mapping, and per
-// box its dimensions, walls and sphere volume fraction (rounded to a power
-// of two in hundredths): the quantities the best launch depends on.
+#ifndef PSM_SOURCE_HASH
+#define PSM_SOURCE_HASH "0"   // a build without build.py
+#endif
+
+// The class of a context: GPU architecture, library sources (picks and times of
+// other kernels say nothing about these), storage form, mapping, and per box
+// its dimensions, walls and sphere volume fraction (rounded to a power of two in
+// hundredths): the quantities the best launch depends on.
 static std::string tune_key(psm_ctx* c) {
     int dev = 0;
     hipDeviceProp_t prop;
     std::string arch = "?";
     if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess) arch = prop.gcnArchName;
     char buf[160];
-    std::snprintf(buf, sizeof buf, "%s|s%d|m%d|n%d", arch.c_str(), c->storage, c->map_mode, c->nbox);
+    std::snprintf(buf, sizeof buf, "%s|k%s|s%d|m%d|n%d", arch.c_str(), PSM_SOURCE_HASH, c->storage, c->map_mode,
+                  c->nbox);
     std::string k = buf;
     for (int b = 0; b < c->nbox; ++b) {
         const psm_box_desc& d = c->desc[b];

@@ -502,6 +502,41 @@ def test_autotune_cache(tmp_path, monkeypatch):
     psm.psm_clear_tune_cache()
 
 
+def test_autotune_picks_of_other_kernels_are_not_taken(tmp_path):
+    """A cache file written by other library sources (or before its lines named
+    them) does not decide the launch: the context is tuned again. One written by
+    the same library does. Each in a process of its own, as the file is read once."""
+    import os
+    import re
+    import subprocess
+    import sys
+
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    cache = tmp_path / "tune.txt"
+    child = (f"import sys; sys.path.insert(0, {root!r})\n"
+             "import paper_2303_11811_amd as psm\n"
+             f"psm.LIB_PATH = {psm.LIB_PATH!r}\n"
+             "eng = psm.Engine([psm.make_desc(50, 20, 16, 0.7)])\n"
+             "import numpy as np\n"
+             "eng.set_equilibrium(0, np.zeros((3, 16000)))\n"
+             "print('tuned', *eng.autotune(trial_steps=1), flush=True)\n"
+             "eng.close()\n")
+
+    def tuned():
+        env = dict(os.environ, PSM_TUNE_CACHE=str(cache))
+        out = subprocess.run([sys.executable, "-c", child], env=env, capture_output=True, text=True, timeout=100)
+        assert out.returncode == 0, out.stderr[-500:]
+        return float(out.stdout.split("tuned")[1].split()[-1])
+
+    _print_case("picks of other kernels")
+    tuned()
+    line = re.sub(r"\S+$", "0.000123", cache.read_text().strip())
+    cache.write_text(re.sub(r"\|k[0-9a-f]+", "|k000000000000", line) + "\n" + re.sub(r"\|k[0-9a-f]+", "", line) + "\n")
+    assert tuned() != 0.000123
+    cache.write_text(line + "\n")
+    assert tuned() == 0.000123
+
+
 def test_state_and_argument_errors_on_a_live_context():
     """The documented codes on a live context, each leaving it usable: more
     spheres than max_particles (PSM_ECAPACITY), radius out of range, box out
