@@ -730,9 +730,10 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
     } while (0)
             if constexpr (FILT) {
                 unsigned long long cm = nc > 0 ? s_cmask[wave][k] : 0ull;
-                // wave-uniform: keep the mask and its loop in scalar registers
+                // wave-uniform: keep the mask and its loop in scalar registers (the
+                // builtin returns an int: its sign must not reach the upper half)
                 cm = ((unsigned long long)__builtin_amdgcn_readfirstlane((unsigned)(cm >> 32)) << 32) |
-                     (unsigned long long)__builtin_amdgcn_readfirstlane((unsigned)cm);
+                     (unsigned)__builtin_amdgcn_readfirstlane((unsigned)cm);
                 if (cm != 0ull) {
                     Slots sl;
                     slots_init(sl);

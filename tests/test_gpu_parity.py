@@ -448,6 +448,23 @@ def test_candidate_filter_is_exact(storage):
             assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("storage", [psm.PSM_FP64, psm.PSM_FP32DEV, psm.PSM_FP16DEV])
+@pytest.mark.parametrize("flags", [psm.PSM_LAUNCH_FILTER, psm.PSM_LAUNCH_FILTER | psm.PSM_LAUNCH_PERSISTENT])
+def test_candidate_filter_of_crowded_tiles_is_exact(flags, storage):
+    """512 tiles that list about 15 to 45 spheres each (one mask bit per sphere, bit
+    31 among them), neighbours sharing many: the filter gives bit for bit what
+    the step without it gives."""
+    _print_case("crowded filter", flags=flags, storage=storage)
+    rng = np.random.default_rng(3)
+    dims, n = (64, 32, 256), 2800
+    x = rng.uniform(0.0, dims, (n, 3))
+    spec = inputs.BoxSpec(dims=dims, tau=0.7, fext=(1e-5, 0.0, 0.0), x=x, r=np.full(n, 2.0),
+                          U=inputs.uniform_velocities(rng, n, 0.01), Om=np.zeros((n, 3)))
+    got = [run_engine(spec, 3, storage=storage, launch=(64, 4, 4, fl))[:5]
+           for fl in (flags & psm.PSM_LAUNCH_PERSISTENT, flags)]
+    assert all(np.array_equal(a, b) for a, b in zip(*got))
+
+
 def test_autotune_picks_an_allowed_launch_and_keeps_parity():
     """The tuner's pick is one of the documented shapes, is the launch the
     context keeps, and the step under it still matches the oracle."""
