@@ -93,13 +93,38 @@ static int best_depth(const psm_box_desc* boxes, int nbox, int storage, int tx, 
     }
 }
 
+// Spheres the list of a tile holds on average with all the spheres of the
+// descriptors there, at their largest radius.
+static double mean_list(const psm_box_desc* boxes, int nbox, int tx, int ty, int tz) {
+    double entries = 0.0, T = 0.0;
+    for (int b = 0; b < nbox; ++b) {
+        const psm_box_desc& d = boxes[b];
+        const int L[3] = {d.nx, d.ny, d.nz}, t[3] = {tx, ty, tz};
+        double tiles = 1.0, touched = d.max_particles;
+        for (int a = 0; a < 3; ++a) {
+            const double nt = cdiv(L[a], t[a]);
+            tiles *= nt;
+            touched *= std::min(nt, 1.0 + 2.0 * (d.max_radius + 1.0) / t[a]);
+        }
+        entries += touched;
+        T += tiles;
+    }
+    return entries / T;
+}
+
 // A tile deeper than that keeps its one list, and up to 8 workgroups share its
 // cells along z, each with its own force partials (one workgroup / shared, us:
 // 32^3 FP16 at 64 x 4 x 8 20.2 / 6.5, 128^3 FP64 at 128 x 2 x 8 129 / 118, 256^3
 // FP32 at 30 % solid and 64 x 4 x 8 555 / 504, the 500 x 200 x 800 bed in FP64 at
-// 128 x 2 x 8 4834 / 4414). Where half the waves of the tiles lie past the box,
-// more parts only stage more spheres for idle waves once the chip holds no more
-// at a time (3, 4 and 5 workgroups on each of 256 CUs): FP32 at 128 x 2 x 2, 32^3,
+// 128 x 2 x 8 4834 / 4414). Each of them stages the whole list before its cells,
+// which is lost time where it is long and the chip is full without it: beyond 8
+// workgroups for each that the chip holds at a time (3, 4 and 5 on each of 256
+// CUs), lists of more than 7 spheres on average are not shared (FP64 353 x 298 x
+// 518 at 128 x 2 x 8, 30 spheres, 4740 / 5446; FP32 310 x 543 x 630 at 256 x 1 x 16,
+// 14 spheres, 4206 / 5077; of 490 launches of random sizes those with up to 4
+// gained 5 % on average, those with 4 to 8 nothing, longer ones lost 5 %). Where
+// half the waves of the tiles lie past the box, more parts only stage more spheres
+// for idle waves once the chip holds no more at a time: FP32 at 128 x 2 x 2, 32^3,
 // 576 parts after it, 8.6 / 7.0, but 64^3, 2048, 13.7 / 15.2; FP16 at 256 x 1 x 4,
 // 128^3, 8192, 49.7 / 52.4. Parts of tiles and their partial slots are counted in int.
 static int z_shift(const psm_box_desc* boxes, int nbox, int storage, int tx, int ty, int tz, long long slots) {
@@ -112,10 +137,13 @@ static int z_shift(const psm_box_desc* boxes, int nbox, int storage, int tx, int
     }
     const bool idle = 2 * waves <= T * (WG / 64);
     const long long resident = 256 * (storage == PSM_FP64 ? 3 : (storage == PSM_FP32DEV ? 4 : 5));
+    const bool long_lists = mean_list(boxes, nbox, tx, ty, tz) > 7.0;
+    long long most = 1LL << 30;   // parts
+    if (long_lists) most = 8 * resident;
+    if (idle) most = resident;
     const int depth = std::max(best_depth(boxes, nbox, storage, tx, ty), tz / 8);
     int shift = 0;
-    while (tz >> (shift + 1) >= depth && std::max(T, slots) << (shift + 1) < (1LL << 30) &&
-           (!idle || T << (shift + 1) <= resident))
+    while (tz >> (shift + 1) >= depth && T << (shift + 1) <= most && std::max(T, slots) << (shift + 1) < (1LL << 30))
         ++shift;
     return shift;
 }
