@@ -442,6 +442,8 @@ struct psm_ctx {
     TileShape ts{64, 4, 16, 0, 0, 16, 0};
     int T_total = 0;
     int grid = 0;
+    bool queued = false;         // persistent grid: parts are taken from the dies' counters, 1 << run at once
+    int run = 0;
     int parity = 0;
     bool have_particles_lists = false;
     bool strict_slots = false;      // a third overlap in a cell is an error
@@ -575,9 +577,25 @@ static void assign_tiles(psm_ctx* c) {
     (void)hipGetDevice(&dev);
     (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
     // one-shot: a workgroup per part of a tile (rounded up to whole XCD rounds);
-    // persistent: as many workgroups as fit at once, each walking its tiles
-    int full = (((c->T_total << c->ts.zshift) + NXCD - 1) / NXCD) * NXCD;
-    int g = c->ts.persistent ? std::min(step_blocks_per_cu(c->storage, step_form(c)) * ncu, full) : full;
+    // persistent: as many workgroups as fit at once, each walking its parts. Each
+    // take from its die's counter is an atomic, one after another (about 80 ns),
+    // which the small parts of shared tiles would wait for: up to four per
+    // workgroup are dealt out without the counter, and of more, runs of at least
+    // 128 KB are taken at once (one by one / so, without spheres, us: FP16 51 x 50 x
+    // 64 at 16 x 16 x 8 27.9 / 6.6, 64 x 76 x 437 at 64 x 4 x 4 69.6 / 27.6, 83 x 214 x 138
+    // at 64 x 4 x 4 108 / 75; FP32 77 x 87 x 58 at 128 x 2 x 8 49.7 / 14.3; FP64 150 x 102
+    // x 188 at 256 x 1 x 2 246 / 180)
+    const int parts = c->T_total << c->ts.zshift;
+    int g = cdiv(parts, NXCD) * NXCD;
+    c->run = 0;
+    c->queued = false;
+    if (c->ts.persistent) {
+        const int resident = step_blocks_per_cu(c->storage, step_form(c)) * ncu;
+        c->queued = c->ts.zshift == 0 || parts > 4 * resident;
+        const int part_bytes = WG * (c->ts.tz >> c->ts.zshift) * 2 * NQ * size;
+        while (c->queued && c->run < c->ts.zshift && part_bytes << c->run < 128 << 10) ++c->run;
+        g = std::min(resident, g);
+    }
     c->grid = std::max(NXCD, g / NXCD * NXCD);
 }
 
@@ -1181,7 +1199,8 @@ static int step_params(psm_ctx* c, int parity, StepParams& kp) {
     kp.h_scale = c->h_scale;
     kp.h_inv = c->h_inv;
     kp.flags = c->d_flags;
-    kp.queue = c->ts.persistent ? c->d_misc + 32 : nullptr;   // ints 32..39 of the counter block
+    kp.run = c->run;
+    kp.queue = c->queued ? c->d_misc + 32 : nullptr;   // ints 32..39 of the counter block
     return PSM_OK;
 }
 

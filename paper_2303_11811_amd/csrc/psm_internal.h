@@ -320,6 +320,7 @@ struct StepParams {
     float h_scale, h_inv;       // FP16 storage scale and its inverse (1 otherwise)
     int* flags;                 // device error word: |= FLAG_SLOT_OVERFLOW when a cell meets a third sphere,
                                 // FLAG_LIST_CUT when a tile's list was cut
+    int run;                    // parts taken from the queue at once: 1 << run
     int* queue;                 // [NXCD] tile counters of the persistent grid (zeroed before the launch), or null
 };
 

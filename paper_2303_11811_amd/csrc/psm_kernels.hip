@@ -503,13 +503,13 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
     const int t_end = (int)(((long long)ka->T_total * (xcd + 1)) / NXCD);
 
     // Tile order: with a queue (persistent grid), the workgroups of a die take
-    // the next tile of its eighth from that die's counter as they finish one;
-    // otherwise workgroup m of a die takes tiles m, m + gx8, ...
+    // the next run of tiles of its eighth from that die's counter as they finish
+    // one; otherwise workgroup m of a die takes tiles m, m + gx8, ...
     __shared__ int s_next;
     int* const queue = ka->queue;
     int t = t_begin + m;
     if (queue) {
-        if (tid == 0) s_next = t_begin + atomicAdd(queue + xcd, 1);
+        if (tid == 0) s_next = t_begin + (atomicAdd(queue + xcd, 1) << ka->run);
         __syncthreads();
         t = __builtin_amdgcn_readfirstlane(s_next);   // uniform: everything of the tile stays scalar
     }
@@ -1001,9 +1001,13 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
         __syncthreads();
         // every thread has read s_next before the barriers of this tile
         if (queue) {
-            if (tid == 0) s_next = t_begin + atomicAdd(queue + xcd, 1);
-            __syncthreads();
-            t = __builtin_amdgcn_readfirstlane(s_next);
+            const int run = step_args()->run;
+            ++t;
+            if (((t - t_begin) & ((1 << run) - 1)) == 0) {
+                if (tid == 0) s_next = t_begin + (atomicAdd(queue + xcd, 1) << run);
+                __syncthreads();
+                t = __builtin_amdgcn_readfirstlane(s_next);
+            }
         } else {
             t += gx8;
         }

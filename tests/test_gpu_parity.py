@@ -326,6 +326,30 @@ def test_persistent_grid_matches_one_workgroup_per_tile(storage):
             assert all(np.array_equal(x, y) for x, y in zip(a, b))
 
 
+@pytest.mark.parametrize("storage", [psm.PSM_FP64, psm.PSM_FP32DEV, psm.PSM_FP16DEV])
+@pytest.mark.parametrize("tz", [1, 4])
+def test_persistent_runs_cover_every_part_once(tz, storage):
+    """A box of many more parts of tiles than the persistent grid has
+    workgroups: taken one by one (depth 1) and in runs of parts that share tiles
+    (depth 4), over eager steps and graph replays, bit for bit the results of
+    one workgroup per part."""
+    _print_case("persistent runs", tz=tz, storage=storage)
+    spec = inputs.random_small((60, 158, 300), 30, (3.0, 6.0), seed=96, tau=0.7, fext=(1e-5, 0, 0))
+    got = []
+    for flags in (0, psm.PSM_LAUNCH_PERSISTENT):
+        eng = make_engine([spec], storage=storage)
+        eng.set_launch(64, 4, tz, flags)
+        eng.set_pdfs(0, initial_f(spec))
+        eng.set_particles(0, spec.x, spec.r, spec.U, spec.Om)
+        eng.step(3)
+        eng.set_graph(True)
+        eng.step(10)
+        eng.step(10)
+        got.append((eng.get_pdfs(0).cpu().numpy(), *eng.get_forces(0)))
+        eng.close()
+    assert all(np.array_equal(a, b) for a, b in zip(*got))
+
+
 def test_kernel_timing_counts_every_eager_launch():
     """Timing events come from a fixed pool that is folded into the totals
     when full: 300 steps (more than the pool's 128 pairs) count 300 launches
