@@ -528,7 +528,7 @@ static int upload_box_table(psm_ctx* c) {
 
 static StepForm step_form(const psm_ctx* c) {
     StepForm f;
-    f.map = c->map_mode != 0;
+    f.map = c->map_mode != 0 && c->P_total > 0;   // without spheres nothing is sampled
     f.filter = c->ts.filter != 0;
     f.walls = c->walls;
     f.cache = c->cache;

@@ -350,6 +350,20 @@ def test_persistent_runs_cover_every_part_once(tz, storage):
     assert all(np.array_equal(a, b) for a, b in zip(*got))
 
 
+@pytest.mark.parametrize("storage", [psm.PSM_FP64, psm.PSM_FP32DEV, psm.PSM_FP16DEV])
+@pytest.mark.parametrize("walls", [False, True])
+def test_sampling_context_without_spheres_is_a_plain_one(walls, storage):
+    """A context whose boxes sample but have no room for spheres steps bit for
+    bit like one with the linear approximation."""
+    _print_case("sampling without spheres", walls=walls, storage=storage)
+    got = []
+    for mapping in (0, 1):
+        spec = inputs.BoxSpec(dims=(37, 18, 11), tau=0.66, fext=(1e-5, -2e-5, 1e-6), mapping=mapping, nsub=4, walls_x=walls,
+                              walls_z=walls, u0=inputs.taylor_green((37, 18, 11), 0.02))
+        got.append(run_engine(spec, 4, storage=storage)[0])
+    assert np.array_equal(*got)
+
+
 def test_kernel_timing_counts_every_eager_launch():
     """Timing events come from a fixed pool that is folded into the totals
     when full: 300 steps (more than the pool's 128 pairs) count 300 launches
