@@ -1336,11 +1336,11 @@ __device__ inline void store_cell_slots(const BoxDev& bx, typename S::T* g, int 
 // Tiles of the state I/O kernels: 256 cells of one z-plane, rows of 16 to 64,
 // one cell per thread, walked like the step's tiles (each die takes a
 // contiguous eighth, so that the lines two x-neighbouring tiles share in a
-// shifted access meet in one L2). HBM bound. With an index division per cell,
-// 64-bit addresses and boundary rules for every value these kernels moved
-// 1.3-5 TB/s, now 5.2-6.5 like the step's own pattern (us at 256^3):
+// shifted access meet in one L2; psm_get_pdfs has a walk of its own). HBM bound.
+// With an index division per cell, 64-bit addresses and boundary rules for every
+// value these kernels moved 1.3-5 TB/s, now 5.2-6.5 like the step's own pattern
+// (us at 256^3):
 //   read-out of rho and u  FP64 904 -> 588, FP32 769 -> 333, FP16 746 -> 209
-//   get_pdfs               FP64 991 -> 942, FP32 784 -> 711, FP16 822 -> 599
 //   set_pdfs               FP64 1210 -> 924, FP32 990 -> 697, FP16 990 -> 593
 // Cells next to a wall or face are left to the general kernels after them.
 struct RowGrid {
@@ -1374,6 +1374,42 @@ __device__ __forceinline__ bool row_cell(const RowGrid& g, const BoxDev& bx, int
     x = ((t - r * g.nbx) << g.shift) + (tid & ((1 << g.shift) - 1));
     y = (r - z * g.nby) * (256 >> g.shift) + (tid >> g.shift);
     return x < bx.nx && y < bx.ny;
+}
+
+// The cell of this thread where a kernel writes 19 canonical values per cell: 256
+// cells of a plane in index order, as they lie in the field, whatever its row
+// length; rows cut into tiles leave partial lines to several workgroups. LINES
+// (every direction of the field starts at a 128-byte line): nontemporal
+// stores, and the dies share consecutive blocks, which keeps the 19 streams
+// close together; else ordinary stores, whose partial lines meet in the L2 of a
+// die that takes a contiguous eighth. psm_get_pdfs, us, tiles / index order with
+// either, FP64: 256^3 928 / 885 / 969, 97 x 92 x 184 130 / 90 / 106, 109 x 272 x 40 83 / 57
+// / 80; not at lines 581 x 455 x 143 3146 / 2578 / 2326, 332 x 134 x 547 1828 / 1440 / 1439;
+// FP32 581 x 455 x 143 2666 / 2150 / 1770.
+struct IndexGrid {
+    int nb, T;            // blocks per plane, and in all
+    unsigned div_nb[2], div_nx[2];
+};
+
+static IndexGrid index_grid(const BoxDev& bx) {
+    IndexGrid g;
+    g.nb = (bx.nx * bx.ny + 255) / 256;
+    g.T = g.nb * bx.nz;
+    udiv_magic(g.nb, g.div_nb);
+    udiv_magic(bx.nx, g.div_nx);
+    return g;
+}
+
+template <bool LINES>
+__device__ __forceinline__ bool index_cell(const IndexGrid& g, const BoxDev& bx, int& x, int& y, int& z) {
+    const int xcd = blockIdx.x % NXCD;
+    const int t = LINES ? (int)blockIdx.x : (int)(((long long)g.T * xcd) / NXCD) + (int)blockIdx.x / NXCD;
+    if (t >= (LINES ? g.T : (int)(((long long)g.T * (xcd + 1)) / NXCD))) return false;
+    z = udiv(t, g.div_nb[0], g.div_nb[1]);
+    const int i = (t - z * g.nb) * 256 + (int)threadIdx.x;
+    y = udiv(i, g.div_nx[0], g.div_nx[1]);
+    x = i - y * bx.nx;
+    return y < bx.ny;
 }
 
 // True for the cells whose values a wall or face enters.
@@ -1624,18 +1660,21 @@ template <class S> __device__ __forceinline__ double canonical(typename S::R v, 
     return S::DEV ? d + wq(q) : d;
 }
 
-template <class S>
-__global__ __launch_bounds__(256) void k_get_pdfs(BoxDev bx, RowGrid rg, int parity, double* __restrict__ f,
+template <class S, bool LINES>
+__global__ __launch_bounds__(256) void k_get_pdfs(BoxDev bx, IndexGrid ig, int parity, double* __restrict__ f,
                                                   float inv) {
     int x, y, z;
-    if (!row_cell(rg, bx, x, y, z) || at_wall(bx, x, y, z)) return;
+    if (!index_cell<LINES>(ig, bx, x, y, z) || at_wall(bx, x, y, z)) return;
     typename S::R v[NQ];
     pull19<S>(bx, parity, x, y, z, v);
     const unsigned i = (unsigned)(x + bx.nx * y);
     const long long p = (long long)z * bx.nx * bx.ny;
 #pragma unroll
-    for (int q = 0; q < NQ; ++q)
-        __builtin_nontemporal_store(canonical<S>(v[q], q, inv), (f + (long long)q * bx.N + p) + i);
+    for (int q = 0; q < NQ; ++q) {
+        double* const at = (f + (long long)q * bx.N + p) + i;
+        if constexpr (LINES) __builtin_nontemporal_store(canonical<S>(v[q], q, inv), at);
+        else *at = canonical<S>(v[q], q, inv);
+    }
 }
 
 template <class S>
@@ -2132,8 +2171,12 @@ hipError_t launch_set_equilibrium(int storage, const BoxDev& bx, int parity, con
 }
 
 hipError_t launch_get_pdfs(int storage, const BoxDev& bx, int parity, double* f, float inv, hipStream_t st) {
-    const RowGrid rg = row_grid(bx);
-    PSM_BY_STORAGE(hipLaunchKernelGGL(k_get_pdfs<S>, dim3(row_blocks(rg)), dim3(256), 0, st, bx, rg, parity, f, inv));
+    const IndexGrid ig = index_grid(bx);
+    const dim3 grid((unsigned)(ig.T + NXCD - 1) / NXCD * NXCD);
+    if (bx.N % 16 == 0 && ((uintptr_t)f & 127) == 0)
+        PSM_BY_STORAGE(hipLaunchKernelGGL((k_get_pdfs<S, true>), grid, dim3(256), 0, st, bx, ig, parity, f, inv))
+    else
+        PSM_BY_STORAGE(hipLaunchKernelGGL((k_get_pdfs<S, false>), grid, dim3(256), 0, st, bx, ig, parity, f, inv))
     if (has_walls(bx))
         PSM_BY_STORAGE(hipLaunchKernelGGL(k_get_pdfs_wall<S>, dim3(blocks_for(wall_cells(bx), 256)), dim3(256), 0, st, bx, parity,
                                           f, inv));

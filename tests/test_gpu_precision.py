@@ -291,3 +291,28 @@ def test_state_io_rounds_once_at_walls(dims, walls, storage):
     got = eng.get_pdfs(0).cpu().numpy()
     eng.close()
     assert np.array_equal(got, _stored(f, storage))
+
+
+@pytest.mark.parametrize("storage", [psm.PSM_FP64, psm.PSM_FP32DEV, psm.PSM_FP16DEV])
+@pytest.mark.parametrize("dims", [(16, 9, 5), (17, 16, 6), (13, 7, 5), (300, 4, 4), (4, 64, 7), (257, 5, 16)])
+@pytest.mark.parametrize("offset", [0, 1, 16])
+def test_pdfs_into_any_field(offset, dims, storage):
+    """psm_get_pdfs into a field that starts at a 128-byte line or not, of a
+    length that keeps every direction there or not, over plane ends inside a
+    block: every value, and nothing beside it."""
+    import torch
+
+    print(f"[case] pdfs into any field offset={offset} dims={dims} storage={storage}", flush=True)
+    N = int(np.prod(dims))
+    f = W[:, None] + (np.random.default_rng(N).random((19, N)) - 0.5) * 4e-3
+    eng = psm.Engine([psm.make_desc(*dims, 0.7)], storage=storage)
+    eng.set_pdfs(0, f)
+    out = torch.full((19 * N + 64,), -7.0, dtype=torch.float64, device=eng.device)
+    assert out.data_ptr() % 128 == 0
+    torch.cuda.synchronize()
+    psm.psm_get_pdfs(eng.ctx, 0, out.data_ptr() + 8 * offset)
+    eng.synchronize()
+    eng.close()
+    got = out.cpu().numpy()
+    assert np.array_equal(got[offset:offset + 19 * N].reshape(19, N), _stored(f, storage))
+    assert np.all(got[:offset] == -7.0) and np.all(got[offset + 19 * N:] == -7.0)
