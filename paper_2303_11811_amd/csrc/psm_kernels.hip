@@ -1400,6 +1400,12 @@ static IndexGrid index_grid(const BoxDev& bx) {
     return g;
 }
 
+// A value of a field that is read out.
+template <bool LINES, class V> __device__ __forceinline__ void put(V* p, V v) {
+    if constexpr (LINES) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
+
 template <bool LINES>
 __device__ __forceinline__ bool index_cell(const IndexGrid& g, const BoxDev& bx, int& x, int& y, int& z) {
     const int xcd = blockIdx.x % NXCD;
@@ -1671,9 +1677,7 @@ __global__ __launch_bounds__(256) void k_get_pdfs(BoxDev bx, IndexGrid ig, int p
     const long long p = (long long)z * bx.nx * bx.ny;
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
-        double* const at = (f + (long long)q * bx.N + p) + i;
-        if constexpr (LINES) __builtin_nontemporal_store(canonical<S>(v[q], q, inv), at);
-        else *at = canonical<S>(v[q], q, inv);
+        put<LINES>((f + (long long)q * bx.N + p) + i, canonical<S>(v[q], q, inv));
     }
 }
 
@@ -1756,9 +1760,14 @@ __global__ void k_macroscopic_wall(BoxDev bx, int parity, double* __restrict__ r
 
 // Dense two-slot solid fractions of one box (read-out, or with B null the
 // overflow count alone), through the same candidate lists and mapping
-// function as the step kernel: one workgroup per tile of the step, the
+// function as the step kernel, by the tiles and parts of tiles of the step, the
 // spheres staged in LDS (256^3: 146 -> 92 us at 24 B per cell). Fewer than
-// three spheres cannot overflow a cell.
+// three spheres cannot overflow a cell. LINES: rows are whole lines (16 cells),
+// stored past the caches. Else tiles leave partial lines to their neighbours in
+// x: the tiles of a row run on one die, whose L2 puts the lines together (581 x
+// 455 x 143 without spheres 391 us with nontemporal stores and rows over all
+// dies, 330 with one die and nontemporal, 197 so; at 10 % solid 436 / 447).
+template <bool LINES>
 __global__ __launch_bounds__(WG) void k_map_dense(BoxDev bx, Particles P, const int* __restrict__ tile_cnt,
                                                   const int* __restrict__ tile_off,
                                                   const int2* __restrict__ tile_ent, int list_cap, TileShape ts,
@@ -1766,7 +1775,13 @@ __global__ __launch_bounds__(WG) void k_map_dense(BoxDev bx, Particles P, const 
                                                   unsigned long long* dropped) {
     __shared__ double s_x[MAXC], s_y[MAXC], s_z[MAXC], s_r[MAXC], s_fr[MAXC];
     __shared__ int s_p[MAXC];
-    const int lt = blockIdx.x, t = bx.tile_base + lt;
+    int lt = blockIdx.x;
+    if (!LINES) {
+        const int m = lt / NXCD, r = udiv(m, bx.div_ntx[0], bx.div_ntx[1]);   // r * NXCD + die: row of tiles
+        lt = (r * NXCD + lt % NXCD) * bx.ntx + m - r * bx.ntx;
+        if (lt >= bx.ntx * bx.nty * bx.ntz) return;
+    }
+    const int t = bx.tile_base + lt;
     const int nc = tile_cnt[t] < list_cap ? tile_cnt[t] : list_cap;
     if (!B && nc < 3) return;
     const int tid = threadIdx.x;
@@ -1781,10 +1796,11 @@ __global__ __launch_bounds__(WG) void k_map_dense(BoxDev bx, Particles P, const 
     const int tcz = udiv(tr, bx.div_nty[0], bx.div_nty[1]);
     const int x = (lt - tr * bx.ntx) * ts.tx + (tid & (ts.tx - 1));
     const int y = (tr - tcz * bx.nty) * ts.ty + (tid >> __builtin_ctz(ts.tx));
-    const int z1 = min((tcz + 1) * ts.tz, bx.nz);
+    // gridDim.y workgroups share the planes of a tile
+    const int depth = ts.tz / (int)gridDim.y, z0 = tcz * ts.tz + (int)blockIdx.y * depth, z1 = min(z0 + depth, bx.nz);
     int lost = 0;
     if (x < bx.nx && y < bx.ny) {
-        for (int z = tcz * ts.tz; z < z1; ++z) {
+        for (int z = z0; z < z1; ++z) {
             Slots sl;
             slots_init(sl);
             for (int c = 0; c < nc; ++c) {
@@ -1800,10 +1816,10 @@ __global__ __launch_bounds__(WG) void k_map_dense(BoxDev bx, Particles P, const 
             lost += sl.dropped;
             const long long n = x + bx.nx * (y + (long long)bx.ny * z);
             if (B) {
-                __builtin_nontemporal_store(sl.c0 >= 0 ? sl.B0 : 0.0, B + n);
-                __builtin_nontemporal_store(sl.c1 >= 0 ? sl.B1 : 0.0, B + bx.N + n);
-                __builtin_nontemporal_store(sl.c0 >= 0 ? sl.c0 - bx.part_base : -1, pid + n);
-                __builtin_nontemporal_store(sl.c1 >= 0 ? sl.c1 - bx.part_base : -1, pid + bx.N + n);
+                put<LINES>(B + n, sl.c0 >= 0 ? sl.B0 : 0.0);
+                put<LINES>(B + bx.N + n, sl.c1 >= 0 ? sl.B1 : 0.0);
+                put<LINES>(pid + n, sl.c0 >= 0 ? sl.c0 - bx.part_base : -1);
+                put<LINES>(pid + bx.N + n, sl.c1 >= 0 ? sl.c1 - bx.part_base : -1);
             }
         }
     }
@@ -2208,8 +2224,17 @@ hipError_t launch_macroscopic(int storage, const BoxDev& bx, int parity, double*
 hipError_t launch_map_dense(const BoxDev& bx, const Particles& P, const int* tile_cnt, const int* tile_off,
                             const int2* tile_ent, int list_cap, TileShape ts, double* B, int* pid,
                             unsigned long long* dropped, hipStream_t st) {
-    hipLaunchKernelGGL(k_map_dense, dim3(bx.ntx * bx.nty * bx.ntz), dim3(WG), 0, st, bx, P, tile_cnt, tile_off,
-                       tile_ent, list_cap, ts, B, pid, dropped);
+    const int rows = bx.nty * bx.ntz;
+    // as many parts of a tile as in the step, and more where that leaves CUs idle
+    // (64^3 at 10 % solid and depth 16: 76 us in one part, 13 shared)
+    int parts = 1 << ts.zshift;
+    while (parts < ts.tz && (long long)rows * bx.ntx * parts < 2048) parts *= 2;
+    if (bx.nx % 16 == 0)
+        hipLaunchKernelGGL(k_map_dense<true>, dim3(rows * bx.ntx, parts), dim3(WG), 0, st, bx, P, tile_cnt, tile_off,
+                           tile_ent, list_cap, ts, B, pid, dropped);
+    else
+        hipLaunchKernelGGL(k_map_dense<false>, dim3((rows + NXCD - 1) / NXCD * NXCD * bx.ntx, parts), dim3(WG), 0,
+                           st, bx, P, tile_cnt, tile_off, tile_ent, list_cap, ts, B, pid, dropped);
     return hipGetLastError();
 }
 

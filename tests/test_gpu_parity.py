@@ -671,6 +671,27 @@ def test_default_depth_keeps_the_results_of_depth_16(storage, dims, launch):
     assert np.all(np.abs(F - F16) <= 1e-13 * scale) and np.all(np.abs(T - T16) <= 1e-13 * scale * 5.0)
 
 
+@pytest.mark.parametrize("dims", [(32, 26, 40), (35, 26, 41), (130, 22, 33)])
+@pytest.mark.parametrize("launch", [(16, 16, 1, 0), (64, 4, 16, 0), (32, 8, 32, 0), (128, 2, 4, psm.PSM_LAUNCH_PERSISTENT)])
+def test_solid_fractions_of_every_row_length_and_depth(launch, dims):
+    """The read-out walks boxes of whole and of partial lines per row, by tiles
+    whose planes several workgroups share: every cell as the oracle maps it, and
+    the overlaps counted once."""
+    _print_case("solid walks", launch=launch, dims=dims)
+    spec = inputs.random_small(dims, 6, (2.5, 5.0), seed=sum(dims), tau=0.7, overlap=True)
+    ref = run_oracle(spec, 1)
+    eng = make_engine([spec])
+    eng.set_launch(*launch)
+    eng.set_equilibrium(0, np.zeros((3, spec.N)))
+    eng.set_particles(0, spec.x, spec.r, spec.U, spec.Om)
+    B, pid = (a.cpu().numpy() for a in eng.get_solid_fraction(0))
+    overlaps = eng.get_stats(0)[2]
+    eng.close()
+    assert overlaps == ref.overflow
+    assert np.array_equal(pid, ref.pid)
+    assert np.allclose(B, ref.B, rtol=0, atol=1e-15)
+
+
 @pytest.mark.parametrize("nsub", [1, 2, 3, 4, 5, 13, 16])
 def test_sampled_fractions_of_every_subdivision(nsub):
     """Sub-division counts are whole numbers: bit for bit the oracle's for
