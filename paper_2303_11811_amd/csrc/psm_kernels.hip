@@ -1342,7 +1342,8 @@ __device__ inline void store_cell_slots(const BoxDev& bx, typename S::T* g, int 
 // (us at 256^3):
 //   read-out of rho and u  FP64 904 -> 588, FP32 769 -> 333, FP16 746 -> 209
 //   set_pdfs               FP64 1210 -> 924, FP32 990 -> 697, FP16 990 -> 593
-// Cells next to a wall or face are left to the general kernels after them.
+// Cells next to a wall or face are left to the general kernels after them (which
+// take a small box alone).
 struct RowGrid {
     int shift;            // rows of 1 << shift cells
     int nbx, nby, T;
@@ -1425,6 +1426,17 @@ __device__ __forceinline__ bool at_wall(const BoxDev& bx, int x, int y, int z) {
 }
 static bool has_walls(const BoxDev& bx) { return bx.walls || bx.walls_xy; }
 
+// A box with walls of at most so many cells: its general kernel alone, see wall_cell().
+static bool general_alone(const BoxDev& bx, int cells) { return has_walls(bx) && bx.N <= cells; }
+static bool general_set_pdfs(const BoxDev& bx, int storage) { return general_alone(bx, storage == 2 ? 1 << 19 : 1 << 20); }
+static bool general_equilibrium(const BoxDev& bx, int storage) {
+    return general_alone(bx, storage == 0 && (bx.walls_xy & 1) ? 1 << 20 : 1 << 19);
+}
+static bool general_macroscopic(const BoxDev& bx) { return general_alone(bx, 3 << 17); }
+static bool general_get_pdfs(const BoxDev& bx, int storage) {
+    return general_alone(bx, 5 << 18) || ((bx.walls_xy & 1) && (storage == 0 || (bx.N > 3 << 20 && bx.nx < 224)));
+}
+
 // Number of those cells, and cell i of them: the two z planes, then of the
 // planes between the two rows at y, then of the rows between the two ends. The
 // kernels over them launch one thread for each (500 x 200 x 800 with walls on
@@ -1435,10 +1447,31 @@ __host__ __device__ inline long long wall_cells(const BoxDev& bx) {
     return (bx.walls ? 2LL * bx.nx * bx.ny : 0) + ((bx.walls_xy & 2) ? 2 * nzi * bx.nx : 0) +
            ((bx.walls_xy & 1) ? 2 * nzi * nyi : 0);
 }
-__device__ __forceinline__ bool wall_cell(const BoxDev& bx, long long i, int& x, int& y, int& z) {
-    if (i >= wall_cells(bx)) return false;
+// ALL: every cell of the box instead, in index order, where one launch of a
+// general kernel takes less than two (all / the two, us: 8 x 15 x 89 between z
+// walls psm_get_pdfs 8 / 12; 64^3 between walls on all sides FP64 psm_get_pdfs 17 /
+// 30, psm_set_pdfs 18 / 31, psm_get_macroscopic 16 / 24, psm_set_equilibrium 22 /
+// 32; 96^3 FP64 51 / 62, 57 / 63, 43 / 39, 65 / 68, FP16 37 / 49, 55 / 48, 46 / 30, 63 /
+// 56), and where psm_get_pdfs would write the ends of rows at x walls apart from
+// the rows, each a line of its own for every direction: in FP64 (124 x 194 x 974
+// 1404 / 1992, 256^3 999 / 1133), in the deviation forms where the rows are short
+// and the field exceeds the caches (FP32 124 x 194 x 974 1314 / 1631, 203 x 385 x 144
+// 612 / 759; but 128^3 119 / 100, 500 x 200 x 400 2029 / 1897). Walls within the
+// kernels of the interior instead: FP32 psm_get_macroscopic of 128^3 between x
+// walls 94 against 54, between z walls 40 against 45.
+template <bool ALL>
+__device__ __forceinline__ bool wall_cell(const BoxDev& bx, int& x, int& y, int& z) {
+    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= (ALL ? (long long)bx.N : wall_cells(bx))) return false;
     unsigned k = (unsigned)i;   // cells of a box are counted in int
     const unsigned nx = bx.nx, plane = nx * bx.ny;
+    if (ALL) {
+        z = k / plane;
+        k -= z * plane;
+        y = k / nx;
+        x = k - y * nx;
+        return true;
+    }
     if (bx.walls) {
         if (k < 2 * plane) {
             z = k < plane ? 0 : bx.nz - 1;
@@ -1638,21 +1671,21 @@ __global__ __launch_bounds__(256) void k_set_equilibrium(BoxDev bx, RowGrid rg, 
     }
 }
 
-// The cells at walls and faces.
-template <class S>
+// The cells at walls and faces, or with ALL every cell.
+template <class S, bool ALL>
 __global__ void k_set_pdfs_wall(BoxDev bx, int parity, const double* __restrict__ f, float scale) {
     int x, y, z;
-    if (!wall_cell(bx, (long long)blockIdx.x * blockDim.x + threadIdx.x, x, y, z)) return;
+    if (!wall_cell<ALL>(bx, x, y, z)) return;
     typename S::T* g = (typename S::T*)bx.grid[parity];
     const long long N = bx.N;
     store_cell_slots<S>(bx, g, x, y, z, scale, [&](int d, long long c) { return f[(long long)d * N + c]; });
 }
 
-template <class S>
+template <class S, bool ALL>
 __global__ void k_set_equilibrium_wall(BoxDev bx, int parity, const double* __restrict__ rho,
                                        const double* __restrict__ u, float scale) {
     int x, y, z;
-    if (!wall_cell(bx, (long long)blockIdx.x * blockDim.x + threadIdx.x, x, y, z)) return;
+    if (!wall_cell<ALL>(bx, x, y, z)) return;
     typename S::T* g = (typename S::T*)bx.grid[parity];
     const long long N = bx.N;
     store_cell_slots<S>(bx, g, x, y, z, scale, [&](int d, long long c) {
@@ -1681,10 +1714,10 @@ __global__ __launch_bounds__(256) void k_get_pdfs(BoxDev bx, IndexGrid ig, int p
     }
 }
 
-template <class S>
+template <class S, bool ALL>
 __global__ void k_get_pdfs_wall(BoxDev bx, int parity, double* __restrict__ f, float inv) {
     int x, y, z;
-    if (!wall_cell(bx, (long long)blockIdx.x * blockDim.x + threadIdx.x, x, y, z)) return;
+    if (!wall_cell<ALL>(bx, x, y, z)) return;
     const long long n = (long long)z * bx.nx * bx.ny + bx.nx * y + x;
     const typename S::T* g = (const typename S::T*)bx.grid[parity];
 #pragma unroll
@@ -1745,11 +1778,11 @@ __global__ __launch_bounds__(256) void k_macroscopic(BoxDev bx, RowGrid rg, int 
     write_fields(bx, x + bx.nx * (y + (long long)bx.ny * z), rho, u, [&](int q) { return canonical<S>(f[q], q, inv); });
 }
 
-template <class S>
+template <class S, bool ALL>
 __global__ void k_macroscopic_wall(BoxDev bx, int parity, double* __restrict__ rho, double* __restrict__ u,
                                    float inv) {
     int x, y, z;
-    if (!wall_cell(bx, (long long)blockIdx.x * blockDim.x + threadIdx.x, x, y, z)) return;
+    if (!wall_cell<ALL>(bx, x, y, z)) return;
     const long long n = (long long)z * bx.nx * bx.ny + bx.nx * y + x;
     const typename S::T* g = (const typename S::T*)bx.grid[parity];
     write_fields(bx, n, rho, u, [&](int q) {
@@ -2160,16 +2193,26 @@ hipError_t launch_download(const DownloadParams& dp, hipStream_t st) {
 
 hipError_t launch_set_pdfs(int storage, const BoxDev& bx, int parity, const double* f, float scale,
                            hipStream_t st) {
+    if (general_set_pdfs(bx, storage)) {
+        PSM_BY_STORAGE(hipLaunchKernelGGL((k_set_pdfs_wall<S, true>), dim3(blocks_for(bx.N, 256)), dim3(256), 0, st,
+                                          bx, parity, f, scale));
+        return hipGetLastError();
+    }
     const RowGrid rg = row_grid(bx);
     PSM_BY_STORAGE(hipLaunchKernelGGL(k_set_pdfs<S>, dim3(row_blocks(rg)), dim3(256), 0, st, bx, rg, parity, f, scale));
     if (has_walls(bx))
-        PSM_BY_STORAGE(hipLaunchKernelGGL(k_set_pdfs_wall<S>, dim3(blocks_for(wall_cells(bx), 256)), dim3(256), 0, st, bx, parity,
-                                          f, scale));
+        PSM_BY_STORAGE(hipLaunchKernelGGL((k_set_pdfs_wall<S, false>), dim3(blocks_for(wall_cells(bx), 256)), dim3(256), 0, st,
+                                          bx, parity, f, scale));
     return hipGetLastError();
 }
 
 hipError_t launch_set_equilibrium(int storage, const BoxDev& bx, int parity, const double* rho, const double* u,
                                   float scale, hipStream_t st) {
+    if (general_equilibrium(bx, storage)) {
+        PSM_BY_STORAGE(hipLaunchKernelGGL((k_set_equilibrium_wall<S, true>), dim3(blocks_for(bx.N, 256)), dim3(256), 0,
+                                          st, bx, parity, rho, u, scale));
+        return hipGetLastError();
+    }
     const RowGrid rg = row_grid(bx);
     // 16 planes per tile read 18; fewer while that leaves CUs idle
     int depth = 16;
@@ -2181,12 +2224,17 @@ hipError_t launch_set_equilibrium(int storage, const BoxDev& bx, int parity, con
         default: PSM_BY_STORAGE(hipLaunchKernelGGL((k_set_equilibrium<S, 6>), grid, dim3(256), 0, st, bx, rg, depth, parity, rho, u, scale));
     }
     if (has_walls(bx))
-        PSM_BY_STORAGE(hipLaunchKernelGGL(k_set_equilibrium_wall<S>, dim3(blocks_for(wall_cells(bx), 256)), dim3(256), 0, st, bx,
-                                          parity, rho, u, scale));
+        PSM_BY_STORAGE(hipLaunchKernelGGL((k_set_equilibrium_wall<S, false>), dim3(blocks_for(wall_cells(bx), 256)), dim3(256), 0, st,
+                                          bx, parity, rho, u, scale));
     return hipGetLastError();
 }
 
 hipError_t launch_get_pdfs(int storage, const BoxDev& bx, int parity, double* f, float inv, hipStream_t st) {
+    if (general_get_pdfs(bx, storage)) {
+        PSM_BY_STORAGE(hipLaunchKernelGGL((k_get_pdfs_wall<S, true>), dim3(blocks_for(bx.N, 256)), dim3(256), 0, st,
+                                          bx, parity, f, inv));
+        return hipGetLastError();
+    }
     const IndexGrid ig = index_grid(bx);
     const dim3 grid((unsigned)(ig.T + NXCD - 1) / NXCD * NXCD);
     if (bx.N % 16 == 0 && ((uintptr_t)f & 127) == 0)
@@ -2194,8 +2242,8 @@ hipError_t launch_get_pdfs(int storage, const BoxDev& bx, int parity, double* f,
     else
         PSM_BY_STORAGE(hipLaunchKernelGGL((k_get_pdfs<S, false>), grid, dim3(256), 0, st, bx, ig, parity, f, inv))
     if (has_walls(bx))
-        PSM_BY_STORAGE(hipLaunchKernelGGL(k_get_pdfs_wall<S>, dim3(blocks_for(wall_cells(bx), 256)), dim3(256), 0, st, bx, parity,
-                                          f, inv));
+        PSM_BY_STORAGE(hipLaunchKernelGGL((k_get_pdfs_wall<S, false>), dim3(blocks_for(wall_cells(bx), 256)), dim3(256), 0, st,
+                                          bx, parity, f, inv));
     return hipGetLastError();
 }
 
@@ -2212,12 +2260,17 @@ hipError_t launch_get_pdfs_at(int storage, const BoxDev& bx, int parity, const i
 
 hipError_t launch_macroscopic(int storage, const BoxDev& bx, int parity, double* rho, double* u, float inv,
                               hipStream_t st) {
+    if (general_macroscopic(bx)) {
+        PSM_BY_STORAGE(hipLaunchKernelGGL((k_macroscopic_wall<S, true>), dim3(blocks_for(bx.N, 256)), dim3(256), 0, st,
+                                          bx, parity, rho, u, inv));
+        return hipGetLastError();
+    }
     const RowGrid rg = row_grid(bx);
     PSM_BY_STORAGE(hipLaunchKernelGGL(k_macroscopic<S>, dim3(row_blocks(rg)), dim3(256), 0, st, bx, rg, parity, rho, u,
                                       inv));
     if (has_walls(bx))
-        PSM_BY_STORAGE(hipLaunchKernelGGL(k_macroscopic_wall<S>, dim3(blocks_for(wall_cells(bx), 256)), dim3(256), 0, st, bx,
-                                          parity, rho, u, inv));
+        PSM_BY_STORAGE(hipLaunchKernelGGL((k_macroscopic_wall<S, false>), dim3(blocks_for(wall_cells(bx), 256)), dim3(256), 0, st,
+                                          bx, parity, rho, u, inv));
     return hipGetLastError();
 }
 

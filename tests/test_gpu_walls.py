@@ -421,3 +421,41 @@ def test_every_wall_cell_is_set_and_read_once(dims, walls):
     # sums of 19 terms of at most 1/3 and 1/18, one rounding per addition
     assert np.all(np.abs(rho - got.sum(0)) <= 19 * 2.0 ** -52)
     assert np.all(np.abs(u - c.T @ got) <= 19 * 2.0 ** -52)
+
+
+@pytest.mark.parametrize("walls", ["x", "y", "z", "xyz"])
+@pytest.mark.parametrize("storage", [psm.PSM_FP64, psm.PSM_FP32DEV, psm.PSM_FP16DEV])
+@pytest.mark.parametrize("dims", [(170, 120, 70), (98, 120, 70)])
+def test_state_between_walls_of_larger_boxes(dims, storage, walls):
+    """Boxes too large for the general state kernels alone (1.4 and 0.8 M cells):
+    the interior kernels and those of the wall cells together set and read
+    every cell (canonical PDFs, density, velocity, equilibrium)."""
+    import torch
+
+    print(f"[case] larger walls {dims} {walls} storage={storage}", flush=True)
+    N = int(np.prod(dims))
+    rng = np.random.default_rng(N + len(walls))
+    w = np.array([1 / 3] + [1 / 18] * 6 + [1 / 36] * 12)
+    c = np.array([(0, 0, 0), (1, 0, 0), (-1, 0, 0), (0, 1, 0), (0, -1, 0), (0, 0, 1), (0, 0, -1), (1, 1, 0),
+                  (-1, -1, 0), (1, -1, 0), (-1, 1, 0), (1, 0, 1), (-1, 0, -1), (1, 0, -1), (-1, 0, 1), (0, 1, 1),
+                  (0, -1, -1), (0, 1, -1), (0, -1, 1)])
+    f = w[:, None] * (1.0 + 0.02 * (rng.random((19, N)) - 0.5))
+    spec = inputs.BoxSpec(dims=dims, tau=0.7, walls_x="x" in walls, walls_y="y" in walls, walls_z="z" in walls)
+    eng = make_engine([spec], storage=storage)
+    eng.set_pdfs(0, f)
+    got = eng.get_pdfs(0).cpu().numpy()
+    rho, u = (a.cpu().numpy() for a in eng.get_macroscopic(0))
+    # stored values d = f - w rounded once, 2^-11 of at most 0.01 w in FP16 with FP64 sums around it
+    bound = {psm.PSM_FP64: 2.0 ** -53, psm.PSM_FP32DEV: 2.0 ** -24 * 0.01 / 3 + 2.0 ** -53,
+             psm.PSM_FP16DEV: 2.0 ** -11 * 0.01 / 3 + 2.0 ** -53}[storage]
+    assert np.all(np.abs(got - f) <= bound)
+    assert np.all(np.abs(rho - got.sum(0)) <= 19 * 2.0 ** -52)
+    assert np.all(np.abs(u - c.T @ got) <= 19 * 2.0 ** -52)
+    u0 = (rng.random((3, N)) - 0.5) * 0.02
+    eng.set_equilibrium(0, torch.as_tensor(u0))
+    got = eng.get_pdfs(0).cpu().numpy()
+    eng.close()
+    cu = c @ u0
+    ref = w[:, None] * (1.0 + 3.0 * cu + 4.5 * cu ** 2 - 1.5 * (u0 ** 2).sum(0))
+    # the equilibrium's 8 roundings, then that of the stored deviation, at most 0.06 w
+    assert np.all(np.abs(got - ref) <= 16 * 2.0 ** -53 * w[:, None] + 6 * bound)
