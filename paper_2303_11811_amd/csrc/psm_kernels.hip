@@ -1793,14 +1793,16 @@ __global__ void k_macroscopic_wall(BoxDev bx, int parity, double* __restrict__ r
 
 // Dense two-slot solid fractions of one box (read-out, or with B null the
 // overflow count alone), through the same candidate lists and mapping
-// function as the step kernel, by the tiles and parts of tiles of the step, the
-// spheres staged in LDS (256^3: 146 -> 92 us at 24 B per cell). Fewer than
-// three spheres cannot overflow a cell. LINES: rows are whole lines (16 cells),
-// stored past the caches. Else tiles leave partial lines to their neighbours in
-// x: the tiles of a row run on one die, whose L2 puts the lines together (581 x
-// 455 x 143 without spheres 391 us with nontemporal stores and rows over all
-// dies, 330 with one die and nontemporal, 197 so; at 10 % solid 436 / 447).
-template <bool LINES>
+// function as the step kernel: a workgroup per plane of a tile, the spheres
+// staged in LDS. Fewer than three spheres cannot overflow a cell. Bound by the
+// writes (24 B per cell) or the mapping. SAMPLE: boxes that sample; the registers
+// of the sampling would halve the waves of the others (256^3 FP64 at 10 % solid
+// 206 us, 142 without them, and 136 with a plane per workgroup; 64^3 and depth 16
+// at 10 % 77, now 9.6). LINES: rows are whole lines (16 cells), stored past the
+// caches. Else tiles leave partial lines to their neighbours in x: the tiles of a
+// row run on one die, whose L2 puts the lines together (581 x 455 x 143 without
+// spheres 391 us with nontemporal stores and a row over all dies, 171 so).
+template <bool LINES, bool SAMPLE>
 __global__ __launch_bounds__(WG) void k_map_dense(BoxDev bx, Particles P, const int* __restrict__ tile_cnt,
                                                   const int* __restrict__ tile_off,
                                                   const int2* __restrict__ tile_ent, int list_cap, TileShape ts,
@@ -1829,34 +1831,27 @@ __global__ __launch_bounds__(WG) void k_map_dense(BoxDev bx, Particles P, const 
     const int tcz = udiv(tr, bx.div_nty[0], bx.div_nty[1]);
     const int x = (lt - tr * bx.ntx) * ts.tx + (tid & (ts.tx - 1));
     const int y = (tr - tcz * bx.nty) * ts.ty + (tid >> __builtin_ctz(ts.tx));
-    // gridDim.y workgroups share the planes of a tile
-    const int depth = ts.tz / (int)gridDim.y, z0 = tcz * ts.tz + (int)blockIdx.y * depth, z1 = min(z0 + depth, bx.nz);
-    int lost = 0;
-    if (x < bx.nx && y < bx.ny) {
-        for (int z = z0; z < z1; ++z) {
-            Slots sl;
-            slots_init(sl);
-            for (int c = 0; c < nc; ++c) {
-                const double dx = min_image((x + 0.5) - s_x[c], bx.L[0], bx.halfL[0]);
-                const double dy = min_image((y + 0.5) - s_y[c], bx.L[1], bx.halfL[1]);
-                const double dz = min_image((z + 0.5) - s_z[c], bx.L[2], bx.halfL[2]);
-                const double b = bx.mapping == 0
-                                     ? overlap_linear(dx, dy, dz, s_r[c], s_fr[c])
-                                     : overlap_subsample(dx, dy, dz, s_r[c], bx.nsub, bx.sub_off, bx.reach);
-                if (b > 0.0) slots_insert(sl, s_p[c], s_p[c], b);
-            }
-            slots_finish(sl);
-            lost += sl.dropped;
-            const long long n = x + bx.nx * (y + (long long)bx.ny * z);
-            if (B) {
-                put<LINES>(B + n, sl.c0 >= 0 ? sl.B0 : 0.0);
-                put<LINES>(B + bx.N + n, sl.c1 >= 0 ? sl.B1 : 0.0);
-                put<LINES>(pid + n, sl.c0 >= 0 ? sl.c0 - bx.part_base : -1);
-                put<LINES>(pid + bx.N + n, sl.c1 >= 0 ? sl.c1 - bx.part_base : -1);
-            }
-        }
+    const int z = tcz * ts.tz + (int)blockIdx.y;
+    if (x >= bx.nx || y >= bx.ny || z >= bx.nz) return;
+    Slots sl;
+    slots_init(sl);
+    for (int c = 0; c < nc; ++c) {
+        const double dx = min_image((x + 0.5) - s_x[c], bx.L[0], bx.halfL[0]);
+        const double dy = min_image((y + 0.5) - s_y[c], bx.L[1], bx.halfL[1]);
+        const double dz = min_image((z + 0.5) - s_z[c], bx.L[2], bx.halfL[2]);
+        const double b = !SAMPLE ? overlap_linear(dx, dy, dz, s_r[c], s_fr[c])
+                                 : overlap_subsample(dx, dy, dz, s_r[c], bx.nsub, bx.sub_off, bx.reach);
+        if (b > 0.0) slots_insert(sl, s_p[c], s_p[c], b);
     }
-    if (lost) atomicAdd(dropped, (unsigned long long)lost);
+    slots_finish(sl);
+    const long long n = x + bx.nx * (y + (long long)bx.ny * z);
+    if (B) {
+        put<LINES>(B + n, sl.c0 >= 0 ? sl.B0 : 0.0);
+        put<LINES>(B + bx.N + n, sl.c1 >= 0 ? sl.B1 : 0.0);
+        put<LINES>(pid + n, sl.c0 >= 0 ? sl.c0 - bx.part_base : -1);
+        put<LINES>(pid + bx.N + n, sl.c1 >= 0 ? sl.c1 - bx.part_base : -1);
+    }
+    if (sl.dropped) atomicAdd(dropped, (unsigned long long)sl.dropped);
 }
 
 // Sum of 4 doubles per thread over the block, in a fixed tree; lane c < 4
@@ -2278,16 +2273,11 @@ hipError_t launch_map_dense(const BoxDev& bx, const Particles& P, const int* til
                             const int2* tile_ent, int list_cap, TileShape ts, double* B, int* pid,
                             unsigned long long* dropped, hipStream_t st) {
     const int rows = bx.nty * bx.ntz;
-    // as many parts of a tile as in the step, and more where that leaves CUs idle
-    // (64^3 at 10 % solid and depth 16: 76 us in one part, 13 shared)
-    int parts = 1 << ts.zshift;
-    while (parts < ts.tz && (long long)rows * bx.ntx * parts < 2048) parts *= 2;
-    if (bx.nx % 16 == 0)
-        hipLaunchKernelGGL(k_map_dense<true>, dim3(rows * bx.ntx, parts), dim3(WG), 0, st, bx, P, tile_cnt, tile_off,
-                           tile_ent, list_cap, ts, B, pid, dropped);
-    else
-        hipLaunchKernelGGL(k_map_dense<false>, dim3((rows + NXCD - 1) / NXCD * NXCD * bx.ntx, parts), dim3(WG), 0,
-                           st, bx, P, tile_cnt, tile_off, tile_ent, list_cap, ts, B, pid, dropped);
+    const bool lines = bx.nx % 16 == 0;
+    const dim3 grid((lines ? rows : (rows + NXCD - 1) / NXCD * NXCD) * bx.ntx, ts.tz);
+    const auto k = bx.mapping == 0 ? (lines ? k_map_dense<true, false> : k_map_dense<false, false>)
+                                   : (lines ? k_map_dense<true, true> : k_map_dense<false, true>);
+    hipLaunchKernelGGL(k, grid, dim3(WG), 0, st, bx, P, tile_cnt, tile_off, tile_ent, list_cap, ts, B, pid, dropped);
     return hipGetLastError();
 }
 
