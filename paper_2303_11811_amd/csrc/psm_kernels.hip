@@ -1383,7 +1383,8 @@ __device__ __forceinline__ bool row_cell(const RowGrid& g, const BoxDev& bx, int
 // (every direction of the field starts at a 128-byte line): nontemporal
 // stores, and the dies share consecutive blocks, which keeps the 19 streams
 // close together; else ordinary stores, whose partial lines meet in the L2 of a
-// die that takes a contiguous eighth. psm_get_pdfs, us, tiles / index order with
+// die that takes a contiguous eighth. Blocks start at lines of the field where
+// planes do not (74 x 131 x 696 FP64 428 -> 390, FP32 362 -> 299). psm_get_pdfs, us, tiles / index order with
 // either, FP64: 256^3 928 / 885 / 969, 97 x 92 x 184 130 / 90 / 106, 109 x 272 x 40 83 / 57
 // / 80; not at lines 581 x 455 x 143 3146 / 2578 / 2326, 332 x 134 x 547 1828 / 1440 / 1439;
 // FP32 581 x 455 x 143 2666 / 2150 / 1770.
@@ -1394,7 +1395,7 @@ struct IndexGrid {
 
 static IndexGrid index_grid(const BoxDev& bx) {
     IndexGrid g;
-    g.nb = (bx.nx * bx.ny + 255) / 256;
+    g.nb = (bx.nx * bx.ny + (bx.nx * bx.ny % 16 ? 15 : 0) + 255) / 256;
     g.T = g.nb * bx.nz;
     udiv_magic(g.nb, g.div_nb);
     udiv_magic(bx.nx, g.div_nx);
@@ -1413,10 +1414,12 @@ __device__ __forceinline__ bool index_cell(const IndexGrid& g, const BoxDev& bx,
     const int t = LINES ? (int)blockIdx.x : (int)(((long long)g.T * xcd) / NXCD) + (int)blockIdx.x / NXCD;
     if (t >= (LINES ? g.T : (int)(((long long)g.T * (xcd + 1)) / NXCD))) return false;
     z = udiv(t, g.div_nb[0], g.div_nb[1]);
-    const int i = (t - z * g.nb) * 256 + (int)threadIdx.x;
+    // blocks start at whole lines of the field also where planes do not
+    const int plane = bx.nx * bx.ny, i = (t - z * g.nb) * 256 + (int)threadIdx.x - ((z & 15) * (plane & 15) & 15);
+    if (i < 0 || i >= plane) return false;
     y = udiv(i, g.div_nx[0], g.div_nx[1]);
     x = i - y * bx.nx;
-    return y < bx.ny;
+    return true;
 }
 
 // True for the cells whose values a wall or face enters.
