@@ -905,3 +905,103 @@ def test_default_launch_lists_a_thin_sheet_of_spheres():
     assert np.array_equal(pid, ref.pid)
     assert_pdfs_close(f, ref.f, 1e-12)
     eng.close()
+
+
+def test_thin_sheet_forces_agree_between_tile_shapes():
+    """The forces of the sheet's spheres in the launch a context starts with
+    and in tiles of another shape: the same terms (B times 2 j - U - U_p of
+    fewer than 200 cells each) in another order, one rounding per addition."""
+    x, y = np.meshgrid(1.0 + 2.2 * np.arange(14), 7.0 + 2.2 * np.arange(5), indexing="ij")
+    pos = np.stack([x.ravel(), y.ravel(), np.full(x.size, 12.0)], axis=1)
+    spec = inputs.BoxSpec(dims=(32, 32, 24), tau=0.8, x=pos, r=np.ones(70), U=np.full((70, 3), 1e-3),
+                          Om=np.zeros((70, 3)), fext=(1e-5, 0.0, 0.0))
+    _print_case("sheet forces")
+    got = []
+    for launch in (None, (128, 2, 2, 0), (16, 16, 1, 0)):
+        f, F, T, _, _, eng = run_engine(spec, 2, launch=launch)
+        eng.close()
+        got.append((f, F, T))
+    A = run_oracle(spec, 2).A
+    for f, F, T in got[1:]:
+        assert np.array_equal(f, got[0][0])
+        assert np.all(np.abs(F - got[0][1]) <= 200 * 2.0 ** -52 * A[:, None])
+        assert np.all(np.abs(T - got[0][2]) <= 200 * 2.0 ** -52 * 2.0 * A[:, None])
+
+
+def _beside(spec, companions, storage, launch, steps=3):
+    """State, fields, totals and forces of spec's box after some steps, with
+    other boxes in its context."""
+    eng = make_engine([spec, *companions], storage=storage)
+    eng.set_launch(*launch)
+    for b, box in enumerate(companions):
+        eng.set_equilibrium(b + 1, np.zeros((3, box.N)))
+    f0 = initial_f(spec)
+    eng.set_pdfs(0, f0)
+    eng.set_particles(0, spec.x, spec.r, spec.U, spec.Om)
+    got = [eng.get_pdfs(0).cpu().numpy()]
+    eng.step(steps)
+    got += [eng.get_pdfs(0).cpu().numpy(), *(a.cpu().numpy() for a in eng.get_macroscopic(0)),
+            *(a.cpu().numpy() for a in eng.get_solid_fraction(0))]
+    F, T = eng.get_forces(0)
+    eng.close()
+    return got, F, T
+
+
+@pytest.mark.parametrize("storage", [psm.PSM_FP64, psm.PSM_FP32DEV, psm.PSM_FP16DEV])
+@pytest.mark.parametrize("walls", ["x", "y", "xyz"])
+@pytest.mark.parametrize("nx", [72, 131])
+def test_padded_rows_between_side_walls_keep_the_results(nx, walls, storage):
+    """Boxes between side walls whose rows are padded to lines (beside a large
+    box) give bit for bit what they give packed (alone)."""
+    from dataclasses import replace
+
+    _print_case("padded rows", nx=nx, walls=walls, storage=storage)
+    spec = inputs.random_small((nx, 24, 22), 5, (2.0, 3.0), seed=nx, tau=0.66, fext=(1e-5, 0, 0), omamp=0.003)
+    spec = replace(spec, **{"walls_" + a: True for a in walls})
+    for k, a in enumerate("xyz"):
+        if a in walls:
+            spec.x[:, k] = np.clip(spec.x[:, k], spec.r + 1.0, spec.dims[k] - spec.r - 1.0)
+    alone, *Fa = _beside(spec, [], storage, (64, 4, 1, 0))
+    beside, *Fb = _beside(spec, [inputs.BoxSpec(dims=(192, 192, 128), tau=0.8)], storage, (64, 4, 1, 0))
+    assert all(np.array_equal(a, b) for a, b in zip(alone + Fa, beside + Fb))
+
+
+@pytest.mark.parametrize("storage", [psm.PSM_FP64, psm.PSM_FP32DEV, psm.PSM_FP16DEV])
+@pytest.mark.parametrize("mapping", [0, 1])
+def test_cached_stores_keep_the_results(mapping, storage):
+    """A box whose grids (28 MiB in FP16, 112 in FP64) are stored through the
+    caches gives bit for bit what it gives beside boxes that take the context
+    past them and past the limit of the streamed loads."""
+    _print_case("cached stores", mapping=mapping, storage=storage)
+    spec = inputs.random_small((96, 72, 56), 12, (2.0, 4.0), seed=97, tau=0.66, fext=(1e-5, 0, 0), omamp=0.003,
+                               mapping=mapping)
+    spec.nsub = 3
+    size = 304 >> storage
+    more = [inputs.BoxSpec(dims=(64, 64, mib * 2 ** 20 // size // 4096), tau=0.8) for mib in (260, 480)]
+    got = [_beside(spec, box, storage, (64, 4, 2, 0)) for box in ([], more[:1], more[1:])]
+    for g, F, T in got[1:]:
+        assert all(np.array_equal(a, b) for a, b in zip([*got[0][0], *got[0][1:]], [*g, F, T]))
+
+
+@pytest.mark.parametrize("storage", [psm.PSM_FP32DEV, psm.PSM_FP16DEV])
+@pytest.mark.parametrize("walls", ["", "z", "xyz"])
+@pytest.mark.parametrize("launch", [(64, 4, 4, 0), (32, 8, 2, 0)])
+def test_shared_tiles_of_the_deviation_forms_keep_the_results(launch, walls, storage):
+    """A box alone, whose tiles several workgroups share, and beside one of so
+    many tiles that each has one workgroup: the same PDFs and fractions bit for
+    bit, forces to the order of their FP64 sums over waves (60 partial sums)."""
+    from dataclasses import replace
+
+    _print_case("shared deviation tiles", launch=launch, walls=walls, storage=storage)
+    spec = inputs.random_small((50, 26, 30), 5, (2.5, 4.0), seed=71, tau=0.66, fext=(1e-5, 0, 0), omamp=0.003)
+    spec = replace(spec, **{"walls_" + a: True for a in walls})
+    for k, a in enumerate("xyz"):
+        if a in walls:
+            spec.x[:, k] = np.clip(spec.x[:, k], spec.r + 1.0, spec.dims[k] - spec.r - 1.0)
+    alone, Fa, Ta = _beside(spec, [], storage, launch)
+    tall = inputs.BoxSpec(dims=(64, 128, 1200), tau=0.8)
+    beside, Fb, Tb = _beside(spec, [tall], storage, launch)
+    assert all(np.array_equal(a, b) for a, b in zip(alone, beside))
+    A = run_oracle(spec, 3).A
+    assert np.all(np.abs(Fa - Fb) <= 60 * 2.0 ** -52 * A[:, None] + 1e-300)
+    assert np.all(np.abs(Ta - Tb) <= 60 * 2.0 ** -52 * 5.0 * A[:, None] + 1e-300)
