@@ -291,12 +291,13 @@ enum psm_launch_flags {
  * tx in {16,32,64,128,256}) and tz cells each along z (tz in
  * {1,2,4,8,16,32}), and psm_launch_flags. A tile has one candidate list; up
  * to 8 workgroups share its cells along z where that keeps more of the chip
- * busy. Rebuilds the tile lists
- * (synchronises); invalidates captured graphs. On failure the previous
- * launch is restored. A context starts with 64 x 4 threads (FP64 boxes that
- * would leave many of them idle, with room for at most 64 spheres each: 32 x 8)
- * and a depth chosen from its storage form and box sizes (its results are those of depth
- * 16). psm_get_launch: host outputs (flags may be NULL). */
+ * busy. Rebuilds the tile lists (synchronises); invalidates captured graphs.
+ * On failure the previous launch is restored. A context starts with 64 x 4
+ * threads (32 x 8 in FP64 where every box would leave many of them idle and has
+ * room for at most 64 spheres) and a depth chosen from its storage form and box
+ * sizes: the PDFs are bit for bit those of depth 16, the forces those but for
+ * the order of their FP64 sums. psm_get_launch: host outputs (flags may be
+ * NULL). */
 int psm_set_launch(psm_ctx* ctx, int tx, int ty, int tz, int flags);
 int psm_get_launch(psm_ctx* ctx, int* tx, int* ty, int* tz, int* flags);
 
@@ -308,11 +309,12 @@ int psm_get_launch(psm_ctx* ctx, int* tx, int* ty, int* tz, int* flags);
  * state after tuning. Synchronises. best_ms: ms per step of the chosen launch
  * in the second round.
  * The pick is cached for the process, keyed by the GPU architecture, the
- * library's sources (another version tunes anew), the storage form, the mapping and, per box, its dimensions, walls and sphere
- * volume fraction (a power-of-two class); a context of a cached class gets
- * the cached launch and time without any trial (its state is then not
- * advanced). If the environment variable PSM_TUNE_CACHE names a file, its
- * entries are read at the first call and new picks are appended to it. */
+ * library's sources (another version tunes anew), the storage form, the
+ * mapping and, per box, its dimensions, walls and sphere volume fraction (a
+ * power-of-two class); a context of a cached class gets the cached launch and
+ * time without any trial (its state is then not advanced). If the environment
+ * variable PSM_TUNE_CACHE names a file, its entries are read at the first call
+ * and new picks are appended to it. */
 int psm_autotune(psm_ctx* ctx, int trial_steps, int* tx, int* ty, int* tz, int* flags, double* best_ms);
 
 /* Forget the autotune picks of this process (the file named by

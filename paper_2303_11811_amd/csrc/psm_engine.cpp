@@ -151,12 +151,12 @@ static int z_shift(const psm_box_desc* boxes, int nbox, int storage, int tx, int
 // Launch of a context that sets none: tiles of 64 x 4 threads of that depth.
 // The FP32 geometry refers to the centres of blocks 64 x 4 cells wide and 16
 // planes deep at every depth, so the results do not depend on the depth
-// chosen. FP64, which has no such reference, takes 32 x 8 threads where the
-// widest box fills at most 3/4 of its 64-wide tiles (us at 64 x 4 / 32 x 8: 68^3
-// 31.4 / 28.8, 80^3 39.9 / 34.2, 96^3 58.9 / 54.4; 132^3, where it would save a
-// sixth, 163 / 183) and a list can hold every sphere: such a tile meets spheres
-// over 8 rows, so its list could overflow with spheres that the lists of 64 x 4
-// tiles hold.
+// chosen (the forces but for the order of their FP64 sums). FP64, which has
+// no such reference, takes 32 x 8 threads where every box fills at most 3/4 of
+// its 64-wide tiles (us at 64 x 4 / 32 x 8: 68^3 31.4 / 28.8, 80^3 39.9 / 34.2,
+// 96^3 58.9 / 54.4; 132^3, where it would save a sixth, 163 / 183) and a list
+// can hold every sphere: such a tile meets spheres over 8 rows, so its list
+// could overflow with spheres that the lists of 64 x 4 tiles hold.
 constexpr int kDefaultRefZ = 16;
 
 static TileShape default_shape(const psm_box_desc* boxes, int nbox, int storage) {

@@ -125,15 +125,6 @@ __device__ __forceinline__ int udiv(int n, unsigned mul, unsigned shift) {
     return mul ? (int)(__umulhi(mul, (unsigned)n) >> shift) : n;
 }
 
-__device__ inline int find_box(const int* tile_base, int nbox, int t) {
-    int lo = 0, hi = nbox - 1;
-    while (lo < hi) {
-        int mid = (lo + hi + 1) >> 1;
-        if (tile_base[mid] <= t) lo = mid; else hi = mid - 1;
-    }
-    return lo;
-}
-
 __device__ inline double wave_sum(double v) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
@@ -398,8 +389,6 @@ __device__ inline void box_tiles(const BoxDev& bx, const TileShape& ts, double x
     az = axis_tiles(lo, hi, bx.nz, ts.tz, bx.ntz);
 }
 
-//   UPLOAD  the spheres of one box first take new columns from pinned host
-//           staging (lane c reads column c), before their tiles are found.
 // Force and torque of global sphere p from its tile partials, for the whole
 // wave: lane l takes tiles l, l + 64, ... of the bounding box in a fixed order,
 // then a fixed butterfly adds the lanes (the same bits on every lane).
@@ -477,7 +466,10 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
     if ((int)blockIdx.x >= ka->grid) {
         // the force reduction of the step before (k_spheres reduces the last
         // step of a call): in a launch of its own it takes 4.5 us behind every
-        // step, a third of a 32^3 step
+        // step, a third of a 32^3 step. A wave per sphere the context has room
+        // for: 8 of 10^6 set, 256^3 FP64, 1587 us a step, 1588 with launches of
+        // its own; those are ahead only where 10^5 are set (1234 / 1197 us,
+        // FP32 684 / 673)
         const int p = (blockIdx.x - ka->grid) * NWAVE + wave;
         if (p >= ka->P_total) return;
         double acc[6];
@@ -1016,8 +1008,11 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(
 
 // ---------------------------------------------------------------------------
 // Work per sphere, one 64-wide wave each:
+//   UPLOAD  the spheres of one box first take new columns from pinned host
+//           staging (lane c reads column c), before their tiles are found.
 //   REDUCE  force and torque of the last step (reduce_sphere; earlier steps of
-//           one call are reduced inside the next step's launch).
+//           one call are reduced inside the next step's launch where the
+//           context has two sets of partials).
 //   SCHEME  sphere update (Sec. 2.2.2) for collision-free spheres:
 //           m = rho_p (4/3) pi r^3, I = (2/5) m r^2; the total force is the
 //           hydrodynamic force of the last step plus m times the box's
@@ -1383,11 +1378,12 @@ __device__ __forceinline__ bool row_cell(const RowGrid& g, const BoxDev& bx, int
 // (every direction of the field starts at a 128-byte line): nontemporal
 // stores, and the dies share consecutive blocks, which keeps the 19 streams
 // close together; else ordinary stores, whose partial lines meet in the L2 of a
-// die that takes a contiguous eighth. Blocks start at lines of the field where
-// planes do not (74 x 131 x 696 FP64 428 -> 390, FP32 362 -> 299). psm_get_pdfs, us, tiles / index order with
-// either, FP64: 256^3 928 / 885 / 969, 97 x 92 x 184 130 / 90 / 106, 109 x 272 x 40 83 / 57
-// / 80; not at lines 581 x 455 x 143 3146 / 2578 / 2326, 332 x 134 x 547 1828 / 1440 / 1439;
-// FP32 581 x 455 x 143 2666 / 2150 / 1770.
+// die that takes a contiguous eighth. psm_get_pdfs, us, tiles / index order with
+// either, FP64: 256^3 928 / 885 / 969, 97 x 92 x 184 130 / 90 / 106,
+// 109 x 272 x 40 83 / 57 / 80; not at lines 581 x 455 x 143 3146 / 2578 / 2326,
+// 332 x 134 x 547 1828 / 1440 / 1439; FP32 581 x 455 x 143 2666 / 2150 / 1770.
+// Blocks start at lines of the field also where planes do not (74 x 131 x 696
+// FP64 428 -> 390 us, FP32 362 -> 299).
 struct IndexGrid {
     int nb, T;            // blocks per plane, and in all
     unsigned div_nb[2], div_nx[2];
@@ -2018,10 +2014,6 @@ hipError_t launch_field_stats_noalloc(const double* f, long long N, double* out,
 
 static inline unsigned blocks_for(long long n, int bs) { return (unsigned)((n + bs - 1) / bs); }
 
-// The step kernel instance for (storage, map, filt): storage psm_storage;
-// map 0 when every box uses the linear approximation, 1 if any box samples;
-// filt the per-wave candidate filter; wall if any box has walls or faces;
-// cached for grids that fit the last-level cache.
 // ---------------------------------------------------------------------------
 // Bandwidth reference for the step's access pattern: the tile walk, pulls and
 // stores of k_psm_step with no arithmetic. SHIFT pulls each direction from
@@ -2102,6 +2094,12 @@ hipError_t launch_pattern_copy(int storage, bool shifted, const StepParams& kp, 
     return hipLaunchKernel(k, dim3(kp.grid), dim3(WG), args, 0, st);
 }
 
+// The step kernel instance for (storage, MAP, FILT, WALL, CACHE): storage
+// psm_storage; MAP 1 if any box samples and the context has room for spheres,
+// else 0 (the linear approximation); FILT the per-wave candidate filter; WALL if
+// any box has walls or faces; CACHE the load and store form (cache_form). The
+// filter, which no context starts with, is built for MIXED grids alone: KEEP and
+// STREAM were measured without it.
 template <int MAP, bool FILT, bool WALL, int CACHE>
 static const void* step_kernel_of(int storage) {
     switch (storage) {
